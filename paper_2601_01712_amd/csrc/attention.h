@@ -9,7 +9,7 @@
 // the visible keys): the kernels produce, per row, head and key split, a reference score m, the
 // sum l of exp(s_j - m) over the split's visible keys and the sum of exp(s_j - m) v_j; m is a
 // running maximum, so nothing overflows, and the splits and the candidate's own key are merged
-// afterwards by softmax_combine_kernel (rowwise.h).
+// afterwards in the layer tail.
 //
 // Keys come in tiles of 64 tokens (layout in common.h): a K tile [64][dh] followed by a V tile
 // stored transposed [dh][64].  Prefix tiles come from the user's K/V space (pool or scratch),
@@ -43,10 +43,10 @@ struct AttnParams {
   const void* knew;   // [new rows][d]
   const void* vnew;
   int n_prows;        // rows before the first new row
-  int gs;             // MFMA kernel: key splits taken by the wavefront groups of one workgroup and added in LDS (1 or 2)
+  int gs;             // key splits taken inside one workgroup and added in LDS: 16-bit 1 or 2 (wavefront groups), fp32 1 or 8 (wavefronts)
 };
 
-// Key-tile schedule of one work item, shared by both kernels.
+// Key-tile schedule of one work item.
 struct TileRange {
   int nkp;       // prefix tiles this item needs
   int nfull;     // leading prefix tiles every row of the item sees completely
@@ -70,77 +70,6 @@ __device__ __forceinline__ TileRange tile_range(const AttnTile& at, const UserDe
   tr.t0 = min(split * per, total);
   tr.t1 = min(tr.t0 + per, total);
   return tr;
-}
-
-// ---- fp32 kernel: one thread per row, keys broadcast from LDS -----------------------------------
-template <int DH, bool SOFTMAX>
-__global__ __launch_bounds__(64) void attn_f32_kernel(AttnParams p) {
-  __shared__ float Ks[kTile * DH];
-  __shared__ float Vs[DH * kTile];
-  const AttnTile at = p.tiles[blockIdx.x];
-  const int head = blockIdx.y, split = blockIdx.z;
-  const UserDesc ud = p.users[at.user];
-  const TileRange tr = tile_range(at, ud, split, p.nsplit);
-  const int t = threadIdx.x;
-  const bool active = t < at.nrows;
-  const int row = at.row0 + (active ? t : 0);
-  const int lim = active ? p.rt.lim[row] : 0;
-
-  float qv[DH], o[DH];
-  const float* qrow = reinterpret_cast<const float*>(p.q) + (size_t)row * p.d + head * DH;
-#pragma unroll
-  for (int f = 0; f < DH; ++f) { qv[f] = qrow[f] * p.score_mul; o[f] = 0.f; }
-  float m = -INFINITY, l = 0.f;   // softmax form: running maximum and sum of exp(s - m)
-
-  for (int tt = tr.t0; tt < tr.t1; ++tt) {
-    const bool is_sfx = tt >= tr.nkp;
-    const float* src;
-    int key0, seg_end;
-    if (!is_sfx) {
-      src = reinterpret_cast<const float*>(ud.kv) + ud.kv_tile0 + (int64_t)tt * ud.kv_tile_stride +
-            (int64_t)p.layer * ud.kv_layer_stride + (int64_t)head * 2 * kTile * DH;
-      key0 = tt * kTile; seg_end = ud.L;
-    } else {
-      int st = tt - tr.nkp;
-      src = reinterpret_cast<const float*>(p.sfx) + ud.sfx_tile0 + (int64_t)st * (2 * kTile * p.d) +
-            (int64_t)head * 2 * kTile * DH;
-      key0 = ud.L + st * kTile; seg_end = ud.L + ud.S;
-    }
-    __syncthreads();
-    for (int i = t; i < kTile * DH; i += 64) { Ks[i] = src[i]; Vs[i] = src[kTile * DH + i]; }
-    __syncthreads();
-    const int vis = min(lim, seg_end) - key0;  // keys [0, vis) of this tile are visible to this row
-    for (int j = 0; j < kTile; ++j) {
-      float s = 0.f;
-#pragma unroll
-      for (int f = 0; f < DH; ++f) s = fmaf(qv[f], Ks[j * DH + f], s);
-      float pj;
-      if constexpr (SOFTMAX) {
-        if (j < vis && s > m) {        // new maximum: bring what was summed so far to the new reference
-          const float c = __expf(m - s);
-          l *= c;
-#pragma unroll
-          for (int f = 0; f < DH; ++f) o[f] *= c;
-          m = s;
-        }
-        pj = (j < vis) ? __expf(s - m) : 0.f;
-        l += pj;
-      } else {
-        pj = (j < vis) ? silu_f32(s) : 0.f;
-      }
-#pragma unroll
-      for (int f = 0; f < DH; ++f) o[f] = fmaf(pj, Vs[f * kTile + j], o[f]);
-    }
-  }
-  if (active) {
-    float* dst = p.part + split * p.split_stride + (size_t)row * p.d + head * DH;
-#pragma unroll
-    for (int f = 0; f < DH; ++f) dst[f] = o[f];
-    if constexpr (SOFTMAX) {
-      float* mlp = p.ml + split * p.ml_stride + ((size_t)row * p.n_heads + head) * 2;
-      mlp[0] = m; mlp[1] = l;
-    }
-  }
 }
 
 // ---- bf16 MFMA kernel ---------------------------------------------------------------------------

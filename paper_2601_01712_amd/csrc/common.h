@@ -145,12 +145,6 @@ __device__ __forceinline__ void st_stream(uint4* p, uint4 v) { __builtin_nontemp
 __device__ __forceinline__ void st_stream(uint2* p, uint2 v) { __builtin_nontemporal_store(u32x2_t{v.x, v.y}, reinterpret_cast<u32x2_t*>(p)); }
 __device__ __forceinline__ void st_stream(float4* p, float4 v) { __builtin_nontemporal_store(f32x4_t{v.x, v.y, v.z, v.w}, reinterpret_cast<f32x4_t*>(p)); }
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
 // v + (v of the lane the DPP control selects), on the vector ALU (no LDS crossbar round trip).
 template <int CTRL>
 __device__ __forceinline__ float dpp_add(float v) {

@@ -18,6 +18,7 @@
 #include "attention.h"
 #include "common.h"
 #include "errors.h"
+#include "fp32.h"
 #include "gemm.h"
 #include "gemm_bf16.h"
 #include "kv_pool.h"
@@ -95,8 +96,8 @@ struct Plan {
   size_t total = 0;
 };
 
-// Rows per attention work item: 64 (fp32), or 128 * nq for the MFMA kernel, nq in {1, 2}.
-static int rows_per_attn_tile(const relaygr_model_config& c, int nq) { return c.dtype == RELAYGR_DTYPE_FP32 ? 64 : 128 * nq; }
+// Rows per attention work item: 32 (fp32: one wavefront), or 128 * nq for the 16-bit kernel, nq in {1, 2}.
+static int rows_per_attn_tile(const relaygr_model_config& c, int nq) { return c.dtype == RELAYGR_DTYPE_FP32 ? 32 : 128 * nq; }
 
 // Lays the call's buffers out in scratch.  Everything is a function of the counts already in p.
 // Bytes at the start of scratch that hold the weights re-packed into MFMA panels (bf16 only).
@@ -143,6 +144,17 @@ static int wanted_splits(int n_tiles, int n_heads, int min_key_tiles) {
   s = std::min(s, 8);
   s = std::min(s, std::max(1, min_key_tiles));
   return std::max(s, 1);
+}
+
+// fp32: a work item is one wavefront over its part of the keys, and 2048 of them (two a SIMD) fill the chip.  As long as the
+// items alone leave SIMDs idle (under 1024), a workgroup's eight wavefronts share an item's keys (gs = 8), and what is
+// still missing comes from splits of the key range (at most 8, at least one 32-key half tile per wavefront in the mean).
+static void fp32_splits(int64_t items, int64_t half_tiles, int* nsplit, int* gs) {
+  *nsplit = 1;
+  *gs = items < 1024 ? kF32Team : 1;
+  if (items <= 0 || *gs == 1) return;
+  const int64_t by_chip = 2048 / (items * kF32Team), by_keys = half_tiles / (items * kF32Team);
+  *nsplit = (int)std::max<int64_t>(1, std::min<int64_t>({by_chip, by_keys, 8}));
 }
 
 extern "C" size_t relaygr_scratch_bytes(const relaygr_model_config* cfg, int32_t max_users,
@@ -291,14 +303,14 @@ extern "C" int relaygr_ctx_create(const relaygr_model_config* cfg, const relaygr
   }
   // Pinned staging for the per-call descriptor blob, sized once from what the scratch buffer can hold: a call
   // has at most one row per d*4 bytes of call scratch (the residual stream alone takes that), one attention
-  // work item per 64 rows plus two per user, and a buffer sized by relaygr_scratch_bytes for max_users holds
+  // work item per 32 rows plus two per user, and a buffer sized by relaygr_scratch_bytes for max_users holds
   // two K/V tiles per user; calls beyond that are refused (RELAYGR_ENOSPC), so no compute call allocates.
   {
     const size_t call_bytes = scratch_bytes - wpack_bytes(*cfg);
     const size_t d = cfg->d_model, e = elem_bytes(*cfg);
     const size_t rows_est = call_bytes / (d * 4) + 1;
     const size_t users_est = std::min<size_t>(call_bytes / (4 * kTile * d * e) + 1, 1 << 16);
-    const size_t tiles_est = rows_est / 64 + 2 * users_est;
+    const size_t tiles_est = rows_est / 32 + 2 * users_est;
     const size_t want = align_up(users_est * sizeof(UserDesc)) + 2 * align_up((users_est + 1) * 4) + align_up(tiles_est * sizeof(AttnTile));
     for (auto& sl : c->staging) {
       hipError_t e1 = hipHostMalloc(&sl.host, want, hipHostMallocDefault);
@@ -520,36 +532,17 @@ static inline bool dispatch_e(int d, F&& f) {
   return false;
 }
 
-template <typename T> struct GemmLaunch;
-
-template <> struct GemmLaunch<float> {
-  static constexpr int BM = kSgemmBM;
-  template <class Epi>
-  static void run(const float* A, const float* W, int K, int r0, int r1, const ColMap& cm, const Epi& epi, hipStream_t st) {
-    int mt = (r1 - r0 + BM - 1) / BM;
-    int total = mt * cm.nblk * (cm.d / kSgemmBN);
-    hipLaunchKernelGGL((gemm_f32_kernel<Epi>), dim3(total), dim3(256), 0, st, A, W, K, r0, r1, cm, mt, epi);
-  }
-};
-
-// bf16: the MFMA kernels of gemm_bf16.h take parameter blocks instead of functors
-template <> struct GemmLaunch<__hip_bfloat16> {
-  static constexpr int BM = 64 * kF1TM;
-};
-template <> struct GemmLaunch<__half> {
-  static constexpr int BM = 64 * kF1TM;
-};
-
 template <typename T>
 static int launch_attention(const relaygr_model_config& cfg, const AttnParams& ap, int n_tiles, int nq, bool softmax, hipStream_t st);   // ap.gs: groups per workgroup
 
 template <bool SM>
 static int launch_attention_f32(const relaygr_model_config& cfg, const AttnParams& ap, int n_tiles, hipStream_t st) {
-  dim3 grid(n_tiles, cfg.n_heads, ap.nsplit);
+  const int items = n_tiles * cfg.n_heads * ap.nsplit, wgs = ap.gs > 1 ? items : (items + kF32Team - 1) / kF32Team;
+  dim3 grid((wgs + 7) / 8 * 8);
   switch (cfg.d_model / cfg.n_heads) {
-    case 32: hipLaunchKernelGGL((attn_f32_kernel<32, SM>), grid, dim3(64), 0, st, ap); break;
-    case 64: hipLaunchKernelGGL((attn_f32_kernel<64, SM>), grid, dim3(64), 0, st, ap); break;
-    case 128: hipLaunchKernelGGL((attn_f32_kernel<128, SM>), grid, dim3(64), 0, st, ap); break;
+    case 32: hipLaunchKernelGGL((attn_f32_kernel<32, SM>), grid, dim3(kF32Team * 64), 0, st, ap); break;
+    case 64: hipLaunchKernelGGL((attn_f32_kernel<64, SM>), grid, dim3(kF32Team * 64), 0, st, ap); break;
+    case 128: hipLaunchKernelGGL((attn_f32_kernel<128, SM>), grid, dim3(kF32Team * 64), 0, st, ap); break;
     default: return fail(RELAYGR_EINVAL, "attention: unsupported d_head");
   }
   LAUNCH_CHECK("attn_f32");
@@ -728,6 +721,12 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
   // sums in LDS -- half the partial sums for the layer tail to read -- where that still gives every compute unit a
   // workgroup (with fewer, e.g. one user with 512 candidates, the attention launch itself gets 25 % slower)
   p.gs = 1;
+  if (!bf16) {
+    int64_t halves = 0;
+    for (const AttnTile& a : tiles_new) halves += 2 * key_tiles(a);
+    for (const AttnTile& a : tiles_prefix) halves += 2 * key_tiles(a);
+    fp32_splits((int64_t)n_tiles_all * H, halves * H, &p.nsplit, &p.gs);
+  }
   if (bf16 && dh == 64 && p.nsplit % 2 == 0 &&
       (int64_t)n_tiles_all * H * (p.nsplit / 2) >= c->n_cus) {
     p.gs = 2;
@@ -780,33 +779,17 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
   const int32_t* d_ns = (const int32_t*)(db + o_ns);
   const AttnTile* d_tiles = (const AttnTile*)(db + o_tiles);
 
-  {
-  ProfScope ps(c, RELAYGR_K_SETUP, st);
-  // (the row tables are built by the first layer's input LayerNorm kernel, which visits every row anyway)
-  if (p.n_prows && std::is_same<T, float>::value) {   // the bf16 f1 epilogue zero-fills the ragged tail itself
-    hipLaunchKernelGGL((zero_kv_tail_kernel<T>), dim3(n), dim3(256), 0, st, d_users, n, NL, H, dh);
-    LAUNCH_CHECK("zero_kv_tail");
-  }
-  if (p.sfx_tiles) {
-    hipLaunchKernelGGL((zero_suffix_tail_kernel<T>), dim3(n), dim3(256), 0, st, d_users, n, sfx, H, dh);
-    LAUNCH_CHECK("zero_suffix_tail");
-  }
-  }
-
   const float alpha = 1.0f / sqrtf((float)dh);
   const float kLog2e = 1.4426950408889634f, kLn2 = 0.69314718055994531f;
   const float q_mul = bf16 ? alpha * kLog2e : 1.0f;       // what f1 multiplies q by before storing it
   const float score_mul = bf16 ? 1.0f : alpha;            // what the attention kernel still applies
-  const float gate_mul = bf16 ? kLn2 : alpha;             // stored q . k  ->  alpha <q,k> for the self term
+  const float gate_mul = kLn2;                            // 16-bit: stored q . k  ->  alpha <q,k> for the self term
   const T* emb_p = (const T*)b->prefix_emb;
   const T* emb_s = (const T*)b->suffix_emb;
   const T* emb_c = (const T*)b->cand_emb;
   const int R = p.n_rows;
   constexpr bool kPanel = !std::is_same<T, float>::value;   // bf16: xh / y are written as MFMA panels
 
-  // 16-bit types: one row-local kernel per layer takes everything between the attention and the next
-  // layer's projections (combine, gate, output projection, residual, next input LayerNorm, score head)
-  constexpr bool fuse_ln = kPanel;
   for (int l = 0; l < NL; ++l) {
     const relaygr_layer_weights& lw = c->layers[l];
     const bool last = (l == NL - 1);
@@ -814,20 +797,19 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
     const int a0 = last ? p.n_prows : 0;
     const bool have_active = a0 < R;
 
-    // step 1: input LayerNorm (first layer also gathers the embeddings into the residual stream);
-    // later layers of the fused bf16 path got it from the previous layer's output projection
-    if (l == 0 || !fuse_ln) {
+    // step 1: input LayerNorm of the first layer, with the gather of the embeddings into the residual stream, the row
+    // tables and the cleared tail tiles; later layers get theirs from the previous layer's tail kernel
+    if (l == 0) {
       ProfScope ps(c, RELAYGR_K_LN, st);
-      dim3 grid((R + kRowsPerBlock - 1) / kRowsPerBlock);
+      const RowBuild rb = {d_users, d_ps, d_ns, n, p.n_prows};
+      TailClear tc = {(R + kRowsPerBlock - 1) / kRowsPerBlock, H, dh, 0, p.sfx_tiles ? (void*)sfx : nullptr};
+      if (!bf16 && p.n_prows) tc.kv_layers = NL;   // the 16-bit projection fills a prefix's ragged tail itself
+      const bool clear = tc.kv_layers > 0 || tc.sfx != nullptr;
+      dim3 grid(tc.row_blocks + (clear ? n * (tc.kv_layers + 1) * H : 0));
       bool ok = dispatch_e(d, [&](auto e) {
         constexpr int E = decltype(e)::value;
-        const RowBuild rb = {d_users, d_ps, d_ns, n, p.n_prows};
-        if (l == 0)
-          hipLaunchKernelGGL((ln_in_kernel<T, E, true, kPanel>), grid, dim3(256), 0, st, x, xh, (const T*)lw.ln_in_g, (const T*)lw.ln_in_b,
-                             emb_p, emb_s, emb_c, rt, rb, 0, R, cfg.ln_eps);
-        else if constexpr (!fuse_ln)
-          hipLaunchKernelGGL((ln_in_kernel<T, E, false, kPanel>), grid, dim3(256), 0, st, x, xh, (const T*)lw.ln_in_g, (const T*)lw.ln_in_b,
-                             emb_p, emb_s, emb_c, rt, rb, 0, R, cfg.ln_eps);
+        hipLaunchKernelGGL((ln_in_kernel<T, E, kPanel>), grid, dim3(256), 0, st, x, xh, (const T*)lw.ln_in_g, (const T*)lw.ln_in_b,
+                           emb_p, emb_s, emb_c, rt, rb, tc, R, cfg.ln_eps);
       });
       if (!ok) return fail(RELAYGR_EINVAL, "unsupported d_model");
       LAUNCH_CHECK("ln_in");
@@ -836,10 +818,18 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
     ColMap all4 = {4, {0, 1, 2, 3}, d}, kv_only = {2, {1, 3, 0, 0}, d};
     auto run_f1 = [&](int r0, int r1, const ColMap& cm) {
       if constexpr (std::is_same<T, float>::value) {
-        F1Epilogue<T> e1;
-        e1.bias = (const T*)lw.b1; e1.u = ubuf; e1.q = qbuf; e1.knew = knew; e1.vnew = vnew; e1.sfx = sfx;
-        e1.users = d_users; e1.rt = rt; e1.d = d; e1.dh = dh; e1.n_prows = p.n_prows; e1.layer = l; e1.q_mul = q_mul;
-        GemmLaunch<T>::run(xh, (const T*)lw.w1, d, r0, r1, cm, e1, st);
+        F1F32Params fp;
+        fp.A = xh; fp.W = (const float*)lw.w1; fp.bias = (const float*)lw.b1; fp.u = ubuf; fp.q = qbuf; fp.knew = knew; fp.vnew = vnew; fp.sfx = sfx;
+        fp.users = d_users; fp.rt = rt; fp.d = d; fp.dh = dh; fp.n_prows = p.n_prows; fp.layer = l; fp.row_begin = r0; fp.row_end = r1; fp.cm = cm;
+        // 128 x 128 tiles once they give every compute unit one, 64 x 64 while those do, 32 x 32 with k cut in four below
+        const int64_t cols = (int64_t)cm.nblk * d;
+        auto tiles = [&](int t) { return (int64_t)((r1 - r0 + t - 1) / t) * (cols / t); };
+        const int tile = (d % 128 == 0 && tiles(128) >= 512) ? 128 : tiles(64) >= 512 ? 64 : 32;
+        fp.n_mtiles = (r1 - r0 + tile - 1) / tile;
+        const dim3 grid((tiles(tile) + 7) / 8 * 8);
+        if (tile == 128) hipLaunchKernelGGL((f1_f32_kernel<2, false>), grid, dim3(256), 0, st, fp);
+        else if (tile == 64) hipLaunchKernelGGL((f1_f32_kernel<1, false>), grid, dim3(256), 0, st, fp);
+        else hipLaunchKernelGGL((f1_f32_kernel<1, true>), grid, dim3(256), 0, st, fp);
       } else {
         F1Params fp;
         fp.A = (const uint16_t*)xh; fp.W = c->w1_packed[l]; fp.bias = (const uint16_t*)lw.b1;
@@ -896,37 +886,25 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
       rc = launch_attention<T>(cfg, ap, nt, nq, softmax, st);
       if (rc != RELAYGR_OK) return rc;
     }
-    // softmax form: merge the key splits and the candidate's own key into the finished o (in part[0]);
-    // the fused 16-bit tail kernel does this merge itself
-    if constexpr (!fuse_ln) if (softmax) {
-      ProfScope ps(c, RELAYGR_K_GATE, st);
-      dim3 grid((R - a0 + kRowsPerBlock - 1) / kRowsPerBlock);
-      dispatch_e(d, [&](auto e) {
-        constexpr int E = decltype(e)::value;
-        hipLaunchKernelGGL((softmax_combine_kernel<T, E>), grid, dim3(256), 0, st, part, ml, p.nsplit, (size_t)R * d, (size_t)R * H * 2,
-                           qbuf, knew, vnew, rt, p.n_prows, a0, R, dh, H, bf16 ? 1.0f : alpha, bf16 ? 1.0f : kLog2e);
-      });
-      LAUNCH_CHECK("softmax_combine");
-    }
-    // steps 3-4: combine splits, self term, 1/n, LayerNorm, gate by u (part of the fused kernel below otherwise)
-    if constexpr (!fuse_ln) {
-      ProfScope ps(c, RELAYGR_K_GATE, st);
-      dim3 grid((R - a0 + kRowsPerBlock - 1) / kRowsPerBlock);
-      dispatch_e(d, [&](auto e) {
-        constexpr int E = decltype(e)::value;
-        hipLaunchKernelGGL((attn_gate_kernel<T, E, kPanel>), grid, dim3(256), 0, st, part, p.nsplit, (size_t)R * d, ubuf, qbuf, knew, vnew, xh,
-                           (const T*)lw.ln_at_g, (const T*)lw.ln_at_b, rt, p.n_prows, a0, R, dh, gate_mul, cfg.ln_eps, softmax ? 1 : 0);
-      });
-      LAUNCH_CHECK("attn_gate");
-    }
-    // step 4: output projection and residual
+    // steps 3-4: combine, self term, 1/n, LayerNorm, gate, output projection, residual, next LayerNorm or score head
     {
       ProfScope ps(c, RELAYGR_K_F2, st);
       if constexpr (std::is_same<T, float>::value) {
-        F2Epilogue<T> e2;
-        e2.bias = (const T*)lw.b2; e2.x = x; e2.d = d;
-        ColMap one = {1, {0, 0, 0, 0}, d};
-        GemmLaunch<T>::run(xh, (const T*)lw.w2, d, a0, R, one, e2, st);
+        TailF32Params fp;
+        fp.part = part; fp.nsplit = p.nsplit; fp.split_stride = (size_t)R * d; fp.ml = ml; fp.ml_stride = (size_t)R * H * 2; fp.n_heads = H;
+        fp.u = ubuf; fp.q = qbuf; fp.knew = knew; fp.vnew = vnew; fp.gate_gain = (const float*)lw.ln_at_g; fp.gate_offs = (const float*)lw.ln_at_b;
+        fp.W = (const float*)lw.w2; fp.bias = (const float*)lw.b2; fp.x = x; fp.xh = last ? nullptr : xh;
+        fp.gain = (const float*)(last ? c->ln_out_g : c->layers[l + 1].ln_in_g);
+        fp.offs = (const float*)(last ? c->ln_out_b : c->layers[l + 1].ln_in_b);
+        fp.rt = rt; fp.n_prows = p.n_prows; fp.dh = dh; fp.row_begin = a0; fp.row_end = R; fp.alpha = alpha; fp.eps = cfg.ln_eps;
+        fp.w_score = (const float*)c->w_score; fp.b_score = c->b_score; fp.scores = last && mode != kPrefill ? scores : nullptr;
+        const dim3 grid((R - a0 + 15) / 16);
+        dispatch_e(d, [&](auto e) {
+          constexpr int D = 64 * decltype(e)::value;
+          constexpr int threads = D >= 256 ? 1024 : D * 4;
+          if (softmax) hipLaunchKernelGGL((tail_f32_kernel<D, true>), grid, dim3(threads), 0, st, fp);
+          else hipLaunchKernelGGL((tail_f32_kernel<D, false>), grid, dim3(threads), 0, st, fp);
+        });
       } else {
         {
           F2LnParams fp;
@@ -982,16 +960,6 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
     LAUNCH_CHECK("f2");
   }
 
-  if constexpr (!fuse_ln) if (mode != kPrefill && p.n_nrows) {   // the fused 16-bit tail kernel has written the scores already
-    ProfScope ps(c, RELAYGR_K_SCORE, st);
-    dim3 grid((p.n_nrows + kRowsPerBlock - 1) / kRowsPerBlock);
-    dispatch_e(d, [&](auto e) {
-      constexpr int E = decltype(e)::value;
-      hipLaunchKernelGGL((score_kernel<T, E>), grid, dim3(256), 0, st, x, (const T*)c->ln_out_g, (const T*)c->ln_out_b,
-                         (const T*)c->w_score, c->b_score, rt, p.n_prows, R, cfg.ln_eps, scores);
-    });
-    LAUNCH_CHECK("score");
-  }
   return RELAYGR_OK;
 }
 

@@ -1,0 +1,485 @@
+// The fp32 path's kernels on the fp32 matrix instructions (v_mfma_f32_32x32x2_f32 / 16x16x4_f32: full fp32 products and
+// sums): attention, the u|v|q|k projection, and the layer tail.  One idea is common to all three.  An fp32 fragment is
+// one float per lane and k-step, so a lane would have to load single floats; but the order in which a contraction walks
+// k is free as long as both operands agree, and with MFMA t of a group of four taking k = 8m + 4g + t (32-row form; g the
+// lane's half) a lane's operands for four MFMAs are four consecutive floats of one row: one 16-byte load straight from
+// row-major memory, no staging, no barrier.  The rows a wavefront reads come back through L1 over the next loads (a row's
+// 128-byte line feeds four of them), and at 64 cycles per MFMA a wavefront asks for at most 2 KiB per 256 cycles.
+#pragma once
+
+#include "attention.h"
+#include "common.h"
+#include "gemm.h"
+#include "rowwise.h"
+
+namespace relaygr {
+
+typedef float f32x4v_t __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ f32x16_t mfma32_f32(float a, float b, f32x16_t c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
+__device__ __forceinline__ f32x4v_t mfma16_f32(float a, float b, f32x4v_t c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+__device__ __forceinline__ float f4_at(const float4& v, int i) { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; }
+
+// ---- attention ------------------------------------------------------------------------------------
+// A wavefront owns 32 rows of one user and head and a range of 32-key half tiles:
+//   S^T[32 keys][32 rows] = K (rows of the MFMA) x Q^T, P = SiLU(S) on the vector ALU, O^T += V^T x P^T,
+// where the accumulator of S^T (lane = row, keys 8*(e/4) + 4g + e%4) is element by element the operand of the second
+// product, and V is stored transposed, so that its operand is again 16 consecutive bytes.  Every operand is loaded
+// straight from the K/V tile; the loads of a half tile's V and of the next one's K are issued a product (2048 cycles at
+// d_head 64) before they are needed.  Nothing is shared, so nothing waits: two wavefronts a SIMD, one's SiLU beside the
+// other's products.  Bound by the matrix pipe: 8 cycles per score element at d_head 64 against about 4.5 of vector ALU.
+// gs = 8: the eight wavefronts of a workgroup take the same rows and consecutive parts of the keys and add their sums
+// in LDS (in a fixed order): calls of few rows fill the chip without writing a partial sum for every part.
+constexpr int kF32Team = 8;
+template <int DH, bool SOFTMAX>
+__global__ __launch_bounds__(kF32Team * 64, 2) void attn_f32_kernel(AttnParams p) {
+  constexpr int KM = DH / 8, DB = DH / 32;
+  constexpr int NT = kF32Team;
+  __shared__ float4 xch[NT][DB * 4][64];             // the team's sums, 4 elements a slot
+  __shared__ float2 xml[SOFTMAX ? NT : 1][SOFTMAX ? 64 : 1];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, g = lane >> 5;
+  const bool team = p.gs > 1;
+  const int total = p.n_tiles * p.n_heads * p.nsplit;
+  const int n_wg = team ? total : (total + NT - 1) / NT;
+  const int wg = xcd_remap(blockIdx.x, n_wg);
+  if (wg >= n_wg) return;
+  const int item = team ? wg : wg * NT + wave;
+  if (item >= total) return;                         // (only without a team, where no wavefront meets a barrier)
+  const int tile_i = item % p.n_tiles, hs = item / p.n_tiles;
+  const int head = hs % p.n_heads, split_ext = hs / p.n_heads;
+  const AttnTile at = p.tiles[tile_i];
+  const UserDesc ud = p.users[at.user];
+  // half tiles this item sees: [prefix | suffix], and this wavefront's part of them
+  const int n_hp = ((at.kind == 0 ? at.pos0 + at.nrows : ud.L) + 31) >> 5;
+  const int n_h = n_hp + (at.kind == 0 ? 0 : (ud.S + 31) >> 5);
+  const int parts = team ? p.nsplit * NT : p.nsplit, part_i = team ? split_ext * NT + wave : split_ext;
+  const int per = (n_h + parts - 1) / parts;
+  const int h0 = min(part_i * per, n_h), h1 = min(h0 + per, n_h);
+
+  const bool ok = l32 < at.nrows;
+  const int row = at.row0 + (ok ? l32 : 0);
+  const int lim = ok ? p.rt.lim[row] : 0;
+  const float* kv = reinterpret_cast<const float*>(ud.kv) + ud.kv_tile0 + (int64_t)p.layer * ud.kv_layer_stride + (int64_t)head * 2 * kTile * DH;
+  const float* sf = reinterpret_cast<const float*>(p.sfx) + ud.sfx_tile0 + (int64_t)head * 2 * kTile * DH;
+  auto tile_of = [&](int h) -> const float* {        // start of the tile half h lies in
+    return h < n_hp ? kv + (int64_t)(h >> 1) * ud.kv_tile_stride : sf + (int64_t)((h - n_hp) >> 1) * (2 * kTile * p.d);
+  };
+  auto half_of = [&](int h) { return (h < n_hp ? h : h - n_hp) & 1; };
+  float4 kf[KM], vf[DB][4], qf[KM];
+  auto load_k = [&](int h) {
+    const float* src = tile_of(h) + (half_of(h) * 32 + l32) * DH + 4 * g;
+#pragma unroll
+    for (int m = 0; m < KM; ++m) kf[m] = *reinterpret_cast<const float4*>(src + 8 * m);
+  };
+  auto load_v = [&](int h) {
+    const float* src = tile_of(h) + kTile * DH + l32 * kTile + half_of(h) * 32 + 4 * g;
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int e4 = 0; e4 < 4; ++e4) vf[db][e4] = *reinterpret_cast<const float4*>(src + db * 32 * kTile + 8 * e4);
+  };
+  f32x16_t o[DB];
+#pragma unroll
+  for (int db = 0; db < DB; ++db)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) o[db][e] = 0.f;
+  float mref = -INFINITY, lsum = 0.f;                // softmax form: running maximum, this lane's sum of exp(s - m)
+
+  constexpr bool AHEAD = DH < 128;                   // d_head 128: K and V fragments take turns in the registers
+  if (h0 < h1) {
+    if constexpr (AHEAD) load_k(h0);
+    const float* qrow = reinterpret_cast<const float*>(p.q) + (size_t)row * p.d + head * DH + 4 * g;
+#pragma unroll
+    for (int m = 0; m < KM; ++m) {
+      const float4 q = *reinterpret_cast<const float4*>(qrow + 8 * m);
+      qf[m] = make_float4(q.x * p.score_mul, q.y * p.score_mul, q.z * p.score_mul, q.w * p.score_mul);
+    }
+    for (int h = h0; h < h1; ++h) {
+      if constexpr (AHEAD) load_v(h);
+      else load_k(h);
+      f32x16_t s;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) s[e] = 0.f;
+#pragma unroll
+      for (int m = 0; m < KM; ++m)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) s = mfma32_f32(f4_at(kf[m], t), f4_at(qf[m], t), s);
+      if constexpr (!AHEAD) load_v(h);
+      else if (h + 1 < h1) load_k(h + 1);
+      const bool is_sfx = h >= n_hp;
+      const int key0 = is_sfx ? ud.L + (h - n_hp) * 32 : h * 32;
+      const int vis = min(lim, is_sfx ? ud.L + ud.S : ud.L) - key0 - 4 * g;   // element e is visible iff 8*(e/4) + e%4 < vis
+      if constexpr (SOFTMAX) {
+        float mx = -INFINITY;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) mx = fmaxf(mx, (8 * (e >> 2) + (e & 3) < vis) ? s[e] : -INFINITY);
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));      // the two lanes of a row share one reference
+        const float mn = fmaxf(mref, mx);
+        if (__builtin_amdgcn_ballot_w64(mn > mref)) {
+          const float c = mn == mref ? 1.0f : __expf(mref - mn);
+          lsum *= c;
+#pragma unroll
+          for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) o[db][e] *= c;
+          mref = mn;
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const bool see = 8 * (e >> 2) + (e & 3) < vis;
+        float pe = SOFTMAX ? __expf(s[e] - mref) : silu_f32(s[e]);
+        pe = see ? pe : 0.f;
+        if constexpr (SOFTMAX) lsum += pe;
+        s[e] = pe;
+      }
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+#pragma unroll
+        for (int db = 0; db < DB; ++db) o[db] = mfma32_f32(f4_at(vf[db][e >> 2], e & 3), s[e], o[db]);
+    }
+  }
+  if constexpr (SOFTMAX) lsum += __shfl_xor(lsum, 32, 64);
+  float* dst = p.part + split_ext * p.split_stride + (size_t)row * p.d + head * DH + 4 * g;
+  float* mlp = p.ml + split_ext * p.ml_stride + ((size_t)row * p.n_heads + head) * 2;
+  if (!team) {
+    if (!ok) return;
+    if constexpr (SOFTMAX) {
+      if (g == 0) *reinterpret_cast<float2*>(mlp) = make_float2(mref, lsum);
+    }
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int e4 = 0; e4 < 4; ++e4)
+        *reinterpret_cast<float4*>(dst + db * 32 + 8 * e4) = make_float4(o[db][4 * e4], o[db][4 * e4 + 1], o[db][4 * e4 + 2], o[db][4 * e4 + 3]);
+    return;
+  }
+#pragma unroll
+  for (int db = 0; db < DB; ++db)
+#pragma unroll
+    for (int e4 = 0; e4 < 4; ++e4) xch[wave][db * 4 + e4][lane] = make_float4(o[db][4 * e4], o[db][4 * e4 + 1], o[db][4 * e4 + 2], o[db][4 * e4 + 3]);
+  if constexpr (SOFTMAX) xml[wave][lane] = make_float2(mref, lsum);
+  __syncthreads();
+  if (!ok) return;
+  float w[NT];                                       // softmax form: what brings the sums to their common maximum
+  if constexpr (SOFTMAX) {
+    float M = -INFINITY, l = 0.f;
+#pragma unroll
+    for (int k = 0; k < NT; ++k) M = fmaxf(M, xml[k][lane].x);
+#pragma unroll
+    for (int k = 0; k < NT; ++k) {
+      const float2 t = xml[k][lane];
+      w[k] = t.x == -INFINITY ? 0.f : __expf(t.x - M);
+      l += w[k] * t.y;
+    }
+    if (wave == 0 && g == 0) *reinterpret_cast<float2*>(mlp) = make_float2(M, l);
+  }
+  for (int c = wave; c < DB * 4; c += NT) {          // each wavefront adds up its share of the features
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int k = 0; k < NT; ++k) {
+      const float4 t = xch[k][c][lane];
+      const float wk = SOFTMAX ? w[k] : 1.0f;
+      v.x += wk * t.x; v.y += wk * t.y; v.z += wk * t.z; v.w += wk * t.w;
+    }
+    *reinterpret_cast<float4*>(dst + (c >> 2) * 32 + 8 * (c & 3)) = v;
+  }
+}
+
+// ---- u | v | q | k projection: SiLU(xh W1^T + b1) and where it goes ---------------------------------
+struct F1F32Params {
+  const float* A;            // xh [rows, d]
+  const float* W;            // W1 [4d, d]
+  const float* bias;
+  float* u; float* q; float* knew; float* vnew; float* sfx;
+  const UserDesc* users;
+  RowTables rt;
+  int d, dh, n_prows, layer, row_begin, row_end, n_mtiles;
+  ColMap cm;
+};
+
+// Stores the four values of rows r0 .. r0+3 in feature c of block blk (0 u, 1 v, 2 q, 3 k).
+__device__ __forceinline__ void f1_f32_store(const F1F32Params& p, int blk, int c, int r0, const float (&v)[4]) {
+  const int head = c / p.dh, f = c - head * p.dh;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int r = r0 + i;
+    if (r >= p.row_end) return;
+    if (blk == 0 || blk == 2) { (blk == 0 ? p.u : p.q)[(size_t)r * p.d + c] = v[i]; continue; }
+    const int kind = p.rt.kind[r];
+    if (kind == kRowCand) { (blk == 3 ? p.knew : p.vnew)[(size_t)(r - p.n_prows) * p.d + c] = v[i]; continue; }
+    const UserDesc& ud = p.users[p.rt.user[r]];
+    const int idx = p.rt.idx[r], rr = idx % kTile;
+    float* base = kind == kRowPrefix ? const_cast<float*>(reinterpret_cast<const float*>(ud.kv)) + ud.kv_tile0 + (int64_t)(idx / kTile) * ud.kv_tile_stride +
+                                           (int64_t)p.layer * ud.kv_layer_stride
+                                     : p.sfx + ud.sfx_tile0 + (int64_t)(idx / kTile) * (2 * kTile * p.d);
+    base += (int64_t)head * 2 * kTile * p.dh;
+    base[blk == 3 ? KvLayout<float>::k_off(rr, f, p.dh) : KvLayout<float>::v_off(rr, f, p.dh)] = v[i];
+  }
+}
+
+// A wavefront multiplies 32*TB tokens by 32*TB features over k, operands straight from row-major memory, PF groups of 8 k
+// in flight.  KSPLIT = false: four wavefronts as 2 x 2 such blocks, each over the whole of k.  KSPLIT = true (TB = 1): the four
+// take a quarter of k each of ONE 32 x 32 block and add in LDS -- for launches of a few hundred rows, where it is the
+// length of the k loop that counts (64 cycles an MFMA, k/2 of them: 3.4 us at d = 256) and not the traffic.
+template <int TB, bool KSPLIT>
+__global__ __launch_bounds__(256, TB == 1 ? 4 : 2) void f1_f32_kernel(F1F32Params p) {
+  constexpr int PF = KSPLIT ? 4 : 2, WG = KSPLIT ? 32 : 64 * TB;  // tokens (and features) of a workgroup
+  __shared__ float red[KSPLIT ? 4 : 1][KSPLIT ? 16 : 1][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, g = lane >> 5;
+  const int nt_blk = p.cm.d / WG, n_nt = p.cm.nblk * nt_blk, total = p.n_mtiles * n_nt;
+  const int logical = xcd_remap(blockIdx.x, total);
+  if (logical >= total) return;
+  const int mt = logical / n_nt, nt = logical - mt * n_nt;
+  const int blk = p.cm.blk[nt / nt_blk];
+  const int m0 = p.row_begin + mt * WG + (KSPLIT ? 0 : (wave >> 1) * 32 * TB);
+  const int c0 = (nt % nt_blk) * WG + (KSPLIT ? 0 : (wave & 1) * 32 * TB);   // first feature inside the block
+  const int k_len = KSPLIT ? p.d >> 2 : p.d, k0 = KSPLIT ? wave * k_len : 0;
+  const float *a[TB], *w[TB];
+#pragma unroll
+  for (int i = 0; i < TB; ++i) {
+    a[i] = p.A + (size_t)min(m0 + 32 * i + l32, p.row_end - 1) * p.d + k0 + 4 * g;
+    w[i] = p.W + (size_t)(blk * p.d + c0 + 32 * i + l32) * p.d + k0 + 4 * g;
+  }
+  f32x16_t acc[TB][TB];                              // tokens x features: lane = feature, tokens 8*(e/4) + 4g + e%4
+#pragma unroll
+  for (int i = 0; i < TB; ++i)
+#pragma unroll
+    for (int j = 0; j < TB; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+  float4 af[PF][TB], wf[PF][TB];
+  auto load = [&](int s, int k) {
+#pragma unroll
+    for (int i = 0; i < TB; ++i) { af[s][i] = *reinterpret_cast<const float4*>(a[i] + k); wf[s][i] = *reinterpret_cast<const float4*>(w[i] + k); }
+  };
+#pragma unroll
+  for (int s = 0; s < PF; ++s)
+    if (8 * s < k_len) load(s, 8 * s);
+  for (int k = 0; k < k_len; k += 8 * PF) {
+#pragma unroll
+    for (int s = 0; s < PF; ++s) {
+      if (k + 8 * s >= k_len) break;                 // (k_len is a multiple of 16)
+      float4 ca[TB], cw[TB];
+#pragma unroll
+      for (int i = 0; i < TB; ++i) { ca[i] = af[s][i]; cw[i] = wf[s][i]; }
+      if (k + 8 * (s + PF) < k_len) load(s, k + 8 * (s + PF));
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int i = 0; i < TB; ++i)
+#pragma unroll
+          for (int j = 0; j < TB; ++j) acc[i][j] = mfma32_f32(f4_at(ca[i], t), f4_at(cw[j], t), acc[i][j]);
+    }
+  }
+  if constexpr (KSPLIT) {
+#pragma unroll
+    for (int e = 0; e < 16; ++e) red[wave][e][lane] = acc[0][0][e];
+    __syncthreads();
+    float v[4];
+    const float b = p.bias[blk * p.d + c0 + l32];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int e = 4 * wave + i;                    // this wavefront finishes tokens 8*wave + 4g + i
+      v[i] = silu_f32(((red[0][e][lane] + red[1][e][lane]) + (red[2][e][lane] + red[3][e][lane])) + b);
+    }
+    f1_f32_store(p, blk, c0 + l32, m0 + 8 * wave + 4 * g, v);
+  } else {
+#pragma unroll
+    for (int j = 0; j < TB; ++j) {
+      const int c = c0 + 32 * j + l32;
+      const float b = p.bias[blk * p.d + c];
+#pragma unroll
+      for (int i = 0; i < TB; ++i)
+#pragma unroll
+        for (int e4 = 0; e4 < 4; ++e4) {
+          float v[4];
+#pragma unroll
+          for (int x = 0; x < 4; ++x) v[x] = silu_f32(acc[i][j][4 * e4 + x] + b);
+          f1_f32_store(p, blk, c, m0 + 32 * i + 8 * e4 + 4 * g, v);
+        }
+    }
+  }
+}
+
+// ---- layer tail: combine, gate, output projection, residual, next LayerNorm or score head ------------
+// As in the 16-bit path everything between the attention and the next projections is local to a row: a workgroup takes 16
+// rows over the full width.  A wavefront gates 16/NW rows (lane = d/64 features) into LDS; the product is feature-major
+// (16x16x4: a lane ends up with 4 consecutive features of one token), W2 streamed from L2 straight into registers, PF
+// groups of 16 k ahead; LayerNorm statistics by two lane exchanges and one exchange between wavefronts.
+struct TailF32Params {
+  const float* part; int nsplit; size_t split_stride;
+  const float* ml; size_t ml_stride; int n_heads;   // softmax form
+  const float* u; const float* q; const float* knew; const float* vnew;
+  const float *gate_gain, *gate_offs;
+  const float *W, *bias;     // W2 [d, d], b2
+  float* x;                  // residual stream, updated in place
+  float* xh;                 // LN(x) for the next layer; nullptr: none wanted
+  const float *gain, *offs;  // next layer's input LayerNorm, or the score head's
+  RowTables rt;
+  int n_prows, dh, row_begin, row_end;
+  float alpha, eps;
+  const float* w_score; float b_score; float* scores;   // last layer of a ranking call
+};
+
+template <int D, bool SM>
+__global__ __launch_bounds__(D >= 256 ? 1024 : D * 4) void tail_f32_kernel(TailF32Params p) {
+  constexpr int E = D / 64, NW = D >= 256 ? 16 : D / 16, FB = D / 16 / NW, MS = D / 16, PF = FB >= 4 ? 2 : FB == 2 ? 4 : MS >= 8 ? 8 : 4, RPW = 16 / NW, YS = D + 4;
+  __shared__ float ys[16][YS];                       // rows 16 bytes apart in banks: 16 lanes' 16-byte reads take 64 banks
+  __shared__ float red[3][NW][16];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int row0 = p.row_begin + blockIdx.x * 16;
+  const int tk = lane & 15, g4 = lane >> 4;
+  // first weight fragments: they depend on nothing
+  const float* w[FB];
+#pragma unroll
+  for (int j = 0; j < FB; ++j) w[j] = p.W + (size_t)((wave * FB + j) * 16 + tk) * D + 4 * g4;
+  float4 wf[PF][FB];
+#pragma unroll
+  for (int s = 0; s < PF; ++s)
+#pragma unroll
+    for (int j = 0; j < FB; ++j) wf[s][j] = *reinterpret_cast<const float4*>(w[j] + 16 * s);
+
+#pragma unroll
+  for (int rr = 0; rr < RPW; ++rr) {
+    const int lr = wave * RPW + rr, r = row0 + lr;
+    float* yrow = &ys[lr][lane * E];
+    if (r >= p.row_end) {
+#pragma unroll
+      for (int i = 0; i < E; ++i) yrow[i] = 0.f;
+      continue;
+    }
+    const size_t base = (size_t)r * D + lane * E;
+    const int kind = p.rt.kind[r];
+    float o[E], ug[E];
+#pragma unroll
+    for (int i = 0; i < E; ++i) { o[i] = 0.f; ug[i] = p.u[base + i]; }
+    float n = (float)p.rt.lim[r], tself = 0.f;
+    float vs[E];
+    const bool cand = kind == kRowCand;
+    if (cand) {
+      const size_t nb = (size_t)(r - p.n_prows) * D + lane * E;
+      float dot = 0.f;
+#pragma unroll
+      for (int i = 0; i < E; ++i) { dot += p.q[base + i] * p.knew[nb + i]; vs[i] = p.vnew[nb + i]; }
+      for (int m = (p.dh / E) >> 1; m > 0; m >>= 1) dot += __shfl_xor(dot, m, 64);   // lanes of one head are consecutive
+      tself = dot * p.alpha;
+    }
+    if constexpr (SM) {
+      // splits and the own key by weights exp(m_s - M)
+      const float* mlr = p.ml + ((size_t)r * p.n_heads + lane * E / p.dh) * 2;
+      float M = cand ? tself : -INFINITY, l = 0.f;
+      for (int s = 0; s < p.nsplit; ++s) M = fmaxf(M, mlr[s * p.ml_stride]);
+      for (int s = 0; s < p.nsplit; ++s) {
+        const float ms = mlr[s * p.ml_stride], wt = ms == -INFINITY ? 0.f : __expf(ms - M);
+        l += wt * mlr[s * p.ml_stride + 1];
+#pragma unroll
+        for (int i = 0; i < E; ++i) o[i] += wt * p.part[s * p.split_stride + base + i];
+      }
+      if (cand) {
+        const float wt = __expf(tself - M);
+        l += wt;
+#pragma unroll
+        for (int i = 0; i < E; ++i) o[i] += wt * vs[i];
+      }
+      n = l;
+    } else {
+      for (int s = 0; s < p.nsplit; ++s)
+#pragma unroll
+        for (int i = 0; i < E; ++i) o[i] += p.part[s * p.split_stride + base + i];
+      if (cand) {
+        const float pe = silu_f32(tself);
+#pragma unroll
+        for (int i = 0; i < E; ++i) o[i] += pe * vs[i];
+        n += 1.0f;
+      }
+    }
+    const float inv_n = 1.0f / n;
+#pragma unroll
+    for (int i = 0; i < E; ++i) o[i] *= inv_n;
+    float mean, rstd;
+    ln_stats<E>(o, D, p.eps, mean, rstd);
+#pragma unroll
+    for (int i = 0; i < E; ++i) yrow[i] = ((o[i] - mean) * rstd * p.gate_gain[lane * E + i] + p.gate_offs[lane * E + i]) * ug[i];
+  }
+  // the accumulators start from the residual row and the bias: element e of acc[j] is feature (wave*FB + j)*16 + 4*g4 + e
+  const int row = row0 + tk;
+  const bool live = row < p.row_end;
+  float* xrow = p.x + (size_t)(live ? row : row0) * D;
+  f32x4v_t acc[FB];
+#pragma unroll
+  for (int j = 0; j < FB; ++j) {
+    const int c = (wave * FB + j) * 16 + 4 * g4;
+    const float4 xv = *reinterpret_cast<const float4*>(xrow + c), bv = *reinterpret_cast<const float4*>(p.bias + c);
+    acc[j] = f32x4v_t{xv.x + bv.x, xv.y + bv.y, xv.z + bv.z, xv.w + bv.w};
+  }
+  __syncthreads();
+  const float* yl = &ys[tk][4 * g4];
+  for (int m0 = 0; m0 < MS; m0 += PF) {
+#pragma unroll
+    for (int s = 0; s < PF; ++s) {
+      const float4 y = *reinterpret_cast<const float4*>(yl + 16 * (m0 + s));
+      float4 cw[FB];
+#pragma unroll
+      for (int j = 0; j < FB; ++j) cw[j] = wf[s][j];
+      if (m0 + s + PF < MS) {
+#pragma unroll
+        for (int j = 0; j < FB; ++j) wf[s][j] = *reinterpret_cast<const float4*>(w[j] + 16 * (m0 + s + PF));
+      }
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int j = 0; j < FB; ++j) acc[j] = mfma16_f32(f4_at(cw[j], t), f4_at(y, t), acc[j]);
+    }
+  }
+  const bool want_score = p.scores != nullptr;
+  float s1 = 0.f;
+#pragma unroll
+  for (int j = 0; j < FB; ++j) {
+    const int c = (wave * FB + j) * 16 + 4 * g4;
+    if (live && !want_score) *reinterpret_cast<float4*>(xrow + c) = make_float4(acc[j][0], acc[j][1], acc[j][2], acc[j][3]);
+    s1 += (acc[j][0] + acc[j][1]) + (acc[j][2] + acc[j][3]);
+  }
+  if (p.xh == nullptr && !want_score) return;        // uniform over the grid
+  // sum over the row: this lane's features, the four lanes of the token, the wavefronts
+  auto row_sum = [&](float v, int k) {
+    v += __shfl_xor(v, 16, 64);
+    v += __shfl_xor(v, 32, 64);
+    if (g4 == 0) red[k][wave][tk] = v;
+    __syncthreads();
+    float t = 0.f;
+#pragma unroll
+    for (int wv = 0; wv < NW; ++wv) t += red[k][wv][tk];
+    return t;
+  };
+  const float mean = row_sum(s1, 0) * (1.0f / (float)D);
+  float s2 = 0.f;
+#pragma unroll
+  for (int j = 0; j < FB; ++j)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { const float c = acc[j][e] - mean; s2 += c * c; }
+  const float rstd = rsqrtf(row_sum(s2, 1) * (1.0f / (float)D) + p.eps);
+  float sc = 0.f;
+#pragma unroll
+  for (int j = 0; j < FB; ++j) {
+    const int c = (wave * FB + j) * 16 + 4 * g4;
+    const float4 gg = *reinterpret_cast<const float4*>(p.gain + c), oo = *reinterpret_cast<const float4*>(p.offs + c);
+    float4 z;
+    z.x = (acc[j][0] - mean) * rstd * gg.x + oo.x;
+    z.y = (acc[j][1] - mean) * rstd * gg.y + oo.y;
+    z.z = (acc[j][2] - mean) * rstd * gg.z + oo.z;
+    z.w = (acc[j][3] - mean) * rstd * gg.w + oo.w;
+    if (want_score) {
+      const float4 ww = *reinterpret_cast<const float4*>(p.w_score + c);
+      sc += (z.x * ww.x + z.y * ww.y) + (z.z * ww.z + z.w * ww.w);
+    } else if (live) {
+      *reinterpret_cast<float4*>(p.xh + (size_t)row * D + c) = z;
+    }
+  }
+  if (want_score) {
+    const float total = row_sum(sc, 2);
+    if (wave == 0 && g4 == 0 && live && p.rt.kind[row] == kRowCand) p.scores[p.rt.src[row]] = total + p.b_score;
+  }
+}
+
+}  // namespace relaygr

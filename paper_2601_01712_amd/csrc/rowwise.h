@@ -1,6 +1,5 @@
-// Row-wise kernels: row-table construction, the three LayerNorm sites, the attention
-// combine + gate, and the score head.  One 64-lane wavefront owns one row of d = 64*E features;
-// lane l holds features [l*E, l*E + E).
+// Row-wise work: row-table construction and the call's first LayerNorm.  One 64-lane wavefront owns one
+// row of d = 64*E features; lane l holds features [l*E, l*E + E).
 #pragma once
 
 #include "common.h"
@@ -21,13 +20,15 @@ struct RowBuild {
 };
 struct RowEntry { int user, kind, idx, lim, src; };
 
-__device__ __forceinline__ RowEntry row_entry(const RowBuild& rb, int r) {
+// The wavefront's lanes compare 64 users' starts at a time: u is the last user with start[u] <= r.
+__device__ __forceinline__ RowEntry row_entry(const RowBuild& rb, int r, int lane) {
   const int32_t* start = (r < rb.n_prows) ? rb.pstart : rb.nstart;
-  int lo = 0, hi = rb.n_users;  // find u with start[u] <= r < start[u+1]
-  while (hi - lo > 1) {
-    int mid = (lo + hi) >> 1;
-    if (start[mid] <= r) lo = mid; else hi = mid;
+  int at_or_before = 0;
+  for (int u0 = 0; u0 < rb.n_users; u0 += 64) {
+    const int u = u0 + lane;
+    at_or_before += __builtin_popcountll(__builtin_amdgcn_ballot_w64(u < rb.n_users && start[min(u, rb.n_users)] <= r));
   }
+  const int lo = at_or_before - 1;
   const UserDesc& ud = rb.users[lo];
   RowEntry e;
   e.user = lo;
@@ -49,11 +50,31 @@ __device__ __forceinline__ void ln_stats(const float (&v)[E], int d, float eps, 
   float s = 0.f;
 #pragma unroll
   for (int e = 0; e < E; ++e) s += v[e];
-  mean = wave_sum(s) / (float)d;
+  mean = wave_sum_dpp(s) / (float)d;
   float q = 0.f;
 #pragma unroll
   for (int e = 0; e < E; ++e) { float c = v[e] - mean; q += c * c; }
-  rstd = rsqrtf(wave_sum(q) / (float)d + eps);
+  rstd = rsqrtf(wave_sum_dpp(q) / (float)d + eps);
+}
+
+// E consecutive values of a row, as fp32, and back (runs of 16 bytes where there are that many).
+template <typename T, int N> struct alignas(N * sizeof(T)) Run { T e[N]; };
+template <typename T, int E>
+__device__ __forceinline__ void ld_row_run(const T* src, float (&v)[E]) {
+  constexpr int RUN = E * (int)sizeof(T) >= 16 ? 16 / (int)sizeof(T) : E;
+#pragma unroll
+  for (int c = 0; c < E; c += RUN) {
+    const Run<T, RUN> b = *reinterpret_cast<const Run<T, RUN>*>(src + c);
+#pragma unroll
+    for (int i = 0; i < RUN; ++i) v[c + i] = Elem<T>::ld(&b.e[i]);
+  }
+}
+template <typename T, int N>
+__device__ __forceinline__ void st_run(T* dst, const float* v) {
+  Run<T, N> b;
+#pragma unroll
+  for (int i = 0; i < N; ++i) Elem<T>::st(&b.e[i], v[i]);
+  *reinterpret_cast<Run<T, N>*>(dst) = b;
 }
 
 // Writes a lane's E consecutive features [lane*E, lane*E+E) of row r, either row-major or into the
@@ -61,262 +82,71 @@ __device__ __forceinline__ void ln_stats(const float (&v)[E], int d, float eps, 
 // straddles a 16-byte fragment chunk unless it is made of whole chunks).
 template <typename T, int E, bool PANEL>
 __device__ __forceinline__ void store_row_run(T* __restrict__ out, int r, int lane, int d, const float (&v)[E]) {
-  if (PANEL) {
-    constexpr int RUN = E < 8 ? E : 8;
+  constexpr int RUN = E * (int)sizeof(T) >= 16 ? 16 / (int)sizeof(T) : E;
 #pragma unroll
-    for (int c = 0; c < E; c += RUN) {
-      T* dst = out + panel_off(r, lane * E + c, d);
-#pragma unroll
-      for (int i = 0; i < RUN; ++i) Elem<T>::st(dst + i, v[c + i]);
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < E; ++i) Elem<T>::st(out + (size_t)r * d + lane * E + i, v[i]);
-  }
+  for (int c = 0; c < E; c += RUN) st_run<T, RUN>(out + (PANEL ? panel_off(r, lane * E + c, d) : (size_t)r * d + lane * E + c), v + c);
 }
 
-// Input LayerNorm of a layer (step 1 of a layer): xh = LN(x; g, b) in the storage type.
-// With GATHER (first layer of a call) the wavefront first works out its row's table entry and writes it
-// for the kernels that follow (the call's row tables are built here, not by a launch of their own), then
-// fetches the row from its embedding array and also writes it to the fp32 residual stream x.
-template <typename T, int E, bool GATHER, bool PANEL>
+// Unused token slots of a ragged last K/V tile must hold finite values: 0 * NaN would otherwise reach the accumulators
+// through the masked-out keys.  The tiles concerned -- the last suffix tile of every user, and in the fp32 path the last
+// tile of every computed prefix in every layer (the 16-bit projection writes those zeros itself) -- are cleared
+// whole, before the first projection fills in their tokens, by extra workgroups of the call's first kernel: one per user, head
+// and (prefix) layer, 16-byte stores.  (As launches of their own, one workgroup per user, they took 13 to 29 us of a call.)
+struct TailClear {
+  int row_blocks;            // workgroups that own rows; the ones behind them clear
+  int n_heads, dh, kv_layers;   // kv_layers: prefix layers to clear (0: none), then one more "layer" for the suffix
+  void* sfx;                 // suffix K/V space; null: no suffix in this call
+};
+template <typename T>
+__device__ __forceinline__ void clear_tail_tile(const TailClear& tc, const UserDesc* users, int job) {
+  const int head = job % tc.n_heads, rest = job / tc.n_heads, layer = rest % (tc.kv_layers + 1);
+  const UserDesc& ud = users[rest / (tc.kv_layers + 1)];
+  T* tile;
+  if (layer < tc.kv_layers) {
+    if (ud.prow0 < 0 || ud.L % kTile == 0 || (layer > 0 && ud.kv_layer_stride == 0)) return;
+    tile = const_cast<T*>(reinterpret_cast<const T*>(ud.kv)) + ud.kv_tile0 + (int64_t)(ud.L / kTile) * ud.kv_tile_stride + (int64_t)layer * ud.kv_layer_stride;
+  } else {
+    if (tc.sfx == nullptr || ud.nrow0 < 0 || ud.S % kTile == 0) return;
+    tile = reinterpret_cast<T*>(tc.sfx) + ud.sfx_tile0 + (int64_t)(ud.S / kTile) * (2 * kTile * tc.dh * tc.n_heads);
+  }
+  uint4* dst = reinterpret_cast<uint4*>(tile + (int64_t)head * 2 * kTile * tc.dh);
+  const int n16 = 2 * kTile * tc.dh * (int)sizeof(T) / 16;
+  for (int i = threadIdx.x; i < n16; i += blockDim.x) dst[i] = make_uint4(0, 0, 0, 0);
+}
+
+// First kernel of a call.  A wavefront works out its row's table entry and writes it for the kernels that follow (the
+// call's row tables are built here, not by a launch of their own), fetches the row from its embedding array, writes it to
+// the fp32 residual stream x and its input LayerNorm (step 1 of the first layer) xh = LN(x; g, b) in the storage type; later
+// layers get theirs from the layer tail.
+template <typename T, int E, bool PANEL>
 __global__ __launch_bounds__(256) void ln_in_kernel(float* __restrict__ x, T* __restrict__ xh,
                                                     const T* __restrict__ gain, const T* __restrict__ offs,
                                                     const T* __restrict__ emb_prefix, const T* __restrict__ emb_suffix,
-                                                    const T* __restrict__ emb_cand, RowTables rt, RowBuild rb,
-                                                    int row_begin, int row_end, float eps) {
+                                                    const T* __restrict__ emb_cand, RowTables rt, RowBuild rb, TailClear tc,
+                                                    int n_rows, float eps) {
   const int d = 64 * E;
-  int r = row_begin + blockIdx.x * kRowsPerBlock + (threadIdx.x >> 6);
-  if (r >= row_end) return;
-  int lane = threadIdx.x & 63;
-  float v[E];
-  int kind, src = 0;
-  if (GATHER) {
-    const RowEntry e = row_entry(rb, r);
-    if (lane == 0) { rt.user[r] = e.user; rt.kind[r] = e.kind; rt.idx[r] = e.idx; rt.lim[r] = e.lim; rt.src[r] = e.src; }
-    kind = e.kind; src = e.src;
-  } else {
-    kind = rt.kind[r];
-  }
-  if (kind == kRowPad) {   // keep filler rows finite
+  if ((int)blockIdx.x >= tc.row_blocks) { clear_tail_tile<T>(tc, rb.users, (int)blockIdx.x - tc.row_blocks); return; }
+  const int r = blockIdx.x * kRowsPerBlock + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (r >= n_rows) return;
+  const int lane = threadIdx.x & 63;
+  float v[E], gv[E], bv[E];
+  ld_row_run<T, E>(gain + lane * E, gv);
+  ld_row_run<T, E>(offs + lane * E, bv);
+  const RowEntry e = row_entry(rb, r, lane);
+  if (lane == 0) { rt.user[r] = e.user; rt.kind[r] = e.kind; rt.idx[r] = e.idx; rt.lim[r] = e.lim; rt.src[r] = e.src; }
+  if (e.kind == kRowPad) {   // keep filler rows finite
 #pragma unroll
     for (int i = 0; i < E; ++i) v[i] = 0.f;
     store_row_run<T, E, PANEL>(xh, r, lane, d, v);
     return;
   }
-  if (GATHER) {
-    const T* e = (kind == kRowPrefix ? emb_prefix : kind == kRowSuffix ? emb_suffix : emb_cand) + (size_t)src * d + lane * E;
-#pragma unroll
-    for (int i = 0; i < E; ++i) { v[i] = Elem<T>::ld(e + i); x[(size_t)r * d + lane * E + i] = v[i]; }
-  } else {
-#pragma unroll
-    for (int i = 0; i < E; ++i) v[i] = x[(size_t)r * d + lane * E + i];
-  }
+  ld_row_run<T, E>((e.kind == kRowPrefix ? emb_prefix : e.kind == kRowSuffix ? emb_suffix : emb_cand) + (size_t)e.src * d + lane * E, v);
+  store_row_run<float, E, false>(x, r, lane, d, v);
   float mean, rstd;
   ln_stats<E>(v, d, eps, mean, rstd);
 #pragma unroll
-  for (int i = 0; i < E; ++i) {
-    int f = lane * E + i;
-    v[i] = (v[i] - mean) * rstd * Elem<T>::ld(gain + f) + Elem<T>::ld(offs + f);
-  }
+  for (int i = 0; i < E; ++i) v[i] = (v[i] - mean) * rstd * gv[i] + bv[i];
   store_row_run<T, E, PANEL>(xh, r, lane, d, v);
-}
-
-// Attention combine + gate (steps 3-4 of a layer, everything after the key loop):
-//   o_i = ( sum over key splits of the partial sums  +  self term for a candidate ) / n_i
-//   y_i = LN(o_i; g_at, b_at) * u_i
-// part holds nsplit unnormalised partial sums [nsplit][rows][d] of SiLU(alpha q.k) v over the key
-// sequence, added here in split order (fixed order => reproducible bits).  A candidate's self
-// term SiLU(alpha <q_c^h, k_c^h>) v_c^h is evaluated here from the row's own q, k, v.
-// qk_mul turns the stored q into alpha*q (q may be stored pre-scaled).
-// With plain_o set, part[0] already holds the finished o_i (softmax form, after
-// softmax_combine_kernel): no split sum, no self term, no 1/n.
-template <typename T, int E, bool PANEL>
-__global__ __launch_bounds__(256) void attn_gate_kernel(const float* __restrict__ part, int nsplit, size_t split_stride,
-                                                        const T* __restrict__ u, const T* __restrict__ q,
-                                                        const T* __restrict__ knew, const T* __restrict__ vnew,
-                                                        T* __restrict__ y, const T* __restrict__ gain,
-                                                        const T* __restrict__ offs, RowTables rt, int n_prows,
-                                                        int row_begin, int row_end, int dh, float qk_mul, float eps,
-                                                        int plain_o) {
-  const int d = 64 * E;
-  int r = row_begin + blockIdx.x * kRowsPerBlock + (threadIdx.x >> 6);
-  if (r >= row_end) return;
-  int lane = threadIdx.x & 63;
-  size_t base = (size_t)r * d + lane * E;
-  float o[E];
-  if (plain_o) nsplit = 1;
-  if (rt.kind[r] == kRowPad) {
-#pragma unroll
-    for (int i = 0; i < E; ++i) o[i] = 0.f;
-    store_row_run<T, E, PANEL>(y, r, lane, d, o);
-    return;
-  }
-#pragma unroll
-  for (int i = 0; i < E; ++i) o[i] = 0.f;
-  for (int s = 0; s < nsplit; ++s) {
-#pragma unroll
-    for (int i = 0; i < E; ++i) o[i] += part[s * split_stride + base + i];
-  }
-  int n = plain_o ? 1 : rt.lim[r];
-  if (rt.kind[r] == kRowCand && !plain_o) {
-    size_t nb = (size_t)(r - n_prows) * d + lane * E;
-    float dot = 0.f;
-#pragma unroll
-    for (int i = 0; i < E; ++i) dot += Elem<T>::ld(q + base + i) * Elem<T>::ld(knew + nb + i);
-    // lanes of one head are dh/E consecutive lanes (a power of two): segmented butterfly
-    for (int m = (dh / E) >> 1; m > 0; m >>= 1) dot += __shfl_xor(dot, m, 64);
-    float p = silu_f32(dot * qk_mul);
-#pragma unroll
-    for (int i = 0; i < E; ++i) o[i] += p * Elem<T>::ld(vnew + nb + i);
-    n += 1;
-  }
-  float inv_n = 1.0f / (float)n;
-#pragma unroll
-  for (int i = 0; i < E; ++i) o[i] *= inv_n;
-  float mean, rstd;
-  ln_stats<E>(o, d, eps, mean, rstd);
-#pragma unroll
-  for (int i = 0; i < E; ++i) {
-    int f = lane * E + i;
-    float z = (o[i] - mean) * rstd * Elem<T>::ld(gain + f) + Elem<T>::ld(offs + f);
-    o[i] = z * Elem<T>::ld(u + base + i);
-  }
-  store_row_run<T, E, PANEL>(y, r, lane, d, o);
-}
-
-// Second attention form (softmax over the visible keys): merges a row's key splits and, for a
-// candidate, its own key into the finished attention output
-//   o_i^h = ( sum_s w_s part_s  +  w_self v_c^h ) / ( sum_s w_s l_s + w_self ),
-//   w_s = exp(m_s - M),  w_self = exp(t_self - M),  M = max(m_s, t_self),
-// where split s delivered part_s = sum_j exp(t_j - m_s) v_j, l_s = sum_j exp(t_j - m_s) and m_s
-// (ml holds m and l as [split][row][head][2]; m_s = -inf and l_s = 0 for a split in which the row
-// sees no key).  Scores are stored scaled by 1/to_log2 relative to base-2 exponents: the fp32 path
-// keeps natural-log scores (to_log2 = log2 e), the 16-bit path stores q pre-multiplied by
-// alpha * log2(e) (to_log2 = 1, qk_mul = 1).  Splits are merged in fixed order.  The result
-// overwrites split 0's partial sums, which the gate then reads with its plain_o flag set.
-template <typename T, int E>
-__global__ __launch_bounds__(256) void softmax_combine_kernel(float* __restrict__ part, const float* __restrict__ ml, int nsplit,
-                                                              size_t split_stride, size_t ml_stride, const T* __restrict__ q,
-                                                              const T* __restrict__ knew, const T* __restrict__ vnew, RowTables rt,
-                                                              int n_prows, int row_begin, int row_end, int dh, int n_heads,
-                                                              float qk_mul, float to_log2) {
-  const int d = 64 * E;
-  int r = row_begin + blockIdx.x * kRowsPerBlock + (threadIdx.x >> 6);
-  if (r >= row_end) return;
-  const int kind = rt.kind[r];
-  if (kind == kRowPad) return;
-  int lane = threadIdx.x & 63;
-  const int head = lane * E / dh;
-  size_t base = (size_t)r * d + lane * E;
-  const float* mlr = ml + ((size_t)r * n_heads + head) * 2;
-  float M = -INFINITY;
-  for (int s = 0; s < nsplit; ++s) M = fmaxf(M, mlr[s * ml_stride]);
-  float tself = 0.f;
-  size_t nb = 0;
-  if (kind == kRowCand) {
-    nb = (size_t)(r - n_prows) * d + lane * E;
-    float dot = 0.f;
-#pragma unroll
-    for (int i = 0; i < E; ++i) dot += Elem<T>::ld(q + base + i) * Elem<T>::ld(knew + nb + i);
-    for (int m = (dh / E) >> 1; m > 0; m >>= 1) dot += __shfl_xor(dot, m, 64);
-    tself = dot * qk_mul;
-    M = fmaxf(M, tself);
-  }
-  float o[E], L = 0.f;
-#pragma unroll
-  for (int i = 0; i < E; ++i) o[i] = 0.f;
-  for (int s = 0; s < nsplit; ++s) {
-    const float ms = mlr[s * ml_stride], ls = mlr[s * ml_stride + 1];
-    const float w = (ms == -INFINITY) ? 0.f : exp2f((ms - M) * to_log2);
-    L += w * ls;
-#pragma unroll
-    for (int i = 0; i < E; ++i) o[i] += w * part[s * split_stride + base + i];
-  }
-  if (kind == kRowCand) {
-    const float w = exp2f((tself - M) * to_log2);
-    L += w;
-#pragma unroll
-    for (int i = 0; i < E; ++i) o[i] += w * Elem<T>::ld(vnew + nb + i);
-  }
-  const float inv = 1.0f / L;
-#pragma unroll
-  for (int i = 0; i < E; ++i) part[base + i] = o[i] * inv;
-}
-
-// Score head: score_c = <w_s, LN(x_c; g_out, b_out)> + b_s for candidate rows, written at the
-// candidate's position in the caller's candidate order.
-template <typename T, int E>
-__global__ __launch_bounds__(256) void score_kernel(const float* __restrict__ x, const T* __restrict__ gain,
-                                                    const T* __restrict__ offs, const T* __restrict__ w_score,
-                                                    float b_score, RowTables rt, int row_begin, int row_end,
-                                                    float eps, float* __restrict__ scores) {
-  const int d = 64 * E;
-  int r = row_begin + blockIdx.x * kRowsPerBlock + (threadIdx.x >> 6);
-  if (r >= row_end) return;
-  if (rt.kind[r] != kRowCand) return;
-  int lane = threadIdx.x & 63;
-  float v[E];
-#pragma unroll
-  for (int i = 0; i < E; ++i) v[i] = x[(size_t)r * d + lane * E + i];
-  float mean, rstd;
-  ln_stats<E>(v, d, eps, mean, rstd);
-  float acc = 0.f;
-#pragma unroll
-  for (int i = 0; i < E; ++i) {
-    int f = lane * E + i;
-    acc += ((v[i] - mean) * rstd * Elem<T>::ld(gain + f) + Elem<T>::ld(offs + f)) * Elem<T>::ld(w_score + f);
-  }
-  acc = wave_sum(acc);
-  if (lane == 0) scores[rt.src[r]] = acc + b_score;
-}
-
-// Zero the unused token slots of each computed prefix's last K/V tile (all layers this call
-// writes), so that a ragged tile never holds stale non-finite bits: 0 * NaN would otherwise
-// reach the accumulators through the masked-out keys.
-template <typename T>
-__global__ void zero_kv_tail_kernel(const UserDesc* __restrict__ users, int n_users, int n_layers, int n_heads, int dh) {
-  int u = blockIdx.x;
-  if (u >= n_users) return;
-  const UserDesc ud = users[u];
-  if (ud.prow0 < 0) return;
-  int tail0 = ud.L % kTile;
-  if (tail0 == 0) return;
-  int64_t tile = ud.L / kTile;
-  int layers = ud.kv_layer_stride ? n_layers : 1;
-  int per_head = (kTile - tail0) * dh;  // elements of K (and of V) to clear per layer and head
-  T* base = const_cast<T*>(reinterpret_cast<const T*>(ud.kv)) + ud.kv_tile0 + tile * ud.kv_tile_stride;
-  int total = layers * n_heads * per_head;
-  for (int i = threadIdx.x; i < total; i += blockDim.x) {
-    int lh = i / per_head, w = i % per_head;
-    int layer = lh / n_heads, head = lh % n_heads;
-    T* kt = base + (int64_t)layer * ud.kv_layer_stride + (int64_t)head * 2 * kTile * dh;
-    int rr = tail0 + w / dh, f = w % dh;
-    Elem<T>::st(kt + KvLayout<T>::k_off(rr, f, dh), 0.f);
-    Elem<T>::st(kt + KvLayout<T>::v_off(rr, f, dh), 0.f);
-  }
-}
-
-// Same for the suffix tiles of every user with a suffix (single-layer scratch space).
-template <typename T>
-__global__ void zero_suffix_tail_kernel(const UserDesc* __restrict__ users, int n_users, T* __restrict__ sfx,
-                                        int n_heads, int dh) {
-  int u = blockIdx.x;
-  if (u >= n_users) return;
-  const UserDesc ud = users[u];
-  int tail0 = ud.S % kTile;
-  if (ud.nrow0 < 0 || tail0 == 0) return;
-  int64_t tile = ud.S / kTile;
-  int per_head = (kTile - tail0) * dh;
-  T* base = sfx + ud.sfx_tile0 + tile * (int64_t)(2 * kTile * dh * n_heads);
-  int total = n_heads * per_head;
-  for (int i = threadIdx.x; i < total; i += blockDim.x) {
-    int head = i / per_head, w = i % per_head;
-    T* kt = base + (int64_t)head * 2 * kTile * dh;
-    int rr = tail0 + w / dh, f = w % dh;
-    Elem<T>::st(kt + KvLayout<T>::k_off(rr, f, dh), 0.f);
-    Elem<T>::st(kt + KvLayout<T>::v_off(rr, f, dh), 0.f);
-  }
 }
 
 }  // namespace relaygr

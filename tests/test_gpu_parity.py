@@ -79,6 +79,20 @@ def test_fp32_head_sizes(d, H):
     run_three_routes(synth.ModelConfig(2, d, H, "fp32"), 50 + H, [150, 70], [5, 0], [20, 66])
 
 
+@pytest.mark.parametrize("attention", ["silu", "softmax"])
+@pytest.mark.parametrize("d,H,L,S,M", [
+    (64, 1, [31, 33, 0], [0, 33, 1], [17, 1, 47]),            # fewer half tiles than a team has wavefronts; 32-row tiles end inside
+    (256, 4, [700], [63], [130]),                             # 32 x 32 projection tiles, k cut in four; one user, key splits
+    (512, 4, [90, 200, 129], [31, 0, 64], [700, 333, 97]),    # 64 x 64 projection tiles, d_head 128
+    (256, 4, [1030, 1100, 999, 1025, 1060, 1111, 1000, 1090], [0, 5, 0, 0, 64, 0, 0, 0], [33] * 8),   # 128 x 128 tiles, no teams
+    (1024, 8, [65], [2], [35]),
+])
+def test_fp32_tiles_teams_and_splits(attention, d, H, L, S, M):
+    """The fp32 kernels at the edges of their tiles and on both sides of each choice by launch size."""
+    boost = BOOST if d <= 256 else None
+    run_three_routes(synth.ModelConfig(2, d, H, "fp32", attention=attention), 900 + d, L, S, M, boost=boost, miss=(1,) if len(L) > 2 else ())
+
+
 # ------------------------------------------------------------------------------------ bf16
 @pytest.mark.parametrize("L,S,M", [
     ([1], [0], [1]), ([63], [0], [5]), ([64], [3], [130]), ([65, 300], [0, 70], [3, 129]),
