@@ -33,44 +33,18 @@ struct AttnParams {
   size_t split_stride;
   float* ml;          // softmax form: [nsplit][rows][n_heads][2] = (m, l) of each row, head and split
   size_t ml_stride;   // floats between the (m, l) tables of consecutive splits
-  int nsplit;
-  int n_tiles;        // work items in this launch
+  int nsplit;         // fp32 kernel: key splits
+  int n_tiles;        // work items in this launch (16-bit: pieces, each with its key range; fp32: row tiles)
   int d, n_heads, layer;
   float score_mul;    // multiplies <q,k> before SiLU (alpha, or 1 if q is stored pre-scaled)
   // MFMA kernel, SiLU form: a candidate's own key (the diagonal of the candidate block: a per-row dot product, never an
-  // M x M tile) is where the sums of one of the row's key splits start (row block qb: split qb mod nsplit), from the
+  // M x M tile) is where the sums of one of the row's pieces start (row block qb: piece qb mod pieces), from the
   // row-major k and v of the new rows; null: left to the layer-tail kernel
   const void* knew;   // [new rows][d]
   const void* vnew;
   int n_prows;        // rows before the first new row
   int gs;             // key splits taken inside one workgroup and added in LDS: 16-bit 1 or 2 (wavefront groups), fp32 1 or 8 (wavefronts)
 };
-
-// Key-tile schedule of one work item.
-struct TileRange {
-  int nkp;       // prefix tiles this item needs
-  int nfull;     // leading prefix tiles every row of the item sees completely
-  int nks;       // suffix tiles
-  int t0, t1;    // this split's range in the concatenated list [prefix tiles | suffix tiles]
-};
-
-__device__ __forceinline__ TileRange tile_range(const AttnTile& at, const UserDesc& ud, int split, int nsplit) {
-  TileRange tr;
-  if (at.kind == 0) {  // prefix rows: causal, keys 0 .. pos0 + nrows - 1
-    tr.nkp = (at.pos0 + at.nrows + kTile - 1) / kTile;
-    tr.nfull = (at.pos0 + 1) / kTile;
-    tr.nks = 0;
-  } else {             // new rows: the whole prefix, then the suffix
-    tr.nkp = (ud.L + kTile - 1) / kTile;
-    tr.nfull = ud.L / kTile;
-    tr.nks = (ud.S + kTile - 1) / kTile;
-  }
-  int total = tr.nkp + tr.nks;
-  int per = (total + nsplit - 1) / nsplit;
-  tr.t0 = min(split * per, total);
-  tr.t1 = min(tr.t0 + per, total);
-  return tr;
-}
 
 // ---- bf16 MFMA kernel ---------------------------------------------------------------------------
 // A workgroup of NW wavefronts owns up to NW*32*NQ rows (each wavefront NQ blocks of 32 rows) of one
@@ -252,22 +226,34 @@ __global__ __launch_bounds__(NW * GS * 64, (DH >= 128 || GS > 1) ? 1 : 512 / (NW
   static_assert(GS * 3 * TILE * 2 >= (GS - 1) * NW * 64 * (DB * NQ * 16 + 2 * NQ) * 4, "the second group's sums fit the rings' LDS");
   __shared__ __attribute__((aligned(16))) uint16_t bufs_all[GS][3][TILE];
 
-  // Work items that stream the same K/V (row tiles of one user, same head and split) get
-  // consecutive logical ids, and each of the 8 XCDs (own L2 each; workgroups are dealt to them
-  // round-robin) takes a contiguous run of logical ids: the K/V tiles are then fetched from HBM
-  // once per XCD and found in its L2 by the neighbouring row tiles.
-  const int total = p.n_tiles * p.n_heads * p.nsplit;
-  const int logical = xcd_remap(blockIdx.x, total);
-  if (logical >= total) return;
-  const int tile_i = logical % p.n_tiles, hs = logical / p.n_tiles;
-  const int head = hs % p.n_heads, split_ext = hs / p.n_heads;
+  // Each of the 8 XCDs (own L2 each; workgroups are dealt to them round-robin) takes whole heads, or with fewer than 8 heads
+  // every (8 / heads)-th item of one head, and walks the list of items in its order, longest first: row tiles of one user are
+  // neighbours in the list, so a K/V tile is fetched from HBM once per XCD that needs it, and every XCD gets the same mix
+  // of long and short items.  (The number of heads is a power of two.)
+  const int xcd = blockIdx.x & 7, turn = blockIdx.x >> 3;
+  int head, tile_i;
+  if (p.n_heads >= 8) {
+    const int per_xcd = p.n_heads >> 3;
+    head = xcd * per_xcd + turn % per_xcd;
+    tile_i = turn / per_xcd;
+  } else {
+    head = xcd % p.n_heads;
+    tile_i = turn * (8 / p.n_heads) + xcd / p.n_heads;
+  }
+  if (tile_i >= p.n_tiles) return;
   const AttnTile at = p.tiles[tile_i];
+  const int split_ext = at.part;
   const UserDesc ud = p.users[at.user];
   const int tid = threadIdx.x, lane = tid & 63;
   const int grp = GS == 1 ? 0 : __builtin_amdgcn_readfirstlane((tid >> 6) / NW);    // wavefront group (a scalar: loop counts below depend on it)
   const int wave = (tid >> 6) - grp * NW;           // wavefront inside its group: its rows, its share of a tile
-  const int split = split_ext * GS + grp, nsplit = p.nsplit * GS;   // this group's key split of all
-  const TileRange tr = tile_range(at, ud, split, nsplit);
+  const int split = split_ext * GS + grp, nsplit = at.parts * GS;   // this group's key split of all
+  struct { int nkp, nfull, t0, t1; } tr;   // prefix tiles in the item's list, those every row sees whole, this group's range
+  tr.nkp = ((at.kind == 0 ? at.pos0 + at.nrows : ud.L) + kTile - 1) / kTile;
+  tr.nfull = (at.kind == 0 ? at.pos0 + 1 : ud.L) / kTile;
+  const int per_group = (at.t1 - at.t0 + GS - 1) / GS;
+  tr.t0 = min(at.t0 + grp * per_group, at.t1);
+  tr.t1 = min(tr.t0 + per_group, at.t1);
   uint16_t (*bufs)[TILE] = bufs_all[grp];
   const int l32 = lane & 31, g = lane >> 5;
 
@@ -374,8 +360,7 @@ __global__ __launch_bounds__(NW * GS * 64, (DH >= 128 || GS > 1) ? 1 : 512 / (NW
   const int nt = tr.t1 - tr.t0;
   int nt_all = nt;                    // barriers every wavefront of the workgroup passes in the tile loop
   if constexpr (GS == 2) {
-    const TileRange tro = tile_range(at, ud, split ^ 1, nsplit);
-    nt_all = max(nt, tro.t1 - tro.t0);
+    nt_all = per_group;
   }
   if (nt == 0) start_from_own_key();
   if (nt > 0) {

@@ -49,7 +49,7 @@ struct UserDesc {
   int32_t prow0;           // first prefix row of this user in the call's row space, -1 if not computed
   int32_t nrow0;           // first new row (suffix rows, then candidates), -1 if the call has none
   int32_t prefix_src0, suffix_src0, cand_src0;  // first row in each embedding array
-  int32_t pad0, pad1;
+  int32_t parts, parts_last;   // 16-bit path: partial sums of a new row of this user, in every layer but the last / in the last
 };
 static_assert(sizeof(UserDesc) == 80, "UserDesc layout");
 
@@ -60,7 +60,10 @@ struct AttnTile {
   int32_t nrows;
   int32_t kind;     // 0: prefix rows (causal over the prefix); 1: new rows
   int32_t pos0;     // prefix rows: position of row0 in the prefix; new rows: index among new rows
-  int32_t pad[3];
+  // 16-bit kernel: an item is one of `parts` pieces of its rows' key sequence, key tiles [t0, t1) of the concatenated list
+  // [prefix tiles | suffix tiles], and writes partial sum number `part`
+  int32_t t0, t1;
+  int16_t part, parts;
 };
 static_assert(sizeof(AttnTile) == 32, "AttnTile layout");
 
@@ -70,6 +73,7 @@ struct RowTables {
   int32_t* idx;    // index inside the user's segment of that kind
   int32_t* lim;    // keys of [prefix | suffix] visible to this row
   int32_t* src;    // row in the embedding array of its kind
+  int32_t* parts;  // attention partial sums of this row: every layer but the last | last layer << 8
 };
 
 template <typename T> struct KvLayout;
@@ -145,11 +149,26 @@ __device__ __forceinline__ void st_stream(uint4* p, uint4 v) { __builtin_nontemp
 __device__ __forceinline__ void st_stream(uint2* p, uint2 v) { __builtin_nontemporal_store(u32x2_t{v.x, v.y}, reinterpret_cast<u32x2_t*>(p)); }
 __device__ __forceinline__ void st_stream(float4* p, float4 v) { __builtin_nontemporal_store(f32x4_t{v.x, v.y, v.z, v.w}, reinterpret_cast<f32x4_t*>(p)); }
 
-// v + (v of the lane the DPP control selects), on the vector ALU (no LDS crossbar round trip).
+// Sum over the wavefront, in every lane, adding lane i to lane i ^ 32, then ^ 16, ^ 8, ^ 4, ^ 2, ^ 1, on the vector ALU: the
+// halves and the 16-lane rows change places (v_permlane32_swap, v_permlane16_swap), and inside a row a rotation by 8 is lane ^ 8, after
+// which values repeat every 8 lanes and a rotation by 4 is lane ^ 4, and so on.
 template <int CTRL>
+// (v + v of the lane the DPP control selects: no LDS crossbar round trip)
 __device__ __forceinline__ float dpp_add(float v) {
   return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
 }
+__device__ __forceinline__ float wave_sum(float v) {
+  typedef unsigned int u2 __attribute__((ext_vector_type(2)));
+  u2 h = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(h[0]) + __uint_as_float(h[1]);
+  h = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(h[0]) + __uint_as_float(h[1]);
+  v = dpp_add<0x128>(v);
+  v = dpp_add<0x124>(v);
+  v = dpp_add<0x122>(v);
+  return dpp_add<0x121>(v);
+}
+
 // Sum over each group of 2, 4, 8, 16 consecutive lanes, left in every lane of the group:
 // quad_perm [1,0,3,2], quad_perm [2,3,0,1], row_half_mirror, row_mirror.
 __device__ __forceinline__ float lanes2_sum(float v) { return dpp_add<0xB1>(v); }

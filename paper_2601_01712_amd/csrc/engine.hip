@@ -87,8 +87,8 @@ struct Plan {
   int n_users = 0;
   int n_prows = 0, n_nrows = 0, n_rows = 0;
   int64_t sfx_tiles = 0, kvs_tiles = 0;   // suffix tiles / recomputed-prefix tiles held in scratch
-  int n_tiles_new = 0, n_tiles_prefix = 0;
-  int nsplit = 1;
+  int n_tiles_new = 0, n_tiles_prefix = 0, n_tiles_last = 0;   // attention work items (16-bit: pieces; last layer's list by itself)
+  int nsplit = 1;       // attention partial sums a row can have (fp32: has)
   int gs = 1;           // key splits added inside an attention workgroup (AttnParams::gs)
   // byte offsets into scratch
   size_t off_x, off_xh, off_u, off_q, off_knew, off_vnew, off_sfx, off_kvs, off_part, off_ml, off_rows, off_blob;
@@ -126,24 +126,28 @@ static void carve(const relaygr_model_config& c, Plan& p) {
   p.off_kvs = take((size_t)p.kvs_tiles * 2 * kTile * d * e);
   p.off_part = take((size_t)p.nsplit * R * d * 4);
   p.off_ml = take((size_t)p.nsplit * R * c.n_heads * 2 * 4);   // softmax form: (m, l) per row, head and split
-  p.off_rows = take(5 * align_up(R * 4));
-  size_t n_tiles = (size_t)p.n_tiles_new + p.n_tiles_prefix;
+  p.off_rows = take(6 * align_up(R * 4));
+  size_t n_tiles = (size_t)p.n_tiles_new + p.n_tiles_prefix + p.n_tiles_last;
   p.blob_bytes = align_up((size_t)p.n_users * sizeof(UserDesc)) + 2 * align_up((size_t)(p.n_users + 1) * 4) +
                  align_up(n_tiles * sizeof(AttnTile));
   p.off_blob = take(p.blob_bytes);
   p.total = o;
 }
 
-// Key-range splits wanted so that the attention launch fills the chip: workgroups = tiles * heads
-// * splits, as many as give every compute unit at most two (one more split and some units get a third
-// workgroup, which the whole launch then waits for), never more splits than a row tile has key tiles.
-static int wanted_splits(int n_tiles, int n_heads, int min_key_tiles) {
-  if (n_tiles <= 0) return 1;
-  int wgs = n_tiles * n_heads;
-  int s = 512 / wgs;
-  s = std::min(s, 8);
-  s = std::min(s, std::max(1, min_key_tiles));
-  return std::max(s, 1);
+// 16-bit attention: how a launch's row tiles (each with its list of 64-key tiles) are cut into pieces along the keys.
+// The chip takes `slots` workgroups at a time and deals the list out longest first, so a launch is done soon after
+// total / slots key tiles a slot unless single items are longer than that: one user's causal prefill has one item of all key
+// tiles and one of two, a jagged batch one user of 16 384 keys among short ones.  Pieces are cut to at most that share, not
+// under kMinPieceTiles (a workgroup's own start and end cost about as much as six key tiles) and not into more than 8; and
+// only for launches of less than kPieceRounds rounds, where there is too little behind the long items to hide them: each
+// further piece of a row is an fp32 partial sum more for the layer tail to read.
+constexpr int kMaxCutItems = 16384;   // pieces a cut list has at most (in each of the two lists)
+constexpr int kMinPieceTiles = 8, kMaxPieces = 8, kPieceRounds = 4;
+static int piece_tiles(int64_t items, int64_t total_key_tiles, int most_key_tiles, int slots) {
+  if (items >= (int64_t)kPieceRounds * slots) return std::max(1, most_key_tiles);
+  int64_t c = (total_key_tiles + slots - 1) / slots;
+  c = std::max<int64_t>({c, kMinPieceTiles, (most_key_tiles + kMaxPieces - 1) / kMaxPieces});
+  return (int)std::max<int64_t>(1, std::min<int64_t>(c, most_key_tiles));
 }
 
 // fp32: a work item is one wavefront over its part of the keys, and 2048 of them (two a SIMD) fill the chip.  As long as the
@@ -173,6 +177,7 @@ extern "C" size_t relaygr_scratch_bytes(const relaygr_model_config* cfg, int32_t
   int rpt = rows_per_attn_tile(*cfg, 1);
   p.n_tiles_new = (int)(max_new_tokens / rpt) + max_users;
   p.n_tiles_prefix = (int)(padded / rpt) + max_users;
+  p.n_tiles_last = p.n_tiles_new + 2 * kMaxCutItems;   // and room for the items that are cut into pieces
   p.nsplit = 1;
   carve(*cfg, p);
   size_t base = wpack_bytes(*cfg) + p.total;
@@ -311,7 +316,7 @@ extern "C" int relaygr_ctx_create(const relaygr_model_config* cfg, const relaygr
     const size_t rows_est = call_bytes / (d * 4) + 1;
     const size_t users_est = std::min<size_t>(call_bytes / (4 * kTile * d * e) + 1, 1 << 16);
     const size_t tiles_est = rows_est / 32 + 2 * users_est;
-    const size_t want = align_up(users_est * sizeof(UserDesc)) + 2 * align_up((users_est + 1) * 4) + align_up(tiles_est * sizeof(AttnTile));
+    const size_t want = align_up(users_est * sizeof(UserDesc)) + 2 * align_up((users_est + 1) * 4) + align_up((2 * tiles_est + 2 * kMaxCutItems) * sizeof(AttnTile));
     for (auto& sl : c->staging) {
       hipError_t e1 = hipHostMalloc(&sl.host, want, hipHostMallocDefault);
       hipError_t e2 = e1 == hipSuccess ? hipEventCreateWithFlags(&sl.done, hipEventDisableTiming) : e1;
@@ -555,8 +560,8 @@ int launch_attention<float>(const relaygr_model_config& cfg, const AttnParams& a
 
 template <typename H, bool SM>
 static int launch_attention16(const relaygr_model_config& cfg, const AttnParams& ap, int n_tiles, int nq, hipStream_t st) {
-  int total = n_tiles * cfg.n_heads * ap.nsplit;
-  dim3 grid((total + 7) / 8 * 8);
+  const int nh = cfg.n_heads;
+  dim3 grid(nh >= 8 ? n_tiles * nh : (n_tiles + 8 / nh - 1) / (8 / nh) * 8);   // the kernel's order of heads and items
   switch (cfg.d_model / cfg.n_heads) {
     case 32: hipLaunchKernelGGL((attn_bf16_kernel<H, 32, 1, 4, SM>), grid, dim3(256), 0, st, ap); break;
     case 64:
@@ -683,57 +688,88 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
   }
   const int rpt = rows_per_attn_tile(cfg, nq);
 
-  // -- attention work items: new-row tiles first (kept when the last layer skips prefix rows),
-  //    each group sorted by key-tile count, longest first
-  std::vector<AttnTile> tiles_new, tiles_prefix;
-  int min_key_tiles = 1 << 30;
+  // -- attention row tiles: new rows first (the last layer skips prefix rows)
+  std::vector<AttnTile> rows_new, rows_prefix;
   for (int u = 0; u < n; ++u) {
     const UserDesc& ud = users[u];
     int Tn = ud.S + ud.M;
     if (ud.nrow0 >= 0)
-      for (int t0 = 0; t0 < Tn; t0 += rpt) {
-        AttnTile at = {u, ud.nrow0 + t0, std::min(rpt, Tn - t0), 1, t0, {0, 0, 0}};
-        tiles_new.push_back(at);
-        min_key_tiles = std::min(min_key_tiles, (ud.L + kTile - 1) / kTile + (ud.S + kTile - 1) / kTile);
-      }
+      for (int t0 = 0; t0 < Tn; t0 += rpt) rows_new.push_back({u, ud.nrow0 + t0, std::min(rpt, Tn - t0), 1, t0, 0, 0, 0, 1});
     if (ud.prow0 >= 0)
-      for (int i0 = 0; i0 < ud.L; i0 += rpt) {
-        AttnTile at = {u, ud.prow0 + i0, std::min(rpt, ud.L - i0), 0, i0, {0, 0, 0}};
-        tiles_prefix.push_back(at);
-      }
+      for (int i0 = 0; i0 < ud.L; i0 += rpt) rows_prefix.push_back({u, ud.prow0 + i0, std::min(rpt, ud.L - i0), 0, i0, 0, 0, 0, 1});
   }
   auto key_tiles = [&](const AttnTile& a) {
     const UserDesc& ud = users[a.user];
     return a.kind == 0 ? (a.pos0 + a.nrows + kTile - 1) / kTile : (ud.L + kTile - 1) / kTile + (ud.S + kTile - 1) / kTile;
   };
-  auto by_cost = [&](const AttnTile& a, const AttnTile& b2) { return key_tiles(a) > key_tiles(b2); };
-  std::stable_sort(tiles_new.begin(), tiles_new.end(), by_cost);
-  std::stable_sort(tiles_prefix.begin(), tiles_prefix.end(), by_cost);
-  p.n_tiles_new = (int)tiles_new.size();
-  p.n_tiles_prefix = (int)tiles_prefix.size();
-  const int n_tiles_all = p.n_tiles_new + p.n_tiles_prefix;
-  if (tiles_prefix.size()) min_key_tiles = 1;   // the first causal tile has a single key tile
-  if (min_key_tiles == (1 << 30)) min_key_tiles = 1;
+  // -- the launch lists (all layers but the last; the last): pieces of the row tiles, longest first
+  std::vector<AttnTile> list_all, list_last;
+  p.gs = 1;
+  int64_t kt_new = 0, kt_prefix = 0;
+  int most_new = 0, most_prefix = 0;
+  for (const AttnTile& a : rows_new) { kt_new += key_tiles(a); most_new = std::max(most_new, key_tiles(a)); }
+  for (const AttnTile& a : rows_prefix) { kt_prefix += key_tiles(a); most_prefix = std::max(most_prefix, key_tiles(a)); }
+  int piece_all = 1 << 20, piece_last = 1 << 20;     // most key tiles of a piece
+  int parts_all = 1, parts_last = 1;                 // partial sums of every row (0: rows differ)
+  if (!bf16) {
+    fp32_splits((int64_t)(rows_new.size() + rows_prefix.size()) * H, 2 * (kt_new + kt_prefix) * H, &p.nsplit, &p.gs);
+    list_all = rows_new;
+    list_all.insert(list_all.end(), rows_prefix.begin(), rows_prefix.end());
+    auto longer = [&](const AttnTile& a, const AttnTile& b2) { return key_tiles(a) > key_tiles(b2); };
+    std::stable_sort(list_all.begin(), list_all.begin() + rows_new.size(), longer);
+    std::stable_sort(list_all.begin() + rows_new.size(), list_all.end(), longer);
+    p.n_tiles_new = (int)rows_new.size();
+    p.n_tiles_prefix = (int)rows_prefix.size();
+  } else {
+    const int slots = dh == 128 ? c->n_cus : 2 * c->n_cus;   // workgroups the chip takes at a time
+    piece_all = piece_tiles((int64_t)(rows_new.size() + rows_prefix.size()) * H, (kt_new + kt_prefix) * H, std::max(most_new, most_prefix ? most_prefix + rpt / kTile : 0), slots);
+    piece_last = piece_tiles((int64_t)rows_new.size() * H, kt_new * H, most_new, slots);
+    // Fills `out` with the pieces of at most `piece` key tiles; returns the most pieces of a row tile.
+    auto cut = [&](bool prefix_rows, int piece, std::vector<AttnTile>& out, int* uniform) {
+      out.clear();
+      int lo = kMaxPieces + 1, hi = 0;
+      auto add = [&](AttnTile a, int parts) {
+        const int nk = key_tiles(a), per = (nk + parts - 1) / parts;
+        lo = std::min(lo, parts); hi = std::max(hi, parts);
+        a.parts = (int16_t)parts;
+        for (int k = 0; k < parts; ++k) { a.part = (int16_t)k; a.t0 = std::min(k * per, nk); a.t1 = std::min(a.t0 + per, nk); out.push_back(a); }
+      };
+      for (const AttnTile& a : rows_new) add(a, std::max(1, (key_tiles(a) + piece - 1) / piece));
+      if (prefix_rows) for (const AttnTile& a : rows_prefix) add(a, causal_parts(a.pos0, rpt, piece));
+      std::stable_sort(out.begin(), out.end(), [](const AttnTile& a, const AttnTile& b2) { return a.t1 - a.t0 > b2.t1 - b2.t0; });
+      *uniform = hi == 0 ? 1 : lo == hi ? lo : 0;
+      return hi;
+    };
+    for (;;) {
+      const int h1 = cut(true, piece_all, list_all, &parts_all), h2 = cut(false, piece_last, list_last, &parts_last);
+      p.nsplit = std::max({1, h1, h2});
+      p.n_tiles_new = (int)list_all.size(); p.n_tiles_prefix = 0; p.n_tiles_last = (int)list_last.size();
+      carve(cfg, p);
+      const bool uncut = list_all.size() == rows_new.size() + rows_prefix.size() && list_last.size() == rows_new.size();
+      if (uncut || (p.total <= cs.bytes && p.nsplit <= kMaxPieces && std::max(list_all.size(), list_last.size()) <= kMaxCutItems)) break;
+      piece_all *= 2; piece_last *= 2;
+    }
+    // d_head 64: two pieces of a row go to the two wavefront groups of one workgroup, which add their
+    // sums in LDS -- half the partial sums for the layer tail to read -- where every row has the same even number of them and
+    // half the workgroups still give every compute unit one (with fewer, e.g. one user with 512 candidates, the attention
+    // launch itself gets 25 % slower)
+    const bool one_list = rows_prefix.empty();
+    if (dh == 64 && one_list && parts_all > 0 && parts_all % 2 == 0 && (int64_t)rows_new.size() * H * (parts_all / 2) >= c->n_cus) {
+      p.gs = 2;
+      piece_all = piece_last = (most_new + parts_all / 2 - 1) / (parts_all / 2);
+      p.nsplit = std::max(cut(true, piece_all, list_all, &parts_all), cut(false, piece_last, list_last, &parts_last));
+      p.n_tiles_new = (int)list_all.size(); p.n_tiles_last = (int)list_last.size();
+    }
+    for (int u = 0; u < n; ++u) {
+      const int nk = (users[u].L + kTile - 1) / kTile + (users[u].S + kTile - 1) / kTile;
+      users[u].parts = std::max(1, (nk + piece_all - 1) / piece_all);
+      users[u].parts_last = std::max(1, (nk + piece_last - 1) / piece_last);
+    }
+  }
 
   // -- scratch
-  p.nsplit = wanted_splits(n_tiles_all, H, min_key_tiles);
-  // d_head 64: two of the key splits go to the two wavefront groups of one workgroup, which add their
-  // sums in LDS -- half the partial sums for the layer tail to read -- where that still gives every compute unit a
-  // workgroup (with fewer, e.g. one user with 512 candidates, the attention launch itself gets 25 % slower)
-  p.gs = 1;
-  if (!bf16) {
-    int64_t halves = 0;
-    for (const AttnTile& a : tiles_new) halves += 2 * key_tiles(a);
-    for (const AttnTile& a : tiles_prefix) halves += 2 * key_tiles(a);
-    fp32_splits((int64_t)n_tiles_all * H, halves * H, &p.nsplit, &p.gs);
-  }
-  if (bf16 && dh == 64 && p.nsplit % 2 == 0 &&
-      (int64_t)n_tiles_all * H * (p.nsplit / 2) >= c->n_cus) {
-    p.gs = 2;
-    p.nsplit /= 2;
-  }
   carve(cfg, p);
-  while (p.total > cs.bytes && p.nsplit > 1) { p.nsplit -= 1; carve(cfg, p); }
+  while (!bf16 && p.total > cs.bytes && p.nsplit > 1) { p.nsplit -= 1; carve(cfg, p); }   // (16-bit: cut to fit above)
   if (p.total > cs.bytes)
     return fail(RELAYGR_ENOSPC, "scratch too small: call needs %zu bytes, %zu are available", p.total, cs.bytes);
   char* S0 = cs.base;
@@ -753,7 +789,7 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
     size_t rb = align_up((size_t)p.n_rows * 4);
     char* r0 = S0 + p.off_rows;
     rt.user = (int32_t*)r0; rt.kind = (int32_t*)(r0 + rb); rt.idx = (int32_t*)(r0 + 2 * rb);
-    rt.lim = (int32_t*)(r0 + 3 * rb); rt.src = (int32_t*)(r0 + 4 * rb);
+    rt.lim = (int32_t*)(r0 + 3 * rb); rt.src = (int32_t*)(r0 + 4 * rb); rt.parts = (int32_t*)(r0 + 5 * rb);
   }
   for (int u = 0; u < n; ++u)
     if (!users[u].kv) users[u].kv = kvs;
@@ -768,8 +804,8 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
   memcpy(hb + o_users, users.data(), (size_t)n * sizeof(UserDesc));
   memcpy(hb + o_ps, pstart.data(), (size_t)(n + 1) * 4);
   memcpy(hb + o_ns, nstart.data(), (size_t)(n + 1) * 4);
-  if (p.n_tiles_new) memcpy(hb + o_tiles, tiles_new.data(), tiles_new.size() * sizeof(AttnTile));
-  if (p.n_tiles_prefix) memcpy(hb + o_tiles + tiles_new.size() * sizeof(AttnTile), tiles_prefix.data(), tiles_prefix.size() * sizeof(AttnTile));
+  if (!list_all.empty()) memcpy(hb + o_tiles, list_all.data(), list_all.size() * sizeof(AttnTile));
+  if (!list_last.empty()) memcpy(hb + o_tiles + list_all.size() * sizeof(AttnTile), list_last.data(), list_last.size() * sizeof(AttnTile));
   char* db = S0 + p.off_blob;
   HIP_TRY(hipMemcpyAsync(db, hb, p.blob_bytes, hipMemcpyHostToDevice, st));
   HIP_TRY(hipEventRecord(slot->done, st));
@@ -801,7 +837,7 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
     // tables and the cleared tail tiles; later layers get theirs from the previous layer's tail kernel
     if (l == 0) {
       ProfScope ps(c, RELAYGR_K_LN, st);
-      const RowBuild rb = {d_users, d_ps, d_ns, n, p.n_prows};
+      const RowBuild rb = {d_users, d_ps, d_ns, n, p.n_prows, rpt, piece_all};
       TailClear tc = {(R + kRowsPerBlock - 1) / kRowsPerBlock, H, dh, 0, p.sfx_tiles ? (void*)sfx : nullptr};
       if (!bf16 && p.n_prows) tc.kv_layers = NL;   // the 16-bit projection fills a prefix's ragged tail itself
       const bool clear = tc.kv_layers > 0 || tc.sfx != nullptr;
@@ -879,8 +915,9 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
     // 16-bit SiLU form: the attention kernel adds the candidates' own keys, so the layer tail does not read q, k, v again
     const bool self_in_attn = bf16 && !softmax;
     ap.knew = self_in_attn ? (const void*)knew : nullptr; ap.vnew = vnew; ap.n_prows = p.n_prows;
-    int nt = last ? p.n_tiles_new : n_tiles_all;
+    const int nt = bf16 ? (int)(last ? list_last : list_all).size() : last ? p.n_tiles_new : p.n_tiles_new + p.n_tiles_prefix;
     ap.n_tiles = nt;
+    if (bf16 && last) ap.tiles = d_tiles + list_all.size();
     if (nt > 0) {
       ProfScope ps(c, RELAYGR_K_ATTN, st);
       rc = launch_attention<T>(cfg, ap, nt, nq, softmax, st);
@@ -916,7 +953,7 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
           fp.offs = last ? (const uint16_t*)c->ln_out_b : (const uint16_t*)c->layers[l + 1].ln_in_b;
           fp.w_score = (const uint16_t*)c->w_score; fp.b_score = c->b_score; fp.scores = score_here ? scores : nullptr;
           fp.row_begin = a0; fp.row_end = R; fp.eps = cfg.ln_eps;
-          fp.part = part; fp.nsplit = p.nsplit; fp.split_stride = (size_t)R * d;
+          fp.part = part; fp.parts_shift = last ? 8 : 0; fp.parts_all = last ? parts_last : parts_all; fp.split_stride = (size_t)R * d;
           fp.u = (const uint16_t*)ubuf; fp.q = self_in_attn ? nullptr : (const uint16_t*)qbuf; fp.knew = (const uint16_t*)knew; fp.vnew = (const uint16_t*)vnew;
           fp.gate_gain = (const uint16_t*)lw.ln_at_g; fp.gate_offs = (const uint16_t*)lw.ln_at_b;
           fp.n_prows = p.n_prows; fp.dh = dh; fp.qk_mul = gate_mul;

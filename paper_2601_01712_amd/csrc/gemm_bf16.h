@@ -573,8 +573,9 @@ __global__ __launch_bounds__(512, 1) void f1_ws_bf16_kernel(F1Params p) {
 // second LayerNorm's gain and offset before the product.
 struct F2LnParams {
   // gate inputs
-  const float* part;        // [nsplit][rows][D] unnormalised attention sums
-  int nsplit;
+  const float* part;        // [pieces][rows][D] unnormalised attention sums; rt.parts says how many a row has
+  int parts_shift;          // 0, or 8 for the last layer
+  int parts_all;            // the same number for every row of the launch, known without the table (0: look it up)
   size_t split_stride;
   const uint16_t* u;        // [rows, D]
   const uint16_t* q;        // [rows, D] (pre-scaled); null: the attention kernel has added the candidates' own keys already
@@ -648,10 +649,10 @@ __device__ __forceinline__ void ld_f32_run(const float* src, float (&v)[E]) {
   }
 }
 
-// The key-split partial sums of G rows, summed in split order, NB splits (all G rows each) in flight at a
-// time: a call with 8 key splits waits for 8 / NB round trips to memory per group of rows, not for one per
-// row and split.  begin() issues the rows' other inputs and the first NB splits; the caller may issue further
-// loads before finish() adds them up and walks the remaining splits.
+// The partial sums of G rows, summed in the order of their pieces, NB pieces (all G rows each) in flight at a
+// time: a row of 8 pieces waits for 8 / NB round trips to memory per group of rows, not for one per
+// row and piece.  begin() issues the rows' other inputs and the first NB pieces; the caller may issue further
+// loads before finish() adds them up and walks the remaining ones.
 // Rows beyond the launch read the workgroup's first row instead and are marked as filler.
 template <int D, bool SM, int G, int NB>
 struct GateLoad {
@@ -659,26 +660,29 @@ struct GateLoad {
   size_t base[G];
   const float* mlr[G];
   float M[G];
+  int cnt[G], cmax;           // pieces of each row (uniform over the wavefront), the most of the group
   float buf[NB][G][E];
   float2 mlb[NB][G];
 
   __device__ __forceinline__ void issue(const F2LnParams& p, int sp0) {
 #pragma unroll
     for (int k = 0; k < NB; ++k) {
-      if (sp0 + k >= p.nsplit) break;      // uniform
+      if (sp0 + k >= cmax) break;      // uniform
 #pragma unroll
       for (int r = 0; r < G; ++r) {
-        ld_f32_run<E>(p.part + (sp0 + k) * p.split_stride + base[r], buf[k][r]);
-        if constexpr (SM) mlb[k][r] = *reinterpret_cast<const float2*>(mlr[r] + (sp0 + k) * p.ml_stride);
+        const int sp = min(sp0 + k, cnt[r] - 1);   // a row with fewer pieces repeats its last one, which add() leaves out
+        ld_f32_run<E>(p.part + sp * p.split_stride + base[r], buf[k][r]);
+        if constexpr (SM) mlb[k][r] = *reinterpret_cast<const float2*>(mlr[r] + sp * p.ml_stride);
       }
     }
   }
   __device__ __forceinline__ void add(const F2LnParams& p, int sp0, GateRow<E, SM> (&gr)[G]) {
 #pragma unroll
     for (int k = 0; k < NB; ++k) {
-      if (sp0 + k >= p.nsplit) break;
+      if (sp0 + k >= cmax) break;
 #pragma unroll
       for (int r = 0; r < G; ++r) {
+        if (sp0 + k >= cnt[r]) continue;
         float w = 1.0f;
         if constexpr (SM) {
           w = (mlb[k][r].x == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mlb[k][r].x - M[r]);
@@ -697,6 +701,8 @@ struct GateLoad {
       const int kind = p.rt.kind[row];
       gr[r].kind = ok ? kind : kRowPad;
       gr[r].n = p.rt.lim[row];
+      cnt[r] = p.parts_all ? p.parts_all : __builtin_amdgcn_readfirstlane((p.rt.parts[row] >> p.parts_shift) & 255);
+      cmax = r == 0 ? cnt[r] : max(cmax, cnt[r]);
       base[r] = (size_t)row * D + lane * E;
       ld_bf16_run<E>(p.u + base[r], gr[r].ub);
       mlr[r] = nullptr;
@@ -714,7 +720,7 @@ struct GateLoad {
         mlr[r] = p.ml + ((size_t)row * p.n_heads + lane * E / p.dh) * 2;
         float m = -INFINITY;
 #pragma unroll
-        for (int sp = 0; sp < 8; ++sp) m = fmaxf(m, mlr[r][(size_t)min(sp, p.nsplit - 1) * p.ml_stride]);   // at most 8 key splits
+        for (int sp = 0; sp < 8; ++sp) m = fmaxf(m, mlr[r][(size_t)min(sp, cnt[r] - 1) * p.ml_stride]);   // at most 8 pieces
         M[r] = m;
       }
       gr[r].mpart = M[r];
@@ -726,7 +732,7 @@ struct GateLoad {
   }
   __device__ __forceinline__ void finish(const F2LnParams& p, GateRow<E, SM> (&gr)[G]) {
     add(p, 0, gr);
-    for (int sp0 = NB; sp0 < p.nsplit; sp0 += NB) {
+    for (int sp0 = NB; sp0 < cmax; sp0 += NB) {
       issue(p, sp0);
       add(p, sp0, gr);
     }

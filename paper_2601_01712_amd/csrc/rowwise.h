@@ -17,8 +17,15 @@ struct RowBuild {
   const int32_t* pstart;
   const int32_t* nstart;
   int n_users, n_prows;
+  int tile_rows, piece_tiles;   // 16-bit attention: rows of a work item, most key tiles of a piece of it (see plan_pieces)
 };
-struct RowEntry { int user, kind, idx, lim, src; };
+struct RowEntry { int user, kind, idx, lim, src, parts; };
+
+// Pieces of the key sequence of the causal work item that starts at position pos0 (a function of the position alone, so
+// that the layer tail and the host agree without a table).
+__host__ __device__ __forceinline__ int causal_parts(int pos0, int tile_rows, int piece_tiles) {
+  return ((pos0 + tile_rows) / kTile + piece_tiles - 1) / piece_tiles;
+}
 
 // The wavefront's lanes compare 64 users' starts at a time: u is the last user with start[u] <= r.
 __device__ __forceinline__ RowEntry row_entry(const RowBuild& rb, int r, int lane) {
@@ -36,7 +43,9 @@ __device__ __forceinline__ RowEntry row_entry(const RowBuild& rb, int r, int lan
     e.idx = r - start[lo];
     if (e.idx < ud.L) { e.kind = kRowPrefix; e.lim = e.idx + 1; e.src = ud.prefix_src0 + e.idx; }
     else              { e.kind = kRowPad; e.lim = 0; e.src = 0; }
+    e.parts = causal_parts(e.idx / rb.tile_rows * rb.tile_rows, rb.tile_rows, rb.piece_tiles);
   } else {
+    e.parts = ud.parts | ud.parts_last << 8;
     int t = r - start[lo];
     if (t < ud.S) { e.kind = kRowSuffix; e.idx = t; e.lim = ud.L + t + 1; e.src = ud.suffix_src0 + t; }
     else          { e.kind = kRowCand; e.idx = t - ud.S; e.lim = ud.L + ud.S; e.src = ud.cand_src0 + e.idx; }
@@ -50,11 +59,11 @@ __device__ __forceinline__ void ln_stats(const float (&v)[E], int d, float eps, 
   float s = 0.f;
 #pragma unroll
   for (int e = 0; e < E; ++e) s += v[e];
-  mean = wave_sum_dpp(s) / (float)d;
+  mean = wave_sum(s) / (float)d;
   float q = 0.f;
 #pragma unroll
   for (int e = 0; e < E; ++e) { float c = v[e] - mean; q += c * c; }
-  rstd = rsqrtf(wave_sum_dpp(q) / (float)d + eps);
+  rstd = rsqrtf(wave_sum(q) / (float)d + eps);
 }
 
 // E consecutive values of a row, as fp32, and back (runs of 16 bytes where there are that many).
@@ -133,7 +142,7 @@ __global__ __launch_bounds__(256) void ln_in_kernel(float* __restrict__ x, T* __
   ld_row_run<T, E>(gain + lane * E, gv);
   ld_row_run<T, E>(offs + lane * E, bv);
   const RowEntry e = row_entry(rb, r, lane);
-  if (lane == 0) { rt.user[r] = e.user; rt.kind[r] = e.kind; rt.idx[r] = e.idx; rt.lim[r] = e.lim; rt.src[r] = e.src; }
+  if (lane == 0) { rt.user[r] = e.user; rt.kind[r] = e.kind; rt.idx[r] = e.idx; rt.lim[r] = e.lim; rt.src[r] = e.src; rt.parts[r] = e.parts; }
   if (e.kind == kRowPad) {   // keep filler rows finite
 #pragma unroll
     for (int i = 0; i < E; ++i) v[i] = 0.f;
