@@ -25,8 +25,6 @@ namespace relaygr {
 
 struct AttnParams {
   const AttnTile* tiles;
-  const UserDesc* users;
-  RowTables rt;
   const void* q;      // [rows][d]
   const void* sfx;    // suffix K/V space (single layer)
   float* part;        // [nsplit][rows][d]
@@ -243,14 +241,14 @@ __global__ __launch_bounds__(NW * GS * 64, (DH >= 128 || GS > 1) ? 1 : 512 / (NW
   if (tile_i >= p.n_tiles) return;
   const AttnTile at = p.tiles[tile_i];
   const int split_ext = at.part;
-  const UserDesc ud = p.users[at.user];
   const int tid = threadIdx.x, lane = tid & 63;
   const int grp = GS == 1 ? 0 : __builtin_amdgcn_readfirstlane((tid >> 6) / NW);    // wavefront group (a scalar: loop counts below depend on it)
   const int wave = (tid >> 6) - grp * NW;           // wavefront inside its group: its rows, its share of a tile
+  const int wave_s = __builtin_amdgcn_readfirstlane(wave);
   const int split = split_ext * GS + grp, nsplit = at.parts * GS;   // this group's key split of all
   struct { int nkp, nfull, t0, t1; } tr;   // prefix tiles in the item's list, those every row sees whole, this group's range
-  tr.nkp = ((at.kind == 0 ? at.pos0 + at.nrows : ud.L) + kTile - 1) / kTile;
-  tr.nfull = (at.kind == 0 ? at.pos0 + 1 : ud.L) / kTile;
+  tr.nkp = ((at.kind == 0 ? at.pos0 + at.nrows : at.L) + kTile - 1) / kTile;
+  tr.nfull = (at.kind == 0 ? at.pos0 + 1 : at.L) / kTile;
   const int per_group = (at.t1 - at.t0 + GS - 1) / GS;
   tr.t0 = min(at.t0 + grp * per_group, at.t1);
   tr.t1 = min(tr.t0 + per_group, at.t1);
@@ -266,7 +264,7 @@ __global__ __launch_bounds__(NW * GS * 64, (DH >= 128 || GS > 1) ? 1 : 512 / (NW
     int lr = wave * 32 * NQ + qb * 32 + l32;
     bool ok = lr < at.nrows;
     int row = at.row0 + (ok ? lr : 0);
-    lim[qb] = ok ? p.rt.lim[row] : 0;
+    lim[qb] = at.lim(lr);
     const uint16_t* qr = qbase + (size_t)row * p.d + head * DH + g * 8;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) qf[qb][ks] = *reinterpret_cast<const uint4*>(qr + ks * 16);
@@ -296,7 +294,7 @@ __global__ __launch_bounds__(NW * GS * 64, (DH >= 128 || GS > 1) ? 1 : 512 / (NW
 #pragma unroll
   for (int qb = 0; qb < NQ; ++qb) {
     const int lr = wave * 32 * NQ + qb * 32 + l32;
-    cand[qb] = own_key && (qb % nsplit) == split && lr < at.nrows && at.pos0 + lr >= ud.S;   // new rows: suffix rows, then candidates
+    cand[qb] = own_key && (qb % nsplit) == split && lr < at.nrows && at.pos0 + lr >= at.S;   // new rows: suffix rows, then candidates
     if (cand[qb]) {
       const size_t nb = (size_t)(at.row0 + lr - p.n_prows) * p.d + head * DH;
       const uint16_t* kn = reinterpret_cast<const uint16_t*>(p.knew) + nb;
@@ -339,24 +337,32 @@ __global__ __launch_bounds__(NW * GS * 64, (DH >= 128 || GS > 1) ? 1 : 512 / (NW
     }
   };
 
-  const uint16_t* kv_base = reinterpret_cast<const uint16_t*>(ud.kv) + ud.kv_tile0 + (int64_t)p.layer * ud.kv_layer_stride +
+  const uint16_t* kv_base = reinterpret_cast<const uint16_t*>(at.kv) + (int64_t)p.layer * at.layer_stride(p.d) +
                             (int64_t)head * TILE;
-  const uint16_t* sfx_base = reinterpret_cast<const uint16_t*>(p.sfx) + ud.sfx_tile0 + (int64_t)head * TILE;
+  const uint16_t* sfx_base = reinterpret_cast<const uint16_t*>(p.sfx) + at.sfx_tile0 + (int64_t)head * TILE;
   const int64_t sfx_stride = (int64_t)2 * kTile * p.d;
 
-  // HBM -> LDS, no registers in between: wavefront w moves the 1 KiB pieces w, w+NW, ... of the tile
+  // HBM -> LDS, no registers in between: each wavefront moves CHUNKS consecutive 1 KiB pieces of the tile, one scalar base and
+  // LDS address per four of them, the rest in the instruction's immediate offset, which counts on both sides (address arithmetic
+  // per piece and lane cost 3 % of the kernel)
   auto issue_tile = [&](int tt, int b) {
-    const uint16_t* src = (tt < tr.nkp) ? kv_base + (int64_t)tt * ud.kv_tile_stride : sfx_base + (int64_t)(tt - tr.nkp) * sfx_stride;
+    const uint16_t* src = (tt < tr.nkp) ? kv_base + (int64_t)tt * at.kv_tile_stride : sfx_base + (int64_t)(tt - tr.nkp) * sfx_stride;
 #pragma unroll
     for (int i = 0; i < CHUNKS; ++i) {
-      const int piece = i * NW + wave;
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + piece * 512 + lane * 8),
-                                       (__attribute__((address_space(3))) void*)(&bufs[b][piece * 512]), 16, 0, 0);
+      const int piece = wave_s * CHUNKS + (i & ~3);
+      auto* gp = (const __attribute__((address_space(1))) void*)(reinterpret_cast<const char*>(src + piece * 512) + lane * 16);
+      auto* lp = (__attribute__((address_space(3))) void*)(&bufs[b][piece * 512]);
+      switch (i & 3) {
+        case 0: __builtin_amdgcn_global_load_lds(gp, lp, 16, 0, 0); break;
+        case 1: __builtin_amdgcn_global_load_lds(gp, lp, 16, 1024, 0); break;
+        case 2: __builtin_amdgcn_global_load_lds(gp, lp, 16, 2048, 0); break;
+        default: __builtin_amdgcn_global_load_lds(gp, lp, 16, 3072, 0); break;
+      }
     }
   };
 
   // a wavefront whose rows all lie beyond the work item's last row only helps move tiles
-  const bool wave_active = wave * 32 * NQ < at.nrows;
+  const bool wave_active = wave_s * 32 * NQ < at.nrows;
   const int nt = tr.t1 - tr.t0;
   int nt_all = nt;                    // barriers every wavefront of the workgroup passes in the tile loop
   if constexpr (GS == 2) {
@@ -393,8 +399,8 @@ __global__ __launch_bounds__(NW * GS * 64, (DH >= 128 || GS > 1) ? 1 : 512 / (NW
       if (MASKED) {
         const int tt = tr.t0 + i;
         const bool is_sfx = tt >= tr.nkp;
-        const int key0 = is_sfx ? ud.L + (tt - tr.nkp) * kTile : tt * kTile;
-        const int seg_end = is_sfx ? ud.L + ud.S : ud.L;
+        const int key0 = is_sfx ? at.L + (tt - tr.nkp) * kTile : tt * kTile;
+        const int seg_end = is_sfx ? at.L + at.S : at.L;
 #pragma unroll
         for (int qb = 0; qb < NQ; ++qb) vis[qb] = min(lim[qb], seg_end) - key0 - 4 * g;
       }

@@ -53,7 +53,16 @@ struct UserDesc {
 };
 static_assert(sizeof(UserDesc) == 80, "UserDesc layout");
 
-// One attention work item: nrows (<= rows per workgroup) consecutive rows of one user.
+// The descriptors of a batch of few users, small enough to be a kernel argument: the call's first kernel then needs no copy
+// to have run before it (see BlobCopy).
+constexpr int kInlineUsers = 16;
+struct InlineBatch {
+  UserDesc users[kInlineUsers];
+  int32_t pstart[kInlineUsers + 1], nstart[kInlineUsers + 1];
+};
+
+// One attention work item: nrows (<= rows per workgroup) consecutive rows of one user, with everything about the user that
+// the attention kernels need (a workgroup's start is a chain of dependent loads: this is one of them instead of three).
 struct AttnTile {
   int32_t user;
   int32_t row0;     // first row in the call's row space
@@ -64,8 +73,19 @@ struct AttnTile {
   // [prefix tiles | suffix tiles], and writes partial sum number `part`
   int32_t t0, t1;
   int16_t part, parts;
+  const void* kv;          // the user's prefix tile 0, layer 0, head 0 (pool slab or scratch)
+  int64_t kv_tile_stride;  // elements between its tiles
+  int64_t sfx_tile0;       // UserDesc::sfx_tile0
+  int32_t L, S;
+  // elements between the layers of a tile: 0 in single-layer scratch (a pool of one layer has the same tile stride, and layer 0)
+  __host__ __device__ __forceinline__ int64_t layer_stride(int d) const { return kv_tile_stride == (int64_t)2 * kTile * d ? 0 : (int64_t)2 * kTile * d; }
+  // keys of [prefix | suffix] that local row lr sees; 0 beyond the item's rows
+  __host__ __device__ __forceinline__ int lim(int lr) const {
+    const int t = pos0 + lr;
+    return lr >= nrows ? 0 : kind == 0 || t < S ? (kind == 0 ? t + 1 : L + t + 1) : L + S;
+  }
 };
-static_assert(sizeof(AttnTile) == 32, "AttnTile layout");
+static_assert(sizeof(AttnTile) == 64, "AttnTile layout");
 
 struct RowTables {
   int32_t* user;

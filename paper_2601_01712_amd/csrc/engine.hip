@@ -141,8 +141,9 @@ static void carve(const relaygr_model_config& c, Plan& p) {
 // under kMinPieceTiles (a workgroup's own start and end cost about as much as six key tiles) and not into more than 8; and
 // only for launches of less than kPieceRounds rounds, where there is too little behind the long items to hide them: each
 // further piece of a row is an fp32 partial sum more for the layer tail to read.
-constexpr int kMaxCutItems = 16384;   // pieces a cut list has at most (in each of the two lists)
-constexpr int kMinPieceTiles = 8, kMaxPieces = 8, kPieceRounds = 4;
+constexpr int kMinPieceTiles = 8, kMaxPieces = 8, kPieceRounds = 4, kMaxSlots = 512;
+// Pieces a cut list has at most: the launch has under kPieceRounds * kMaxSlots (row tile, head) pairs, each cut in at most kMaxPieces.
+static int max_cut_items(const relaygr_model_config& c) { return kMaxPieces * kPieceRounds * kMaxSlots / c.n_heads; }
 static int piece_tiles(int64_t items, int64_t total_key_tiles, int most_key_tiles, int slots) {
   if (items >= (int64_t)kPieceRounds * slots) return std::max(1, most_key_tiles);
   int64_t c = (total_key_tiles + slots - 1) / slots;
@@ -177,7 +178,7 @@ extern "C" size_t relaygr_scratch_bytes(const relaygr_model_config* cfg, int32_t
   int rpt = rows_per_attn_tile(*cfg, 1);
   p.n_tiles_new = (int)(max_new_tokens / rpt) + max_users;
   p.n_tiles_prefix = (int)(padded / rpt) + max_users;
-  p.n_tiles_last = p.n_tiles_new + 2 * kMaxCutItems;   // and room for the items that are cut into pieces
+  p.n_tiles_last = p.n_tiles_new + 2 * max_cut_items(*cfg);   // and room for the items that are cut into pieces
   p.nsplit = 1;
   carve(*cfg, p);
   size_t base = wpack_bytes(*cfg) + p.total;
@@ -223,11 +224,17 @@ static int static_scratch(char** out, int* dev_out = nullptr) {
 
 // ---- context ----------------------------------------------------------------------------------
 constexpr int kStagingSlots = 4;
+constexpr size_t kInlineBlobBytes = 128 << 10, kSlotFlagBytes = 256;   // batches whose descriptors the first kernel fetches itself
+static_assert(kInlineBlobBytes / kBlobChunk * 4 <= kSlotFlagBytes, "a flag per chunk");
 struct StagingSlot {
-  void* host = nullptr;
-  size_t bytes = 0;
+  void* host = nullptr;       // pinned: flags of the kernel that reads the slot, then the descriptors
+  size_t bytes = 0;           // of descriptors
   hipEvent_t done = nullptr;
-  bool pending = false;
+  bool pending = false;       // a copy command may still read it: `done` follows
+  uint32_t seq = 0;           // calls whose first kernel has read (or will read) it
+  int chunks = 0;             // workgroups of the last of them, each of which sets its flag to seq
+  uint32_t* flags() const { return (uint32_t*)host; }
+  char* blob() const { return (char*)host + kSlotFlagBytes; }
 };
 
 struct ProfRec { int cls; hipEvent_t a, b; };
@@ -307,24 +314,25 @@ extern "C" int relaygr_ctx_create(const relaygr_model_config* cfg, const relaygr
     if (e != hipSuccess) { delete c; return fail(RELAYGR_EHIP, "ctx_create: packing weights: %s", hipGetErrorString(e)); }
   }
   // Pinned staging for the per-call descriptor blob, sized once from what the scratch buffer can hold: a call
-  // has at most one row per d*4 bytes of call scratch (the residual stream alone takes that), one attention
-  // work item per 32 rows plus two per user, and a buffer sized by relaygr_scratch_bytes for max_users holds
+  // has at most one row per d*(8 + 3e) bytes of call scratch (residual stream, one partial sum, normalised row, u and q), one
+  // attention work item per 32 (16-bit: 128, in two lists, and the pieces of a cut list) rows plus two per user, and a buffer sized by relaygr_scratch_bytes for max_users holds
   // two K/V tiles per user; calls beyond that are refused (RELAYGR_ENOSPC), so no compute call allocates.
   {
     const size_t call_bytes = scratch_bytes - wpack_bytes(*cfg);
     const size_t d = cfg->d_model, e = elem_bytes(*cfg);
-    const size_t rows_est = call_bytes / (d * 4) + 1;
+    const size_t rows_est = call_bytes / (d * (8 + 3 * e)) + 1;
     const size_t users_est = std::min<size_t>(call_bytes / (4 * kTile * d * e) + 1, 1 << 16);
-    const size_t tiles_est = rows_est / 32 + 2 * users_est;
-    const size_t want = align_up(users_est * sizeof(UserDesc)) + 2 * align_up((users_est + 1) * 4) + align_up((2 * tiles_est + 2 * kMaxCutItems) * sizeof(AttnTile));
+    const size_t tiles_est = is_half16(*cfg) ? 2 * (rows_est / 128 + 2 * users_est + max_cut_items(*cfg)) : rows_est / 32 + 2 * users_est;
+    const size_t want = align_up(users_est * sizeof(UserDesc)) + 2 * align_up((users_est + 1) * 4) + align_up(tiles_est * sizeof(AttnTile));
     for (auto& sl : c->staging) {
-      hipError_t e1 = hipHostMalloc(&sl.host, want, hipHostMallocDefault);
+      hipError_t e1 = hipHostMalloc(&sl.host, kSlotFlagBytes + want, hipHostMallocDefault);
       hipError_t e2 = e1 == hipSuccess ? hipEventCreateWithFlags(&sl.done, hipEventDisableTiming) : e1;
       if (e1 != hipSuccess || e2 != hipSuccess) {
         relaygr_ctx_destroy(c);
         return fail(RELAYGR_EHIP, "ctx_create: pinned staging of %zu bytes: %s", want, hipGetErrorString(e1 != hipSuccess ? e1 : e2));
       }
       sl.bytes = want;
+      memset(sl.host, 0, kSlotFlagBytes);
     }
   }
   {
@@ -351,6 +359,9 @@ extern "C" void relaygr_ctx_destroy(relaygr_ctx* c) {
   if (!c) return;
   for (auto& r : c->prof_recs) { (void)hipEventSynchronize(r.b); (void)hipEventDestroy(r.a); (void)hipEventDestroy(r.b); }
   for (auto e : c->prof_free) (void)hipEventDestroy(e);
+  for (auto& s : c->staging)
+    for (int k = 0; k < s.chunks; ++k)
+      if (__atomic_load_n(s.flags() + k, __ATOMIC_ACQUIRE) != s.seq) { (void)hipDeviceSynchronize(); break; }   // a kernel may still read the slot
   for (auto& s : c->staging) {
     if (s.done) { if (s.pending) (void)hipEventSynchronize(s.done); (void)hipEventDestroy(s.done); }
     if (s.host) (void)hipHostFree(s.host);
@@ -360,8 +371,8 @@ extern "C" void relaygr_ctx_destroy(relaygr_ctx* c) {
 }
 
 // Pinned staging for the descriptor blob: a ring of slots allocated at context creation, each guarded by an
-// event so that a slot is not rewritten while an earlier call's copy may still read it.  The only host wait of
-// a compute call is here: when the upload of the call kStagingSlots calls ago has not completed yet.
+// event, or by flags that the kernel reading it sets, so that a slot is not rewritten while an earlier call may still read it.
+// The only host wait of a compute call is here: when the call kStagingSlots calls ago has not read its slot yet.
 static int staging_acquire(relaygr_ctx* c, size_t bytes, StagingSlot** out) {
   StagingSlot& s = c->staging[c->next_slot];
   if (s.bytes < bytes)
@@ -369,6 +380,19 @@ static int staging_acquire(relaygr_ctx* c, size_t bytes, StagingSlot** out) {
                 "too many users or row tiles for one call)", bytes, s.bytes);
   c->next_slot = (c->next_slot + 1) % kStagingSlots;
   if (s.pending) { HIP_TRY(hipEventSynchronize(s.done)); s.pending = false; }
+  // the first kernel of the call that used the slot last sets one flag per chunk it has read; should it not run within about
+  // a second (a stream held up by the caller), wait for the device instead of spinning on
+  for (int k = 0; k < s.chunks; ++k) {
+    int64_t spins = 0;
+    while (__atomic_load_n(s.flags() + k, __ATOMIC_ACQUIRE) != s.seq) {
+      __builtin_ia32_pause();
+      if (++spins == 20000000) {
+        HIP_TRY(hipDeviceSynchronize());
+        if (__atomic_load_n(s.flags() + k, __ATOMIC_ACQUIRE) != s.seq) return fail(RELAYGR_EHIP, "a staging slot was never read");
+      }
+    }
+  }
+  s.chunks = 0;
   *out = &s;
   return RELAYGR_OK;
 }
@@ -597,7 +621,7 @@ static int check_offsets(const int32_t* off, int n, const char* what) {
 }
 
 template <typename T>
-static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode mode, float* scores, const CallScratch& cs, hipStream_t st) {
+static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode mode, float* scores, const CallScratch& cs, hipStream_t st, bool capturing) {
   const relaygr_model_config& cfg = c->cfg;
   const int d = cfg.d_model, H = cfg.n_heads, dh = d / H, NL = cfg.n_layers, n = b->n_users;
   const bool bf16 = is_half16(cfg);   // either 16-bit type: the MFMA path
@@ -694,9 +718,9 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
     const UserDesc& ud = users[u];
     int Tn = ud.S + ud.M;
     if (ud.nrow0 >= 0)
-      for (int t0 = 0; t0 < Tn; t0 += rpt) rows_new.push_back({u, ud.nrow0 + t0, std::min(rpt, Tn - t0), 1, t0, 0, 0, 0, 1});
+      for (int t0 = 0; t0 < Tn; t0 += rpt) rows_new.push_back({u, ud.nrow0 + t0, std::min(rpt, Tn - t0), 1, t0, 0, 0, 0, 1, nullptr, ud.kv_tile_stride, ud.sfx_tile0, ud.L, ud.S});
     if (ud.prow0 >= 0)
-      for (int i0 = 0; i0 < ud.L; i0 += rpt) rows_prefix.push_back({u, ud.prow0 + i0, std::min(rpt, ud.L - i0), 0, i0, 0, 0, 0, 1});
+      for (int i0 = 0; i0 < ud.L; i0 += rpt) rows_prefix.push_back({u, ud.prow0 + i0, std::min(rpt, ud.L - i0), 0, i0, 0, 0, 0, 1, nullptr, ud.kv_tile_stride, ud.sfx_tile0, ud.L, ud.S});
   }
   auto key_tiles = [&](const AttnTile& a) {
     const UserDesc& ud = users[a.user];
@@ -721,7 +745,7 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
     p.n_tiles_new = (int)rows_new.size();
     p.n_tiles_prefix = (int)rows_prefix.size();
   } else {
-    const int slots = dh == 128 ? c->n_cus : 2 * c->n_cus;   // workgroups the chip takes at a time
+    const int slots = std::min(kMaxSlots, dh == 128 ? c->n_cus : 2 * c->n_cus);   // workgroups the chip takes at a time
     piece_all = piece_tiles((int64_t)(rows_new.size() + rows_prefix.size()) * H, (kt_new + kt_prefix) * H, std::max(most_new, most_prefix ? most_prefix + rpt / kTile : 0), slots);
     piece_last = piece_tiles((int64_t)rows_new.size() * H, kt_new * H, most_new, slots);
     // Fills `out` with the pieces of at most `piece` key tiles; returns the most pieces of a row tile.
@@ -746,20 +770,21 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
       p.n_tiles_new = (int)list_all.size(); p.n_tiles_prefix = 0; p.n_tiles_last = (int)list_last.size();
       carve(cfg, p);
       const bool uncut = list_all.size() == rows_new.size() + rows_prefix.size() && list_last.size() == rows_new.size();
-      if (uncut || (p.total <= cs.bytes && p.nsplit <= kMaxPieces && std::max(list_all.size(), list_last.size()) <= kMaxCutItems)) break;
+      if (uncut || (p.total <= cs.bytes && p.nsplit <= kMaxPieces)) break;
       piece_all *= 2; piece_last *= 2;
     }
     // d_head 64: two pieces of a row go to the two wavefront groups of one workgroup, which add their
     // sums in LDS -- half the partial sums for the layer tail to read -- where every row has the same even number of them and
     // half the workgroups still give every compute unit one (with fewer, e.g. one user with 512 candidates, the attention
     // launch itself gets 25 % slower)
-    const bool one_list = rows_prefix.empty();
+    const bool one_list = rows_prefix.empty();       // the last layer's list is then the same: not sent twice
     if (dh == 64 && one_list && parts_all > 0 && parts_all % 2 == 0 && (int64_t)rows_new.size() * H * (parts_all / 2) >= c->n_cus) {
       p.gs = 2;
       piece_all = piece_last = (most_new + parts_all / 2 - 1) / (parts_all / 2);
       p.nsplit = std::max(cut(true, piece_all, list_all, &parts_all), cut(false, piece_last, list_last, &parts_last));
       p.n_tiles_new = (int)list_all.size(); p.n_tiles_last = (int)list_last.size();
     }
+    if (one_list) { list_last.clear(); p.n_tiles_last = 0; carve(cfg, p); }
     for (int u = 0; u < n; ++u) {
       const int nk = (users[u].L + kTile - 1) / kTile + (users[u].S + kTile - 1) / kTile;
       users[u].parts = std::max(1, (nk + piece_all - 1) / piece_all);
@@ -793,6 +818,8 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
   }
   for (int u = 0; u < n; ++u)
     if (!users[u].kv) users[u].kv = kvs;
+  for (auto* list : {&list_all, &list_last})
+    for (AttnTile& a : *list) a.kv = (const char*)users[a.user].kv + users[a.user].kv_tile0 * (int64_t)sizeof(T);
 
   // -- descriptor blob: users | pstart | nstart | tiles(new, prefix)
   StagingSlot* slot;
@@ -800,16 +827,29 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
   if (rc != RELAYGR_OK) return rc;
   size_t o_users = 0, o_ps = align_up((size_t)n * sizeof(UserDesc)), o_ns = o_ps + align_up((size_t)(n + 1) * 4),
          o_tiles = o_ns + align_up((size_t)(n + 1) * 4);
-  char* hb = (char*)slot->host;
+  char* hb = slot->blob();
   memcpy(hb + o_users, users.data(), (size_t)n * sizeof(UserDesc));
   memcpy(hb + o_ps, pstart.data(), (size_t)(n + 1) * 4);
   memcpy(hb + o_ns, nstart.data(), (size_t)(n + 1) * 4);
   if (!list_all.empty()) memcpy(hb + o_tiles, list_all.data(), list_all.size() * sizeof(AttnTile));
   if (!list_last.empty()) memcpy(hb + o_tiles + list_all.size() * sizeof(AttnTile), list_last.data(), list_last.size() * sizeof(AttnTile));
   char* db = S0 + p.off_blob;
-  HIP_TRY(hipMemcpyAsync(db, hb, p.blob_bytes, hipMemcpyHostToDevice, st));
-  HIP_TRY(hipEventRecord(slot->done, st));
-  slot->pending = true;
+  // few users: the first kernel fetches the descriptors itself; many, or a stream under capture: a copy command brings them
+  const bool inline_batch = n <= kInlineUsers && p.blob_bytes <= kInlineBlobBytes && !capturing;
+  BlobCopy bc = {};
+  InlineBatch ib = {};
+  int copy_blocks = 0;
+  if (inline_batch) {
+    memcpy(ib.users, users.data(), (size_t)n * sizeof(UserDesc));
+    memcpy(ib.pstart, pstart.data(), (size_t)(n + 1) * 4);
+    memcpy(ib.nstart, nstart.data(), (size_t)(n + 1) * 4);
+    copy_blocks = (int)((p.blob_bytes + kBlobChunk - 1) / kBlobChunk);
+    bc = {(const uint4*)hb, (uint4*)db, slot->flags(), ++slot->seq, (int)(p.blob_bytes / 16)};
+  } else {
+    HIP_TRY(hipMemcpyAsync(db, hb, p.blob_bytes, hipMemcpyHostToDevice, st));
+    HIP_TRY(hipEventRecord(slot->done, st));
+    slot->pending = true;
+  }
   const UserDesc* d_users = (const UserDesc*)(db + o_users);
   const int32_t* d_ps = (const int32_t*)(db + o_ps);
   const int32_t* d_ns = (const int32_t*)(db + o_ns);
@@ -838,15 +878,20 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
     if (l == 0) {
       ProfScope ps(c, RELAYGR_K_LN, st);
       const RowBuild rb = {d_users, d_ps, d_ns, n, p.n_prows, rpt, piece_all};
-      TailClear tc = {(R + kRowsPerBlock - 1) / kRowsPerBlock, H, dh, 0, p.sfx_tiles ? (void*)sfx : nullptr};
+      TailClear tc = {(R + kRowsPerBlock - 1) / kRowsPerBlock, 0, H, dh, 0, p.sfx_tiles ? (void*)sfx : nullptr};
       if (!bf16 && p.n_prows) tc.kv_layers = NL;   // the 16-bit projection fills a prefix's ragged tail itself
-      const bool clear = tc.kv_layers > 0 || tc.sfx != nullptr;
-      dim3 grid(tc.row_blocks + (clear ? n * (tc.kv_layers + 1) * H : 0));
+      if (tc.kv_layers > 0 || tc.sfx != nullptr) tc.jobs = n * (tc.kv_layers + 1) * H;
+      dim3 grid(tc.row_blocks + tc.jobs + copy_blocks);
       bool ok = dispatch_e(d, [&](auto e) {
         constexpr int E = decltype(e)::value;
-        hipLaunchKernelGGL((ln_in_kernel<T, E, kPanel>), grid, dim3(256), 0, st, x, xh, (const T*)lw.ln_in_g, (const T*)lw.ln_in_b,
-                           emb_p, emb_s, emb_c, rt, rb, tc, R, cfg.ln_eps);
+        if (inline_batch)
+          hipLaunchKernelGGL((ln_in_kernel<T, E, kPanel, true>), grid, dim3(256), 0, st, x, xh, (const T*)lw.ln_in_g, (const T*)lw.ln_in_b,
+                             emb_p, emb_s, emb_c, rt, rb, tc, bc, ib, R, cfg.ln_eps);
+        else
+          hipLaunchKernelGGL((ln_in_kernel<T, E, kPanel, false>), grid, dim3(256), 0, st, x, xh, (const T*)lw.ln_in_g, (const T*)lw.ln_in_b,
+                             emb_p, emb_s, emb_c, rt, rb, tc, bc, ib, R, cfg.ln_eps);
       });
+      if (inline_batch) slot->chunks = copy_blocks;   // (set once the kernel that will set the flags is on its stream)
       if (!ok) return fail(RELAYGR_EINVAL, "unsupported d_model");
       LAUNCH_CHECK("ln_in");
     }
@@ -909,15 +954,16 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
     if (!have_active) continue;
     // step 3: attention partial sums
     AttnParams ap;
-    ap.tiles = d_tiles; ap.users = d_users; ap.rt = rt; ap.q = qbuf; ap.sfx = sfx; ap.part = part;
+    ap.tiles = d_tiles; ap.q = qbuf; ap.sfx = sfx; ap.part = part;
     ap.split_stride = (size_t)R * d; ap.nsplit = p.nsplit; ap.d = d; ap.n_heads = H; ap.layer = l; ap.score_mul = score_mul;
     ap.ml = ml; ap.ml_stride = (size_t)R * H * 2; ap.gs = p.gs;
     // 16-bit SiLU form: the attention kernel adds the candidates' own keys, so the layer tail does not read q, k, v again
     const bool self_in_attn = bf16 && !softmax;
     ap.knew = self_in_attn ? (const void*)knew : nullptr; ap.vnew = vnew; ap.n_prows = p.n_prows;
-    const int nt = bf16 ? (int)(last ? list_last : list_all).size() : last ? p.n_tiles_new : p.n_tiles_new + p.n_tiles_prefix;
+    const bool own_list = bf16 && last && p.n_prows > 0;
+    const int nt = own_list ? p.n_tiles_last : bf16 ? (int)list_all.size() : last ? p.n_tiles_new : p.n_tiles_new + p.n_tiles_prefix;
     ap.n_tiles = nt;
-    if (bf16 && last) ap.tiles = d_tiles + list_all.size();
+    if (own_list) ap.tiles = d_tiles + list_all.size();
     if (nt > 0) {
       ProfScope ps(c, RELAYGR_K_ATTN, st);
       rc = launch_attention<T>(cfg, ap, nt, nq, softmax, st);
@@ -1044,9 +1090,9 @@ static int run(relaygr_ctx* c, relaygr_kv_pool* pool, const relaygr_batch* b, Mo
   // and against the context's other calls by whoever launches that graph)
   const bool capturing = stream_is_capturing(st);
   if (!capturing && c->has_call && c->last_stream != st) HIP_TRY(order_behind(st, c->last_stream, c->call_done));
-  if (c->cfg.dtype == RELAYGR_DTYPE_FP32) rc = run_typed<float>(c, kp, b, mode, scores, cs, st);
-  else if (c->cfg.dtype == RELAYGR_DTYPE_FP16) rc = run_typed<__half>(c, kp, b, mode, scores, cs, st);
-  else rc = run_typed<__hip_bfloat16>(c, kp, b, mode, scores, cs, st);
+  if (c->cfg.dtype == RELAYGR_DTYPE_FP32) rc = run_typed<float>(c, kp, b, mode, scores, cs, st, capturing);
+  else if (c->cfg.dtype == RELAYGR_DTYPE_FP16) rc = run_typed<__half>(c, kp, b, mode, scores, cs, st, capturing);
+  else rc = run_typed<__hip_bfloat16>(c, kp, b, mode, scores, cs, st, capturing);
   if (!capturing) { c->last_stream = st; c->has_call = true; }
   return rc;
 }

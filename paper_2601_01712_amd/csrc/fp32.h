@@ -48,21 +48,20 @@ __global__ __launch_bounds__(kF32Team * 64, 2) void attn_f32_kernel(AttnParams p
   const int tile_i = item % p.n_tiles, hs = item / p.n_tiles;
   const int head = hs % p.n_heads, split_ext = hs / p.n_heads;
   const AttnTile at = p.tiles[tile_i];
-  const UserDesc ud = p.users[at.user];
   // half tiles this item sees: [prefix | suffix], and this wavefront's part of them
-  const int n_hp = ((at.kind == 0 ? at.pos0 + at.nrows : ud.L) + 31) >> 5;
-  const int n_h = n_hp + (at.kind == 0 ? 0 : (ud.S + 31) >> 5);
+  const int n_hp = ((at.kind == 0 ? at.pos0 + at.nrows : at.L) + 31) >> 5;
+  const int n_h = n_hp + (at.kind == 0 ? 0 : (at.S + 31) >> 5);
   const int parts = team ? p.nsplit * NT : p.nsplit, part_i = team ? split_ext * NT + wave : split_ext;
   const int per = (n_h + parts - 1) / parts;
   const int h0 = min(part_i * per, n_h), h1 = min(h0 + per, n_h);
 
   const bool ok = l32 < at.nrows;
   const int row = at.row0 + (ok ? l32 : 0);
-  const int lim = ok ? p.rt.lim[row] : 0;
-  const float* kv = reinterpret_cast<const float*>(ud.kv) + ud.kv_tile0 + (int64_t)p.layer * ud.kv_layer_stride + (int64_t)head * 2 * kTile * DH;
-  const float* sf = reinterpret_cast<const float*>(p.sfx) + ud.sfx_tile0 + (int64_t)head * 2 * kTile * DH;
+  const int lim = at.lim(l32);
+  const float* kv = reinterpret_cast<const float*>(at.kv) + (int64_t)p.layer * at.layer_stride(p.d) + (int64_t)head * 2 * kTile * DH;
+  const float* sf = reinterpret_cast<const float*>(p.sfx) + at.sfx_tile0 + (int64_t)head * 2 * kTile * DH;
   auto tile_of = [&](int h) -> const float* {        // start of the tile half h lies in
-    return h < n_hp ? kv + (int64_t)(h >> 1) * ud.kv_tile_stride : sf + (int64_t)((h - n_hp) >> 1) * (2 * kTile * p.d);
+    return h < n_hp ? kv + (int64_t)(h >> 1) * at.kv_tile_stride : sf + (int64_t)((h - n_hp) >> 1) * (2 * kTile * p.d);
   };
   auto half_of = [&](int h) { return (h < n_hp ? h : h - n_hp) & 1; };
   float4 kf[KM], vf[DB][4], qf[KM];
@@ -107,8 +106,8 @@ __global__ __launch_bounds__(kF32Team * 64, 2) void attn_f32_kernel(AttnParams p
       if constexpr (!AHEAD) load_v(h);
       else if (h + 1 < h1) load_k(h + 1);
       const bool is_sfx = h >= n_hp;
-      const int key0 = is_sfx ? ud.L + (h - n_hp) * 32 : h * 32;
-      const int vis = min(lim, is_sfx ? ud.L + ud.S : ud.L) - key0 - 4 * g;   // element e is visible iff 8*(e/4) + e%4 < vis
+      const int key0 = is_sfx ? at.L + (h - n_hp) * 32 : h * 32;
+      const int vis = min(lim, is_sfx ? at.L + at.S : at.L) - key0 - 4 * g;   // element e is visible iff 8*(e/4) + e%4 < vis
       if constexpr (SOFTMAX) {
         float mx = -INFINITY;
 #pragma unroll

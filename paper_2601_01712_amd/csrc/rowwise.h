@@ -27,26 +27,34 @@ __host__ __device__ __forceinline__ int causal_parts(int pos0, int tile_rows, in
   return ((pos0 + tile_rows) / kTile + piece_tiles - 1) / piece_tiles;
 }
 
-// The wavefront's lanes compare 64 users' starts at a time: u is the last user with start[u] <= r.
-__device__ __forceinline__ RowEntry row_entry(const RowBuild& rb, int r, int lane) {
-  const int32_t* start = (r < rb.n_prows) ? rb.pstart : rb.nstart;
-  int at_or_before = 0;
-  for (int u0 = 0; u0 < rb.n_users; u0 += 64) {
-    const int u = u0 + lane;
-    at_or_before += __builtin_popcountll(__builtin_amdgcn_ballot_w64(u < rb.n_users && start[min(u, rb.n_users)] <= r));
+// u is the last user with start[u] <= r: the wavefront's lanes compare 64 users' starts at a time, or, for a batch that came as a
+// kernel argument, scalar compares do.
+template <bool INLINE>
+__device__ __forceinline__ RowEntry row_entry(const RowBuild& rb, const InlineBatch& ib, int r, int lane) {
+  int lo = -1;
+  if constexpr (INLINE) {
+    const int32_t* start = (r < rb.n_prows) ? ib.pstart : ib.nstart;
+#pragma unroll
+    for (int u = 0; u < kInlineUsers; ++u) lo += u < rb.n_users && start[u] <= r ? 1 : 0;
+  } else {
+    const int32_t* start = (r < rb.n_prows) ? rb.pstart : rb.nstart;
+    for (int u0 = 0; u0 < rb.n_users; u0 += 64) {
+      const int u = u0 + lane;
+      lo += __builtin_popcountll(__builtin_amdgcn_ballot_w64(u < rb.n_users && start[min(u, rb.n_users)] <= r));
+    }
   }
-  const int lo = at_or_before - 1;
-  const UserDesc& ud = rb.users[lo];
+  const UserDesc& ud = INLINE ? ib.users[lo] : rb.users[lo];
+  const int first = r < rb.n_prows ? (INLINE ? ib.pstart[lo] : rb.pstart[lo]) : (INLINE ? ib.nstart[lo] : rb.nstart[lo]);
   RowEntry e;
   e.user = lo;
   if (r < rb.n_prows) {
-    e.idx = r - start[lo];
+    e.idx = r - first;
     if (e.idx < ud.L) { e.kind = kRowPrefix; e.lim = e.idx + 1; e.src = ud.prefix_src0 + e.idx; }
     else              { e.kind = kRowPad; e.lim = 0; e.src = 0; }
     e.parts = causal_parts(e.idx / rb.tile_rows * rb.tile_rows, rb.tile_rows, rb.piece_tiles);
   } else {
     e.parts = ud.parts | ud.parts_last << 8;
-    int t = r - start[lo];
+    int t = r - first;
     if (t < ud.S) { e.kind = kRowSuffix; e.idx = t; e.lim = ud.L + t + 1; e.src = ud.suffix_src0 + t; }
     else          { e.kind = kRowCand; e.idx = t - ud.S; e.lim = ud.L + ud.S; e.src = ud.cand_src0 + e.idx; }
   }
@@ -102,14 +110,13 @@ __device__ __forceinline__ void store_row_run(T* __restrict__ out, int r, int la
 // whole, before the first projection fills in their tokens, by extra workgroups of the call's first kernel: one per user, head
 // and (prefix) layer, 16-byte stores.  (As launches of their own, one workgroup per user, they took 13 to 29 us of a call.)
 struct TailClear {
-  int row_blocks;            // workgroups that own rows; the ones behind them clear
+  int row_blocks, jobs;      // workgroups that own rows; then `jobs` workgroups that clear
   int n_heads, dh, kv_layers;   // kv_layers: prefix layers to clear (0: none), then one more "layer" for the suffix
   void* sfx;                 // suffix K/V space; null: no suffix in this call
 };
 template <typename T>
-__device__ __forceinline__ void clear_tail_tile(const TailClear& tc, const UserDesc* users, int job) {
-  const int head = job % tc.n_heads, rest = job / tc.n_heads, layer = rest % (tc.kv_layers + 1);
-  const UserDesc& ud = users[rest / (tc.kv_layers + 1)];
+__device__ __forceinline__ void clear_tail_tile(const TailClear& tc, const UserDesc& ud, int job) {
+  const int head = job % tc.n_heads, layer = job / tc.n_heads % (tc.kv_layers + 1);
   T* tile;
   if (layer < tc.kv_layers) {
     if (ud.prow0 < 0 || ud.L % kTile == 0 || (layer > 0 && ud.kv_layer_stride == 0)) return;
@@ -123,25 +130,50 @@ __device__ __forceinline__ void clear_tail_tile(const TailClear& tc, const UserD
   for (int i = threadIdx.x; i < n16; i += blockDim.x) dst[i] = make_uint4(0, 0, 0, 0);
 }
 
+// The rest of a small batch's descriptors -- what the later kernels read -- is fetched from the call's pinned staging slot
+// by the last workgroups of the first kernel, kBlobChunk bytes each, beside the rows' work; each then tells the host in `flags`
+// (pinned too) that its part of the slot has been read.  A copy command and the event behind it took 6 to 19 us of a call.
+constexpr int kBlobChunk = 4096;
+struct BlobCopy {
+  const uint4* src;          // pinned host memory; null: a copy command has brought the descriptors
+  uint4* dst;
+  uint32_t* flags;
+  uint32_t seq;
+  int n16;                   // 16-byte pieces
+};
+
 // First kernel of a call.  A wavefront works out its row's table entry and writes it for the kernels that follow (the
 // call's row tables are built here, not by a launch of their own), fetches the row from its embedding array, writes it to
 // the fp32 residual stream x and its input LayerNorm (step 1 of the first layer) xh = LN(x; g, b) in the storage type; later
 // layers get theirs from the layer tail.
-template <typename T, int E, bool PANEL>
+template <typename T, int E, bool PANEL, bool INLINE>
 __global__ __launch_bounds__(256) void ln_in_kernel(float* __restrict__ x, T* __restrict__ xh,
                                                     const T* __restrict__ gain, const T* __restrict__ offs,
                                                     const T* __restrict__ emb_prefix, const T* __restrict__ emb_suffix,
-                                                    const T* __restrict__ emb_cand, RowTables rt, RowBuild rb, TailClear tc,
-                                                    int n_rows, float eps) {
+                                                    const T* __restrict__ emb_cand, RowTables rt, RowBuild rb, TailClear tc, BlobCopy bc,
+                                                    InlineBatch ib, int n_rows, float eps) {
   const int d = 64 * E;
-  if ((int)blockIdx.x >= tc.row_blocks) { clear_tail_tile<T>(tc, rb.users, (int)blockIdx.x - tc.row_blocks); return; }
+  if ((int)blockIdx.x >= tc.row_blocks) {
+    const int job = (int)blockIdx.x - tc.row_blocks, chunk = job - tc.jobs;
+    if (chunk < 0) {
+      const int u = job / (tc.n_heads * (tc.kv_layers + 1));
+      if constexpr (INLINE) clear_tail_tile<T>(tc, ib.users[u], job);
+      else clear_tail_tile<T>(tc, rb.users[u], job);
+    } else {
+      const int i = chunk * (kBlobChunk / 16) + (int)threadIdx.x;
+      if (i < bc.n16) bc.dst[i] = bc.src[i];
+      __syncthreads();       // every thread has its piece: the slot is free
+      if (threadIdx.x == 0) __hip_atomic_store(bc.flags + chunk, bc.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+    return;
+  }
   const int r = blockIdx.x * kRowsPerBlock + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (r >= n_rows) return;
   const int lane = threadIdx.x & 63;
   float v[E], gv[E], bv[E];
   ld_row_run<T, E>(gain + lane * E, gv);
   ld_row_run<T, E>(offs + lane * E, bv);
-  const RowEntry e = row_entry(rb, r, lane);
+  const RowEntry e = row_entry<INLINE>(rb, ib, r, lane);
   if (lane == 0) { rt.user[r] = e.user; rt.kind[r] = e.kind; rt.idx[r] = e.idx; rt.lim[r] = e.lim; rt.src[r] = e.src; rt.parts[r] = e.parts; }
   if (e.kind == kRowPad) {   // keep filler rows finite
 #pragma unroll
