@@ -322,7 +322,8 @@ extern "C" int relaygr_ctx_create(const relaygr_model_config* cfg, const relaygr
     const size_t d = cfg->d_model, e = elem_bytes(*cfg);
     const size_t rows_est = call_bytes / (d * (8 + 3 * e)) + 1;
     const size_t users_est = std::min<size_t>(call_bytes / (4 * kTile * d * e) + 1, 1 << 16);
-    const size_t tiles_est = is_half16(*cfg) ? 2 * (rows_est / 128 + 2 * users_est + max_cut_items(*cfg)) : rows_est / 32 + 2 * users_est;
+    const size_t cut = max_cut_items(*cfg);
+    const size_t tiles_est = is_half16(*cfg) ? std::max(rows_est / 128 + 2 * users_est, cut) + std::max(rows_est / 128 + users_est, cut) : rows_est / 32 + 2 * users_est;
     const size_t want = align_up(users_est * sizeof(UserDesc)) + 2 * align_up((users_est + 1) * 4) + align_up(tiles_est * sizeof(AttnTile));
     for (auto& sl : c->staging) {
       hipError_t e1 = hipHostMalloc(&sl.host, kSlotFlagBytes + want, hipHostMallocDefault);
@@ -984,9 +985,8 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
         const dim3 grid((R - a0 + 15) / 16);
         dispatch_e(d, [&](auto e) {
           constexpr int D = 64 * decltype(e)::value;
-          constexpr int threads = D >= 256 ? 1024 : D * 4;
-          if (softmax) hipLaunchKernelGGL((tail_f32_kernel<D, true>), grid, dim3(threads), 0, st, fp);
-          else hipLaunchKernelGGL((tail_f32_kernel<D, false>), grid, dim3(threads), 0, st, fp);
+          if (softmax) hipLaunchKernelGGL((tail_f32_kernel<D, true>), grid, dim3(1024), 0, st, fp);
+          else hipLaunchKernelGGL((tail_f32_kernel<D, false>), grid, dim3(1024), 0, st, fp);
         });
       } else {
         {

@@ -254,7 +254,7 @@ __global__ __launch_bounds__(256, TB == 1 ? 4 : 2) void f1_f32_kernel(F1F32Param
   };
 #pragma unroll
   for (int s = 0; s < PF; ++s)
-    if (8 * s < k_len) load(s, 8 * s);
+    load(s, min(8 * s, k_len - 8));
   for (int k = 0; k < k_len; k += 8 * PF) {
 #pragma unroll
     for (int s = 0; s < PF; ++s) {
@@ -262,7 +262,7 @@ __global__ __launch_bounds__(256, TB == 1 ? 4 : 2) void f1_f32_kernel(F1F32Param
       float4 ca[TB], cw[TB];
 #pragma unroll
       for (int i = 0; i < TB; ++i) { ca[i] = af[s][i]; cw[i] = wf[s][i]; }
-      if (k + 8 * (s + PF) < k_len) load(s, k + 8 * (s + PF));
+      load(s, min(k + 8 * (s + PF), k_len - 8));       // unconditional, so that the compiler can count what is outstanding
 #pragma unroll
       for (int t = 0; t < 4; ++t)
 #pragma unroll
@@ -303,7 +303,7 @@ __global__ __launch_bounds__(256, TB == 1 ? 4 : 2) void f1_f32_kernel(F1F32Param
 
 // ---- layer tail: combine, gate, output projection, residual, next LayerNorm or score head ------------
 // As in the 16-bit path everything between the attention and the next projections is local to a row: a workgroup takes 16
-// rows over the full width.  A wavefront gates 16/NW rows (lane = d/64 features) into LDS; the product is feature-major
+// rows over the full width.  Each of its 16 wavefronts gates a row (lane = d/64 features) into LDS; the product is feature-major
 // (16x16x4: a lane ends up with 4 consecutive features of one token), W2 streamed from L2 straight into registers, PF
 // groups of 16 k ahead; LayerNorm statistics by two lane exchanges and one exchange between wavefronts.
 struct TailF32Params {
@@ -322,85 +322,117 @@ struct TailF32Params {
 };
 
 template <int D, bool SM>
-__global__ __launch_bounds__(D >= 256 ? 1024 : D * 4) void tail_f32_kernel(TailF32Params p) {
-  constexpr int E = D / 64, NW = D >= 256 ? 16 : D / 16, FB = D / 16 / NW, MS = D / 16, PF = FB >= 4 ? 2 : FB == 2 ? 4 : MS >= 8 ? 8 : 4, RPW = 16 / NW, YS = D + 4;
+__global__ __launch_bounds__(1024) void tail_f32_kernel(TailF32Params p) {
+  constexpr int E = D / 64, NW = D >= 256 ? 16 : D / 16;   // wavefronts that take part in the product (all 16 gate a row each)
+  constexpr int FB = D / 16 / NW, MS = D / 16, PF = FB >= 4 ? 2 : FB == 2 ? 4 : MS >= 8 ? 8 : 4, YS = D + 4;
+  constexpr int NB = E >= 16 ? 1 : E >= 8 ? (SM ? 2 : 4) : 8;   // partial sums of the row in flight
   __shared__ float ys[16][YS];                       // rows 16 bytes apart in banks: 16 lanes' 16-byte reads take 64 banks
   __shared__ float red[3][NW][16];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int row0 = p.row_begin + blockIdx.x * 16;
   const int tk = lane & 15, g4 = lane >> 4;
-  // first weight fragments: they depend on nothing
-  const float* w[FB];
+  const bool product = wave < NW;
+
+  // this wavefront's row: everything that depends on no other load first
+  const int r = min(row0 + wave, p.row_end - 1);
+  const bool real = row0 + wave < p.row_end;
+  const size_t base = (size_t)r * D + lane * E;
+  float pb[NB][E];
+  auto load_parts = [&](int s0) {
 #pragma unroll
-  for (int j = 0; j < FB; ++j) w[j] = p.W + (size_t)((wave * FB + j) * 16 + tk) * D + 4 * g4;
+    for (int k = 0; k < NB; ++k)
+      if (s0 + k < p.nsplit) ld_row_run<float, E>(p.part + (s0 + k) * p.split_stride + base, pb[k]);
+  };
+  load_parts(0);
+  float ug[E], qs[E], ks[E], vs[E], gg[E], go[E];
+  ld_row_run<float, E>(p.u + base, ug);
+  const bool new_row = r >= p.n_prows;               // only a new row can be a candidate, which has q, k and v rows
+#pragma unroll
+  for (int i = 0; i < E; ++i) qs[i] = ks[i] = vs[i] = 0.f;
+  if (new_row) {
+    const size_t nb = (size_t)(r - p.n_prows) * D + lane * E;
+    ld_row_run<float, E>(p.q + base, qs);
+    ld_row_run<float, E>(p.knew + nb, ks);
+    ld_row_run<float, E>(p.vnew + nb, vs);
+  }
+  const int kind = p.rt.kind[r], seen = p.rt.lim[r];
+  float ms[8], ls[8];
+  if constexpr (SM) {
+    const float* mlr = p.ml + ((size_t)r * p.n_heads + lane * E / p.dh) * 2;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      const float2 t = *reinterpret_cast<const float2*>(mlr + min(s, p.nsplit - 1) * p.ml_stride);
+      ms[s] = s < p.nsplit ? t.x : -INFINITY;
+      ls[s] = t.y;
+    }
+  }
+  constexpr bool EARLY = E < 16;                     // d = 1024: the registers do not allow it
+  if constexpr (EARLY) {
+    ld_row_run<float, E>(p.gate_gain + lane * E, gg);
+    ld_row_run<float, E>(p.gate_offs + lane * E, go);
+  }
+  // first weight fragments
+  const float* w[FB];
   float4 wf[PF][FB];
 #pragma unroll
-  for (int s = 0; s < PF; ++s)
+  for (int j = 0; j < FB; ++j) w[j] = p.W + (size_t)(((product ? wave : 0) * FB + j) * 16 + tk) * D + 4 * g4;
+  auto first_w = [&]() {
 #pragma unroll
-    for (int j = 0; j < FB; ++j) wf[s][j] = *reinterpret_cast<const float4*>(w[j] + 16 * s);
+    for (int s = 0; s < PF; ++s)
+#pragma unroll
+      for (int j = 0; j < FB; ++j) wf[s][j] = *reinterpret_cast<const float4*>(w[j] + 16 * s);
+  };
+  if constexpr (EARLY) first_w();
 
+  const bool cand = kind == kRowCand;
+  float o[E], n = (float)seen, dot = 0.f, M = -INFINITY, l = 0.f;
 #pragma unroll
-  for (int rr = 0; rr < RPW; ++rr) {
-    const int lr = wave * RPW + rr, r = row0 + lr;
-    float* yrow = &ys[lr][lane * E];
-    if (r >= p.row_end) {
+  for (int i = 0; i < E; ++i) { o[i] = 0.f; dot += qs[i] * ks[i]; }
+  for (int m = (p.dh / E) >> 1; m > 0; m >>= 1) dot += __shfl_xor(dot, m, 64);   // lanes of one head are consecutive
+  const float tself = dot * p.alpha;
+  if constexpr (SM) {                                // pieces and the own key by weights exp(m_s - M)
+    M = cand ? tself : -INFINITY;
 #pragma unroll
-      for (int i = 0; i < E; ++i) yrow[i] = 0.f;
-      continue;
-    }
-    const size_t base = (size_t)r * D + lane * E;
-    const int kind = p.rt.kind[r];
-    float o[E], ug[E];
-#pragma unroll
-    for (int i = 0; i < E; ++i) { o[i] = 0.f; ug[i] = p.u[base + i]; }
-    float n = (float)p.rt.lim[r], tself = 0.f;
-    float vs[E];
-    const bool cand = kind == kRowCand;
-    if (cand) {
-      const size_t nb = (size_t)(r - p.n_prows) * D + lane * E;
-      float dot = 0.f;
-#pragma unroll
-      for (int i = 0; i < E; ++i) { dot += p.q[base + i] * p.knew[nb + i]; vs[i] = p.vnew[nb + i]; }
-      for (int m = (p.dh / E) >> 1; m > 0; m >>= 1) dot += __shfl_xor(dot, m, 64);   // lanes of one head are consecutive
-      tself = dot * p.alpha;
-    }
-    if constexpr (SM) {
-      // splits and the own key by weights exp(m_s - M)
-      const float* mlr = p.ml + ((size_t)r * p.n_heads + lane * E / p.dh) * 2;
-      float M = cand ? tself : -INFINITY, l = 0.f;
-      for (int s = 0; s < p.nsplit; ++s) M = fmaxf(M, mlr[s * p.ml_stride]);
-      for (int s = 0; s < p.nsplit; ++s) {
-        const float ms = mlr[s * p.ml_stride], wt = ms == -INFINITY ? 0.f : __expf(ms - M);
-        l += wt * mlr[s * p.ml_stride + 1];
-#pragma unroll
-        for (int i = 0; i < E; ++i) o[i] += wt * p.part[s * p.split_stride + base + i];
-      }
-      if (cand) {
-        const float wt = __expf(tself - M);
-        l += wt;
-#pragma unroll
-        for (int i = 0; i < E; ++i) o[i] += wt * vs[i];
-      }
-      n = l;
-    } else {
-      for (int s = 0; s < p.nsplit; ++s)
-#pragma unroll
-        for (int i = 0; i < E; ++i) o[i] += p.part[s * p.split_stride + base + i];
-      if (cand) {
-        const float pe = silu_f32(tself);
-#pragma unroll
-        for (int i = 0; i < E; ++i) o[i] += pe * vs[i];
-        n += 1.0f;
-      }
-    }
-    const float inv_n = 1.0f / n;
-#pragma unroll
-    for (int i = 0; i < E; ++i) o[i] *= inv_n;
-    float mean, rstd;
-    ln_stats<E>(o, D, p.eps, mean, rstd);
-#pragma unroll
-    for (int i = 0; i < E; ++i) yrow[i] = ((o[i] - mean) * rstd * p.gate_gain[lane * E + i] + p.gate_offs[lane * E + i]) * ug[i];
+    for (int s = 0; s < 8; ++s) M = fmaxf(M, ms[s]);
   }
+#pragma unroll
+  for (int s0 = 0; s0 < 8; s0 += NB) {
+    if (s0 >= p.nsplit) break;
+    if (s0 > 0) load_parts(s0);
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+      if (s0 + k >= p.nsplit) break;
+      float wt = 1.0f;
+      if constexpr (SM) {
+        wt = ms[s0 + k] == -INFINITY ? 0.f : __expf(ms[s0 + k] - M);
+        l += wt * ls[s0 + k];
+      }
+#pragma unroll
+      for (int i = 0; i < E; ++i) o[i] += wt * pb[k][i];
+    }
+  }
+  if (cand) {
+    const float pe = SM ? __expf(tself - M) : silu_f32(tself);
+#pragma unroll
+    for (int i = 0; i < E; ++i) o[i] += pe * vs[i];
+    l += pe;
+    n += 1.0f;
+  }
+  const float inv_n = 1.0f / (SM ? l : n);
+#pragma unroll
+  for (int i = 0; i < E; ++i) o[i] *= inv_n;
+  {
+    float mean, rstd, y[E];
+    ln_stats<E>(o, D, p.eps, mean, rstd);
+    if constexpr (!EARLY) {
+      ld_row_run<float, E>(p.gate_gain + lane * E, gg);
+      ld_row_run<float, E>(p.gate_offs + lane * E, go);
+    }
+#pragma unroll
+    for (int i = 0; i < E; ++i) y[i] = real ? ((o[i] - mean) * rstd * gg[i] + go[i]) * ug[i] : 0.f;
+    store_row_run<float, E, false>(&ys[0][0], wave, lane, YS, y);
+  }
+  if constexpr (!EARLY) first_w();
   // the accumulators start from the residual row and the bias: element e of acc[j] is feature (wave*FB + j)*16 + 4*g4 + e
   const int row = row0 + tk;
   const bool live = row < p.row_end;
@@ -408,23 +440,22 @@ __global__ __launch_bounds__(D >= 256 ? 1024 : D * 4) void tail_f32_kernel(TailF
   f32x4v_t acc[FB];
 #pragma unroll
   for (int j = 0; j < FB; ++j) {
-    const int c = (wave * FB + j) * 16 + 4 * g4;
+    const int c = ((product ? wave : 0) * FB + j) * 16 + 4 * g4;
     const float4 xv = *reinterpret_cast<const float4*>(xrow + c), bv = *reinterpret_cast<const float4*>(p.bias + c);
     acc[j] = f32x4v_t{xv.x + bv.x, xv.y + bv.y, xv.z + bv.z, xv.w + bv.w};
   }
   __syncthreads();
   const float* yl = &ys[tk][4 * g4];
-  for (int m0 = 0; m0 < MS; m0 += PF) {
+  if (product) for (int m0 = 0; m0 < MS; m0 += PF) {
 #pragma unroll
     for (int s = 0; s < PF; ++s) {
       const float4 y = *reinterpret_cast<const float4*>(yl + 16 * (m0 + s));
       float4 cw[FB];
 #pragma unroll
       for (int j = 0; j < FB; ++j) cw[j] = wf[s][j];
-      if (m0 + s + PF < MS) {
+      // (unconditional, so that the compiler can count what is outstanding)
 #pragma unroll
-        for (int j = 0; j < FB; ++j) wf[s][j] = *reinterpret_cast<const float4*>(w[j] + 16 * (m0 + s + PF));
-      }
+      for (int j = 0; j < FB; ++j) wf[s][j] = *reinterpret_cast<const float4*>(w[j] + 16 * min(m0 + s + PF, MS - 1));
 #pragma unroll
       for (int t = 0; t < 4; ++t)
 #pragma unroll
@@ -436,7 +467,7 @@ __global__ __launch_bounds__(D >= 256 ? 1024 : D * 4) void tail_f32_kernel(TailF
 #pragma unroll
   for (int j = 0; j < FB; ++j) {
     const int c = (wave * FB + j) * 16 + 4 * g4;
-    if (live && !want_score) *reinterpret_cast<float4*>(xrow + c) = make_float4(acc[j][0], acc[j][1], acc[j][2], acc[j][3]);
+    if (product && live && !want_score) *reinterpret_cast<float4*>(xrow + c) = make_float4(acc[j][0], acc[j][1], acc[j][2], acc[j][3]);
     s1 += (acc[j][0] + acc[j][1]) + (acc[j][2] + acc[j][3]);
   }
   if (p.xh == nullptr && !want_score) return;        // uniform over the grid
@@ -444,7 +475,7 @@ __global__ __launch_bounds__(D >= 256 ? 1024 : D * 4) void tail_f32_kernel(TailF
   auto row_sum = [&](float v, int k) {
     v += __shfl_xor(v, 16, 64);
     v += __shfl_xor(v, 32, 64);
-    if (g4 == 0) red[k][wave][tk] = v;
+    if (product && g4 == 0) red[k][wave][tk] = v;
     __syncthreads();
     float t = 0.f;
 #pragma unroll
@@ -461,6 +492,7 @@ __global__ __launch_bounds__(D >= 256 ? 1024 : D * 4) void tail_f32_kernel(TailF
   float sc = 0.f;
 #pragma unroll
   for (int j = 0; j < FB; ++j) {
+    if (!product) break;
     const int c = (wave * FB + j) * 16 + 4 * g4;
     const float4 gg = *reinterpret_cast<const float4*>(p.gain + c), oo = *reinterpret_cast<const float4*>(p.offs + c);
     float4 z;
