@@ -165,6 +165,10 @@ __host__ __device__ __forceinline__ size_t panel_off(int row, int k, int K) {
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
+// (the address-space forms are for pointers that were themselves loaded from memory: the compiler cannot tell that those are
+// global addresses and would use flat stores, which also hold up the LDS counter)
+typedef __attribute__((address_space(1))) u32x4_t gu32x4_t;
+__device__ __forceinline__ gu32x4_t* as_global16(uint16_t* p) { return (gu32x4_t*)p; }
 __device__ __forceinline__ void st_stream(uint4* p, uint4 v) { __builtin_nontemporal_store(u32x4_t{v.x, v.y, v.z, v.w}, reinterpret_cast<u32x4_t*>(p)); }
 __device__ __forceinline__ void st_stream(uint2* p, uint2 v) { __builtin_nontemporal_store(u32x2_t{v.x, v.y}, reinterpret_cast<u32x2_t*>(p)); }
 __device__ __forceinline__ void st_stream(float4* p, float4 v) { __builtin_nontemporal_store(f32x4_t{v.x, v.y, v.z, v.w}, reinterpret_cast<f32x4_t*>(p)); }

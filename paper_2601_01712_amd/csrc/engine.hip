@@ -919,23 +919,24 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
         fp.users = d_users; fp.rt = rt; fp.d = d; fp.dh = dh; fp.n_prows = p.n_prows; fp.layer = l;
         fp.row_begin = r0; fp.row_end = r1; fp.n_mtiles = (r1 - r0 + 64 * kF1TM - 1) / (64 * kF1TM);
         fp.cm = cm; fp.q_mul = q_mul; fp.stream_out = (r1 - r0) >= kF1StreamMinRows ? 1 : 0;
-        // launches of a few thousand rows take the weight-stationary kernel: one persistent workgroup per compute unit,
+        // small tiles, deep pipeline, as long as they fit the chip at once (two a compute unit)
+        const int small = (r1 - r0 + 64 * kF1SmallTM - 1) / (64 * kF1SmallTM) * cm.nblk * (d / (64 * kF1TN));
+        if (small <= 2 * c->n_cus) {
+          fp.n_mtiles = (r1 - r0 + 64 * kF1SmallTM - 1) / (64 * kF1SmallTM);
+          hipLaunchKernelGGL((f1_gemm_bf16_kernel<HT, kF1SmallTM, kF1SmallStages>), dim3((small + 7) / 8 * 8), dim3(256), 0, st, fp);
+          return;
+        }
+        // then the weight-stationary kernel: one persistent workgroup per compute unit,
         // (compute units / column slices) row groups, a multiple of 8 so that each XCD takes whole row groups
         const int n_slices = cm.nblk * (d / 128);
         const int n_rg = d <= 512 ? (c->n_cus / n_slices) & ~7 : 0;
-        if (r1 - r0 >= kF1WsMinRows && (r0 & 63) == 0 && n_rg >= 8) {
+        if ((r0 & 63) == 0 && n_rg >= 8) {
           const dim3 grid(n_slices * n_rg);
           switch (d) {
             case 128: hipLaunchKernelGGL((f1_ws_bf16_kernel<HT, 128>), grid, dim3(512), 0, st, fp); break;
             case 256: hipLaunchKernelGGL((f1_ws_bf16_kernel<HT, 256>), grid, dim3(512), 0, st, fp); break;
             default: hipLaunchKernelGGL((f1_ws_bf16_kernel<HT, 512>), grid, dim3(512), 0, st, fp); break;
           }
-          return;
-        }
-        if (r1 - r0 <= kF1SmallMaxRows) {       // a few hundred rows: small tiles, deep pipeline
-          fp.n_mtiles = (r1 - r0 + 64 * kF1SmallTM - 1) / (64 * kF1SmallTM);
-          int total = fp.n_mtiles * cm.nblk * (d / (64 * kF1TN));
-          hipLaunchKernelGGL((f1_gemm_bf16_kernel<HT, kF1SmallTM, kF1SmallStages>), dim3((total + 7) / 8 * 8), dim3(256), 0, st, fp);
           return;
         }
         int total = fp.n_mtiles * cm.nblk * (d / (64 * kF1TN));

@@ -18,6 +18,8 @@
 // fragment, and what the fp32 residual update wants).
 #pragma once
 
+#include <type_traits>
+
 #include "common.h"
 #include "gemm.h"
 
@@ -154,14 +156,22 @@ struct F1Params {
 };
 
 
+__device__ __forceinline__ void st_out(uint16_t* dst, uint4 v, int stream) {
+  gu32x4_t* g = as_global16(dst);
+  if (stream) __builtin_nontemporal_store(u32x4_t{v.x, v.y, v.z, v.w}, g);
+  else *g = u32x4_t{v.x, v.y, v.z, v.w};
+}
+
 constexpr int kF1TM = 4, kF1TN = 2, kF1Stages = 3;   // 256 tokens x 128 features per workgroup
 constexpr int kStageLd = 64 * kF1TN + 8;          // epilogue staging row stride (elements)
 // Launches of a few hundred rows (one user's candidates): the big tile gives the chip a few dozen workgroups, each
 // waiting a memory round trip per k-step with two stages in flight.  The small tile (64 tokens) with six stages has
 // more than a third of K = 512 in flight per workgroup and four times the workgroups; six stages are 72 KiB of LDS, so
 // that a compute unit holds two such workgroups and a launch of up to 512 of them (2048 rows at d = 512) runs in one
-// round (with eight stages, one workgroup per unit: 2048 rows 30 % slower, 512 rows the same).
-constexpr int kF1SmallTM = 1, kF1SmallStages = 6, kF1SmallMaxRows = 4095;
+// round.  That is where its range ends: at d = 512 2048 rows take 12.9 us and 2112 rows 19.8 us, against 15.1 us for the
+// weight-stationary kernel below (d = 256: 4000 rows 9.4 against 11.0 us, 4100 rows 13.7 against 11.7 us; d = 1024, whose
+// alternative is the big tile: 1024 rows 22.1 against 29.0 us, 1500 rows 35.8 against 31.0 us).
+constexpr int kF1SmallTM = 1, kF1SmallStages = 6;
 
 template <typename H, int TM, int NSTAGE>
 __global__ __launch_bounds__(256, TM == 4 ? 2 : 1) void f1_gemm_bf16_kernel(F1Params p) {
@@ -182,35 +192,37 @@ __global__ __launch_bounds__(256, TM == 4 ? 2 : 1) void f1_gemm_bf16_kernel(F1Pa
   const int c0 = (nt % ntiles_per_blk) * G::BNf;            // first feature inside the block
   const int n0 = blk * p.cm.d + c0;
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, g = lane >> 5;
-  const int d = p.d, dh = p.dh;
+  const int d = p.d, dh = p.dh, dh_sh = 31 - __builtin_clz(dh);   // d_head is a power of two
 
   // A tile of prefix rows is one user's consecutive prefix positions starting at a multiple of 256
   // (row-space alignment), possibly followed by padding rows.
   const bool prefix_tile = m0 < p.n_prows;
+  const int pos0 = prefix_tile ? p.rt.idx[m0] : 0;         // a multiple of 64
+  const UserDesc& tud = p.users[prefix_tile ? p.rt.user[m0] : 0];
+  const int L = tud.L, Lceil = (L + kTile - 1) / kTile * kTile;
+  if (prefix_tile && pos0 >= Lceil) return;                // filler behind the user's last K/V tile
+  uint16_t* kvb = reinterpret_cast<uint16_t*>(const_cast<void*>(tud.kv)) + tud.kv_tile0 + (int64_t)(pos0 >> 6) * tud.kv_tile_stride +
+                  (int64_t)p.layer * tud.kv_layer_stride;  // the K/V tile of the first 64 rows
+  const int64_t kv_stride = tud.kv_tile_stride;
   f32x16_t acc[TM][TN];
 
   if (blk == 1 && prefix_tile) {
     // ---- V of prefix rows: token-major product; the accumulator of a 32-token x 32-feature block
     // is, lane for lane, two V-tile fragments (m = 0, 1), stored as 1 KiB contiguous runs.
     gemm_mainloop<H, TM, TN, NSTAGE, false>(p.A, p.W, d, m0, n0, lds, acc);
-    const int user = p.rt.user[m0];
-    const UserDesc ud = p.users[user];
-    const int pos0 = p.rt.idx[m0];
-    const int L = ud.L, Lceil = (L + kTile - 1) / kTile * kTile;
-    uint16_t* kvb = reinterpret_cast<uint16_t*>(const_cast<void*>(ud.kv)) + ud.kv_tile0 + (int64_t)p.layer * ud.kv_layer_stride;
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
       const int c = c0 + wn * 64 + j * 32;                  // first feature of this 32-feature block
-      const int head = c / dh, db = (c - head * dh) >> 5;
+      const int head = c >> dh_sh, db = (c - (head << dh_sh)) >> 5;
       const float bias = H::to_f32(p.bias[n0 + wn * 64 + j * 32 + l32]);
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
         const int tok0 = pos0 + wm * (32 * TM) + i * 32;    // first token of this 32-token block
         if (tok0 >= Lceil) continue;
         const int kb = (tok0 >> 5) & 1;
-        uint16_t* frag = kvb + (int64_t)(tok0 >> 6) * ud.kv_tile_stride + (int64_t)head * 2 * kTile * dh + kTile * dh;
+        uint16_t* frag = kvb + (int64_t)((tok0 - pos0) >> 6) * kv_stride + head * 2 * kTile * dh + kTile * dh;
 #pragma unroll
         for (int m = 0; m < 2; ++m) {
           uint32_t w[4];
@@ -227,7 +239,7 @@ __global__ __launch_bounds__(256, TM == 4 ? 2 : 1) void f1_gemm_bf16_kernel(F1Pa
             w[2 * h] = H::pack2(v[0], v[1]);
             w[2 * h + 1] = H::pack2(v[2], v[3]);
           }
-          *reinterpret_cast<uint4*>(frag + (((db * 2 + kb) * 2 + m) * 64 + lane) * 8) = make_uint4(w[0], w[1], w[2], w[3]);
+          st_out(frag + (((db * 2 + kb) * 2 + m) * 64 + lane) * 8, make_uint4(w[0], w[1], w[2], w[3]), 0);
         }
       }
     }
@@ -237,17 +249,21 @@ __global__ __launch_bounds__(256, TM == 4 ? 2 : 1) void f1_gemm_bf16_kernel(F1Pa
   // ---- everything else: feature-major product, staged through LDS as [token][feature] so that
   // every global store is a 16-byte chunk of 8 consecutive features of one token.
   // In the store phase a thread owns 16-byte chunk (tid & 15) of rows (tid >> 4) + 16*it of the
-  // tile; fetch those rows' kinds now, so that the lookups complete under the main loop.
+  // tile; the kinds of new rows (candidate or suffix) are fetched now, and the biases, so that they arrive under the main loop.
   constexpr int ITS = ROWS / 16;                 // 16 rows per pass of the store phase
+  const bool by_kind = (blk == 1 || blk == 3) && !prefix_tile;
   int kinds[ITS];
 #pragma unroll
-  for (int it = 0; it < ITS; ++it) {
-    const int row = m0 + (tid >> 4) + 16 * it;
-    kinds[it] = row < p.row_end ? p.rt.kind[row] : kRowPad;
+  for (int it = 0; it < ITS; ++it) kinds[it] = kRowCand;
+  if (by_kind) {
+#pragma unroll
+    for (int it = 0; it < ITS; ++it) kinds[it] = p.rt.kind[min(m0 + (tid >> 4) + 16 * it, p.row_end - 1)];
   }
-  // a prefix tile belongs to one user and holds consecutive prefix positions from pos0 on
-  const int tile_user = prefix_tile ? p.rt.user[m0] : 0;
-  const int pos0 = prefix_tile ? p.rt.idx[m0] : 0;
+  uint2 bias[TN][4];
+#pragma unroll
+  for (int j = 0; j < TN; ++j)
+#pragma unroll
+    for (int e4 = 0; e4 < 4; ++e4) bias[j][e4] = *reinterpret_cast<const uint2*>(p.bias + n0 + wn * 64 + j * 32 + 8 * e4 + 4 * g);
   gemm_mainloop<H, TM, TN, NSTAGE, true>(p.A, p.W, d, m0, n0, lds, acc);
   const float mul = (blk == 2) ? p.q_mul : 1.0f;
 #pragma unroll
@@ -255,7 +271,7 @@ __global__ __launch_bounds__(256, TM == 4 ? 2 : 1) void f1_gemm_bf16_kernel(F1Pa
 #pragma unroll
     for (int e4 = 0; e4 < 4; ++e4) {
       const int f = wn * 64 + j * 32 + 8 * e4 + 4 * g;  // 4 consecutive features held by this lane
-      const uint2 bb = *reinterpret_cast<const uint2*>(p.bias + n0 + f);
+      const uint2 bb = bias[j][e4];
       const float b0 = H::to_f32(bb.x & 0xFFFF), b1 = H::to_f32(bb.x >> 16);
       const float b2 = H::to_f32(bb.y & 0xFFFF), b3 = H::to_f32(bb.y >> 16);
 #pragma unroll
@@ -268,50 +284,40 @@ __global__ __launch_bounds__(256, TM == 4 ? 2 : 1) void f1_gemm_bf16_kernel(F1Pa
       }
     }
   __syncthreads();
-  const UserDesc tud = p.users[tile_user];
   // ROWS tokens x 16 chunks of 8 features
+  const int t0 = tid >> 4, fc = tid & 15, c = c0 + fc * 8;   // c: feature inside the block
+  const int head = c >> dh_sh, f = c - (head << dh_sh);
+  const int n_rows = p.row_end - m0;
+  // (u and q of filler rows are written too: nothing reads them, and a filler row's inputs are zeros)
+  uint16_t* rows_out = (blk == 0 ? p.u + (size_t)m0 * d : blk == 2 ? p.q + (size_t)m0 * d : (blk == 3 ? p.knew : p.vnew) + ((int64_t)m0 - p.n_prows) * d) + c;
 #pragma unroll
   for (int it = 0; it < ITS; ++it) {
-    const int t = (tid >> 4) + 16 * it, fc = tid & 15;
-    const int row = m0 + t;
-    if (row >= p.row_end) continue;
-    const int kind = kinds[it];
-    if (kind == kRowPad && (blk == 0 || blk == 2)) continue;
+    const int t = t0 + 16 * it;
+    if (t >= n_rows) continue;
     uint4 val = *reinterpret_cast<const uint4*>(&lds[t * kStageLd + fc * 8]);
-    const int c = c0 + fc * 8;                             // feature inside the block
-    if (blk == 0) { *reinterpret_cast<uint4*>(p.u + (size_t)row * d + c) = val; continue; }
-    if (blk == 2) { *reinterpret_cast<uint4*>(p.q + (size_t)row * d + c) = val; continue; }
-    if (kind == kRowCand) {
-      *reinterpret_cast<uint4*>((blk == 3 ? p.knew : p.vnew) + (size_t)(row - p.n_prows) * d + c) = val;
-      continue;
-    }
-    const int head = c / dh, f = c - head * dh;
-    uint16_t* base;
-    int idx;
-    if (kind == kRowSuffix) {
-      const UserDesc& ud = p.users[p.rt.user[row]];
-      idx = p.rt.idx[row];
-      base = p.sfx + ud.sfx_tile0 + (int64_t)(idx >> 6) * (2 * kTile * d) + (int64_t)head * 2 * kTile * dh;
-    } else {   // prefix row or filler of a prefix tile (blk == 3 here: V of prefix tiles took the other path)
-      idx = pos0 + t;
-      if (idx >= (tud.L + kTile - 1) / kTile * kTile) continue;   // filler beyond the user's last tile
-      if (kind == kRowPad) val = make_uint4(0, 0, 0, 0);          // ragged tail of the last tile: zeros
-      base = reinterpret_cast<uint16_t*>(const_cast<void*>(tud.kv)) + tud.kv_tile0 + (int64_t)(idx >> 6) * tud.kv_tile_stride +
-             (int64_t)p.layer * tud.kv_layer_stride + (int64_t)head * 2 * kTile * dh;
-    }
-    const int rr = idx & 63;
-    if (blk == 3) {
-      *reinterpret_cast<uint4*>(base + KvLayout16::k_off(rr, f, dh)) = val;
-    } else {   // V of a suffix row: its 8 features go to 8 different fragments
-      const uint16_t* e = reinterpret_cast<const uint16_t*>(&val);
+    if (blk == 3 && prefix_tile) {                           // K of prefix rows (V took the other path)
+      const int pos = pos0 + t;
+      if (pos >= Lceil) continue;                            // filler beyond the user's last tile
+      if (pos >= L) val = make_uint4(0, 0, 0, 0);            // ragged tail of the last tile: zeros
+      st_out(kvb + (int64_t)(it >> 2) * kv_stride + head * 2 * kTile * dh + KvLayout16::k_off(t & 63, f, dh), val, 0);
+    } else if (kinds[it] == kRowCand) {
+      st_out(rows_out + (size_t)t * d, val, 0);
+    } else {                                                 // k or v of a suffix row
+      const int row = m0 + t, idx = p.rt.idx[row], rr = idx & 63;
+      uint16_t* base = p.sfx + p.users[p.rt.user[row]].sfx_tile0 + (int64_t)(idx >> 6) * (2 * kTile * d) + head * 2 * kTile * dh;
+      if (blk == 3) {
+        st_out(base + KvLayout16::k_off(rr, f, dh), val, 0);
+      } else {   // V: its 8 features go to 8 different fragments
+        const uint32_t w[4] = {val.x, val.y, val.z, val.w};
 #pragma unroll
-      for (int x = 0; x < 8; ++x) base[KvLayout16::v_off(rr, f + x, dh)] = e[x];
+        for (int x = 0; x < 8; ++x) base[KvLayout16::v_off(rr, f + x, dh)] = (uint16_t)(w[x >> 1] >> (16 * (x & 1)));
+      }
     }
   }
 }
 
 // ---- f1, weight-stationary form ----------------------------------------------------------------
-// For launches of a few thousand rows and more.  One persistent workgroup of 8 wavefronts per compute unit
+// For launches of two thousand rows and more.  One persistent workgroup of 8 wavefronts per compute unit
 // keeps a 128-feature slice of W1 (128 x D, up to 128 KiB) in LDS for its whole life and walks 64-row units
 // of its share of the rows; the workgroups of one XCD take the same row groups, so that a token panel comes
 // from memory once per XCD.  Each wavefront owns whole units (64 rows x 128 features, 2 x 4 MFMA blocks):
@@ -329,7 +335,6 @@ __global__ __launch_bounds__(256, TM == 4 ? 2 : 1) void f1_gemm_bf16_kernel(F1Pa
 // launches keep plain stores, because what they write fits the L2s and the attention and layer-tail kernels
 // read it straight back (8192 rows: the layer tail is 2 us slower behind streaming stores).
 constexpr int kF1WsPF = 4;          // k-steps of token fragments in flight per wavefront
-constexpr int kF1WsMinRows = 4096;  // below this the tiled kernel's many small workgroups fill the chip better
 constexpr int kF1StreamMinRows = 16384;   // from here on a launch writes 64 MiB and more (at d = 512): streaming stores
 constexpr int kTailVr8MaxRows = 1024;   // layer tail: launches of at most this many rows use 8-row workgroups (d = 256, 512),
 constexpr int kTailVr16MaxRows = 4096;  // of at most this many 16-row workgroups: still at most one workgroup per compute unit
@@ -346,32 +351,32 @@ __device__ __forceinline__ void f1_ws_mainloop(const uint16_t* __restrict__ tp0,
   }
 #pragma unroll
   for (int j = 0; j < 4; ++j) ff[0][j] = *reinterpret_cast<const uint4*>(wlane + j * 512);
-#pragma unroll 1
-  for (int ks0 = 0; ks0 < KS; ks0 += PF) {
+  // The last PF k-steps are a copy of the loop's body without loads: were the loads inside the loop conditional, the
+  // compiler could not count them and would wait for ALL outstanding ones wherever it needs the oldest.
+  auto k_steps = [&](auto more_tag, int ks0) {
+    constexpr bool MORE = decltype(more_tag)::value;
 #pragma unroll
     for (int pf = 0; pf < PF; ++pf) {
       const int ks = ks0 + pf, cur = pf & 1, nxt = cur ^ 1;
-      if (ks + 1 < KS) {
+      if (MORE || pf + 1 < PF) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) ff[nxt][j] = *reinterpret_cast<const uint4*>(wlane + ((ks + 1) * 4 + j) * 512);
       }
-      __builtin_amdgcn_sched_barrier(0);   // the next k-step's LDS reads stay ahead of this k-step's MFMAs
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j)
           acc[i][j] = FEATURE_MAJOR ? H::mfma(ff[cur][j], t[pf][i], acc[i][j]) : H::mfma(t[pf][i], ff[cur][j], acc[i][j]);
-      if (ks + PF < KS) {
+      if constexpr (MORE) {
         t[pf][0] = *reinterpret_cast<const uint4*>(tp0 + (size_t)(ks + PF) * 2048);
         t[pf][1] = *reinterpret_cast<const uint4*>(tp1 + (size_t)(ks + PF) * 2048);
       }
     }
-  }
-}
-
-__device__ __forceinline__ void st_out(uint4* dst, uint4 v, int stream) {
-  if (stream) st_stream(dst, v);
-  else *dst = v;
+  };
+#pragma unroll 1
+  for (int ks0 = 0; ks0 < KS - PF; ks0 += PF) k_steps(std::true_type(), ks0);
+  k_steps(std::false_type(), KS - PF);
 }
 
 template <typename H, int D>
@@ -380,8 +385,9 @@ __global__ __launch_bounds__(512, 1) void f1_ws_bf16_kernel(F1Params p) {
   static_assert(KS % kF1WsPF == 0 && (KS * 4) % 8 == 0, "shape");
   __shared__ __attribute__((aligned(16))) uint16_t wl[KS * 2048];       // 128 features x D, fragment order
   __shared__ __attribute__((aligned(16))) uint16_t stage[8 * 32 * 64];   // per wavefront: 32 tokens x 64 features
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, g = lane >> 5;
-  const int d = p.d, dh = p.dh;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, g = lane >> 5;
+  constexpr int d = D;
+  const int dh = p.dh, dh_sh = 31 - __builtin_clz(dh);       // d_head is a power of two
   const int slices_per_blk = d >> 7;
   const int n_slices = p.cm.nblk * slices_per_blk;
   const int n_rg = (int)gridDim.x / n_slices;                 // row groups: a multiple of 8 (host)
@@ -417,7 +423,15 @@ __global__ __launch_bounds__(512, 1) void f1_ws_bf16_kernel(F1Params p) {
     // a unit of prefix rows lies inside one user's (256-aligned) prefix region: consecutive positions from pos0
     const bool prefix_unit = m0 < p.n_prows;
     const int tile_user = prefix_unit ? p.rt.user[m0] : 0;
-    const int pos0 = prefix_unit ? p.rt.idx[m0] : 0;
+    const int pos0 = prefix_unit ? p.rt.idx[m0] : 0;           // a multiple of 64: the unit is one K/V tile
+    const UserDesc& tud = p.users[tile_user];
+    const int L = tud.L;
+    if (prefix_unit && pos0 >= (L + kTile - 1) / kTile * kTile) continue;   // filler behind the user's last tile
+    // the unit's K/V tile (all heads)
+    uint16_t* tile = reinterpret_cast<uint16_t*>(const_cast<void*>(tud.kv)) + tud.kv_tile0 + (int64_t)(pos0 >> 6) * tud.kv_tile_stride +
+                     (int64_t)p.layer * tud.kv_layer_stride;
+    // new rows: candidates throughout (their k and v go row-major, as u and q do), or suffix rows among them
+    const int kind_row = m0 + lane < p.row_end ? p.rt.kind[m0 + lane] : kRowCand;
     f32x16_t acc[2][4];
 
     if (blk == 1 && prefix_unit) {
@@ -431,19 +445,14 @@ __global__ __launch_bounds__(512, 1) void f1_ws_bf16_kernel(F1Params p) {
           for (int e = 0; e < 16; ++e) acc[i][j][e] = b;
       }
       f1_ws_mainloop<H, D, false>(tp0, tp1, wlane, acc);
-      const UserDesc ud = p.users[tile_user];
-      const int L = ud.L, Lceil = (L + kTile - 1) / kTile * kTile;
-      uint16_t* kvb = reinterpret_cast<uint16_t*>(const_cast<void*>(ud.kv)) + ud.kv_tile0 + (int64_t)p.layer * ud.kv_layer_stride;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int c = c0 + j * 32;
-        const int head = c / dh, db = (c - head * dh) >> 5;
+        const int head = c >> dh_sh, db = (c - (head << dh_sh)) >> 5;
+        uint16_t* frag = tile + head * 2 * kTile * dh + kTile * dh;
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-          const int tok0 = pos0 + i * 32;
-          if (tok0 >= Lceil) continue;
-          const int kb = (tok0 >> 5) & 1;
-          uint16_t* frag = kvb + (int64_t)(tok0 >> 6) * ud.kv_tile_stride + (int64_t)head * 2 * kTile * dh + kTile * dh;
+          const int tok0 = pos0 + i * 32, kb = i;
 #pragma unroll
           for (int m = 0; m < 2; ++m) {
             uint32_t w[4];
@@ -460,7 +469,7 @@ __global__ __launch_bounds__(512, 1) void f1_ws_bf16_kernel(F1Params p) {
               w[2 * h] = H::pack2(v[0], v[1]);
               w[2 * h + 1] = H::pack2(v[2], v[3]);
             }
-            st_out(reinterpret_cast<uint4*>(frag + (((db * 2 + kb) * 2 + m) * 64 + lane) * 8), make_uint4(w[0], w[1], w[2], w[3]), p.stream_out);
+            st_out(frag + (((db * 2 + kb) * 2 + m) * 64 + lane) * 8, make_uint4(w[0], w[1], w[2], w[3]), p.stream_out);
           }
         }
       }
@@ -482,16 +491,14 @@ __global__ __launch_bounds__(512, 1) void f1_ws_bf16_kernel(F1Params p) {
         }
       }
     f1_ws_mainloop<H, D, true>(tp0, tp1, wlane, acc);
-    const UserDesc tud = p.users[tile_user];
+    const bool any_suffix = !prefix_unit && __builtin_amdgcn_ballot_w64(kind_row != kRowCand) != 0;
+    // where 16-byte chunk (row tk of block i, features c0 + jh*64 + fc*8 ..) goes: row-major, or the K tile of a prefix unit
+    const bool row_major = blk == 0 || blk == 2 || !prefix_unit;
+    const int tk0 = lane >> 3;                                   // this lane stores chunk lane & 7 of rows tk0 + 8 n of a 32-row block
+    uint16_t* rows_out = blk == 0 ? p.u + (size_t)m0 * d : blk == 2 ? p.q + (size_t)m0 * d : (blk == 3 ? p.knew : p.vnew) + ((int64_t)m0 - p.n_prows) * d;
+    const int n_rows = p.row_end - m0;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      // this lane stores 16-byte chunk lane & 7 of rows (lane >> 3) + 8 n of the 32-row block, n = 0..3
-      int kinds[4];
-#pragma unroll
-      for (int n = 0; n < 4; ++n) {
-        const int row = m0 + i * 32 + (lane >> 3) + 8 * n;
-        kinds[n] = row < p.row_end ? p.rt.kind[row] : -1;
-      }
 #pragma unroll
       for (int jh = 0; jh < 2; ++jh) {
 #pragma unroll
@@ -507,46 +514,46 @@ __global__ __launch_bounds__(512, 1) void f1_ws_bf16_kernel(F1Params p) {
           }
         }
         __builtin_amdgcn_wave_barrier();   // LDS serves a wavefront's accesses in order: the reads below see the writes above
+        int fc = lane & 7;
+        // (opaque to the compiler: otherwise it hoists the index arithmetic of the rare suffix-V scatter below out of
+        // the unit loop, 32 values per lane that it then has to spill -- 16 MiB of scratch writes per launch)
+        asm volatile("" : "+v"(fc));
+        const int c = c0 + jh * 64 + fc * 8;                     // feature inside the block
+        const int head = c >> dh_sh, f = c - (head << dh_sh);
+        auto staged = [&](int n) {                               // chunk fc of row tk0 + 8 n (tk & 7 == tk0 & 7)
+          return *reinterpret_cast<const uint4*>(st + (tk0 + 8 * n) * 64 + ((fc ^ (tk0 & 7)) << 3));
+        };
+        if (row_major && !(any_suffix && (blk == 1 || blk == 3))) {
+          // (u and q of filler rows are written too: nothing reads them, and a filler row's inputs are zeros)
+          uint16_t* dst = rows_out + (i * 32 + tk0) * d + c;
 #pragma unroll
-        for (int n = 0; n < 4; ++n) {
-          const int tk = (lane >> 3) + 8 * n;
-          int fc = lane & 7;
-          // (opaque to the compiler: otherwise it hoists the index arithmetic of the rare suffix-V scatter below out of
-          // the unit loop, 32 values per lane that it then has to spill -- 16 MiB of scratch writes per launch)
-          asm volatile("" : "+v"(fc));
-          uint4 val = *reinterpret_cast<const uint4*>(st + tk * 64 + ((fc ^ (tk & 7)) << 3));
-          const int row = m0 + i * 32 + tk;
-          const int kind = kinds[n];
-          if (kind < 0) continue;                                // beyond the launch's last row
-          if (kind == kRowPad && (blk == 0 || blk == 2)) continue;
-          const int c = c0 + jh * 64 + fc * 8;                   // feature inside the block
-          if (blk == 0) { st_out(reinterpret_cast<uint4*>(p.u + (size_t)row * d + c), val, p.stream_out); continue; }
-          if (blk == 2) { st_out(reinterpret_cast<uint4*>(p.q + (size_t)row * d + c), val, p.stream_out); continue; }
-          if (kind == kRowCand) {
-            st_out(reinterpret_cast<uint4*>((blk == 3 ? p.knew : p.vnew) + (size_t)(row - p.n_prows) * d + c), val, p.stream_out);
-            continue;
-          }
-          const int head = c / dh, f = c - head * dh;
-          uint16_t* base;
-          int pos;
-          if (kind == kRowSuffix) {
-            const UserDesc& ud = p.users[p.rt.user[row]];
-            pos = p.rt.idx[row];
-            base = p.sfx + ud.sfx_tile0 + (int64_t)(pos >> 6) * (2 * kTile * d) + (int64_t)head * 2 * kTile * dh;
-          } else {   // prefix row or filler of a prefix unit (blk == 3 here: V of prefix units took the other path)
-            pos = pos0 + i * 32 + tk;
-            if (pos >= (tud.L + kTile - 1) / kTile * kTile) continue;   // filler beyond the user's last tile
-            if (kind == kRowPad) val = make_uint4(0, 0, 0, 0);          // ragged tail of the last tile: zeros
-            base = reinterpret_cast<uint16_t*>(const_cast<void*>(tud.kv)) + tud.kv_tile0 + (int64_t)(pos >> 6) * tud.kv_tile_stride +
-                   (int64_t)p.layer * tud.kv_layer_stride + (int64_t)head * 2 * kTile * dh;
-          }
-          const int rr = pos & 63;
-          if (blk == 3) {
-            st_out(reinterpret_cast<uint4*>(base + KvLayout16::k_off(rr, f, dh)), val, p.stream_out);
-          } else {   // V of a suffix row: its 8 features go to 8 different fragments
-            const uint16_t* e = reinterpret_cast<const uint16_t*>(&val);
+          for (int n = 0; n < 4; ++n)
+            if (i * 32 + tk0 + 8 * n < n_rows) st_out(dst + n * 8 * d, staged(n), p.stream_out);
+        } else if (prefix_unit) {                                // K of prefix rows (V took the other path)
+          uint16_t* kt = tile + head * 2 * kTile * dh;
 #pragma unroll
-            for (int x = 0; x < 8; ++x) base[KvLayout16::v_off(rr, f + x, dh)] = e[x];
+          for (int n = 0; n < 4; ++n) {
+            const int rr = i * 32 + tk0 + 8 * n;
+            uint4 v = staged(n);
+            if (pos0 + rr >= L) v = make_uint4(0, 0, 0, 0);       // ragged tail of the last tile: zeros
+            st_out(kt + KvLayout16::k_off(rr, f, dh), v, p.stream_out);
+          }
+        } else {                                                 // k or v of new rows with suffix rows among them
+#pragma unroll 1
+          for (int n = 0; n < 4; ++n) {
+            const int rl = i * 32 + tk0 + 8 * n, row = m0 + rl;
+            if (rl >= n_rows) break;
+            const uint4 v = staged(n);
+            if (p.rt.kind[row] == kRowCand) { st_out(rows_out + rl * d + c, v, p.stream_out); continue; }
+            const int pos = p.rt.idx[row], rr = pos & 63;
+            uint16_t* base = p.sfx + p.users[p.rt.user[row]].sfx_tile0 + (int64_t)(pos >> 6) * (2 * kTile * d) + head * 2 * kTile * dh;
+            if (blk == 3) {
+              st_out(base + KvLayout16::k_off(rr, f, dh), v, p.stream_out);
+            } else {   // V: its 8 features go to 8 different fragments
+              const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+              for (int x = 0; x < 8; ++x) base[KvLayout16::v_off(rr, f + x, dh)] = (uint16_t)(w[x >> 1] >> (16 * (x & 1)));
+            }
           }
         }
         __builtin_amdgcn_wave_barrier();   // the next pass overwrites the staging area
