@@ -853,7 +853,7 @@ __device__ __forceinline__ void l2_touch(const void* base, int lines, int share,
 // pulling 16 KiB of split partial sums per row through its own memory path; with VR = 8 or 16 four times or
 // twice as many units share that.
 template <typename H, int D, int NW, int RB, bool SM, int OCC = 1, int VR = 32>
-__global__ __launch_bounds__(NW * 64, OCC) void f2_ln_bf16_kernel(F2LnParams p) {
+__global__ __launch_bounds__(NW * 64, OCC == 2 ? 4 : 1) void f2_ln_bf16_kernel(F2LnParams p) {
   constexpr int KS = D / 16;            // k-steps
   constexpr int FB = D / 32 / NW;       // 32-feature blocks per wavefront
   constexpr int PF = FB >= 4 ? 2 : (OCC == 2 ? 4 : 8);   // k-steps of weight fragments in flight per wavefront (16 spills: 38 % slower)
@@ -976,7 +976,9 @@ __global__ __launch_bounds__(NW * 64, OCC) void f2_ln_bf16_kernel(F2LnParams p) 
         lno[j][e4] = *reinterpret_cast<const uint2*>(p.offs + c);
       }
   }
-  for (int ks0 = 0; ks0 < KS; ks0 += PF) {
+  // (the last PF k-steps apart from the loop, so that the loads in it are unconditional: see f1_ws_mainloop)
+  auto k_steps = [&](auto more_tag, int ks0) {
+    constexpr bool MORE = decltype(more_tag)::value;
 #pragma unroll
     for (int i = 0; i < PF; ++i) {
       const int ks = (ks0 + i + rot) & (KS - 1);
@@ -987,12 +989,15 @@ __global__ __launch_bounds__(NW * 64, OCC) void f2_ln_bf16_kernel(F2LnParams p) 
       for (int j = 0; j < FB; ++j)
 #pragma unroll
         for (int b = 0; b < RB; ++b) acc[b][j] = H::mfma(wf[i][j], tf[b], acc[b][j]);
-      if (ks0 + i + PF < KS) {
+      if constexpr (MORE) {
 #pragma unroll
         for (int j = 0; j < FB; ++j) wf[i][j] = *reinterpret_cast<const uint4*>(wbase[j] + (size_t)((ks + PF) & (KS - 1)) * 2048);
       }
     }
-  }
+  };
+#pragma unroll 1
+  for (int ks0 = 0; ks0 < KS - PF; ks0 += PF) k_steps(std::true_type(), ks0);
+  k_steps(std::false_type(), KS - PF);
 
   // the new residual rows go back; their sums start the LayerNorm statistics
   const bool want_score = p.scores != nullptr;
