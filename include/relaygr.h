@@ -226,7 +226,7 @@ int  relaygr_rank_with_cache(relaygr_ctx* ctx, relaygr_kv_pool* pool, const rela
  * same scores as relaygr_rank_with_cache, but the call's working buffers (residual stream, projections,
  * attention partial sums, row tables, batch descriptors) are laid out in a buffer that lives inside the
  * library -- RELAYGR_STATIC_SCRATCH_BYTES of device memory per GPU, held from the moment the library is
- * loaded until the process ends -- instead of in the context's scratch buffer (of which only the re-packed
+ * loaded until the process ends (and 4 MiB beside it for batch descriptors) -- instead of in the context's scratch buffer (of which only the re-packed
  * weights at its head are read).  The call allocates and frees nothing, on the device or pinned on the host.
  * A call whose buffers do not fit (about 2000 suffix + candidate rows at d_model 512 with eight key-range
  * splits; fewer splits are tried first) is RELAYGR_ENOSPC and nothing is enqueued.  Every call on a GPU,

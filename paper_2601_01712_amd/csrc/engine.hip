@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -11,6 +12,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <thread>
 #include <type_traits>
 #include <vector>
 
@@ -193,7 +195,10 @@ extern "C" size_t relaygr_scratch_bytes(const relaygr_model_config* cfg, int32_t
 // device address is looked up once per device (hipGetSymbolAddress, with that device current) and that
 // pointer is what kernels, copies and fills are given.
 constexpr size_t kStaticScratchBytes = RELAYGR_STATIC_SCRATCH_BYTES;
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+// Room beside it for the descriptors (64-byte work items, in two lists, and six row tables: at most 132 bytes a row), so that
+// they take nothing from what a call's rows may use: 16-bit d = 128, where rows are smallest, fits 30 000 rows in 64 MiB.
+constexpr size_t kStaticDescriptorBytes = (size_t)4 << 20;
+static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + kStaticDescriptorBytes];
 
 constexpr int kMaxDevices = 64;
 static std::mutex g_static_mu;
@@ -234,6 +239,17 @@ struct StagingSlot {
   uint32_t seq = 0;           // calls whose first kernel has read (or will read) it
   int chunks = 0;             // workgroups of the last of them, each of which sets its flag to seq
   uint32_t* flags() const { return (uint32_t*)host; }
+  // Waits for that kernel: it is on its stream (chunks is 0 otherwise), so this ends when the stream gets there.  Polls for
+  // about a millisecond, then sleeps between looks.  (No wait for the device: that would also wait for streams
+  // that have nothing to do with the call, and fail while one of them is being captured.)
+  void wait_read() {
+    for (int k = 0, looks = 0; k < chunks; ++k)
+      while (__atomic_load_n(flags() + k, __ATOMIC_ACQUIRE) != seq) {
+        if (++looks < 20000) __builtin_ia32_pause();
+        else std::this_thread::sleep_for(std::chrono::microseconds(20));
+      }
+    chunks = 0;
+  }
   char* blob() const { return (char*)host + kSlotFlagBytes; }
 };
 
@@ -258,6 +274,7 @@ struct relaygr_ctx {
   std::vector<const uint16_t*> w1_packed, w2_packed;   // bf16: panels at the start of scratch
   int n_cus = 256;                      // compute units of the device the context was created on
   StagingSlot staging[kStagingSlots];   // pinned, allocated once at creation
+  void* staging_mem = nullptr;          // of all slots
   int next_slot = 0;
   // A context's calls share its scratch, so they must not overlap on the GPU.  On one stream they cannot; a call
   // on another stream than the one before it is made to wait for what that stream holds (order_behind).
@@ -325,15 +342,19 @@ extern "C" int relaygr_ctx_create(const relaygr_model_config* cfg, const relaygr
     const size_t cut = max_cut_items(*cfg);
     const size_t tiles_est = is_half16(*cfg) ? std::max(rows_est / 128 + 2 * users_est, cut) + std::max(rows_est / 128 + users_est, cut) : rows_est / 32 + 2 * users_est;
     const size_t want = align_up(users_est * sizeof(UserDesc)) + 2 * align_up((users_est + 1) * 4) + align_up(tiles_est * sizeof(AttnTile));
-    for (auto& sl : c->staging) {
-      hipError_t e1 = hipHostMalloc(&sl.host, kSlotFlagBytes + want, hipHostMallocDefault);
-      hipError_t e2 = e1 == hipSuccess ? hipEventCreateWithFlags(&sl.done, hipEventDisableTiming) : e1;
-      if (e1 != hipSuccess || e2 != hipSuccess) {
-        relaygr_ctx_destroy(c);
-        return fail(RELAYGR_EHIP, "ctx_create: pinned staging of %zu bytes: %s", want, hipGetErrorString(e1 != hipSuccess ? e1 : e2));
-      }
+    // (one allocation for all slots: each costs a few hundred microseconds)
+    const size_t each = align_up(kSlotFlagBytes + want);
+    hipError_t e1 = hipHostMalloc(&c->staging_mem, kStagingSlots * each, hipHostMallocDefault);
+    for (int k = 0; k < kStagingSlots && e1 == hipSuccess; ++k) {
+      StagingSlot& sl = c->staging[k];
+      sl.host = (char*)c->staging_mem + k * each;
       sl.bytes = want;
       memset(sl.host, 0, kSlotFlagBytes);
+      e1 = hipEventCreateWithFlags(&sl.done, hipEventDisableTiming);
+    }
+    if (e1 != hipSuccess) {
+      relaygr_ctx_destroy(c);
+      return fail(RELAYGR_EHIP, "ctx_create: pinned staging of %d x %zu bytes: %s", kStagingSlots, each, hipGetErrorString(e1));
     }
   }
   {
@@ -360,13 +381,11 @@ extern "C" void relaygr_ctx_destroy(relaygr_ctx* c) {
   if (!c) return;
   for (auto& r : c->prof_recs) { (void)hipEventSynchronize(r.b); (void)hipEventDestroy(r.a); (void)hipEventDestroy(r.b); }
   for (auto e : c->prof_free) (void)hipEventDestroy(e);
-  for (auto& s : c->staging)
-    for (int k = 0; k < s.chunks; ++k)
-      if (__atomic_load_n(s.flags() + k, __ATOMIC_ACQUIRE) != s.seq) { (void)hipDeviceSynchronize(); break; }   // a kernel may still read the slot
   for (auto& s : c->staging) {
+    s.wait_read();
     if (s.done) { if (s.pending) (void)hipEventSynchronize(s.done); (void)hipEventDestroy(s.done); }
-    if (s.host) (void)hipHostFree(s.host);
   }
+  if (c->staging_mem) (void)hipHostFree(c->staging_mem);
   if (c->call_done) (void)hipEventDestroy(c->call_done);
   delete c;
 }
@@ -381,19 +400,7 @@ static int staging_acquire(relaygr_ctx* c, size_t bytes, StagingSlot** out) {
                 "too many users or row tiles for one call)", bytes, s.bytes);
   c->next_slot = (c->next_slot + 1) % kStagingSlots;
   if (s.pending) { HIP_TRY(hipEventSynchronize(s.done)); s.pending = false; }
-  // the first kernel of the call that used the slot last sets one flag per chunk it has read; should it not run within about
-  // a second (a stream held up by the caller), wait for the device instead of spinning on
-  for (int k = 0; k < s.chunks; ++k) {
-    int64_t spins = 0;
-    while (__atomic_load_n(s.flags() + k, __ATOMIC_ACQUIRE) != s.seq) {
-      __builtin_ia32_pause();
-      if (++spins == 20000000) {
-        HIP_TRY(hipDeviceSynchronize());
-        if (__atomic_load_n(s.flags() + k, __ATOMIC_ACQUIRE) != s.seq) return fail(RELAYGR_EHIP, "a staging slot was never read");
-      }
-    }
-  }
-  s.chunks = 0;
+  s.wait_read();
   *out = &s;
   return RELAYGR_OK;
 }
@@ -892,9 +899,9 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
           hipLaunchKernelGGL((ln_in_kernel<T, E, kPanel, false>), grid, dim3(256), 0, st, x, xh, (const T*)lw.ln_in_g, (const T*)lw.ln_in_b,
                              emb_p, emb_s, emb_c, rt, rb, tc, bc, ib, R, cfg.ln_eps);
       });
-      if (inline_batch) slot->chunks = copy_blocks;   // (set once the kernel that will set the flags is on its stream)
       if (!ok) return fail(RELAYGR_EINVAL, "unsupported d_model");
       LAUNCH_CHECK("ln_in");
+      if (inline_batch) slot->chunks = copy_blocks;   // now the kernel that will set the flags is on its stream
     }
     // step 2: projections
     ColMap all4 = {4, {0, 1, 2, 3}, d}, kv_only = {2, {1, 3, 0, 0}, d};
@@ -1115,7 +1122,7 @@ extern "C" int relaygr_rank_with_cache_static(relaygr_ctx* ctx, relaygr_kv_pool*
   int dev = 0;
   int rc = static_scratch(&base, &dev);      // a table lookup after the first call on this device
   if (rc != RELAYGR_OK) return rc;
-  const CallScratch cs = {base, kStaticScratchBytes};
+  const CallScratch cs = {base, kStaticScratchBytes + kStaticDescriptorBytes};
   {
     // one caller at a time enqueues on the shared array, behind the call that used it last
     std::lock_guard<std::mutex> lk(g_static_mu);

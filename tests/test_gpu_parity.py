@@ -154,6 +154,52 @@ def test_four_key_splits_on_128_row_items_pair_up_inside_workgroups(attention):
     run_three_routes(synth.ModelConfig(2, 512, 8, "bf16", attention=attention), 613, [1100], [0], [2048])
 
 
+@pytest.mark.parametrize("attention", ["silu", "softmax"])
+@pytest.mark.parametrize("d,H,L,S,M", [
+    (128, 2, [4200], [21], [300]),                     # d_head 64, one user: eight pieces for the longest row tiles, one for the first
+    (128, 4, [2100, 70, 900], [0, 40, 3], [130, 40, 1]),   # d_head 32: users with different numbers of pieces in one launch
+    (256, 2, [1500, 600, 0], [64, 0, 5], [200, 64, 33]),   # d_head 128; a user whose only keys are its suffix
+])
+def test_rows_with_different_numbers_of_key_pieces(attention, d, H, L, S, M):
+    """Few or unequal work items are cut along the keys (causal prefix rows by their position, new rows by their user's
+    length), so rows of one launch reach the layer tail with different numbers of partial sums, and the last layer's
+    list is cut differently from the others'.  One user is ranked without a cached prefix."""
+    run_three_routes(synth.ModelConfig(2, d, H, "bf16", attention=attention), 700 + d + H, L, S, M, boost=BOOST, miss=(1,) if len(L) > 1 else ())
+
+
+@pytest.mark.parametrize("d,H,M", [(512, 8, 2048), (512, 8, 2049), (256, 4, 4096), (256, 4, 4097)])
+def test_row_counts_on_both_sides_of_the_projection_kernels_border(d, H, M):
+    """The last launch size whose 64-row tiles fit the chip at once, and the first that takes the weight-stationary kernel."""
+    run_three_routes(synth.ModelConfig(1, d, H, "bf16"), 750, [64], [0], [M])
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("n", [16, 17])
+def test_descriptors_as_an_argument_and_by_copy(dtype, n):
+    """16 users travel in the first kernel's arguments, 17 by a copy command.  Then calls of two different batches in turn, more
+    of them than there are staging slots and none waited for: every one must have seen its own descriptors."""
+    cfg = synth.ModelConfig(2, 128, 2, dtype)
+    L, S, M = [70 + 13 * u for u in range(n)], [u % 3 * 33 for u in range(n)], [5 + 7 * u for u in range(n)]
+    run_three_routes(cfg, 770 + n, L, S, M, miss=(2, n - 1))
+    weights, batch = build_case(cfg, 790 + n, L, S, M)
+    h = Harness(cfg, weights, batch)
+    try:
+        h.prefill()
+        subs = []
+        for users in (list(range(n)), list(range(n - 1, -1, -2))):
+            sub = h.sub_batch(users)
+            sub.set_handles([h.handles[u] for u in users])
+            subs.append(sub)
+        want = [rg.relaygr_rank_with_cache(h.ctx, h.pool, s).clone() for s in subs]
+        torch.cuda.synchronize()
+        got = [rg.relaygr_rank_with_cache(h.ctx, h.pool, subs[i % 2]) for i in range(11)]
+        torch.cuda.synchronize()
+        for i, g in enumerate(got):
+            assert torch.equal(g, want[i % 2]), f"call {i}"
+    finally:
+        h.close()
+
+
 # ------------------------------------------------------------------------------------ fp16
 @pytest.mark.parametrize("L,S,M", [
     ([1], [0], [1]), ([65, 300], [0, 70], [3, 129]), ([513, 0, 128], [64, 2, 0], [257, 9, 1]), ([1000], [17], [400]),
