@@ -916,9 +916,9 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
         const int tile = (d % 128 == 0 && tiles(128) >= 512) ? 128 : tiles(64) >= 512 ? 64 : 32;
         fp.n_mtiles = (r1 - r0 + tile - 1) / tile;
         const dim3 grid((tiles(tile) + 7) / 8 * 8);
-        if (tile == 128) hipLaunchKernelGGL((f1_f32_kernel<2, false>), grid, dim3(256), 0, st, fp);
-        else if (tile == 64) hipLaunchKernelGGL((f1_f32_kernel<1, false>), grid, dim3(256), 0, st, fp);
-        else hipLaunchKernelGGL((f1_f32_kernel<1, true>), grid, dim3(256), 0, st, fp);
+        if (tile == 128) hipLaunchKernelGGL((f1_f32_kernel<2, 0>), grid, dim3(256), 0, st, fp);
+        else if (tile == 64) hipLaunchKernelGGL((f1_f32_kernel<1, 0>), grid, dim3(256), 0, st, fp);
+        else dispatch_e(d, [&](auto e) { hipLaunchKernelGGL((f1_f32_kernel<1, 16 * decltype(e)::value>), grid, dim3(256), 0, st, fp); });
       } else {
         F1Params fp;
         fp.A = (const uint16_t*)xh; fp.W = c->w1_packed[l]; fp.bias = (const uint16_t*)lw.b1;

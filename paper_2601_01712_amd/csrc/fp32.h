@@ -197,15 +197,15 @@ struct F1F32Params {
   ColMap cm;
 };
 
-// Stores the four values of rows r0 .. r0+3 in feature c of block blk (0 u, 1 v, 2 q, 3 k).
-__device__ __forceinline__ void f1_f32_store(const F1F32Params& p, int blk, int c, int r0, const float (&v)[4]) {
+// Stores the four values of rows r0 .. r0+3 (of these kinds, read for v and k only) in feature c of block blk (0 u, 1 v, 2 q, 3 k).
+__device__ __forceinline__ void f1_f32_store(const F1F32Params& p, int blk, int c, int r0, const float (&v)[4], const int (&kinds)[4]) {
   const int head = c / p.dh, f = c - head * p.dh;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int r = r0 + i;
     if (r >= p.row_end) return;
     if (blk == 0 || blk == 2) { (blk == 0 ? p.u : p.q)[(size_t)r * p.d + c] = v[i]; continue; }
-    const int kind = p.rt.kind[r];
+    const int kind = kinds[i];
     if (kind == kRowCand) { (blk == 3 ? p.knew : p.vnew)[(size_t)(r - p.n_prows) * p.d + c] = v[i]; continue; }
     const UserDesc& ud = p.users[p.rt.user[r]];
     const int idx = p.rt.idx[r], rr = idx % kTile;
@@ -218,12 +218,15 @@ __device__ __forceinline__ void f1_f32_store(const F1F32Params& p, int blk, int 
 }
 
 // A wavefront multiplies 32*TB tokens by 32*TB features over k, operands straight from row-major memory, PF groups of 8 k
-// in flight.  KSPLIT = false: four wavefronts as 2 x 2 such blocks, each over the whole of k.  KSPLIT = true (TB = 1): the four
+// in flight.  KSLICE = 0: four wavefronts as 2 x 2 such blocks, each over the whole of k.  KSLICE = d/4 (TB = 1): the four
 // take a quarter of k each of ONE 32 x 32 block and add in LDS -- for launches of a few hundred rows, where it is the
-// length of the k loop that counts (64 cycles an MFMA, k/2 of them: 3.4 us at d = 256) and not the traffic.
-template <int TB, bool KSPLIT>
+// length of the k loop that counts (64 cycles an MFMA, k/2 of them: 3.4 us at d = 256) and not the traffic.  At its 64 (or
+// fewer) k a wavefront asks for both operands whole, and for the bias and row kinds its end needs, before its first product:
+// 512 rows at d = 256 11.2 -> 8.5 us, the d = 64 request's 16 rows 5.2 -> 4.0 us a launch.
+template <int TB, int KSLICE>
 __global__ __launch_bounds__(256, TB == 1 ? 4 : 2) void f1_f32_kernel(F1F32Params p) {
-  constexpr int PF = KSPLIT ? 4 : 2, WG = KSPLIT ? 32 : 64 * TB;  // tokens (and features) of a workgroup
+  constexpr bool KSPLIT = KSLICE > 0;
+  constexpr int PF = KSPLIT ? (KSLICE >= 64 ? 8 : KSLICE / 8) : 2, WG = KSPLIT ? 32 : 64 * TB;  // tokens (and features) of a workgroup
   __shared__ float red[KSPLIT ? 4 : 1][KSPLIT ? 16 : 1][64];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l32 = lane & 31, g = lane >> 5;
   const int nt_blk = p.cm.d / WG, n_nt = p.cm.nblk * nt_blk, total = p.n_mtiles * n_nt;
@@ -233,7 +236,7 @@ __global__ __launch_bounds__(256, TB == 1 ? 4 : 2) void f1_f32_kernel(F1F32Param
   const int blk = p.cm.blk[nt / nt_blk];
   const int m0 = p.row_begin + mt * WG + (KSPLIT ? 0 : (wave >> 1) * 32 * TB);
   const int c0 = (nt % nt_blk) * WG + (KSPLIT ? 0 : (wave & 1) * 32 * TB);   // first feature inside the block
-  const int k_len = KSPLIT ? p.d >> 2 : p.d, k0 = KSPLIT ? wave * k_len : 0;
+  const int k_len = KSPLIT ? KSLICE : p.d, k0 = KSPLIT ? wave * k_len : 0;
   const float *a[TB], *w[TB];
 #pragma unroll
   for (int i = 0; i < TB; ++i) {
@@ -247,6 +250,15 @@ __global__ __launch_bounds__(256, TB == 1 ? 4 : 2) void f1_f32_kernel(F1F32Param
     for (int j = 0; j < TB; ++j)
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+  // what the end of the cut form waits for, asked for now: its bias and the kinds of the four rows this wavefront finishes
+  float b_early = 0.f;
+  int kinds[4] = {};
+  if constexpr (KSPLIT) {
+    b_early = p.bias[blk * p.d + c0 + l32];
+    if (blk == 1 || blk == 3)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) kinds[i] = p.rt.kind[min(m0 + 8 * wave + 4 * g + i, p.row_end - 1)];
+  }
   float4 af[PF][TB], wf[PF][TB];
   auto load = [&](int s, int k) {
 #pragma unroll
@@ -255,6 +267,7 @@ __global__ __launch_bounds__(256, TB == 1 ? 4 : 2) void f1_f32_kernel(F1F32Param
 #pragma unroll
   for (int s = 0; s < PF; ++s)
     load(s, min(8 * s, k_len - 8));
+  if constexpr (KSPLIT) __builtin_amdgcn_sched_barrier(0);   // all of them before the first product: the compiler would spread them to save registers
   for (int k = 0; k < k_len; k += 8 * PF) {
 #pragma unroll
     for (int s = 0; s < PF; ++s) {
@@ -262,7 +275,7 @@ __global__ __launch_bounds__(256, TB == 1 ? 4 : 2) void f1_f32_kernel(F1F32Param
       float4 ca[TB], cw[TB];
 #pragma unroll
       for (int i = 0; i < TB; ++i) { ca[i] = af[s][i]; cw[i] = wf[s][i]; }
-      load(s, min(k + 8 * (s + PF), k_len - 8));       // unconditional, so that the compiler can count what is outstanding
+      if (8 * PF != KSLICE) load(s, min(k + 8 * (s + PF), k_len - 8));       // unconditional, so that the compiler can count what is outstanding
 #pragma unroll
       for (int t = 0; t < 4; ++t)
 #pragma unroll
@@ -276,13 +289,12 @@ __global__ __launch_bounds__(256, TB == 1 ? 4 : 2) void f1_f32_kernel(F1F32Param
     for (int e = 0; e < 16; ++e) red[wave][e][lane] = acc[0][0][e];
     __syncthreads();
     float v[4];
-    const float b = p.bias[blk * p.d + c0 + l32];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int e = 4 * wave + i;                    // this wavefront finishes tokens 8*wave + 4g + i
-      v[i] = silu_f32(((red[0][e][lane] + red[1][e][lane]) + (red[2][e][lane] + red[3][e][lane])) + b);
+      v[i] = silu_f32(((red[0][e][lane] + red[1][e][lane]) + (red[2][e][lane] + red[3][e][lane])) + b_early);
     }
-    f1_f32_store(p, blk, c0 + l32, m0 + 8 * wave + 4 * g, v);
+    f1_f32_store(p, blk, c0 + l32, m0 + 8 * wave + 4 * g, v, kinds);
   } else {
 #pragma unroll
     for (int j = 0; j < TB; ++j) {
@@ -295,7 +307,11 @@ __global__ __launch_bounds__(256, TB == 1 ? 4 : 2) void f1_f32_kernel(F1F32Param
           float v[4];
 #pragma unroll
           for (int x = 0; x < 4; ++x) v[x] = silu_f32(acc[i][j][4 * e4 + x] + b);
-          f1_f32_store(p, blk, c, m0 + 32 * i + 8 * e4 + 4 * g, v);
+          int kinds[4] = {};
+          if (blk == 1 || blk == 3)
+#pragma unroll
+            for (int x = 0; x < 4; ++x) kinds[x] = p.rt.kind[min(m0 + 32 * i + 8 * e4 + 4 * g + x, p.row_end - 1)];
+          f1_f32_store(p, blk, c, m0 + 32 * i + 8 * e4 + 4 * g, v, kinds);
         }
     }
   }
