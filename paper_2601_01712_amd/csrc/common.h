@@ -31,27 +31,9 @@
 #include <hip/hip_fp16.h>
 #include <stdint.h>
 
+#include "plan.h"
+
 namespace relaygr {
-
-constexpr int kTile = 64;   // tokens per K/V tile
-
-// kRowPad: filler between users in the prefix region of the row space (prefix rows of a user start
-// at an aligned row so that GEMM tiles never straddle users); it carries the user and a position >= L.
-enum RowKind : int32_t { kRowPrefix = 0, kRowSuffix = 1, kRowCand = 2, kRowPad = 3 };
-
-struct UserDesc {
-  const void* kv;          // space holding this user's prefix K/V (pool slab or scratch)
-  int64_t kv_tile0;        // element offset of the user's tile 0, layer 0, head 0
-  int64_t kv_tile_stride;  // elements between consecutive tiles
-  int64_t kv_layer_stride; // elements between layers (0 in single-layer scratch)
-  int64_t sfx_tile0;       // element offset of the user's suffix tile 0 in the suffix scratch space
-  int32_t L, S, M;
-  int32_t prow0;           // first prefix row of this user in the call's row space, -1 if not computed
-  int32_t nrow0;           // first new row (suffix rows, then candidates), -1 if the call has none
-  int32_t prefix_src0, suffix_src0, cand_src0;  // first row in each embedding array
-  int32_t parts, parts_last;   // 16-bit path: partial sums of a new row of this user, in every layer but the last / in the last
-};
-static_assert(sizeof(UserDesc) == 80, "UserDesc layout");
 
 // The descriptors of a batch of few users, small enough to be a kernel argument: the call's first kernel then needs no copy
 // to have run before it (see BlobCopy).
@@ -60,32 +42,6 @@ struct InlineBatch {
   UserDesc users[kInlineUsers];
   int32_t pstart[kInlineUsers + 1], nstart[kInlineUsers + 1];
 };
-
-// One attention work item: nrows (<= rows per workgroup) consecutive rows of one user, with everything about the user that
-// the attention kernels need (a workgroup's start is a chain of dependent loads: this is one of them instead of three).
-struct AttnTile {
-  int32_t user;
-  int32_t row0;     // first row in the call's row space
-  int32_t nrows;
-  int32_t kind;     // 0: prefix rows (causal over the prefix); 1: new rows
-  int32_t pos0;     // prefix rows: position of row0 in the prefix; new rows: index among new rows
-  // 16-bit kernel: an item is one of `parts` pieces of its rows' key sequence, key tiles [t0, t1) of the concatenated list
-  // [prefix tiles | suffix tiles], and writes partial sum number `part`
-  int32_t t0, t1;
-  int16_t part, parts;
-  const void* kv;          // the user's prefix tile 0, layer 0, head 0 (pool slab or scratch)
-  int64_t kv_tile_stride;  // elements between its tiles
-  int64_t sfx_tile0;       // UserDesc::sfx_tile0
-  int32_t L, S;
-  // elements between the layers of a tile: 0 in single-layer scratch (a pool of one layer has the same tile stride, and layer 0)
-  __host__ __device__ __forceinline__ int64_t layer_stride(int d) const { return kv_tile_stride == (int64_t)2 * kTile * d ? 0 : (int64_t)2 * kTile * d; }
-  // keys of [prefix | suffix] that local row lr sees; 0 beyond the item's rows
-  __host__ __device__ __forceinline__ int lim(int lr) const {
-    const int t = pos0 + lr;
-    return lr >= nrows ? 0 : kind == 0 || t < S ? (kind == 0 ? t + 1 : L + t + 1) : L + S;
-  }
-};
-static_assert(sizeof(AttnTile) == 64, "AttnTile layout");
 
 struct RowTables {
   int32_t* user;

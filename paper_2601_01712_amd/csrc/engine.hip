@@ -89,9 +89,8 @@ struct Plan {
   int n_users = 0;
   int n_prows = 0, n_nrows = 0, n_rows = 0;
   int64_t sfx_tiles = 0, kvs_tiles = 0;   // suffix tiles / recomputed-prefix tiles held in scratch
-  int n_tiles_new = 0, n_tiles_prefix = 0, n_tiles_last = 0;   // attention work items (16-bit: pieces; last layer's list by itself)
+  int n_tiles = 0;      // attention work items (16-bit: pieces, the last layer's list by itself)
   int nsplit = 1;       // attention partial sums a row can have (fp32: has)
-  int gs = 1;           // key splits added inside an attention workgroup (AttnParams::gs)
   // byte offsets into scratch
   size_t off_x, off_xh, off_u, off_q, off_knew, off_vnew, off_sfx, off_kvs, off_part, off_ml, off_rows, off_blob;
   size_t blob_bytes = 0;
@@ -129,28 +128,10 @@ static void carve(const relaygr_model_config& c, Plan& p) {
   p.off_part = take((size_t)p.nsplit * R * d * 4);
   p.off_ml = take((size_t)p.nsplit * R * c.n_heads * 2 * 4);   // softmax form: (m, l) per row, head and split
   p.off_rows = take(6 * align_up(R * 4));
-  size_t n_tiles = (size_t)p.n_tiles_new + p.n_tiles_prefix + p.n_tiles_last;
   p.blob_bytes = align_up((size_t)p.n_users * sizeof(UserDesc)) + 2 * align_up((size_t)(p.n_users + 1) * 4) +
-                 align_up(n_tiles * sizeof(AttnTile));
+                 align_up((size_t)p.n_tiles * sizeof(AttnTile));
   p.off_blob = take(p.blob_bytes);
   p.total = o;
-}
-
-// 16-bit attention: how a launch's row tiles (each with its list of 64-key tiles) are cut into pieces along the keys.
-// The chip takes `slots` workgroups at a time and deals the list out longest first, so a launch is done soon after
-// total / slots key tiles a slot unless single items are longer than that: one user's causal prefill has one item of all key
-// tiles and one of two, a jagged batch one user of 16 384 keys among short ones.  Pieces are cut to at most that share, not
-// under kMinPieceTiles (a workgroup's own start and end cost about as much as six key tiles) and not into more than 8; and
-// only for launches of less than kPieceRounds rounds, where there is too little behind the long items to hide them: each
-// further piece of a row is an fp32 partial sum more for the layer tail to read.
-constexpr int kMinPieceTiles = 8, kMaxPieces = 8, kPieceRounds = 4, kMaxSlots = 512;
-// Pieces a cut list has at most: the launch has under kPieceRounds * kMaxSlots (row tile, head) pairs, each cut in at most kMaxPieces.
-static int max_cut_items(const relaygr_model_config& c) { return kMaxPieces * kPieceRounds * kMaxSlots / c.n_heads; }
-static int piece_tiles(int64_t items, int64_t total_key_tiles, int most_key_tiles, int slots) {
-  if (items >= (int64_t)kPieceRounds * slots) return std::max(1, most_key_tiles);
-  int64_t c = (total_key_tiles + slots - 1) / slots;
-  c = std::max<int64_t>({c, kMinPieceTiles, (most_key_tiles + kMaxPieces - 1) / kMaxPieces});
-  return (int)std::max<int64_t>(1, std::min<int64_t>(c, most_key_tiles));
 }
 
 // fp32: a work item is one wavefront over its part of the keys, and 2048 of them (two a SIMD) fill the chip.  As long as the
@@ -178,9 +159,8 @@ extern "C" size_t relaygr_scratch_bytes(const relaygr_model_config* cfg, int32_t
   p.sfx_tiles = max_new_tokens / kTile + max_users;
   p.kvs_tiles = max_prefix_tokens / kTile + max_users;
   int rpt = rows_per_attn_tile(*cfg, 1);
-  p.n_tiles_new = (int)(max_new_tokens / rpt) + max_users;
-  p.n_tiles_prefix = (int)(padded / rpt) + max_users;
-  p.n_tiles_last = p.n_tiles_new + 2 * max_cut_items(*cfg);   // and room for the items that are cut into pieces
+  const int tiles_new = (int)(max_new_tokens / rpt) + max_users, tiles_prefix = (int)(padded / rpt) + max_users;
+  p.n_tiles = 2 * tiles_new + tiles_prefix + 2 * max_cut_items(cfg->n_heads);   // the last layer's list too, and room for the items that are cut into pieces
   p.nsplit = 1;
   carve(*cfg, p);
   size_t base = wpack_bytes(*cfg) + p.total;
@@ -339,7 +319,7 @@ extern "C" int relaygr_ctx_create(const relaygr_model_config* cfg, const relaygr
     const size_t d = cfg->d_model, e = elem_bytes(*cfg);
     const size_t rows_est = call_bytes / (d * (8 + 3 * e)) + 1;
     const size_t users_est = std::min<size_t>(call_bytes / (4 * kTile * d * e) + 1, 1 << 16);
-    const size_t cut = max_cut_items(*cfg);
+    const size_t cut = max_cut_items(cfg->n_heads);
     const size_t tiles_est = is_half16(*cfg) ? std::max(rows_est / 128 + 2 * users_est, cut) + std::max(rows_est / 128 + users_est, cut) : rows_est / 32 + 2 * users_est;
     const size_t want = align_up(users_est * sizeof(UserDesc)) + 2 * align_up((users_est + 1) * 4) + align_up(tiles_est * sizeof(AttnTile));
     // (one allocation for all slots: each costs a few hundred microseconds)
@@ -706,99 +686,33 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
     if (!scores && b->cand_off && b->cand_off[n] > 0) return fail(RELAYGR_EINVAL, "scores_dev is null");
   }
 
-  // Rows per attention work item.  The MFMA kernel reads half as much LDS and L2 per score element
-  // with 256-row items (two row blocks per wavefront); use them when that still yields at least
-  // one workgroup per compute unit.
-  int nq = 1;
-  if (bf16 && (dh == 64 || dh == 128)) {
-    int64_t items256 = 0;
-    for (int u = 0; u < n; ++u) {
-      if (users[u].nrow0 >= 0) items256 += (users[u].S + users[u].M + 255) / 256;
-      if (users[u].prow0 >= 0) items256 += (users[u].L + 255) / 256;
-    }
-    if (items256 * H >= 256) nq = 2;
-  }
+  const int nq = bf16 ? attn_row_blocks(users, H, dh) : 1;
   const int rpt = rows_per_attn_tile(cfg, nq);
 
-  // -- attention row tiles: new rows first (the last layer skips prefix rows)
+  // -- attention row tiles, and the launch lists made of them (all layers but the last; the last): longest items first
   std::vector<AttnTile> rows_new, rows_prefix;
-  for (int u = 0; u < n; ++u) {
-    const UserDesc& ud = users[u];
-    int Tn = ud.S + ud.M;
-    if (ud.nrow0 >= 0)
-      for (int t0 = 0; t0 < Tn; t0 += rpt) rows_new.push_back({u, ud.nrow0 + t0, std::min(rpt, Tn - t0), 1, t0, 0, 0, 0, 1, nullptr, ud.kv_tile_stride, ud.sfx_tile0, ud.L, ud.S});
-    if (ud.prow0 >= 0)
-      for (int i0 = 0; i0 < ud.L; i0 += rpt) rows_prefix.push_back({u, ud.prow0 + i0, std::min(rpt, ud.L - i0), 0, i0, 0, 0, 0, 1, nullptr, ud.kv_tile_stride, ud.sfx_tile0, ud.L, ud.S});
-  }
-  auto key_tiles = [&](const AttnTile& a) {
-    const UserDesc& ud = users[a.user];
-    return a.kind == 0 ? (a.pos0 + a.nrows + kTile - 1) / kTile : (ud.L + kTile - 1) / kTile + (ud.S + kTile - 1) / kTile;
-  };
-  // -- the launch lists (all layers but the last; the last): pieces of the row tiles, longest first
-  std::vector<AttnTile> list_all, list_last;
-  p.gs = 1;
-  int64_t kt_new = 0, kt_prefix = 0;
-  int most_new = 0, most_prefix = 0;
-  for (const AttnTile& a : rows_new) { kt_new += key_tiles(a); most_new = std::max(most_new, key_tiles(a)); }
-  for (const AttnTile& a : rows_prefix) { kt_prefix += key_tiles(a); most_prefix = std::max(most_prefix, key_tiles(a)); }
-  int piece_all = 1 << 20, piece_last = 1 << 20;     // most key tiles of a piece
-  int parts_all = 1, parts_last = 1;                 // partial sums of every row (0: rows differ)
+  attn_row_tiles(users, rpt, rows_new, rows_prefix);
+  AttnCut cut;
   if (!bf16) {
-    fp32_splits((int64_t)(rows_new.size() + rows_prefix.size()) * H, 2 * (kt_new + kt_prefix) * H, &p.nsplit, &p.gs);
-    list_all = rows_new;
-    list_all.insert(list_all.end(), rows_prefix.begin(), rows_prefix.end());
-    auto longer = [&](const AttnTile& a, const AttnTile& b2) { return key_tiles(a) > key_tiles(b2); };
-    std::stable_sort(list_all.begin(), list_all.begin() + rows_new.size(), longer);
-    std::stable_sort(list_all.begin() + rows_new.size(), list_all.end(), longer);
-    p.n_tiles_new = (int)rows_new.size();
-    p.n_tiles_prefix = (int)rows_prefix.size();
+    int64_t half_tiles = 0;
+    for (auto* rows : {&rows_new, &rows_prefix})
+      for (const AttnTile& a : *rows) half_tiles += 2 * key_tiles(a) * H;
+    fp32_splits((int64_t)(rows_new.size() + rows_prefix.size()) * H, half_tiles, &cut.nsplit, &cut.gs);
+    cut.all = rows_new;
+    cut.all.insert(cut.all.end(), rows_prefix.begin(), rows_prefix.end());
+    auto longer = [](const AttnTile& a, const AttnTile& b2) { return key_tiles(a) > key_tiles(b2); };
+    std::stable_sort(cut.all.begin(), cut.all.begin() + rows_new.size(), longer);
+    std::stable_sort(cut.all.begin() + rows_new.size(), cut.all.end(), longer);
   } else {
-    const int slots = std::min(kMaxSlots, dh == 128 ? c->n_cus : 2 * c->n_cus);   // workgroups the chip takes at a time
-    piece_all = piece_tiles((int64_t)(rows_new.size() + rows_prefix.size()) * H, (kt_new + kt_prefix) * H, std::max(most_new, most_prefix ? most_prefix + rpt / kTile : 0), slots);
-    piece_last = piece_tiles((int64_t)rows_new.size() * H, kt_new * H, most_new, slots);
-    // Fills `out` with the pieces of at most `piece` key tiles; returns the most pieces of a row tile.
-    auto cut = [&](bool prefix_rows, int piece, std::vector<AttnTile>& out, int* uniform) {
-      out.clear();
-      int lo = kMaxPieces + 1, hi = 0;
-      auto add = [&](AttnTile a, int parts) {
-        const int nk = key_tiles(a), per = (nk + parts - 1) / parts;
-        lo = std::min(lo, parts); hi = std::max(hi, parts);
-        a.parts = (int16_t)parts;
-        for (int k = 0; k < parts; ++k) { a.part = (int16_t)k; a.t0 = std::min(k * per, nk); a.t1 = std::min(a.t0 + per, nk); out.push_back(a); }
-      };
-      for (const AttnTile& a : rows_new) add(a, std::max(1, (key_tiles(a) + piece - 1) / piece));
-      if (prefix_rows) for (const AttnTile& a : rows_prefix) add(a, causal_parts(a.pos0, rpt, piece));
-      std::stable_sort(out.begin(), out.end(), [](const AttnTile& a, const AttnTile& b2) { return a.t1 - a.t0 > b2.t1 - b2.t0; });
-      *uniform = hi == 0 ? 1 : lo == hi ? lo : 0;
-      return hi;
-    };
-    for (;;) {
-      const int h1 = cut(true, piece_all, list_all, &parts_all), h2 = cut(false, piece_last, list_last, &parts_last);
-      p.nsplit = std::max({1, h1, h2});
-      p.n_tiles_new = (int)list_all.size(); p.n_tiles_prefix = 0; p.n_tiles_last = (int)list_last.size();
+    cut_attention(rows_new, rows_prefix, H, dh, rpt, c->n_cus, cut, [&](const AttnCut& k) {
+      p.nsplit = k.nsplit; p.n_tiles = (int)(k.all.size() + k.last.size());
       carve(cfg, p);
-      const bool uncut = list_all.size() == rows_new.size() + rows_prefix.size() && list_last.size() == rows_new.size();
-      if (uncut || (p.total <= cs.bytes && p.nsplit <= kMaxPieces)) break;
-      piece_all *= 2; piece_last *= 2;
-    }
-    // d_head 64: two pieces of a row go to the two wavefront groups of one workgroup, which add their
-    // sums in LDS -- half the partial sums for the layer tail to read -- where every row has the same even number of them and
-    // half the workgroups still give every compute unit one (with fewer, e.g. one user with 512 candidates, the attention
-    // launch itself gets 25 % slower)
-    const bool one_list = rows_prefix.empty();       // the last layer's list is then the same: not sent twice
-    if (dh == 64 && one_list && parts_all > 0 && parts_all % 2 == 0 && (int64_t)rows_new.size() * H * (parts_all / 2) >= c->n_cus) {
-      p.gs = 2;
-      piece_all = piece_last = (most_new + parts_all / 2 - 1) / (parts_all / 2);
-      p.nsplit = std::max(cut(true, piece_all, list_all, &parts_all), cut(false, piece_last, list_last, &parts_last));
-      p.n_tiles_new = (int)list_all.size(); p.n_tiles_last = (int)list_last.size();
-    }
-    if (one_list) { list_last.clear(); p.n_tiles_last = 0; carve(cfg, p); }
-    for (int u = 0; u < n; ++u) {
-      const int nk = (users[u].L + kTile - 1) / kTile + (users[u].S + kTile - 1) / kTile;
-      users[u].parts = std::max(1, (nk + piece_all - 1) / piece_all);
-      users[u].parts_last = std::max(1, (nk + piece_last - 1) / piece_last);
-    }
+      return p.total <= cs.bytes;
+    });
+    set_user_parts(users, cut);
   }
+  p.nsplit = cut.nsplit;
+  p.n_tiles = (int)(cut.all.size() + cut.last.size());
 
   // -- scratch
   carve(cfg, p);
@@ -826,7 +740,7 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
   }
   for (int u = 0; u < n; ++u)
     if (!users[u].kv) users[u].kv = kvs;
-  for (auto* list : {&list_all, &list_last})
+  for (auto* list : {&cut.all, &cut.last})
     for (AttnTile& a : *list) a.kv = (const char*)users[a.user].kv + users[a.user].kv_tile0 * (int64_t)sizeof(T);
 
   // -- descriptor blob: users | pstart | nstart | tiles(new, prefix)
@@ -839,8 +753,8 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
   memcpy(hb + o_users, users.data(), (size_t)n * sizeof(UserDesc));
   memcpy(hb + o_ps, pstart.data(), (size_t)(n + 1) * 4);
   memcpy(hb + o_ns, nstart.data(), (size_t)(n + 1) * 4);
-  if (!list_all.empty()) memcpy(hb + o_tiles, list_all.data(), list_all.size() * sizeof(AttnTile));
-  if (!list_last.empty()) memcpy(hb + o_tiles + list_all.size() * sizeof(AttnTile), list_last.data(), list_last.size() * sizeof(AttnTile));
+  if (!cut.all.empty()) memcpy(hb + o_tiles, cut.all.data(), cut.all.size() * sizeof(AttnTile));
+  if (!cut.last.empty()) memcpy(hb + o_tiles + cut.all.size() * sizeof(AttnTile), cut.last.data(), cut.last.size() * sizeof(AttnTile));
   char* db = S0 + p.off_blob;
   // few users: the first kernel fetches the descriptors itself; many, or a stream under capture: a copy command brings them
   const bool inline_batch = n <= kInlineUsers && p.blob_bytes <= kInlineBlobBytes && !capturing;
@@ -885,7 +799,7 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
     // tables and the cleared tail tiles; later layers get theirs from the previous layer's tail kernel
     if (l == 0) {
       ProfScope ps(c, RELAYGR_K_LN, st);
-      const RowBuild rb = {d_users, d_ps, d_ns, n, p.n_prows, rpt, piece_all};
+      const RowBuild rb = {d_users, d_ps, d_ns, n, p.n_prows, rpt, cut.piece_all};
       TailClear tc = {(R + kRowsPerBlock - 1) / kRowsPerBlock, 0, H, dh, 0, p.sfx_tiles ? (void*)sfx : nullptr};
       if (!bf16 && p.n_prows) tc.kv_layers = NL;   // the 16-bit projection fills a prefix's ragged tail itself
       if (tc.kv_layers > 0 || tc.sfx != nullptr) tc.jobs = n * (tc.kv_layers + 1) * H;
@@ -965,14 +879,14 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
     AttnParams ap;
     ap.tiles = d_tiles; ap.q = qbuf; ap.sfx = sfx; ap.part = part;
     ap.split_stride = (size_t)R * d; ap.nsplit = p.nsplit; ap.d = d; ap.n_heads = H; ap.layer = l; ap.score_mul = score_mul;
-    ap.ml = ml; ap.ml_stride = (size_t)R * H * 2; ap.gs = p.gs;
+    ap.ml = ml; ap.ml_stride = (size_t)R * H * 2; ap.gs = cut.gs;
     // 16-bit SiLU form: the attention kernel adds the candidates' own keys, so the layer tail does not read q, k, v again
     const bool self_in_attn = bf16 && !softmax;
     ap.knew = self_in_attn ? (const void*)knew : nullptr; ap.vnew = vnew; ap.n_prows = p.n_prows;
     const bool own_list = bf16 && last && p.n_prows > 0;
-    const int nt = own_list ? p.n_tiles_last : bf16 ? (int)list_all.size() : last ? p.n_tiles_new : p.n_tiles_new + p.n_tiles_prefix;
+    const int nt = (int)(own_list ? cut.last.size() : !bf16 && last ? rows_new.size() : cut.all.size());   // (fp32: new rows first)
     ap.n_tiles = nt;
-    if (own_list) ap.tiles = d_tiles + list_all.size();
+    if (own_list) ap.tiles = d_tiles + cut.all.size();
     if (nt > 0) {
       ProfScope ps(c, RELAYGR_K_ATTN, st);
       rc = launch_attention<T>(cfg, ap, nt, nq, softmax, st);
@@ -1007,7 +921,7 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
           fp.offs = last ? (const uint16_t*)c->ln_out_b : (const uint16_t*)c->layers[l + 1].ln_in_b;
           fp.w_score = (const uint16_t*)c->w_score; fp.b_score = c->b_score; fp.scores = score_here ? scores : nullptr;
           fp.row_begin = a0; fp.row_end = R; fp.eps = cfg.ln_eps;
-          fp.part = part; fp.parts_shift = last ? 8 : 0; fp.parts_all = last ? parts_last : parts_all; fp.split_stride = (size_t)R * d;
+          fp.part = part; fp.parts_shift = last ? 8 : 0; fp.parts_all = last ? cut.parts_last : cut.parts_all; fp.split_stride = (size_t)R * d;
           fp.u = (const uint16_t*)ubuf; fp.q = self_in_attn ? nullptr : (const uint16_t*)qbuf; fp.knew = (const uint16_t*)knew; fp.vnew = (const uint16_t*)vnew;
           fp.gate_gain = (const uint16_t*)lw.ln_at_g; fp.gate_offs = (const uint16_t*)lw.ln_at_b;
           fp.n_prows = p.n_prows; fp.dh = dh; fp.qk_mul = gate_mul;

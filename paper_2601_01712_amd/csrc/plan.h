@@ -1,0 +1,209 @@
+// The plan of a call's attention work: its row tiles, how a launch's row tiles are cut along the keys, and how many partial
+// sums every row of the row space then has.  The list of work items is made on the host and the rows' entries on the GPU,
+// and the layer tail reads as many partial sums as a row's entry says, so both are worked out by the functions here.
+// No HIP in this file: the tests compile it with the host compiler.
+#pragma once
+
+#include <stdint.h>
+
+#include <algorithm>
+#include <vector>
+
+#ifdef __HIP__
+#define RELAYGR_HD __host__ __device__ __forceinline__
+#else
+#define RELAYGR_HD inline
+#endif
+
+namespace relaygr {
+
+constexpr int kTile = 64;   // tokens per K/V tile
+
+// kRowPad: filler between users in the prefix region of the row space (prefix rows of a user start
+// at an aligned row so that GEMM tiles never straddle users); it carries the user and a position >= L.
+enum RowKind : int32_t { kRowPrefix = 0, kRowSuffix = 1, kRowCand = 2, kRowPad = 3 };
+
+struct UserDesc {
+  const void* kv;          // space holding this user's prefix K/V (pool slab or scratch)
+  int64_t kv_tile0;        // element offset of the user's tile 0, layer 0, head 0
+  int64_t kv_tile_stride;  // elements between consecutive tiles
+  int64_t kv_layer_stride; // elements between layers (0 in single-layer scratch)
+  int64_t sfx_tile0;       // element offset of the user's suffix tile 0 in the suffix scratch space
+  int32_t L, S, M;
+  int32_t prow0;           // first prefix row of this user in the call's row space, -1 if not computed
+  int32_t nrow0;           // first new row (suffix rows, then candidates), -1 if the call has none
+  int32_t prefix_src0, suffix_src0, cand_src0;  // first row in each embedding array
+  int32_t parts, parts_last;   // 16-bit path: partial sums of a new row of this user, in every layer but the last / in the last
+};
+static_assert(sizeof(UserDesc) == 80, "UserDesc layout");
+
+// One attention work item: nrows (<= rows per workgroup) consecutive rows of one user, with everything about the user that
+// the attention kernels need (a workgroup's start is a chain of dependent loads: this is one of them instead of three).
+struct AttnTile {
+  int32_t user;
+  int32_t row0;     // first row in the call's row space
+  int32_t nrows;
+  int32_t kind;     // 0: prefix rows (causal over the prefix); 1: new rows
+  int32_t pos0;     // prefix rows: position of row0 in the prefix; new rows: index among new rows
+  // 16-bit kernel: an item is one of `parts` pieces of its rows' key sequence, key tiles [t0, t1) of the concatenated list
+  // [prefix tiles | suffix tiles], and writes partial sum number `part`
+  int32_t t0, t1;
+  int16_t part, parts;
+  const void* kv;          // the user's prefix tile 0, layer 0, head 0 (pool slab or scratch)
+  int64_t kv_tile_stride;  // elements between its tiles
+  int64_t sfx_tile0;       // UserDesc::sfx_tile0
+  int32_t L, S;
+  // elements between the layers of a tile: 0 in single-layer scratch (a pool of one layer has the same tile stride, and layer 0)
+  RELAYGR_HD int64_t layer_stride(int d) const { return kv_tile_stride == (int64_t)2 * kTile * d ? 0 : (int64_t)2 * kTile * d; }
+  // keys of [prefix | suffix] that local row lr sees; 0 beyond the item's rows
+  RELAYGR_HD int lim(int lr) const {
+    const int t = pos0 + lr;
+    return lr >= nrows ? 0 : kind == 0 || t < S ? (kind == 0 ? t + 1 : L + t + 1) : L + S;
+  }
+};
+static_assert(sizeof(AttnTile) == 64, "AttnTile layout");
+
+// A row's entry in the row tables: its user, kind, index inside that user's prefix / suffix / candidates, number of keys of
+// [prefix | suffix] it sees, row in the embedding array of its kind, and attention partial sums (RowTables::parts).
+struct RowEntry { int user, kind, idx, lim, src, parts; };
+
+// Pieces of the key sequence of the causal work item that starts at position pos0 (a function of the position alone, so
+// that the layer tail and the host agree without a table).
+RELAYGR_HD int causal_parts(int pos0, int tile_rows, int piece_tiles) {
+  return ((pos0 + tile_rows) / kTile + piece_tiles - 1) / piece_tiles;
+}
+
+// Entry of row t of a user's prefix rows (filler rows behind the prefix included), or of its new rows (suffix, then candidates).
+RELAYGR_HD RowEntry row_entry_at(const UserDesc& ud, int user, bool prefix_region, int t, int tile_rows, int piece_tiles) {
+  RowEntry e;
+  e.user = user;
+  if (prefix_region) {
+    e.idx = t;
+    if (t < ud.L) { e.kind = kRowPrefix; e.lim = t + 1; e.src = ud.prefix_src0 + t; }
+    else          { e.kind = kRowPad; e.lim = 0; e.src = 0; }
+    // (a filler row's sums are read and dropped; behind the user's last row tile its position could ask for more than any real row has)
+    e.parts = t < ud.L ? causal_parts(t / tile_rows * tile_rows, tile_rows, piece_tiles) : 1;
+  } else {
+    e.parts = ud.parts | ud.parts_last << 8;
+    if (t < ud.S) { e.kind = kRowSuffix; e.idx = t; e.lim = ud.L + t + 1; e.src = ud.suffix_src0 + t; }
+    else          { e.kind = kRowCand; e.idx = t - ud.S; e.lim = ud.L + ud.S; e.src = ud.cand_src0 + e.idx; }
+  }
+  return e;
+}
+
+// Key tiles in a row tile's list [prefix | suffix].
+inline int key_tiles(const AttnTile& a) {
+  return a.kind == 0 ? (a.pos0 + a.nrows + kTile - 1) / kTile : (a.L + kTile - 1) / kTile + (a.S + kTile - 1) / kTile;
+}
+
+// 32-row blocks per wavefront of the 16-bit kernel (a work item is 128 rows of each).  It reads half as much LDS and L2 per
+// score element with 256-row items; they are used when that still yields at least one workgroup per compute unit.
+inline int attn_row_blocks(const std::vector<UserDesc>& users, int heads, int dh) {
+  if (dh != 64 && dh != 128) return 1;
+  int64_t items256 = 0;
+  for (const UserDesc& ud : users) {
+    if (ud.nrow0 >= 0) items256 += (ud.S + ud.M + 255) / 256;
+    if (ud.prow0 >= 0) items256 += (ud.L + 255) / 256;
+  }
+  return items256 * heads >= 256 ? 2 : 1;
+}
+
+// The call's row tiles of at most tile_rows rows: new rows, and the prefix rows that are computed in this call.
+inline void attn_row_tiles(const std::vector<UserDesc>& users, int tile_rows, std::vector<AttnTile>& rows_new, std::vector<AttnTile>& rows_prefix) {
+  for (int u = 0; u < (int)users.size(); ++u) {
+    const UserDesc& ud = users[u];
+    const int Tn = ud.S + ud.M;
+    if (ud.nrow0 >= 0)
+      for (int t0 = 0; t0 < Tn; t0 += tile_rows) rows_new.push_back({u, ud.nrow0 + t0, std::min(tile_rows, Tn - t0), 1, t0, 0, 0, 0, 1, nullptr, ud.kv_tile_stride, ud.sfx_tile0, ud.L, ud.S});
+    if (ud.prow0 >= 0)
+      for (int i0 = 0; i0 < ud.L; i0 += tile_rows) rows_prefix.push_back({u, ud.prow0 + i0, std::min(tile_rows, ud.L - i0), 0, i0, 0, 0, 0, 1, nullptr, ud.kv_tile_stride, ud.sfx_tile0, ud.L, ud.S});
+  }
+}
+
+// 16-bit attention: how a launch's row tiles (each with its list of 64-key tiles) are cut into pieces along the keys.
+// The chip takes `slots` workgroups at a time and deals the list out longest first, so a launch is done soon after
+// total / slots key tiles a slot unless single items are longer than that: one user's causal prefill has one item of all key
+// tiles and one of two, a jagged batch one user of 16 384 keys among short ones.  Pieces are cut to at most that share, not
+// under kMinPieceTiles (a workgroup's own start and end cost about as much as six key tiles) and not into more than 8; and
+// only for launches of less than kPieceRounds rounds, where there is too little behind the long items to hide them: each
+// further piece of a row is an fp32 partial sum more for the layer tail to read.
+constexpr int kMinPieceTiles = 8, kMaxPieces = 8, kPieceRounds = 4, kMaxSlots = 512;
+// Pieces a cut list has at most: the launch has under kPieceRounds * kMaxSlots (row tile, head) pairs, each cut in at most kMaxPieces.
+inline int max_cut_items(int n_heads) { return kMaxPieces * kPieceRounds * kMaxSlots / n_heads; }
+inline int piece_tiles(int64_t items, int64_t total_key_tiles, int most_key_tiles, int slots) {
+  if (items >= (int64_t)kPieceRounds * slots) return std::max(1, most_key_tiles);
+  int64_t c = (total_key_tiles + slots - 1) / slots;
+  c = std::max<int64_t>({c, kMinPieceTiles, (most_key_tiles + kMaxPieces - 1) / kMaxPieces});
+  return (int)std::max<int64_t>(1, std::min<int64_t>(c, most_key_tiles));
+}
+
+// The launch lists of a call's attention and what the layer tail has to know of them.
+struct AttnCut {
+  std::vector<AttnTile> all, last;                   // every layer but the last; the last layer (no prefix rows)
+  int piece_all = 1 << 20, piece_last = 1 << 20;     // most key tiles of a piece
+  int parts_all = 1, parts_last = 1;                 // partial sums of every row (0: rows differ)
+  int nsplit = 1;                                    // partial sums a row can have (fp32: has)
+  int gs = 1;                                        // key splits added inside an attention workgroup (AttnParams::gs)
+};
+
+// Fills `out` with the pieces of at most `piece` key tiles, longest first; returns the most pieces of a row tile.
+inline int cut_pieces(const std::vector<AttnTile>& rows_new, const std::vector<AttnTile>* rows_prefix, int tile_rows, int piece, std::vector<AttnTile>& out, int* uniform) {
+  out.clear();
+  int lo = kMaxPieces + 1, hi = 0;
+  auto add = [&](AttnTile a, int parts) {
+    const int nk = key_tiles(a), per = (nk + parts - 1) / parts;
+    lo = std::min(lo, parts); hi = std::max(hi, parts);
+    a.parts = (int16_t)parts;
+    for (int k = 0; k < parts; ++k) { a.part = (int16_t)k; a.t0 = std::min(k * per, nk); a.t1 = std::min(a.t0 + per, nk); out.push_back(a); }
+  };
+  for (const AttnTile& a : rows_new) add(a, std::max(1, (key_tiles(a) + piece - 1) / piece));
+  if (rows_prefix) for (const AttnTile& a : *rows_prefix) add(a, causal_parts(a.pos0, tile_rows, piece));
+  std::stable_sort(out.begin(), out.end(), [](const AttnTile& a, const AttnTile& b) { return a.t1 - a.t0 > b.t1 - b.t0; });
+  *uniform = hi == 0 ? 1 : lo == hi ? lo : 0;
+  return hi;
+}
+
+// The 16-bit path's lists.  fits(cut): whether a call cut like that fits its scratch; asked until it does or nothing is cut.
+template <class Fits>
+inline void cut_attention(const std::vector<AttnTile>& rows_new, const std::vector<AttnTile>& rows_prefix, int heads, int dh, int tile_rows, int n_cus, AttnCut& c, Fits fits) {
+  int64_t kt_new = 0, kt_prefix = 0;
+  int most_new = 0, most_prefix = 0;
+  for (const AttnTile& a : rows_new) { kt_new += key_tiles(a); most_new = std::max(most_new, key_tiles(a)); }
+  for (const AttnTile& a : rows_prefix) { kt_prefix += key_tiles(a); most_prefix = std::max(most_prefix, key_tiles(a)); }
+  const int slots = std::min(kMaxSlots, dh == 128 ? n_cus : 2 * n_cus);   // workgroups the chip takes at a time
+  c.piece_all = piece_tiles((int64_t)(rows_new.size() + rows_prefix.size()) * heads, (kt_new + kt_prefix) * heads, std::max(most_new, most_prefix ? most_prefix + tile_rows / kTile : 0), slots);
+  c.piece_last = piece_tiles((int64_t)rows_new.size() * heads, kt_new * heads, most_new, slots);
+  auto cut = [&]() {
+    const int h1 = cut_pieces(rows_new, &rows_prefix, tile_rows, c.piece_all, c.all, &c.parts_all);
+    const int h2 = cut_pieces(rows_new, nullptr, tile_rows, c.piece_last, c.last, &c.parts_last);
+    c.nsplit = std::max({1, h1, h2});
+  };
+  for (;;) {
+    cut();
+    const bool uncut = c.all.size() == rows_new.size() + rows_prefix.size() && c.last.size() == rows_new.size();
+    if (uncut || (fits(c) && c.nsplit <= kMaxPieces)) break;
+    c.piece_all *= 2; c.piece_last *= 2;
+  }
+  // d_head 64: two pieces of a row go to the two wavefront groups of one workgroup, which add their
+  // sums in LDS -- half the partial sums for the layer tail to read -- where every row has the same even number of them and
+  // half the workgroups still give every compute unit one (with fewer, e.g. one user with 512 candidates, the attention
+  // launch itself gets 25 % slower)
+  const bool one_list = rows_prefix.empty();       // the last layer's list is then the same: not sent twice
+  if (dh == 64 && one_list && c.parts_all > 0 && c.parts_all % 2 == 0 && (int64_t)rows_new.size() * heads * (c.parts_all / 2) >= n_cus) {
+    c.gs = 2;
+    c.piece_all = c.piece_last = (most_new + c.parts_all / 2 - 1) / (c.parts_all / 2);
+    cut();
+  }
+  if (one_list) c.last.clear();
+}
+
+// Partial sums of the users' new rows.
+inline void set_user_parts(std::vector<UserDesc>& users, const AttnCut& c) {
+  for (UserDesc& ud : users) {
+    const int nk = (ud.L + kTile - 1) / kTile + (ud.S + kTile - 1) / kTile;
+    ud.parts = std::max(1, (nk + c.piece_all - 1) / c.piece_all);
+    ud.parts_last = std::max(1, (nk + c.piece_last - 1) / c.piece_last);
+  }
+}
+
+}  // namespace relaygr

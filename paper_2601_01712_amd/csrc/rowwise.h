@@ -17,15 +17,8 @@ struct RowBuild {
   const int32_t* pstart;
   const int32_t* nstart;
   int n_users, n_prows;
-  int tile_rows, piece_tiles;   // 16-bit attention: rows of a work item, most key tiles of a piece of it (see plan_pieces)
+  int tile_rows, piece_tiles;   // 16-bit attention: rows of a work item, most key tiles of a piece of it (AttnCut::piece_all)
 };
-struct RowEntry { int user, kind, idx, lim, src, parts; };
-
-// Pieces of the key sequence of the causal work item that starts at position pos0 (a function of the position alone, so
-// that the layer tail and the host agree without a table).
-__host__ __device__ __forceinline__ int causal_parts(int pos0, int tile_rows, int piece_tiles) {
-  return ((pos0 + tile_rows) / kTile + piece_tiles - 1) / piece_tiles;
-}
 
 // u is the last user with start[u] <= r: the wavefront's lanes compare 64 users' starts at a time, or, for a batch that came as a
 // kernel argument, scalar compares do.
@@ -45,20 +38,7 @@ __device__ __forceinline__ RowEntry row_entry(const RowBuild& rb, const InlineBa
   }
   const UserDesc& ud = INLINE ? ib.users[lo] : rb.users[lo];
   const int first = r < rb.n_prows ? (INLINE ? ib.pstart[lo] : rb.pstart[lo]) : (INLINE ? ib.nstart[lo] : rb.nstart[lo]);
-  RowEntry e;
-  e.user = lo;
-  if (r < rb.n_prows) {
-    e.idx = r - first;
-    if (e.idx < ud.L) { e.kind = kRowPrefix; e.lim = e.idx + 1; e.src = ud.prefix_src0 + e.idx; }
-    else              { e.kind = kRowPad; e.lim = 0; e.src = 0; }
-    e.parts = causal_parts(e.idx / rb.tile_rows * rb.tile_rows, rb.tile_rows, rb.piece_tiles);
-  } else {
-    e.parts = ud.parts | ud.parts_last << 8;
-    int t = r - first;
-    if (t < ud.S) { e.kind = kRowSuffix; e.idx = t; e.lim = ud.L + t + 1; e.src = ud.suffix_src0 + t; }
-    else          { e.kind = kRowCand; e.idx = t - ud.S; e.lim = ud.L + ud.S; e.src = ud.cand_src0 + e.idx; }
-  }
-  return e;
+  return row_entry_at(ud, lo, r < rb.n_prows, r - first, rb.tile_rows, rb.piece_tiles);
 }
 
 // ---- LayerNorm helpers -----------------------------------------------------------------------

@@ -1,0 +1,77 @@
+"""The 16-bit path's attention plan (csrc/plan.h), built with the host compiler: pieces cover every row tile's keys once, and no
+row of the row space -- filler rows between users included -- is said to have more partial sums than the call lays out.  The
+layer tail reads what the row's entry says even where it drops the values, so this cannot be seen in any output."""
+import ctypes as C
+import os
+import random
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def shim(tmp_path_factory):
+    if shutil.which("g++") is None:
+        pytest.skip("no g++")
+    lib = tmp_path_factory.mktemp("plan") / "attn_plan.so"
+    subprocess.run(["g++", "-std=c++17", "-O2", "-Wall", "-Wextra", "-Werror", "-shared", "-fPIC", os.path.join(HERE, "attn_plan_shim.cpp"), "-o", str(lib)], check=True)
+    return C.CDLL(str(lib))
+
+
+def check(shim, L, S=None, M=None, computed=None, heads=8, dh=64, n_cus=256, most_sums=8):
+    n = len(L)
+    new_rows = M is not None
+    arr = [np.asarray(a if a is not None else [0] * n, np.int32) for a in (L, S, M)]
+    comp = np.asarray([1] * n if computed is None else computed, np.uint8)
+    info, msg = np.zeros(5, np.int32), C.create_string_buffer(256)
+    rc = shim.plan_check(n, *(a.ctypes.data_as(C.c_void_p) for a in arr), comp.ctypes.data_as(C.c_void_p), int(new_rows), heads, dh, n_cus, most_sums,
+                         info.ctypes.data_as(C.c_void_p), msg)
+    assert rc == 0, f"L {list(L)} S {S} M {M} computed {computed} heads {heads} d_head {dh} units {n_cus} sums {most_sums}: {msg.value.decode()}"
+    return dict(zip(("blocks", "nsplit", "gs", "items", "filler"), info.tolist()))
+
+
+@pytest.mark.parametrize("L,heads,dh", [
+    ([2574, 9519], 2, 64),             # pieces of 25 key tiles; the filler rows from position 9600 would be 7 pieces of a possible 6
+    ([3953, 8010, 346, 1573], 2, 64),  # 21; 7 of 6
+    ([3841], 8, 128), ([3968], 8, 128),   # 31; 3 of 2
+])
+def test_filler_rows_have_no_more_sums_than_the_call_lays_out(shim, L, heads, dh):
+    got = check(shim, L, heads=heads, dh=dh)
+    assert got["blocks"] == 1 and got["nsplit"] > 1 and got["filler"] >= 1
+
+
+def test_two_splits_share_a_workgroup_where_every_row_has_an_even_number(shim):
+    assert check(shim, [4096] * 16, [0] * 16, [512] * 16, [0] * 16) == {"blocks": 2, "nsplit": 1, "gs": 2, "items": 32, "filler": 0}
+
+
+@pytest.mark.parametrize("heads,dh", [(4, 32), (16, 32), (1, 128), (2, 64), (4, 64), (8, 64), (16, 64), (2, 128), (8, 128)])
+def test_every_row_has_the_sums_its_pieces_write(shim, heads, dh):
+    rng = random.Random(heads * 1000 + dh)
+    for _ in range(300):
+        n = rng.choice([1, 1, 2, 3, 5, 17])
+        top = rng.choice([300, 3000, 20000 if n < 5 else 5000])
+
+        def length(lo):
+            return rng.choice([lo, rng.randint(lo, top), rng.randint(lo, top) // 64 * 64 + rng.choice([0, 1, 63]), rng.randint(lo, top) // 256 * 256 + rng.choice([0, 1, 127, 128, 129])])
+
+        L = [length(0) for _ in range(n)]
+        kind = rng.choice(["prefill", "rank", "full", "mixed"])
+        S = M = None
+        computed = [int(l > 0) for l in L]
+        if kind != "prefill":
+            S = [rng.choice([0, 0, rng.randint(1, 200)]) for _ in range(n)]
+            M = [rng.choice([0, 1, 128, 129, rng.randint(1, 2000)]) for _ in range(n)]
+            if kind == "rank":
+                computed = [0] * n
+            elif kind == "mixed":
+                computed = [c and rng.randint(0, 1) for c in computed]
+        if kind == "prefill":
+            L = [max(1, l) for l in L]
+            computed = [1] * n
+        if sum(L) + sum(M or []) == 0:
+            continue
+        check(shim, L, S, M, computed, heads, dh, rng.choice([256, 256, 304, 64]), rng.choice([8, 8, 1, 2, 3, 5]))
