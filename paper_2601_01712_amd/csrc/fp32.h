@@ -452,16 +452,20 @@ __global__ __launch_bounds__(1024) void tail_f32_kernel(TailF32Params p) {
     store_row_run<float, E, false>(&ys[0][0], wave, lane, YS, y);
   }
   if constexpr (!EARLY) first_w();
-  // the accumulators start from the residual row and the bias: element e of acc[j] is feature (wave*FB + j)*16 + 4*g4 + e
+  // element e of acc[j] is feature (wave*FB + j)*16 + 4*g4 + e.  The product is summed by itself and added to the residual row
+  // once, at the end: sums that start from the residual value, which is much larger, round to its last place in every step
+  // (scores of the two-layer d = 64 model 4.9e-7 from the same model in float64, against 1.2e-7)
   const int row = row0 + tk;
   const bool live = row < p.row_end;
   float* xrow = p.x + (size_t)(live ? row : row0) * D;
   f32x4v_t acc[FB];
+  float4 xv[FB], bv[FB];
 #pragma unroll
   for (int j = 0; j < FB; ++j) {
     const int c = ((product ? wave : 0) * FB + j) * 16 + 4 * g4;
-    const float4 xv = *reinterpret_cast<const float4*>(xrow + c), bv = *reinterpret_cast<const float4*>(p.bias + c);
-    acc[j] = f32x4v_t{xv.x + bv.x, xv.y + bv.y, xv.z + bv.z, xv.w + bv.w};
+    xv[j] = *reinterpret_cast<const float4*>(xrow + c);
+    bv[j] = *reinterpret_cast<const float4*>(p.bias + c);
+    acc[j] = f32x4v_t{0.f, 0.f, 0.f, 0.f};
   }
   __syncthreads();
   const float* yl = &ys[tk][4 * g4];
@@ -486,6 +490,8 @@ __global__ __launch_bounds__(1024) void tail_f32_kernel(TailF32Params p) {
 #pragma unroll
   for (int j = 0; j < FB; ++j) {
     const int c = (wave * FB + j) * 16 + 4 * g4;
+    acc[j][0] = xv[j].x + (acc[j][0] + bv[j].x); acc[j][1] = xv[j].y + (acc[j][1] + bv[j].y);
+    acc[j][2] = xv[j].z + (acc[j][2] + bv[j].z); acc[j][3] = xv[j].w + (acc[j][3] + bv[j].w);
     if (product && live && !want_score) *reinterpret_cast<float4*>(xrow + c) = make_float4(acc[j][0], acc[j][1], acc[j][2], acc[j][3]);
     s1 += (acc[j][0] + acc[j][1]) + (acc[j][2] + acc[j][3]);
   }

@@ -79,6 +79,24 @@ def test_fp32_head_sizes(d, H):
     run_three_routes(synth.ModelConfig(2, d, H, "fp32"), 50 + H, [150, 70], [5, 0], [20, 66])
 
 
+@pytest.mark.parametrize("layers,d,H", [(2, 64, 2), (4, 128, 2)])
+def test_fp32_scores_are_off_by_a_rounding_per_layer(layers, d, H):
+    """At these widths the products of a layer add little to the error of the residual row it updates, which is rounded once: 2^-24
+    a layer at most, and about two more in the score head (normalised row, weighted sum).  Output sums that start from the residual
+    value instead round to its last place d / 4 times a layer and end up at 7 to 15 times 2^-24."""
+    cfg = synth.ModelConfig(layers, d, H, "fp32")
+    weights, batch = build_case(cfg, 47, [200, 90], [3, 0], [256, 256])
+    want = np.concatenate(list(oracle_scores(cfg, weights, batch).values()))
+    h = Harness(cfg, weights, batch)
+    try:
+        h.prefill()
+        for got in (h.rank_cached(), h.rank_full()):
+            rel = float(np.linalg.norm(got - want) / np.linalg.norm(want))
+            assert rel <= (layers + 2) * 2.0 ** -24, rel * 2.0 ** 24
+    finally:
+        h.close()
+
+
 @pytest.mark.parametrize("attention", ["silu", "softmax"])
 @pytest.mark.parametrize("d,H,L,S,M", [
     (64, 1, [31, 33, 0], [0, 33, 1], [17, 1, 47]),            # fewer half tiles than a team has wavefronts; 32-row tiles end inside
