@@ -35,10 +35,11 @@
  *     memory; it owns host-side metadata and, per context, a small pinned staging
  *     area allocated in relaygr_ctx_create (no compute call allocates or frees).
  *   - Compute calls enqueue work on the given HIP stream and return without
- *     synchronising the device or the stream.  One bounded host wait exists: a
- *     call's batch descriptors go through a ring of four pinned staging slots, so
- *     the fifth call in a row waits until the upload of the first has completed
- *     (microseconds once the stream has reached it).  Buffers passed to a call
+ *     synchronising the device or the stream.  One host wait exists: a call's batch
+ *     descriptors go through a ring of four pinned staging slots, so the fifth call in a
+ *     row waits until the GPU has read the first one's (microseconds once the stream has
+ *     reached that call, however long that takes; RELAYGR_EHIP if the stream has failed,
+ *     or has run dry without reading them).  Buffers passed to a call
  *     must stay valid and unmodified until that stream has passed the call's work.  A context is one model slot:
  *     its calls share its scratch buffer and staging area, so they run one after the other on the GPU: a call
  *     given another stream than the context's previous call is made to wait for the work that stream holds at

@@ -4,7 +4,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <chrono>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -12,7 +11,6 @@
 #include <mutex>
 #include <new>
 #include <string>
-#include <thread>
 #include <type_traits>
 #include <vector>
 
@@ -25,6 +23,7 @@
 #include "gemm_bf16.h"
 #include "kv_pool.h"
 #include "rowwise.h"
+#include "staging.h"
 
 using namespace relaygr;
 
@@ -211,6 +210,25 @@ static int static_scratch(char** out, int* dev_out = nullptr) {
 constexpr int kStagingSlots = 4;
 constexpr size_t kInlineBlobBytes = 128 << 10, kSlotFlagBytes = 256;   // batches whose descriptors the first kernel fetches itself
 static_assert(kInlineBlobBytes / kBlobChunk * 4 <= kSlotFlagBytes, "a flag per chunk");
+
+// Whether a stream has work left, asked in a way that is safe next to another stream's capture.
+static StreamState stream_state(hipStream_t st) {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) { (void)hipGetLastError(); return StreamState::kBusy; }
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  hipError_t e = hipStreamIsCapturing(st, &cap);
+  const bool captured = e == hipSuccess && cap != hipStreamCaptureStatusNone;   // (a question would end the capture)
+  if (e == hipSuccess && !captured) e = hipStreamQuery(st);
+  if (e != hipSuccess) (void)hipGetLastError();      // the answer, not an error of the call that asks
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  if (captured) return StreamState::kBusy;
+  switch (e) {
+    case hipErrorNotReady: case hipErrorStreamCaptureUnsupported: case hipErrorStreamCaptureImplicit: return StreamState::kBusy;
+    case hipSuccess: case hipErrorInvalidHandle: case hipErrorContextIsDestroyed: case hipErrorInvalidValue: return StreamState::kDrained;   // (the others: destroyed by its owner)
+    default: return StreamState::kFailed;
+  }
+}
+
 struct StagingSlot {
   void* host = nullptr;       // pinned: flags of the kernel that reads the slot, then the descriptors
   size_t bytes = 0;           // of descriptors
@@ -219,16 +237,14 @@ struct StagingSlot {
   uint32_t seq = 0;           // calls whose first kernel has read (or will read) it
   int chunks = 0;             // workgroups of the last of them, each of which sets its flag to seq
   uint32_t* flags() const { return (uint32_t*)host; }
-  // Waits for that kernel: it is on its stream (chunks is 0 otherwise), so this ends when the stream gets there.  Polls for
-  // about a millisecond, then sleeps between looks.  (No wait for the device: that would also wait for streams
-  // that have nothing to do with the call, and fail while one of them is being captured.)
-  void wait_read() {
-    for (int k = 0, looks = 0; k < chunks; ++k)
-      while (__atomic_load_n(flags() + k, __ATOMIC_ACQUIRE) != seq) {
-        if (++looks < 20000) __builtin_ia32_pause();
-        else std::this_thread::sleep_for(std::chrono::microseconds(20));
-      }
+  hipStream_t stream = nullptr;   // where that kernel is
+  // Waits for that kernel: it is on its stream (chunks is 0 otherwise).  False: it will not come (wait_for_flags).
+  bool wait_read() {
+    if (chunks == 0) return true;
+    const hipStream_t st = stream;
+    if (!wait_for_flags(flags(), chunks, seq, [st] { return stream_state(st); })) return false;
     chunks = 0;
+    return true;
   }
   char* blob() const { return (char*)host + kSlotFlagBytes; }
 };
@@ -361,11 +377,12 @@ extern "C" void relaygr_ctx_destroy(relaygr_ctx* c) {
   if (!c) return;
   for (auto& r : c->prof_recs) { (void)hipEventSynchronize(r.b); (void)hipEventDestroy(r.a); (void)hipEventDestroy(r.b); }
   for (auto e : c->prof_free) (void)hipEventDestroy(e);
+  bool read = true;   // (memory that a kernel may still read is not given back)
   for (auto& s : c->staging) {
-    s.wait_read();
+    read = s.wait_read() && read;
     if (s.done) { if (s.pending) (void)hipEventSynchronize(s.done); (void)hipEventDestroy(s.done); }
   }
-  if (c->staging_mem) (void)hipHostFree(c->staging_mem);
+  if (c->staging_mem && read) (void)hipHostFree(c->staging_mem);
   if (c->call_done) (void)hipEventDestroy(c->call_done);
   delete c;
 }
@@ -380,7 +397,8 @@ static int staging_acquire(relaygr_ctx* c, size_t bytes, StagingSlot** out) {
                 "too many users or row tiles for one call)", bytes, s.bytes);
   c->next_slot = (c->next_slot + 1) % kStagingSlots;
   if (s.pending) { HIP_TRY(hipEventSynchronize(s.done)); s.pending = false; }
-  s.wait_read();
+  if (!s.wait_read())
+    return fail(RELAYGR_EHIP, "the kernel that reads an earlier call's descriptors has not run: the stream it was put on failed");
   *out = &s;
   return RELAYGR_OK;
 }
@@ -815,7 +833,7 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
       });
       if (!ok) return fail(RELAYGR_EINVAL, "unsupported d_model");
       LAUNCH_CHECK("ln_in");
-      if (inline_batch) slot->chunks = copy_blocks;   // now the kernel that will set the flags is on its stream
+      if (inline_batch) { slot->chunks = copy_blocks; slot->stream = st; }   // now the kernel that will set the flags is on its stream
     }
     // step 2: projections
     ColMap all4 = {4, {0, 1, 2, 3}, d}, kv_only = {2, {1, 3, 0, 0}, d};

@@ -218,6 +218,49 @@ def test_descriptors_as_an_argument_and_by_copy(dtype, n):
         h.close()
 
 
+def test_calls_that_wait_long_for_a_staging_slot():
+    """Calls behind tens of milliseconds of other work on their stream: the fifth waits until the GPU has read the first one's
+    descriptors, past the point where it asks the stream whether that will ever happen; once with a capture open on another stream."""
+    cfg = synth.ModelConfig(2, 128, 2, "bf16")
+    weights, batch = build_case(cfg, 781, [200, 90], [4, 0], [70, 30])
+    h = Harness(cfg, weights, batch)
+    a = torch.randn(8192, 8192, device="cuda:0")
+    b, other = torch.empty_like(a), torch.zeros(64, device="cuda:0")
+    st, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    outs = [torch.empty(100, device="cuda:0") for _ in range(6)]
+
+    def calls():
+        with torch.cuda.stream(st):
+            for _ in range(600):
+                torch.sin(a, out=b)
+        for o in outs:
+            rg.relaygr_rank_with_cache(h.ctx, h.pool, h.dbatch, o, stream=st)
+
+    try:
+        h.prefill()
+        want = torch.from_numpy(h.rank_cached())
+        torch.cuda.synchronize()
+        for capture in (False, True):
+            for o in outs:
+                o.zero_()
+            torch.cuda.synchronize()
+            if capture:
+                with torch.cuda.graph(graph):
+                    other += 1
+                    calls()
+            else:
+                calls()
+            torch.cuda.synchronize()
+            for o in outs:
+                assert torch.equal(o.cpu(), want)
+        for n in (1, 2):
+            graph.replay()
+            torch.cuda.synchronize()
+            assert bool((other == n).all())
+    finally:
+        h.close()
+
+
 # ------------------------------------------------------------------------------------ fp16
 @pytest.mark.parametrize("L,S,M", [
     ([1], [0], [1]), ([65, 300], [0, 70], [3, 129]), ([513, 0, 128], [64, 2, 0], [257, 9, 1]), ([1000], [17], [400]),
