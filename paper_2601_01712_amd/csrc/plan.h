@@ -121,33 +121,56 @@ inline void attn_row_tiles(const std::vector<UserDesc>& users, int tile_rows, st
 }
 
 // 16-bit attention: how a launch's row tiles (each with its list of 64-key tiles) are cut into pieces along the keys.
-// The chip takes `slots` workgroups at a time and deals the list out longest first, so a launch is done soon after
-// total / slots key tiles a slot unless single items are longer than that: one user's causal prefill has one item of all key
-// tiles and one of two, a jagged batch one user of 16 384 keys among short ones.  Pieces are cut to at most that share, not
-// under kMinPieceTiles (a workgroup's own start and end cost about as much as six key tiles) and not into more than 8; and
-// only for launches of less than kPieceRounds rounds, where there is too little behind the long items to hide them: each
-// further piece of a row is an fp32 partial sum more for the layer tail to read.
-constexpr int kMinPieceTiles = 8, kMaxPieces = 8, kPieceRounds = 4, kMaxSlots = 512;
+// The chip takes `slots` workgroups at a time and deals the list out longest first.  Unequal items: a launch is done soon after
+// total / slots key tiles a slot unless single items are longer than that (one user's causal prefill has one item of all key
+// tiles and one of two, a jagged batch one user of 16 384 keys among short ones), so pieces are cut to at most that share.  Items
+// of about the same length: into as many pieces each as fit the chip at once, for one more would put a third workgroup on some
+// compute units, or a second on some of those that a pair of pieces fills, and the launch would wait for it (12 users of 4096 keys
+// and 300 candidates at d = 256: 4 pieces 255 us a call, 3 pieces 200; 40 of 1024 keys and 128 candidates at d = 512: 2 pieces
+// 690, uncut 636).  Only launches of less than kPieceRounds rounds are cut, as there is too little behind their long items to hide
+// them: each further piece of a row is an fp32 partial sum more for the layer tail to read, and so a piece has kMinPieceTiles key
+// tiles (a workgroup's own start and end cost about as much as six).
+// Launches that leave more than half of the slots free are another matter: their pieces run by themselves, and the shorter
+// chain is worth more than the sums.  Where a call computes no prefix, its rows are cut into as many pieces as keep half of the
+// slots free, of no less than kFinePieceTiles.  (d = 512, one user, us a call in pieces of 8 / 4 / 2 / 1 tiles: 512 keys and 64
+// candidates 257 / 238 / 231 / 231, 1024 and 512 263 / 250 / 254; 2048 and 64 in pieces of 8 / 4 263 / 247.  More than half full:
+// 8 users at d = 128 with 2048 keys and 272 new rows, 240 pieces of 7 tiles 115, 336 of 5 126; d = 1024, 2048 keys and 512
+// candidates, 128 pieces of 8 on 256 slots 611, 256 of 4 646.)  It is a number of pieces and no length, so that as long as
+// a launch is that small a row's sums do not depend on how long the histories of the call's other users are.
+constexpr int kMinPieceTiles = 8, kFinePieceTiles = 2, kMaxPieces = 8, kPieceRounds = 4, kMaxSlots = 512;
 // Pieces a cut list has at most: the launch has under kPieceRounds * kMaxSlots (row tile, head) pairs, each cut in at most kMaxPieces.
 inline int max_cut_items(int n_heads) { return kMaxPieces * kPieceRounds * kMaxSlots / n_heads; }
-inline int piece_tiles(int64_t items, int64_t total_key_tiles, int most_key_tiles, int slots) {
-  if (items >= (int64_t)kPieceRounds * slots) return std::max(1, most_key_tiles);
-  int64_t c = (total_key_tiles + slots - 1) / slots;
-  c = std::max<int64_t>({c, kMinPieceTiles, (most_key_tiles + kMaxPieces - 1) / kMaxPieces});
+inline int piece_tiles(int64_t items, int64_t total_key_tiles, int least_key_tiles, int most_key_tiles, int slots) {
+  if (items >= (int64_t)kPieceRounds * slots || items == 0) return std::max(1, most_key_tiles);
+  auto into = [&](int64_t pieces) { pieces = std::max<int64_t>(1, std::min<int64_t>(pieces, kMaxPieces)); return (most_key_tiles + pieces - 1) / pieces; };
+  const bool equal = 4 * (int64_t)least_key_tiles >= 3 * (int64_t)most_key_tiles;
+  int64_t c = equal ? into(slots / items) : (total_key_tiles + slots - 1) / slots;
+  c = std::max<int64_t>({c, kMinPieceTiles, into(kMaxPieces)});
   return (int)std::max<int64_t>(1, std::min<int64_t>(c, most_key_tiles));
+}
+
+inline int fine_pieces(int64_t items, int slots) { return items == 0 ? 1 : (int)std::max<int64_t>(1, std::min<int64_t>(slots / 2 / items, kMaxPieces)); }
+
+// Pieces of a row tile of new rows with nk key tiles.
+inline int new_row_parts(int nk, int piece, int fine) {
+  if (nk == 0) return 1;
+  const int parts = std::max((nk + piece - 1) / piece, std::min(fine, (nk + kFinePieceTiles - 1) / kFinePieceTiles));
+  const int per = (nk + parts - 1) / parts;
+  return (nk + per - 1) / per;                       // (none of them empty)
 }
 
 // The launch lists of a call's attention and what the layer tail has to know of them.
 struct AttnCut {
   std::vector<AttnTile> all, last;                   // every layer but the last; the last layer (no prefix rows)
   int piece_all = 1 << 20, piece_last = 1 << 20;     // most key tiles of a piece
+  int fine = 1;                                      // pieces a row tile of new rows has even if they are shorter (fine_pieces)
   int parts_all = 1, parts_last = 1;                 // partial sums of every row (0: rows differ)
   int nsplit = 1;                                    // partial sums a row can have (fp32: has)
   int gs = 1;                                        // key splits added inside an attention workgroup (AttnParams::gs)
 };
 
-// Fills `out` with the pieces of at most `piece` key tiles, longest first; returns the most pieces of a row tile.
-inline int cut_pieces(const std::vector<AttnTile>& rows_new, const std::vector<AttnTile>* rows_prefix, int tile_rows, int piece, std::vector<AttnTile>& out, int* uniform) {
+// Fills `out` with the pieces of at most `piece` key tiles (new rows: new_row_parts of them), longest first; returns the most pieces of a row tile.
+inline int cut_pieces(const std::vector<AttnTile>& rows_new, const std::vector<AttnTile>* rows_prefix, int tile_rows, int piece, int fine, std::vector<AttnTile>& out, int* uniform) {
   out.clear();
   int lo = kMaxPieces + 1, hi = 0;
   auto add = [&](AttnTile a, int parts) {
@@ -156,7 +179,7 @@ inline int cut_pieces(const std::vector<AttnTile>& rows_new, const std::vector<A
     a.parts = (int16_t)parts;
     for (int k = 0; k < parts; ++k) { a.part = (int16_t)k; a.t0 = std::min(k * per, nk); a.t1 = std::min(a.t0 + per, nk); out.push_back(a); }
   };
-  for (const AttnTile& a : rows_new) add(a, std::max(1, (key_tiles(a) + piece - 1) / piece));
+  for (const AttnTile& a : rows_new) add(a, new_row_parts(key_tiles(a), piece, fine));
   if (rows_prefix) for (const AttnTile& a : *rows_prefix) add(a, causal_parts(a.pos0, tile_rows, piece));
   std::stable_sort(out.begin(), out.end(), [](const AttnTile& a, const AttnTile& b) { return a.t1 - a.t0 > b.t1 - b.t0; });
   *uniform = hi == 0 ? 1 : lo == hi ? lo : 0;
@@ -167,30 +190,33 @@ inline int cut_pieces(const std::vector<AttnTile>& rows_new, const std::vector<A
 template <class Fits>
 inline void cut_attention(const std::vector<AttnTile>& rows_new, const std::vector<AttnTile>& rows_prefix, int heads, int dh, int tile_rows, int n_cus, AttnCut& c, Fits fits) {
   int64_t kt_new = 0, kt_prefix = 0;
-  int most_new = 0, most_prefix = 0;
-  for (const AttnTile& a : rows_new) { kt_new += key_tiles(a); most_new = std::max(most_new, key_tiles(a)); }
-  for (const AttnTile& a : rows_prefix) { kt_prefix += key_tiles(a); most_prefix = std::max(most_prefix, key_tiles(a)); }
+  int least_new = 1 << 30, most_new = 0, least_prefix = 1 << 30, most_prefix = 0;
+  for (const AttnTile& a : rows_new) { const int k = key_tiles(a); kt_new += k; least_new = std::min(least_new, k); most_new = std::max(most_new, k); }
+  for (const AttnTile& a : rows_prefix) { const int k = key_tiles(a); kt_prefix += k; least_prefix = std::min(least_prefix, k); most_prefix = std::max(most_prefix, k); }
   const int slots = std::min(kMaxSlots, dh == 128 ? n_cus : 2 * n_cus);   // workgroups the chip takes at a time
-  c.piece_all = piece_tiles((int64_t)(rows_new.size() + rows_prefix.size()) * heads, (kt_new + kt_prefix) * heads, std::max(most_new, most_prefix ? most_prefix + tile_rows / kTile : 0), slots);
-  c.piece_last = piece_tiles((int64_t)rows_new.size() * heads, kt_new * heads, most_new, slots);
+  c.piece_all = piece_tiles((int64_t)(rows_new.size() + rows_prefix.size()) * heads, (kt_new + kt_prefix) * heads, std::min(least_new, least_prefix),
+                            std::max(most_new, most_prefix ? most_prefix + tile_rows / kTile : 0), slots);
+  c.piece_last = piece_tiles((int64_t)rows_new.size() * heads, kt_new * heads, least_new, most_new, slots);
+  const bool one_list = rows_prefix.empty();       // the last layer's list is then the same: not sent twice
+  if (one_list) c.fine = fine_pieces((int64_t)rows_new.size() * heads, slots);
   auto cut = [&]() {
-    const int h1 = cut_pieces(rows_new, &rows_prefix, tile_rows, c.piece_all, c.all, &c.parts_all);
-    const int h2 = cut_pieces(rows_new, nullptr, tile_rows, c.piece_last, c.last, &c.parts_last);
+    const int h1 = cut_pieces(rows_new, &rows_prefix, tile_rows, c.piece_all, c.fine, c.all, &c.parts_all);
+    const int h2 = cut_pieces(rows_new, nullptr, tile_rows, c.piece_last, c.fine, c.last, &c.parts_last);
     c.nsplit = std::max({1, h1, h2});
   };
   for (;;) {
     cut();
     const bool uncut = c.all.size() == rows_new.size() + rows_prefix.size() && c.last.size() == rows_new.size();
     if (uncut || (fits(c) && c.nsplit <= kMaxPieces)) break;
-    c.piece_all *= 2; c.piece_last *= 2;
+    c.piece_all *= 2; c.piece_last *= 2; c.fine = std::max(1, c.fine / 2);
   }
   // d_head 64: two pieces of a row go to the two wavefront groups of one workgroup, which add their
   // sums in LDS -- half the partial sums for the layer tail to read -- where every row has the same even number of them and
   // half the workgroups still give every compute unit one (with fewer, e.g. one user with 512 candidates, the attention
   // launch itself gets 25 % slower)
-  const bool one_list = rows_prefix.empty();       // the last layer's list is then the same: not sent twice
   if (dh == 64 && one_list && c.parts_all > 0 && c.parts_all % 2 == 0 && (int64_t)rows_new.size() * heads * (c.parts_all / 2) >= n_cus) {
     c.gs = 2;
+    c.fine = 1;
     c.piece_all = c.piece_last = (most_new + c.parts_all / 2 - 1) / (c.parts_all / 2);
     cut();
   }
@@ -201,8 +227,8 @@ inline void cut_attention(const std::vector<AttnTile>& rows_new, const std::vect
 inline void set_user_parts(std::vector<UserDesc>& users, const AttnCut& c) {
   for (UserDesc& ud : users) {
     const int nk = (ud.L + kTile - 1) / kTile + (ud.S + kTile - 1) / kTile;
-    ud.parts = std::max(1, (nk + c.piece_all - 1) / c.piece_all);
-    ud.parts_last = std::max(1, (nk + c.piece_last - 1) / c.piece_last);
+    ud.parts = new_row_parts(nk, c.piece_all, c.fine);
+    ud.parts_last = new_row_parts(nk, c.piece_last, c.fine);
   }
 }
 

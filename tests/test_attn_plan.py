@@ -48,6 +48,21 @@ def test_two_splits_share_a_workgroup_where_every_row_has_an_even_number(shim):
     assert check(shim, [4096] * 16, [0] * 16, [512] * 16, [0] * 16) == {"blocks": 2, "nsplit": 1, "gs": 2, "items": 32, "filler": 0}
 
 
+@pytest.mark.parametrize("L,S,M,heads,dh,sums,items", [
+    # a launch that leaves half of the chip free is cut finer than eight key tiles
+    ([512], [0], [64], 8, 64, 4, 4), ([1024], [0], [512], 8, 64, 8, 32), ([2048], [0], [64], 8, 64, 8, 8), ([200], [0], [64], 8, 64, 2, 2),
+    ([2048], [0], [256], 4, 128, 8, 16), ([512] * 24, [0] * 24, [32] * 24, 4, 64, 2, 48),
+    # and one that does not, is not
+    ([2048] * 8, [16] * 8, [256] * 8, 2, 64, 5, 120), ([2048], [0], [512], 8, 128, 4, 16), ([2048], [0], [1024], 8, 64, 4, 32),
+    # equal items are cut into no more pieces than the chip takes at a time (512 workgroups, 256 at d_head 128)
+    ([4096] * 12, [0] * 12, [300] * 12, 4, 64, 3, 108), ([1024] * 40, [0] * 40, [128] * 40, 8, 64, 1, 40),
+    ([4096] * 10, [0] * 10, [300] * 10, 8, 64, 2, 60), ([2048] * 8, [0] * 8, [256] * 8, 8, 128, 2, 32),
+])
+def test_pieces_of_equal_items_fit_the_chip_and_small_launches_are_cut_finer(shim, L, S, M, heads, dh, sums, items):
+    got = check(shim, L, S, M, [0] * len(L), heads, dh)
+    assert (got["nsplit"] * got["gs"], got["items"]) == (sums, items)
+
+
 @pytest.mark.parametrize("heads,dh", [(4, 32), (16, 32), (1, 128), (2, 64), (4, 64), (8, 64), (16, 64), (2, 128), (8, 128)])
 def test_every_row_has_the_sums_its_pieces_write(shim, heads, dh):
     rng = random.Random(heads * 1000 + dh)
