@@ -250,14 +250,16 @@ int  relaygr_rank_full_recompute(relaygr_ctx* ctx, const relaygr_batch* batch,
 
 /* ---- measurement ---------------------------------------------------------------------- */
 
-/* Kernel classes of the layer sequence, for per-kernel timing. */
-#define RELAYGR_K_SETUP 0   /* row tables, tail clearing                       */
-#define RELAYGR_K_LN    1   /* input LayerNorm (and first-layer gather)        */
+/* Kernel classes of the layer sequence, for per-kernel timing.  SETUP, GATE and SCORE have no launches of
+ * their own (0 ms, 0 launches): their work is done, and counted, in LN (SETUP) and F2 (GATE and SCORE). */
+#define RELAYGR_K_SETUP 0   /* always 0                                        */
+#define RELAYGR_K_LN    1   /* first input LayerNorm, embedding gather, row tables, tail clearing */
 #define RELAYGR_K_F1    2   /* u|v|q|k projection GEMM + SiLU + K/V scatter     */
 #define RELAYGR_K_ATTN  3   /* pointwise-SiLU attention over the key sequence   */
-#define RELAYGR_K_GATE  4   /* split combine, self term, 1/n, LayerNorm, gate   */
-#define RELAYGR_K_F2    5   /* output projection GEMM + residual                */
-#define RELAYGR_K_SCORE 6   /* final LayerNorm + score head                     */
+#define RELAYGR_K_GATE  4   /* always 0                                         */
+#define RELAYGR_K_F2    5   /* layer tail: split combine, self term, 1/n, LayerNorm, gate, output projection, residual,
+                               next input LayerNorm or score head */
+#define RELAYGR_K_SCORE 6   /* always 0                                         */
 #define RELAYGR_K_COUNT 7
 
 /* Turns per-launch timing on for the classes in class_mask (bit k = class k; 0 turns it off) and

@@ -36,7 +36,10 @@
 namespace relaygr {
 
 // The descriptors of a batch of few users, small enough to be a kernel argument: the call's first kernel then needs no copy
-// to have run before it (see BlobCopy).
+// to have run before it (see BlobCopy).  The argument is the faster one at every number of users that it could hold (the 4 KiB
+// of kernel arguments are full at a little over 40): us a call with it and with the copy command, d = 256, 4 layers, 512 keys and
+// 32 candidates a user, 4 users 75 / 80, 16 83 / 86, 24 87 / 91, 40 99 / 103.  So this line is no crossover: it is where the
+// argument, which the first launch of every call carries whole, is 1.4 KiB.
 constexpr int kInlineUsers = 16;
 struct InlineBatch {
   UserDesc users[kInlineUsers];
@@ -110,24 +113,11 @@ __host__ __device__ __forceinline__ size_t panel_off(int row, int k, int K) {
   return ((size_t)panel * (K >> 4) + ks) * 2048 + (size_t)rb * 512 + (g * 32 + l32) * 8 + j;
 }
 
-// Streaming stores (the `nt` hint): for kernel outputs that nothing in the same launch reads back.  A plain store
-// allocates its line in the XCD's L2, and a launch that writes tens of megabytes pushes out the operand lines the
-// workgroups of that XCD share (token panels, weight slices, K/V tiles), which are then fetched again and again
-// from the memory side; marked non-temporal, the output lines leave L2 first.  Measured on the projection GEMM
-// at 65 536 rows: 225 us with plain stores, 152 us with these (150 us with no stores at all).  Not a general win:
-// a workgroup ends only when its stores are acknowledged, which a streaming store is later than a cached one --
-// the attention kernel's partial sums and the layer tail's outputs, written once at the end of short-lived
-// workgroups, got 13 % and 5-17 % slower with it and keep plain stores.
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
 // (the address-space forms are for pointers that were themselves loaded from memory: the compiler cannot tell that those are
 // global addresses and would use flat stores, which also hold up the LDS counter)
 typedef __attribute__((address_space(1))) u32x4_t gu32x4_t;
 __device__ __forceinline__ gu32x4_t* as_global16(uint16_t* p) { return (gu32x4_t*)p; }
-__device__ __forceinline__ void st_stream(uint4* p, uint4 v) { __builtin_nontemporal_store(u32x4_t{v.x, v.y, v.z, v.w}, reinterpret_cast<u32x4_t*>(p)); }
-__device__ __forceinline__ void st_stream(uint2* p, uint2 v) { __builtin_nontemporal_store(u32x2_t{v.x, v.y}, reinterpret_cast<u32x2_t*>(p)); }
-__device__ __forceinline__ void st_stream(float4* p, float4 v) { __builtin_nontemporal_store(f32x4_t{v.x, v.y, v.z, v.w}, reinterpret_cast<f32x4_t*>(p)); }
 
 // Sum over the wavefront, in every lane, adding lane i to lane i ^ 32, then ^ 16, ^ 8, ^ 4, ^ 2, ^ 1, on the vector ALU: the
 // halves and the 16-lane rows change places (v_permlane32_swap, v_permlane16_swap), and inside a row a rotation by 8 is lane ^ 8, after

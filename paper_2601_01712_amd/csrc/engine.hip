@@ -796,10 +796,9 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
   const AttnTile* d_tiles = (const AttnTile*)(db + o_tiles);
 
   const float alpha = 1.0f / sqrtf((float)dh);
-  const float kLog2e = 1.4426950408889634f, kLn2 = 0.69314718055994531f;
+  const float kLog2e = 1.4426950408889634f;
   const float q_mul = bf16 ? alpha * kLog2e : 1.0f;       // what f1 multiplies q by before storing it
   const float score_mul = bf16 ? 1.0f : alpha;            // what the attention kernel still applies
-  const float gate_mul = kLn2;                            // 16-bit: stored q . k  ->  alpha <q,k> for the self term
   const T* emb_p = (const T*)b->prefix_emb;
   const T* emb_s = (const T*)b->suffix_emb;
   const T* emb_c = (const T*)b->cand_emb;
@@ -842,10 +841,10 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
         F1F32Params fp;
         fp.A = xh; fp.W = (const float*)lw.w1; fp.bias = (const float*)lw.b1; fp.u = ubuf; fp.q = qbuf; fp.knew = knew; fp.vnew = vnew; fp.sfx = sfx;
         fp.users = d_users; fp.rt = rt; fp.d = d; fp.dh = dh; fp.n_prows = p.n_prows; fp.layer = l; fp.row_begin = r0; fp.row_end = r1; fp.cm = cm;
-        // 128 x 128 tiles once they give every compute unit one, 64 x 64 while those do, 32 x 32 with k cut in four below
+        // 128 x 128 tiles once they give every compute unit two, 64 x 64 while those do, 32 x 32 with k cut in four below
         const int64_t cols = (int64_t)cm.nblk * d;
         auto tiles = [&](int t) { return (int64_t)((r1 - r0 + t - 1) / t) * (cols / t); };
-        const int tile = (d % 128 == 0 && tiles(128) >= 512) ? 128 : tiles(64) >= 512 ? 64 : 32;
+        const int tile = (d % 128 == 0 && tiles(128) >= 2 * c->n_cus) ? 128 : tiles(64) >= 2 * c->n_cus ? 64 : 32;
         fp.n_mtiles = (r1 - r0 + tile - 1) / tile;
         const dim3 grid((tiles(tile) + 7) / 8 * 8);
         if (tile == 128) hipLaunchKernelGGL((f1_f32_kernel<2, 0>), grid, dim3(256), 0, st, fp);
@@ -942,7 +941,7 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
           fp.part = part; fp.parts_shift = last ? 8 : 0; fp.parts_all = last ? cut.parts_last : cut.parts_all; fp.split_stride = (size_t)R * d;
           fp.u = (const uint16_t*)ubuf; fp.q = self_in_attn ? nullptr : (const uint16_t*)qbuf; fp.knew = (const uint16_t*)knew; fp.vnew = (const uint16_t*)vnew;
           fp.gate_gain = (const uint16_t*)lw.ln_at_g; fp.gate_offs = (const uint16_t*)lw.ln_at_b;
-          fp.n_prows = p.n_prows; fp.dh = dh; fp.qk_mul = gate_mul;
+          fp.n_prows = p.n_prows; fp.dh = dh;
           fp.ml = softmax ? ml : nullptr; fp.ml_stride = (size_t)R * H * 2; fp.n_heads = H;
           // two row blocks per workgroup halve the passes over W2 once that still leaves every
           // compute unit two workgroups

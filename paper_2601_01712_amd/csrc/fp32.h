@@ -27,7 +27,8 @@ __device__ __forceinline__ float f4_at(const float4& v, int i) { return i == 0 ?
 // product, and V is stored transposed, so that its operand is again 16 consecutive bytes.  Every operand is loaded
 // straight from the K/V tile; the loads of a half tile's V and of the next one's K are issued a product (2048 cycles at
 // d_head 64) before they are needed.  Nothing is shared, so nothing waits: two wavefronts a SIMD, one's SiLU beside the
-// other's products.  Bound by the matrix pipe: 8 cycles per score element at d_head 64 against about 4.5 of vector ALU.
+// other's products.  The products take 4 cycles of a SIMD's matrix pipe per score element at d_head 64, 7 of the 19 us below; the
+// rest is SiLU on the vector ALU and what two wavefronts do not hide of each other's waits.
 // gs = 8: the eight wavefronts of a workgroup take the same rows and consecutive parts of the keys and add their sums
 // in LDS (in a fixed order): calls of few rows fill the chip without writing a partial sum for every part.
 // 512 rows x 2048 keys x 4 heads of 64: 19 us a launch (57 TFLOP/s); one thread per row over LDS-broadcast keys took 277.

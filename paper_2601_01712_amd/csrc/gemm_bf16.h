@@ -155,7 +155,14 @@ struct F1Params {
   int stream_out;           // weight-stationary kernel: outputs leave with streaming stores (launches that write far more than L2 holds)
 };
 
-
+// Streaming stores (the `nt` hint): for kernel outputs that nothing in the same launch reads back.  A plain store
+// allocates its line in the XCD's L2, and a launch that writes tens of megabytes pushes out the operand lines the
+// workgroups of that XCD share (token panels, weight slices, K/V tiles), which are then fetched again and again
+// from the memory side; marked non-temporal, the output lines leave L2 first.  Measured on the projection GEMM
+// at 65 536 rows: 225 us with plain stores, 152 us with these (150 us with no stores at all).  Not a general win:
+// a workgroup ends only when its stores are acknowledged, which a streaming store is later than a cached one --
+// the attention kernel's partial sums and the layer tail's outputs, written once at the end of short-lived
+// workgroups, got 13 % and 5-17 % slower with it and keep plain stores.
 __device__ __forceinline__ void st_out(uint16_t* dst, uint4 v, int stream) {
   gu32x4_t* g = as_global16(dst);
   if (stream) __builtin_nontemporal_store(u32x4_t{v.x, v.y, v.z, v.w}, g);
@@ -329,7 +336,7 @@ __global__ __launch_bounds__(256, TM == 4 ? 2 : 1) void f1_gemm_bf16_kernel(F1Pa
 // 4 KiB of wavefront-private LDS (32 tokens x 64 features, 16-byte chunks swizzled by token so that neither
 // the 8-byte writes nor the 16-byte reads pile up on a bank) and leave as 128-byte row segments; V of prefix
 // rows takes the token-major product, whose accumulators are V-tile fragments as they stand.  Launches that
-// write far more than the L2s hold use streaming stores (see st_stream): with plain stores the output lines
+// write far more than the L2s hold use streaming stores (see st_out): with plain stores the output lines
 // evict the token panels the workgroups of an XCD share and the kernel runs at the speed of the re-fetches
 // (65 536 x 2048 x 512 stand-alone: 225 us plain, 152 us streaming, 205 us for the tiled kernel above); small
 // launches keep plain stores, because what they write fits the L2s and the attention and layer-tail kernels
@@ -591,7 +598,6 @@ struct F2LnParams {
   const uint16_t* gate_gain;
   const uint16_t* gate_offs;
   int n_prows, dh;
-  float qk_mul;             // stored q . k -> alpha <q, k>
   // softmax form (kernels instantiated with SM): part holds sums of exp2(t - m) v, ml the (m, l) of every row, head and
   // split as [split][row][head][2]; the splits and the candidate's own key are merged here
   const float* ml;
