@@ -129,7 +129,10 @@ inline void attn_row_tiles(const std::vector<UserDesc>& users, int tile_rows, st
 // and 300 candidates at d = 256: 4 pieces 255 us a call, 3 pieces 200; 40 of 1024 keys and 128 candidates at d = 512: 2 pieces
 // 690, uncut 636).  Only launches of less than kPieceRounds rounds are cut, as there is too little behind their long items to hide
 // them: each further piece of a row is an fp32 partial sum more for the layer tail to read, and so a piece has kMinPieceTiles key
-// tiles (a workgroup's own start and end cost about as much as six).
+// tiles (a workgroup's own start and end cost about as much as six).  Equal items of at most 32 rows are one wavefront's work each,
+// and three of a workgroup's four only help to move tiles: their chain is what the launch takes, and where two pieces each fit the
+// chip they are cut in two from kMinPieceTiles / 2 on (512 keys, us a call uncut and in two pieces of 4 tiles: 40 users of 32
+// candidates at d = 256 103 / 99.5, 30 at d = 512 and d_head 128 147 / 137; with 100 candidates, 20 users at d = 512 153 / 159).
 // Launches that leave more than half of the slots free are another matter: their pieces run by themselves, and the shorter
 // chain is worth more than the sums.  Where a call computes no prefix, its rows are cut into as many pieces as keep half of the
 // slots free, of no less than kFinePieceTiles.  (d = 512, one user, us a call in pieces of 8 / 4 / 2 / 1 tiles: 512 keys and 64
@@ -140,12 +143,13 @@ inline void attn_row_tiles(const std::vector<UserDesc>& users, int tile_rows, st
 constexpr int kMinPieceTiles = 8, kFinePieceTiles = 2, kMaxPieces = 8, kPieceRounds = 4, kMaxSlots = 512;
 // Pieces a cut list has at most: the launch has under kPieceRounds * kMaxSlots (row tile, head) pairs, each cut in at most kMaxPieces.
 inline int max_cut_items(int n_heads) { return kMaxPieces * kPieceRounds * kMaxSlots / n_heads; }
-inline int piece_tiles(int64_t items, int64_t total_key_tiles, int least_key_tiles, int most_key_tiles, int slots) {
+inline int piece_tiles(int64_t items, int64_t total_key_tiles, int least_key_tiles, int most_key_tiles, int most_rows, int slots) {
   if (items >= (int64_t)kPieceRounds * slots || items == 0) return std::max(1, most_key_tiles);
   auto into = [&](int64_t pieces) { pieces = std::max<int64_t>(1, std::min<int64_t>(pieces, kMaxPieces)); return (most_key_tiles + pieces - 1) / pieces; };
   const bool equal = 4 * (int64_t)least_key_tiles >= 3 * (int64_t)most_key_tiles;
   int64_t c = equal ? into(slots / items) : (total_key_tiles + slots - 1) / slots;
   c = std::max<int64_t>({c, kMinPieceTiles, into(kMaxPieces)});
+  if (equal && most_rows <= 32 && slots / items >= 2) c = std::min(c, std::max<int64_t>(kMinPieceTiles / 2, into(2)));
   return (int)std::max<int64_t>(1, std::min<int64_t>(c, most_key_tiles));
 }
 
@@ -190,13 +194,13 @@ inline int cut_pieces(const std::vector<AttnTile>& rows_new, const std::vector<A
 template <class Fits>
 inline void cut_attention(const std::vector<AttnTile>& rows_new, const std::vector<AttnTile>& rows_prefix, int heads, int dh, int tile_rows, int n_cus, AttnCut& c, Fits fits) {
   int64_t kt_new = 0, kt_prefix = 0;
-  int least_new = 1 << 30, most_new = 0, least_prefix = 1 << 30, most_prefix = 0;
-  for (const AttnTile& a : rows_new) { const int k = key_tiles(a); kt_new += k; least_new = std::min(least_new, k); most_new = std::max(most_new, k); }
+  int least_new = 1 << 30, most_new = 0, least_prefix = 1 << 30, most_prefix = 0, most_rows = 0;
+  for (const AttnTile& a : rows_new) { const int k = key_tiles(a); kt_new += k; least_new = std::min(least_new, k); most_new = std::max(most_new, k); most_rows = std::max(most_rows, a.nrows); }
   for (const AttnTile& a : rows_prefix) { const int k = key_tiles(a); kt_prefix += k; least_prefix = std::min(least_prefix, k); most_prefix = std::max(most_prefix, k); }
   const int slots = std::min(kMaxSlots, dh == 128 ? n_cus : 2 * n_cus);   // workgroups the chip takes at a time
   c.piece_all = piece_tiles((int64_t)(rows_new.size() + rows_prefix.size()) * heads, (kt_new + kt_prefix) * heads, std::min(least_new, least_prefix),
-                            std::max(most_new, most_prefix ? most_prefix + tile_rows / kTile : 0), slots);
-  c.piece_last = piece_tiles((int64_t)rows_new.size() * heads, kt_new * heads, least_new, most_new, slots);
+                            std::max(most_new, most_prefix ? most_prefix + tile_rows / kTile : 0), most_prefix ? tile_rows : most_rows, slots);
+  c.piece_last = piece_tiles((int64_t)rows_new.size() * heads, kt_new * heads, least_new, most_new, most_rows, slots);
   const bool one_list = rows_prefix.empty();       // the last layer's list is then the same: not sent twice
   if (one_list) c.fine = fine_pieces((int64_t)rows_new.size() * heads, slots);
   auto cut = [&]() {

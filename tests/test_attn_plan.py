@@ -56,6 +56,7 @@ def test_two_splits_share_a_workgroup_where_every_row_has_an_even_number(shim):
     ([2048] * 8, [16] * 8, [256] * 8, 2, 64, 5, 120), ([2048], [0], [512], 8, 128, 4, 16), ([2048], [0], [1024], 8, 64, 4, 32),
     # equal items are cut into no more pieces than the chip takes at a time (512 workgroups, 256 at d_head 128)
     ([4096] * 12, [0] * 12, [300] * 12, 4, 64, 3, 108), ([1024] * 40, [0] * 40, [128] * 40, 8, 64, 1, 40),
+    ([512] * 40, [0] * 40, [32] * 40, 4, 64, 2, 80), ([512] * 40, [0] * 40, [33] * 40, 4, 64, 1, 40), ([512] * 65, [0] * 65, [32] * 65, 4, 64, 1, 65),
     ([4096] * 10, [0] * 10, [300] * 10, 8, 64, 2, 60), ([2048] * 8, [0] * 8, [256] * 8, 8, 128, 2, 32),
 ])
 def test_pieces_of_equal_items_fit_the_chip_and_small_launches_are_cut_finer(shim, L, S, M, heads, dh, sums, items):
