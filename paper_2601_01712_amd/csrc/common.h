@@ -113,6 +113,13 @@ __host__ __device__ __forceinline__ size_t panel_off(int row, int k, int K) {
   return ((size_t)panel * (K >> 4) + ks) * 2048 + (size_t)rb * 512 + (g * 32 + l32) * 8 + j;
 }
 
+// Barrier for data that went through LDS only: unlike __syncthreads() it does not wait for global stores and loads in flight.
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 // (the address-space forms are for pointers that were themselves loaded from memory: the compiler cannot tell that those are
 // global addresses and would use flat stores, which also hold up the LDS counter)
@@ -137,6 +144,15 @@ __device__ __forceinline__ float wave_sum(float v) {
   v = dpp_add<0x124>(v);
   v = dpp_add<0x122>(v);
   return dpp_add<0x121>(v);
+}
+
+// Sum over the four lanes l, l ^ 16, l ^ 32, l ^ 48, in each of them.
+__device__ __forceinline__ float rows4_sum(float v) {
+  typedef unsigned int u2 __attribute__((ext_vector_type(2)));
+  u2 h = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(h[0]) + __uint_as_float(h[1]);
+  h = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(h[0]) + __uint_as_float(h[1]);
 }
 
 // Sum over each group of 2, 4, 8, 16 consecutive lanes, left in every lane of the group:

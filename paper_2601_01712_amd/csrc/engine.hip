@@ -318,8 +318,8 @@ extern "C" int relaygr_ctx_create(const relaygr_model_config* cfg, const relaygr
       int c1 = (int)(4 * d * d / 8), c2 = (int)(d * d / 8);
       hipLaunchKernelGGL(pack_weight_kernel, dim3((c1 + 255) / 256), dim3(256), 0, 0, (const uint16_t*)c->layers[l].w1,
                          (uint16_t*)w1p, (int)(4 * d), (int)d);
-      hipLaunchKernelGGL(pack_weight_kernel, dim3((c2 + 255) / 256), dim3(256), 0, 0, (const uint16_t*)c->layers[l].w2,
-                         (uint16_t*)w2p, (int)d, (int)d);
+      hipLaunchKernelGGL(pack_weight16_kernel, dim3((c2 + 255) / 256), dim3(256), 0, 0, (const uint16_t*)c->layers[l].w2,
+                         (uint16_t*)w2p, (int)d);
       c->w1_packed.push_back(w1p);
       c->w2_packed.push_back(w2p);
     }
@@ -943,7 +943,7 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
           fp.gate_gain = (const uint16_t*)lw.ln_at_g; fp.gate_offs = (const uint16_t*)lw.ln_at_b;
           fp.n_prows = p.n_prows; fp.dh = dh;
           fp.ml = softmax ? ml : nullptr; fp.ml_stride = (size_t)R * H * 2; fp.n_heads = H;
-          // two row blocks per workgroup halve the passes over W2 once that still leaves every
+          // four row blocks of 16 per workgroup halve the passes over W2 once that still leaves every
           // compute unit two workgroups
           const int rows = R - a0;
           const bool rb2 = d <= 512 && rows >= 64 * 384;
@@ -952,26 +952,29 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
           const bool vr8 = (d == 256 || d == 512) && rows <= kTailVr8MaxRows;
           const bool vr16 = (d == 256 || d == 512) && !vr8 && rows <= kTailVr16MaxRows;
           dim3 grid(vr8 ? (rows + 7) / 8 : vr16 ? (rows + 15) / 16 : (rows + (rb2 ? 63 : 31)) / (rb2 ? 64 : 32));
+          const bool few = p.nsplit <= 2;   // (every row has at most two partial sums)
           auto launch_tail = [&](auto sm) {
             constexpr bool SM = decltype(sm)::value;
             switch (d) {
               case 128:
-                if (rb2) hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 128, 4, 2, SM>), grid, dim3(256), 0, st, fp);
-                else hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 128, 4, 1, SM>), grid, dim3(256), 0, st, fp);
+                if (rb2) hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 128, 4, 4, SM>), grid, dim3(256), 0, st, fp);
+                else hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 128, 4, 2, SM>), grid, dim3(256), 0, st, fp);
                 break;
               case 256:
-                if (rb2) hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 256, 8, 2, SM>), grid, dim3(512), 0, st, fp);
-                else if (vr8) hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 256, 8, 1, SM, 1, 8>), grid, dim3(512), 0, st, fp);
-                else if (vr16) hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 256, 8, 1, SM, 1, 16>), grid, dim3(512), 0, st, fp);
-                else hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 256, 8, 1, SM>), grid, dim3(512), 0, st, fp);
+                if (rb2) hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 256, 8, 4, SM>), grid, dim3(512), 0, st, fp);
+                else if (vr8) hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 256, 8, 1, SM, 1, 8, 4, 8>), grid, dim3(512), 0, st, fp);
+                else if (vr16 && few) hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 256, 8, 1, SM, 1, 16, 4, 2>), grid, dim3(512), 0, st, fp);
+                else if (vr16) hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 256, 8, 1, SM, 1, 16, 4, 8>), grid, dim3(512), 0, st, fp);
+                else hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 256, 8, 2, SM>), grid, dim3(512), 0, st, fp);
                 break;
               case 512:
-                if (rb2) hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 512, 8, 2, SM, 2>), grid, dim3(512), 0, st, fp);
-                else if (vr8) hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 512, 8, 1, SM, 1, 8>), grid, dim3(512), 0, st, fp);
-                else if (vr16) hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 512, 8, 1, SM, 1, 16>), grid, dim3(512), 0, st, fp);
-                else hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 512, 8, 1, SM>), grid, dim3(512), 0, st, fp);
+                if (rb2) hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 512, 8, 4, SM, 2>), grid, dim3(512), 0, st, fp);
+                else if (vr8) hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 512, 8, 1, SM, 1, 8, 4, 8>), grid, dim3(512), 0, st, fp);
+                else if (vr16 && few) hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 512, 8, 1, SM, 1, 16, 4, 2>), grid, dim3(512), 0, st, fp);
+                else if (vr16) hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 512, 8, 1, SM, 1, 16, 4, 8>), grid, dim3(512), 0, st, fp);
+                else hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 512, 8, 2, SM>), grid, dim3(512), 0, st, fp);
                 break;
-              default: hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 1024, 8, 1, SM>), grid, dim3(512), 0, st, fp); break;
+              default: hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 1024, 8, 2, SM>), grid, dim3(512), 0, st, fp); break;
             }
           };
           if (softmax) launch_tail(std::true_type());

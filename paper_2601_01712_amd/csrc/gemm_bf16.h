@@ -39,6 +39,23 @@ __global__ void pack_weight_kernel(const uint16_t* __restrict__ w, uint16_t* __r
   *reinterpret_cast<uint4*>(packed + panel_off(n, kc * 8, K)) = v;
 }
 
+// Wavefronts of a layer-tail workgroup, and the 16-feature blocks of W2 that each of them multiplies by.
+constexpr int tail_waves(int d) { return d <= 128 ? 4 : 8; }
+constexpr int tail_blocks(int d) { return d / 16 / tail_waves(d); }
+
+// Re-packs a row-major [d, d] weight for the layer tail: 1 KiB fragments of 16 rows x 32 k in the 16x16x32 MFMA's operand order
+// (lane = ((k/8)%4)*16 + n%16), in the order in which a wavefront reads its tail_blocks(d) blocks: [wavefront][k/32][block][lane][8].
+// (With [block][k/32] the wavefronts of a workgroup were at the same few of an L2's channels at any time, at d = 512 every 16 KiB.)
+__global__ void pack_weight16_kernel(const uint16_t* __restrict__ w, uint16_t* __restrict__ packed, int d) {
+  int idx = blockIdx.x * blockDim.x + threadIdx.x;   // one 8-element chunk per thread
+  int chunks_per_row = d >> 3;
+  if (idx >= d * chunks_per_row) return;
+  int n = idx / chunks_per_row, kc = idx - n * chunks_per_row;
+  uint4 v = *reinterpret_cast<const uint4*>(w + (size_t)n * d + kc * 8);
+  const int fb = tail_blocks(d), blk = n >> 4;
+  *reinterpret_cast<uint4*>(packed + (((size_t)(blk / fb * (d >> 5) + (kc >> 2)) * fb + blk % fb) * 64 + (kc & 3) * 16 + (n & 15)) * 8) = v;
+}
+
 // ---- main loop ----------------------------------------------------------------------------------
 // Workgroup tile: 64*TM tokens x 64*TN features, 4 wavefronts as 2 x 2, each owning TM x TN blocks of
 // 32 x 32.  LDS holds a ring of NSTAGE stages of [token pieces | feature pieces], a piece being one
@@ -574,17 +591,22 @@ __global__ __launch_bounds__(512, 1) void f1_ws_bf16_kernel(F1Params p) {
 //   y  = LN((sum of key-split partial sums + a candidate's self term) / n; g_at, b_at) * u
 //   x <- x + y W2^T + b2
 //   xh = LN(x; next layer's g_in, b_in)
-// so one workgroup takes 32*RB rows over the full width D and does all three: y never goes to HBM,
+// so one workgroup takes up to 16*TB rows over the full width D and does all three: y never goes to HBM,
 // the residual row is read and written once, and two row-wise passes disappear.  Each wavefront
-// gates ROWS/NW rows (lane = D/64 consecutive features, DPP reductions) and writes them into LDS as
-// MFMA token fragments shared by all wavefronts; it owns D/32/NW feature blocks of the product and
-// streams its own slice of the packed W2 from L2 straight into registers (no wavefront shares
-// weights with another, so LDS would add nothing), PF k-steps ahead.  Feature-major product: a lane
-// ends up with one token and runs of 4 features, so the row statistics of the second LayerNorm are
-// a lane-local sum, one cross-half shuffle and one exchange between wavefronts through LDS.  Global
-// loads that depend on no result go out as early as the registers allow: the rows' split sums, u and
-// the residual rows before the first wait, the weight fragments once the split buffers are free, the
-// second LayerNorm's gain and offset before the product.
+// gates VROWS/NW rows (lane = D/64 consecutive features, DPP reductions) and writes them into LDS as
+// MFMA token fragments shared by all wavefronts; it owns FB = D/16/NW feature blocks of the product and
+// streams its own slice of the packed W2 (no wavefront shares weights with another) from L2 straight into registers, PF k-steps
+// ahead, and in small launches the first WL k-steps into LDS beside them.  The 16x16x32 product: a block of 16 rows is the smallest,
+// and launches of a few hundred rows take 8 or 16 rows per workgroup (the 32x32x16 one multiplied 24 empty rows beside 8).
+// Feature-major: a lane ends up with one token and runs of 4 features, so the row statistics of the second LayerNorm are
+// a lane-local sum, two lane exchanges and one exchange between wavefronts through LDS.
+// What bounds it: a chain of memory round trips.  A compute unit takes about 64 bytes a clock, and W2 is 512 KB of that for every
+// workgroup (d = 512), so global loads that depend on no result go out as early as the registers allow: the rows' split sums, W2's first
+// k-steps and the residual rows before the first wait; and every wait is for its own loads only, which takes loads the compiler can
+// count (none behind a branch, none in the global_load_lds form: see BufferView) and barriers that wait for LDS alone.
+// Of the launch's time from its first workgroup's start to its last one's end, at 512 rows of 8 pieces, d = 512: split sums summed after
+// 2.2 us, tokens written 2.7, first weights there 4.6, product 6.5, statistics 7.6, end 9.4; before (32x32x16, weights requested
+// behind the sums, two-pass statistics behind barriers that waited for the residual stores) 2.3, 3.2, 4.6, 7.4, 9.1, 10.5.
 struct F2LnParams {
   // gate inputs
   const float* part;        // [pieces][rows][D] unnormalised attention sums; rt.parts says how many a row has
@@ -677,34 +699,31 @@ struct GateLoad {
   float buf[NB][G][E];
   float2 mlb[NB][G];
 
+  // (NB pieces of every row without a condition, so that the compiler can count the loads and wait for these alone: a row with
+  // fewer pieces repeats its last one, a cache hit, which add() leaves out)
   __device__ __forceinline__ void issue(const F2LnParams& p, int sp0) {
 #pragma unroll
-    for (int k = 0; k < NB; ++k) {
-      if (sp0 + k >= cmax) break;      // uniform
+    for (int k = 0; k < NB; ++k)
 #pragma unroll
       for (int r = 0; r < G; ++r) {
-        const int sp = min(sp0 + k, cnt[r] - 1);   // a row with fewer pieces repeats its last one, which add() leaves out
+        const int sp = min(sp0 + k, cnt[r] - 1);
         ld_f32_run<E>(p.part + sp * p.split_stride + base[r], buf[k][r]);
         if constexpr (SM) mlb[k][r] = *reinterpret_cast<const float2*>(mlr[r] + sp * p.ml_stride);
       }
-    }
   }
   __device__ __forceinline__ void add(const F2LnParams& p, int sp0, GateRow<E, SM> (&gr)[G]) {
 #pragma unroll
-    for (int k = 0; k < NB; ++k) {
-      if (sp0 + k >= cmax) break;
+    for (int k = 0; k < NB; ++k)
 #pragma unroll
       for (int r = 0; r < G; ++r) {
-        if (sp0 + k >= cnt[r]) continue;
-        float w = 1.0f;
+        float w = sp0 + k < cnt[r] ? 1.0f : 0.0f;      // (a branch here, and the compiler would move the loads behind it)
         if constexpr (SM) {
-          w = (mlb[k][r].x == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mlb[k][r].x - M[r]);
+          w = (mlb[k][r].x == -INFINITY) ? 0.f : w * __builtin_amdgcn_exp2f(mlb[k][r].x - M[r]);
           gr[r].lpart += w * mlb[k][r].y;
         }
 #pragma unroll
-        for (int i = 0; i < E; ++i) gr[r].o[i] += w * buf[k][r][i];
+        for (int i = 0; i < E; ++i) gr[r].o[i] = fmaf(w, buf[k][r][i], gr[r].o[i]);
       }
-    }
   }
   __device__ __forceinline__ void begin(const F2LnParams& p, int row_first, int row_safe, int lane, GateRow<E, SM> (&gr)[G]) {
 #pragma unroll
@@ -745,19 +764,27 @@ struct GateLoad {
   }
   __device__ __forceinline__ void finish(const F2LnParams& p, GateRow<E, SM> (&gr)[G]) {
     add(p, 0, gr);
-    for (int sp0 = NB; sp0 < cmax; sp0 += NB) {
-      issue(p, sp0);
-      add(p, sp0, gr);
+    if constexpr (NB < kMaxPieces) {
+      for (int sp0 = NB; sp0 < cmax; sp0 += NB) {
+        issue(p, sp0);
+        add(p, sp0, gr);
+      }
     }
   }
 };
 
-// Finishes G rows at once (their reductions interleave) and writes y (bf16) into the token
-// fragments: local row lr0 + i of the workgroup goes to row block (lr0+i)/32, row (lr0+i)%32.
-template <typename H, int D, int G, bool SM, int FRAG>
+// Token fragments of the layer tail in LDS: blocks of 16 rows, in each the 16-byte chunk of row r and features 8c .. 8c+7 at
+// chunk c * 16 + (r ^ c) % 16.  The product's operand (lane: row lane % 16, chunk 4 k-step + lane / 16) is then four whole runs of
+// 256 bytes, and a row's chunks, which the gate's lanes write together, lie on different banks.
+template <int D>
+__device__ __forceinline__ int tok_off(int row, int c) { return ((row >> 4) * (D * 2) + c * 16 + ((row ^ c) & 15)) * 8; }
+
+// Finishes G rows at once (their reductions interleave) and writes y (16 bits) into the token fragments: rows lr0 .. lr0 + G - 1
+// of the workgroup.
+template <typename H, int D, int G, bool SM>
 __device__ __forceinline__ void finish_gate_rows(const F2LnParams& p, GateRow<D / 64, SM> (&gr)[G], int lane, uint16_t* tok, int lr0,
                                                  const uint32_t (&gw)[D / 128], const uint32_t (&ow)[D / 128]) {
-  constexpr int E = D / 64, KS = D / 16;
+  constexpr int E = D / 64;
   float s[G], inv_n[G];
 #pragma unroll
   for (int r = 0; r < G; ++r) {
@@ -812,15 +839,11 @@ __device__ __forceinline__ void finish_gate_rows(const F2LnParams& p, GateRow<D 
       if (gr[r].kind == kRowPad) { two[0] = 0.f; two[1] = 0.f; }
       yw[i] = H::pack2(two[0], two[1]);
     }
-    // feature f of a row block's local row rr sits at fragment f/16, lane (f/8 % 2)*32 + rr, element f%8
-    const int lr = lr0 + r;
-    uint16_t* tokb = tok + (lr >> 5) * KS * FRAG;
-    const int rr = lr & 31;
     constexpr int RUN = E < 8 ? E : 8;
 #pragma unroll
     for (int c = 0; c < E; c += RUN) {
       const int f = lane * E + c;
-      uint16_t* dst = tokb + (f >> 4) * FRAG + (((f >> 3) & 1) * 32 + rr) * 8 + (f & 7);
+      uint16_t* dst = tok + tok_off<D>(lr0 + r, f >> 3) + (f & 7);
       if constexpr (RUN == 2) *reinterpret_cast<uint32_t*>(dst) = yw[c / 2];
       else if constexpr (RUN == 4) *reinterpret_cast<uint2*>(dst) = make_uint2(yw[c / 2], yw[c / 2 + 1]);
       else *reinterpret_cast<uint4*>(dst) = make_uint4(yw[c / 2], yw[c / 2 + 1], yw[c / 2 + 2], yw[c / 2 + 3]);
@@ -854,36 +877,39 @@ __device__ __forceinline__ void l2_touch(const void* base, int lines, int share,
 // phase (memory) overlaps the other's product phase (L2 and matrix cores) when a launch has several
 // workgroups per unit: fewer k-steps and gate rows in flight, and the weight fragments and the
 // residual rows are requested after the gate instead of before it.
-// VR < 32: a workgroup takes only VR rows (a partly filled row block).  For launches of a few hundred to a
+// VR < 16 * TB: a workgroup takes only VR rows (a partly filled row block).  For launches of a few hundred to a
 // few thousand rows (one user per call): with 32 rows each they would occupy a few dozen compute units, each
 // pulling 16 KiB of split partial sums per row through its own memory path; with VR = 8 or 16 four times or
 // twice as many units share that.
-template <typename H, int D, int NW, int RB, bool SM, int OCC = 1, int VR = 32>
+// NB: pieces of each row's sums in flight: two where a wavefront has rows enough, all eight where it has one or two and the launch
+// has more than two pieces.
+// WL > 0: launches of at most one workgroup per compute unit.  The first WL k-steps of each wavefront's weights go straight to
+// LDS and the next PF into registers, all requested before the gate, which waits for other memory; the product then finds them there.
+template <typename H, int D, int NW, int TB, bool SM, int OCC = 1, int VR = 16 * TB, int WL = 0, int NB = D >= 1024 ? 1 : 2>
 __global__ __launch_bounds__(NW * 64, OCC == 2 ? 4 : 1) void f2_ln_bf16_kernel(F2LnParams p) {
-  constexpr int KS = D / 16;            // k-steps
-  constexpr int FB = D / 32 / NW;       // 32-feature blocks per wavefront
-  constexpr int PF = FB >= 4 ? 2 : (OCC == 2 ? 4 : 8);   // k-steps of weight fragments in flight per wavefront (16 spills: 38 % slower)
-  constexpr int ROWS = 32 * RB;         // rows per workgroup: RB blocks of 32 share one pass over W2
-  static_assert(FB >= 1 && FB * NW * 32 == D && KS % PF == 0, "shape");
-  static_assert(RB * KS * 1024 <= 65536, "token fragments fit static LDS");
-  // A row's 16-byte chunks go to the same place of consecutive fragments: with fragments exactly 1 KiB apart all
-  // 64 lanes of such a write would hit one bank, so fragments sit 16 bytes further apart where static LDS allows it
-  constexpr int FRAG = 512 + (RB == 1 ? 8 : 0);   // elements between token fragments
-  __shared__ __attribute__((aligned(16))) uint16_t tok[RB * KS * FRAG];   // ROWS tokens x D, fragment order
-  float* red = reinterpret_cast<float*>(tok);                             // reused after the product: [2][NW][ROWS]
-  static_assert(VR == 32 || (RB == 1 && OCC == 1 && VR % NW == 0 && VR < 32), "partly filled row blocks: one or two rows per wavefront");
-  constexpr int VROWS = VR < 32 ? VR : ROWS;   // rows this workgroup really has
+  constexpr int KS = D / 32;            // k-steps
+  constexpr int FB = D / 16 / NW;       // 16-feature blocks per wavefront
+  constexpr int PF = FB >= 8 ? 1 : (OCC == 2 ? 2 : 4);   // k-steps of weight fragments in flight per wavefront
+  constexpr int ROWS = 16 * TB;         // rows of the product: TB blocks of 16 share one pass over W2
+  static_assert(NW == tail_waves(D) && FB == tail_blocks(D) && FB * NW * 16 == D && (KS - WL) % PF == 0 && KS - WL >= PF, "shape");
+  __shared__ __attribute__((aligned(16))) uint16_t tok[ROWS * D];         // tok_off
+  __shared__ __attribute__((aligned(16))) uint16_t wlds[WL > 0 ? NW * WL * FB * 512 : 8];
+  // per wavefront: sums, squares and score parts of ROWS rows (where the weights fill the LDS, in the wavefront's own part of them)
+  constexpr int RED = WL > 0 ? WL * FB * 256 : 3 * ROWS;
+  static_assert(RED >= 3 * ROWS, "room for the rows' sums");
+  __shared__ float red_own[WL > 0 ? 1 : NW * RED];
+  float* red = WL > 0 ? reinterpret_cast<float*>(wlds) : red_own;
+  constexpr int VROWS = VR;             // rows this workgroup really has
+  static_assert(VROWS <= ROWS && VROWS % NW == 0, "whole rows per wavefront");
   const int row0 = p.row_begin + blockIdx.x * VROWS;
   if (row0 >= p.row_end) return;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, g = lane >> 5;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, q = lane >> 4;
 
-  // The gate makes the tokens: each wavefront takes ROWS/NW rows, a few at a time
+  // The gate makes the tokens: each wavefront takes VROWS/NW rows, a few at a time
   // so that their loads are in flight together.  The first group's loads go out before anything
   // else, since they are what the workgroup needs first.
-  constexpr int RPW = VROWS / NW, GMAX = OCC == 2 ? 2 : (RB * FB >= 4 ? (D >= 1024 ? 1 : 2) : (SM ? 2 : 4)), GROUP = RPW < GMAX ? RPW : GMAX;
+  constexpr int RPW = VROWS / NW, GMAX = OCC == 2 ? 2 : (D >= 1024 ? 1 : TB * FB >= 16 ? 2 : (SM ? 2 : 4)), GROUP = RPW < GMAX ? RPW : GMAX;
   static_assert(RPW >= 1 && RPW % GROUP == 0, "rows per wavefront");
-  // splits in flight per group of rows: what the registers allow (all 8 when a wavefront has one row)
-  constexpr int NB = VR < 32 ? (64 / (GROUP * (D / 64)) > 8 ? 8 : 64 / (GROUP * (D / 64))) : (D >= 1024 ? 1 : 2);
   GateRow<D / 64, SM> gr[GROUP];
   uint32_t gw[D / 128], ow[D / 128];
   GateLoad<D, SM, GROUP, NB> gl;
@@ -891,61 +917,80 @@ __global__ __launch_bounds__(NW * 64, OCC == 2 ? 4 : 1) void f2_ln_bf16_kernel(F
   ld_bf16_run<D / 64>(p.gate_gain + lane * (D / 64), gw);
   ld_bf16_run<D / 64>(p.gate_offs + lane * (D / 64), ow);
 
-  // L2 warm-up of W2 (every workgroup streams all of it, in step): the workgroups of an XCD (every
-  // eighth one) each ask for a slice now, so that the product phase below finds W2 in L2
-  const int wgs_per_xcd = (int)gridDim.x >> 3;
-  const int n_slices = wgs_per_xcd < 1 ? 1 : (wgs_per_xcd < 16 ? wgs_per_xcd : 16);
-  int touched[4];
-  l2_touch<4>(p.W, D * D / 64, ((int)blockIdx.x >> 3) % n_slices, n_slices, (int)threadIdx.x, NW * 64, touched);
-
-  // this wavefront's weight fragments: feature block fb lives in panel fb/4, row block fb%4
-  const uint16_t* wbase[FB];
-#pragma unroll
-  for (int j = 0; j < FB; ++j) {
-    const int fb = wave * FB + j;
-    wbase[j] = p.W + (size_t)(fb >> 2) * KS * 2048 + (fb & 3) * 512 + lane * 8;
-  }
+  // this wavefront's weight fragments: feature blocks wave*FB .. +FB-1, each KS fragments of 1 KiB
+  const BufferView w2(p.W, D * D * 2);
+  auto w_off = [&](int j, int ks) { return ((wave * KS + (ks & (KS - 1))) * FB + j) * 1024; };
+  static_assert((KS & (KS - 1)) == 0, "k-steps: a power of two");
   // the workgroups of an XCD walk the k-steps from different starting points, so that at any moment
   // they ask the XCD's L2 for different slices of W2 instead of all for the same one
   // (the sum over k then runs in a different order per block; for prefix rows the starting point is
   // taken from the block's position inside its user's prefix, not from the block index, so that a user's
   // place in the batch does not enter the K/V that a pre-inference leaves in the pool)
-  static_assert((KS & (KS - 1)) == 0, "k-steps: a power of two");
-  const int blk_id = row0 < p.n_prows ? p.rt.idx[row0] / ROWS : (int)blockIdx.x;
+  const int blk_id = row0 >= p.n_prows ? (int)blockIdx.x : WL > 0 ? (row0 & (kPrefixRowAlign - 1)) / VROWS : p.rt.idx[row0] / VROWS;
   const int rot = ((blk_id >> 3) * PF) & (KS - 1);
+  if constexpr (WL > 0) {
+#pragma unroll
+    for (int i = 0; i < WL; ++i)
+#pragma unroll
+      for (int j = 0; j < FB; ++j)
+        w2.load_lds(wlds + ((wave * WL + i) * FB + j) * 512, lane * 16, w_off(j, PF + i + rot));
+  }
+
+  // L2 warm-up of W2 (every workgroup streams all of it, in step): the workgroups of an XCD (every
+  // eighth one) each ask for a slice now, so that the product phase below finds W2 in L2
+  int touched[4] = {0, 0, 0, 0};
+  if constexpr (WL == 0) {
+    const int wgs_per_xcd = (int)gridDim.x >> 3;
+    const int n_slices = wgs_per_xcd < 1 ? 1 : (wgs_per_xcd < 16 ? wgs_per_xcd : 16);
+    l2_touch<4>(p.W, D * D / 64, ((int)blockIdx.x >> 3) % n_slices, n_slices, (int)threadIdx.x, NW * 64, touched);
+  }
+
   uint4 wf[PF][FB];
   auto prefetch_w = [&]() {
 #pragma unroll
     for (int i = 0; i < PF; ++i)
 #pragma unroll
-      for (int j = 0; j < FB; ++j) wf[i][j] = *reinterpret_cast<const uint4*>(wbase[j] + (size_t)((i + rot) & (KS - 1)) * 2048);
+      for (int j = 0; j < FB; ++j) wf[i][j] = w2.load(lane * 16, w_off(j, i + rot));
   };
   // The accumulators start from the residual row plus the bias, fetched now so that the gate and
   // the product hide the latency (the row's kind is only needed when results are stored): element
-  // e of acc[b][j] is feature (wave*FB + j)*32 + 8*(e/4) + 4*g + e%4 of token row0 + 32*b + l32.
-  bool in_range[RB], live[RB];
-  float* xrow[RB];
-  int kind_ep[RB];
-  f32x16_t acc[RB][FB];
-  auto init_acc = [&]() {
+  // r of acc[b][j] is feature (wave*FB + j)*16 + 4*q + r of token row0 + 16*b + l16.
+  bool in_range[TB], live[TB];
+  float* const x0 = p.x + (size_t)row0 * D;
+  auto x_off = [&](int b) { return in_range[b] ? (16 * b + l16) * D : 0; };
+  int kind_ep[TB];
+  f32x4_t acc[TB][FB];
+  uint2 b2[FB];
+  auto load_residual = [&]() {
 #pragma unroll
-    for (int b = 0; b < RB; ++b) {
-      const int row = row0 + 32 * b + l32;
-      in_range[b] = row < p.row_end && 32 * b + l32 < VROWS;
+    for (int b = 0; b < TB; ++b) {
+      const int row = row0 + 16 * b + l16;
+      in_range[b] = row < p.row_end && 16 * b + l16 < VROWS;
       kind_ep[b] = p.rt.kind[in_range[b] ? row : row0];
-      xrow[b] = p.x + (size_t)(in_range[b] ? row : row0) * D;
 #pragma unroll
-      for (int j = 0; j < FB; ++j)
+      for (int j = 0; j < FB; ++j) acc[b][j] = *reinterpret_cast<const f32x4_t*>(x0 + x_off(b) + (wave * FB + j) * 16 + 4 * q);
+    }
 #pragma unroll
-        for (int e4 = 0; e4 < 4; ++e4) {
-          const int c = (wave * FB + j) * 32 + 8 * e4 + 4 * g;
-          const uint2 bb = *reinterpret_cast<const uint2*>(p.bias + c);
-          const float4 v = *reinterpret_cast<const float4*>(xrow[b] + c);
-          acc[b][j][4 * e4] = v.x + H::to_f32(bb.x & 0xFFFF);
-          acc[b][j][4 * e4 + 1] = v.y + H::to_f32(bb.x >> 16);
-          acc[b][j][4 * e4 + 2] = v.z + H::to_f32(bb.y & 0xFFFF);
-          acc[b][j][4 * e4 + 3] = v.w + H::to_f32(bb.y >> 16);
-        }
+    for (int j = 0; j < FB; ++j) b2[j] = *reinterpret_cast<const uint2*>(p.bias + (wave * FB + j) * 16 + 4 * q);
+  };
+  auto add_bias = [&]() {
+#pragma unroll
+    for (int j = 0; j < FB; ++j) {
+      const f32x4_t bv = {H::to_f32(b2[j].x & 0xFFFF), H::to_f32(b2[j].x >> 16), H::to_f32(b2[j].y & 0xFFFF), H::to_f32(b2[j].y >> 16)};
+#pragma unroll
+      for (int b = 0; b < TB; ++b) acc[b][j] += bv;
+    }
+  };
+  // gain and offset of the LayerNorm that follows the product: requested early where the registers allow it,
+  // so that the output pass does not wait for them
+  constexpr bool EARLY_LN = OCC == 1 && FB <= 4;
+  uint2 lng[FB], lno[FB];
+  auto load_ln = [&]() {
+#pragma unroll
+    for (int j = 0; j < FB; ++j) {
+      const int c = (wave * FB + j) * 16 + 4 * q;
+      lng[j] = *reinterpret_cast<const uint2*>(p.gain + c);
+      lno[j] = *reinterpret_cast<const uint2*>(p.offs + c);
     }
   };
 
@@ -953,160 +998,149 @@ __global__ __launch_bounds__(NW * 64, OCC == 2 ? 4 : 1) void f2_ln_bf16_kernel(F
   // split buffers are free; then the first rows are reduced and written as token fragments, and
   // further groups of rows follow.
   constexpr bool EARLY_W = OCC == 1 && !SM && D < 1024;      // elsewhere the registers do not allow it
-  if constexpr (EARLY_W) init_acc();
+  constexpr bool W_FIRST = EARLY_W && WL > 0 && GROUP == 1;  // (with a single row's sums in flight there is room for the weights too)
+  constexpr bool LN_FIRST = EARLY_LN && WL > 0 && KS == PF + WL;
+  if constexpr (W_FIRST) prefetch_w();
+  if constexpr (EARLY_W) load_residual();
+  if constexpr (LN_FIRST) load_ln();
   gl.finish(p, gr);
-  if constexpr (EARLY_W) prefetch_w();                       // in flight while the rows are normalised and written to LDS
-  finish_gate_rows<H, D, GROUP, SM, FRAG>(p, gr, lane, tok, wave * RPW, gw, ow);
+  if constexpr (EARLY_W && !W_FIRST) prefetch_w();           // in flight while the rows are normalised and written to LDS
+  finish_gate_rows<H, D, GROUP, SM>(p, gr, lane, tok, wave * RPW, gw, ow);
 #pragma unroll
   for (int r0 = GROUP; r0 < RPW; r0 += GROUP) {
     gl.begin(p, row0 + wave * RPW + r0, row0, lane, gr);
     gl.finish(p, gr);
-    finish_gate_rows<H, D, GROUP, SM, FRAG>(p, gr, lane, tok, wave * RPW + r0, gw, ow);
+    finish_gate_rows<H, D, GROUP, SM>(p, gr, lane, tok, wave * RPW + r0, gw, ow);
   }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
+  if constexpr (WL > 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // this wavefront's weights are in LDS
+  lds_barrier();
   if ((touched[0] ^ touched[1] ^ touched[2] ^ touched[3]) == 0x5a17c0de && p.eps < 0.f) red[0] = 0.f;   // never taken: keeps the warm-up loads
-  if constexpr (!EARLY_W) { prefetch_w(); init_acc(); }
-
-  // gain and offset of the LayerNorm that follows the product: requested now where the registers allow it,
-  // so that the output pass does not wait for them
-  constexpr bool EARLY_LN = OCC == 1 && FB <= 2;
-  uint2 lng[FB][4], lno[FB][4];
-  if constexpr (EARLY_LN) {
+  if constexpr (!EARLY_W) { prefetch_w(); load_residual(); }
+  __builtin_amdgcn_sched_barrier(0);                         // (the residual rows are not waited for before this)
+  add_bias();
+  if constexpr (EARLY_LN && WL == 0) load_ln();
+  auto multiply = [&](int ks, const uint4 (&w)[FB]) {
+    const uint16_t* tk = &tok[tok_off<D>(l16, 4 * ks + q)];      // (the same chunk of every block of 16 rows)
 #pragma unroll
-    for (int j = 0; j < FB; ++j)
+    for (int b = 0; b < TB; ++b) {
+      const uint4 tf = *reinterpret_cast<const uint4*>(tk + b * (16 * D));
 #pragma unroll
-      for (int e4 = 0; e4 < 4; ++e4) {
-        const int c = (wave * FB + j) * 32 + 8 * e4 + 4 * g;
-        lng[j][e4] = *reinterpret_cast<const uint2*>(p.gain + c);
-        lno[j][e4] = *reinterpret_cast<const uint2*>(p.offs + c);
-      }
-  }
+      for (int j = 0; j < FB; ++j) acc[b][j] = H::mfma16(w[j], tf, acc[b][j]);
+    }
+  };
   // (the last PF k-steps apart from the loop, so that the loads in it are unconditional: see f1_ws_mainloop)
-  auto k_steps = [&](auto more_tag, int ks0) {
+  auto k_steps = [&](auto more_tag, int ks0, int next) {
     constexpr bool MORE = decltype(more_tag)::value;
 #pragma unroll
     for (int i = 0; i < PF; ++i) {
       const int ks = (ks0 + i + rot) & (KS - 1);
-      uint4 tf[RB];
-#pragma unroll
-      for (int b = 0; b < RB; ++b) tf[b] = *reinterpret_cast<const uint4*>(&tok[(b * KS + ks) * FRAG + lane * 8]);
-#pragma unroll
-      for (int j = 0; j < FB; ++j)
-#pragma unroll
-        for (int b = 0; b < RB; ++b) acc[b][j] = H::mfma(wf[i][j], tf[b], acc[b][j]);
+      multiply(ks, wf[i]);
       if constexpr (MORE) {
 #pragma unroll
-        for (int j = 0; j < FB; ++j) wf[i][j] = *reinterpret_cast<const uint4*>(wbase[j] + (size_t)((ks + PF) & (KS - 1)) * 2048);
+        for (int j = 0; j < FB; ++j) wf[i][j] = w2.load(lane * 16, w_off(j, ks + next));
       }
     }
   };
+  int ks0 = 0;
+  if constexpr (WL > 0) {      // the k-steps in registers, which then take the first ones behind those in LDS, and while these come, the ones in LDS
+    k_steps(std::integral_constant<bool, (KS > PF + WL)>(), 0, PF + WL);
+#pragma unroll
+    for (int i = 0; i < WL; ++i) {
+      uint4 wv[FB];
+#pragma unroll
+      for (int j = 0; j < FB; ++j) wv[j] = *reinterpret_cast<const uint4*>(wlds + ((wave * WL + i) * FB + j) * 512 + lane * 8);
+      multiply((PF + i + rot) & (KS - 1), wv);
+    }
+    ks0 = PF + WL;
+    if constexpr (EARLY_LN && !LN_FIRST) load_ln();
+  }
+  if constexpr (KS > (WL > 0 ? PF + WL : 0)) {
 #pragma unroll 1
-  for (int ks0 = 0; ks0 < KS - PF; ks0 += PF) k_steps(std::true_type(), ks0);
-  k_steps(std::false_type(), KS - PF);
+    for (; ks0 < KS - PF; ks0 += PF) k_steps(std::true_type(), ks0, PF);
+    k_steps(std::false_type(), KS - PF, PF);
+  }
 
   // the new residual rows go back; their sums start the LayerNorm statistics
   const bool want_score = p.scores != nullptr;
-  float s1[RB];
+  float s1[TB];
 #pragma unroll
-  for (int b = 0; b < RB; ++b) {
+  for (int b = 0; b < TB; ++b) {
     live[b] = in_range[b] && kind_ep[b] != kRowPad;
     s1[b] = 0.f;
 #pragma unroll
-    for (int j = 0; j < FB; ++j)
-#pragma unroll
-      for (int e4 = 0; e4 < 4; ++e4) {
-        const int c = (wave * FB + j) * 32 + 8 * e4 + 4 * g;
-        const float4 v = make_float4(acc[b][j][4 * e4], acc[b][j][4 * e4 + 1], acc[b][j][4 * e4 + 2], acc[b][j][4 * e4 + 3]);
-        if (live[b] && !want_score) *reinterpret_cast<float4*>(xrow[b] + c) = v;   // nothing reads x after the score head
-        s1[b] += (v.x + v.y) + (v.z + v.w);
-      }
+    for (int j = 0; j < FB; ++j) {
+      const f32x4_t v = acc[b][j];
+      if (live[b] && !want_score) *reinterpret_cast<f32x4_t*>(x0 + x_off(b) + (wave * FB + j) * 16 + 4 * q) = v;   // nothing reads x after the score head
+      s1[b] += (v[0] + v[1]) + (v[2] + v[3]);
+    }
   }
   if (p.xh == nullptr && !want_score) return;          // uniform over the grid
 
-  // LayerNorm of the new residual rows: two passes over the registers, sums exchanged through LDS
-  __syncthreads();                      // every wavefront is done reading tok
+  // LayerNorm of the new residual rows.  Every wavefront has the sum and the squares around its own mean of its FB * 16 features; one
+  // exchange through LDS makes them the row's: squares around the row's mean are those around the parts' means plus the parts'
+  // distances.  (Barriers that leave the residual rows' stores in flight: __syncthreads() would wait for them.)
+  constexpr float kOwn = FB * 16;
+  float* mine = red + wave * RED;
 #pragma unroll
-  for (int b = 0; b < RB; ++b) {
-    s1[b] += __shfl_xor(s1[b], 32, 64);
-    if (g == 0) red[wave * ROWS + 32 * b + l32] = s1[b];
-  }
-  __syncthreads();
-  float mean[RB], s2[RB];
-#pragma unroll
-  for (int b = 0; b < RB; ++b) {
-    mean[b] = 0.f;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) mean[b] += red[w * ROWS + 32 * b + l32];
-    mean[b] *= 1.0f / (float)D;
-    s2[b] = 0.f;
+  for (int b = 0; b < TB; ++b) {
+    s1[b] = rows4_sum(s1[b]);
+    const float m = s1[b] * (1.0f / kOwn);
+    float s2 = 0.f;
 #pragma unroll
     for (int j = 0; j < FB; ++j)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) { const float c = acc[b][j][e] - mean[b]; s2[b] += c * c; }
-    s2[b] += __shfl_xor(s2[b], 32, 64);
-    if (g == 0) red[(NW + wave) * ROWS + 32 * b + l32] = s2[b];
+      for (int e = 0; e < 4; ++e) { const float c = acc[b][j][e] - m; s2 += c * c; }
+    s2 = rows4_sum(s2);
+    if (q == 0) { mine[16 * b + l16] = s1[b]; mine[ROWS + 16 * b + l16] = s2; }
   }
-  __syncthreads();
-  float score_part[RB];
+  lds_barrier();
+  const uint16_t* gain = p.gain + wave * FB * 16 + 4 * q;
+  const uint16_t* offs = p.offs + wave * FB * 16 + 4 * q;
 #pragma unroll
-  for (int b = 0; b < RB; ++b) {
-    float var = 0.f;
+  for (int b = 0; b < TB; ++b) {
+    float ps[NW], mean = 0.f, var = 0.f;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) var += red[(NW + w) * ROWS + 32 * b + l32];
+    for (int w = 0; w < NW; ++w) { ps[w] = red[w * RED + 16 * b + l16]; mean += ps[w]; }
+    mean *= 1.0f / (float)D;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) { const float c = ps[w] * (1.0f / kOwn) - mean; var += red[w * RED + ROWS + 16 * b + l16] + kOwn * c * c; }
     const float rstd = rsqrtf(var * (1.0f / (float)D) + p.eps);
-    if (want_score) {       // uniform over the grid: the score head's dot product, reduced like the statistics below
-      float sc = 0.f;
+    float sc = 0.f;
+    // the row's place in the panels: its 16-byte chunk of features 16 j + 8 (q / 2), 4 features each for two lanes
+    uint16_t* out = p.xh + (in_range[b] ? panel_off(row0 + 16 * b + l16, wave * FB * 16 + 4 * q, D) : 0);
 #pragma unroll
-      for (int j = 0; j < FB; ++j)
-#pragma unroll
-        for (int e4 = 0; e4 < 4; ++e4) {
-          const int c = (wave * FB + j) * 32 + 8 * e4 + 4 * g;
-          const uint2 gg = EARLY_LN ? lng[j][e4] : *reinterpret_cast<const uint2*>(p.gain + c);
-          const uint2 oo = EARLY_LN ? lno[j][e4] : *reinterpret_cast<const uint2*>(p.offs + c);
-          const uint2 ww = *reinterpret_cast<const uint2*>(p.w_score + c);
-          sc += ((acc[b][j][4 * e4] - mean[b]) * rstd * H::to_f32(gg.x & 0xFFFF) + H::to_f32(oo.x & 0xFFFF)) * H::to_f32(ww.x & 0xFFFF);
-          sc += ((acc[b][j][4 * e4 + 1] - mean[b]) * rstd * H::to_f32(gg.x >> 16) + H::to_f32(oo.x >> 16)) * H::to_f32(ww.x >> 16);
-          sc += ((acc[b][j][4 * e4 + 2] - mean[b]) * rstd * H::to_f32(gg.y & 0xFFFF) + H::to_f32(oo.y & 0xFFFF)) * H::to_f32(ww.y & 0xFFFF);
-          sc += ((acc[b][j][4 * e4 + 3] - mean[b]) * rstd * H::to_f32(gg.y >> 16) + H::to_f32(oo.y >> 16)) * H::to_f32(ww.y >> 16);
-        }
-      score_part[b] = sc + __shfl_xor(sc, 32, 64);
-      continue;
-    }
-    if (!in_range[b]) continue;
-    const int row = row0 + 32 * b + l32;
-#pragma unroll
-    for (int j = 0; j < FB; ++j)
-#pragma unroll
-      for (int e4 = 0; e4 < 4; ++e4) {
-        const int c = (wave * FB + j) * 32 + 8 * e4 + 4 * g;
-        const uint2 gg = EARLY_LN ? lng[j][e4] : *reinterpret_cast<const uint2*>(p.gain + c);
-        const uint2 oo = EARLY_LN ? lno[j][e4] : *reinterpret_cast<const uint2*>(p.offs + c);
-        float z0 = (acc[b][j][4 * e4] - mean[b]) * rstd * H::to_f32(gg.x & 0xFFFF) + H::to_f32(oo.x & 0xFFFF);
-        float z1 = (acc[b][j][4 * e4 + 1] - mean[b]) * rstd * H::to_f32(gg.x >> 16) + H::to_f32(oo.x >> 16);
-        float z2 = (acc[b][j][4 * e4 + 2] - mean[b]) * rstd * H::to_f32(gg.y & 0xFFFF) + H::to_f32(oo.y & 0xFFFF);
-        float z3 = (acc[b][j][4 * e4 + 3] - mean[b]) * rstd * H::to_f32(gg.y >> 16) + H::to_f32(oo.y >> 16);
+    for (int j = 0; j < FB; ++j) {
+      const uint2 gg = EARLY_LN ? lng[j] : *reinterpret_cast<const uint2*>(gain + j * 16);
+      const uint2 oo = EARLY_LN ? lno[j] : *reinterpret_cast<const uint2*>(offs + j * 16);
+      float z0 = (acc[b][j][0] - mean) * rstd * H::to_f32(gg.x & 0xFFFF) + H::to_f32(oo.x & 0xFFFF);
+      float z1 = (acc[b][j][1] - mean) * rstd * H::to_f32(gg.x >> 16) + H::to_f32(oo.x >> 16);
+      float z2 = (acc[b][j][2] - mean) * rstd * H::to_f32(gg.y & 0xFFFF) + H::to_f32(oo.y & 0xFFFF);
+      float z3 = (acc[b][j][3] - mean) * rstd * H::to_f32(gg.y >> 16) + H::to_f32(oo.y >> 16);
+      if (want_score) {       // uniform over the grid: the score head's dot product, reduced like the statistics above
+        const uint2 ww = *reinterpret_cast<const uint2*>(p.w_score + (wave * FB + j) * 16 + 4 * q);
+        sc += z0 * H::to_f32(ww.x & 0xFFFF);
+        sc += z1 * H::to_f32(ww.x >> 16);
+        sc += z2 * H::to_f32(ww.y & 0xFFFF);
+        sc += z3 * H::to_f32(ww.y >> 16);
+      } else if (in_range[b]) {
         if (!live[b]) z0 = z1 = z2 = z3 = 0.f;     // filler rows stay finite
-        f32x2_t lo = {z0, z1}, hi = {z2, z3};
-        uint2 out;
-        out.x = H::pack2(lo[0], lo[1]);
-        out.y = H::pack2(hi[0], hi[1]);
-        *reinterpret_cast<uint2*>(p.xh + panel_off(row, c, D)) = out;
+        *reinterpret_cast<uint2*>(out + j * 2048) = make_uint2(H::pack2(z0, z1), H::pack2(z2, z3));
       }
+    }
+    if (want_score) {
+      sc = rows4_sum(sc);
+      if (q == 0) mine[2 * ROWS + 16 * b + l16] = sc;
+    }
   }
   if (want_score) {
-    __syncthreads();                    // the variance sums have been read
+    lds_barrier();
+    if (wave == 0 && q == 0) {
 #pragma unroll
-    for (int b = 0; b < RB; ++b)
-      if (g == 0) red[wave * ROWS + 32 * b + l32] = score_part[b];
-    __syncthreads();
-    if (wave == 0 && g == 0) {
-#pragma unroll
-      for (int b = 0; b < RB; ++b) {
+      for (int b = 0; b < TB; ++b) {
         float total = p.b_score;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) total += red[w * ROWS + 32 * b + l32];
-        const int row = row0 + 32 * b + l32;
+        for (int w = 0; w < NW; ++w) total += red[w * RED + 2 * ROWS + 16 * b + l16];
+        const int row = row0 + 16 * b + l16;
         if (in_range[b] && kind_ep[b] == kRowCand) p.scores[p.rt.src[row]] = total;
       }
     }
