@@ -125,6 +125,10 @@ typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 // global addresses and would use flat stores, which also hold up the LDS counter)
 typedef __attribute__((address_space(1))) u32x4_t gu32x4_t;
 __device__ __forceinline__ gu32x4_t* as_global16(uint16_t* p) { return (gu32x4_t*)p; }
+// 16 bytes from LDS, as a vector and to be kept one: behind a direct load to LDS the compiler waits for ALL outstanding loads before it
+// reads LDS as a struct like uint4 (the reads become those of its members, which it takes for what the load may have written), so that
+// a ring of stages in flight is emptied at every step.
+__device__ __forceinline__ u32x4_t lds_read16(const uint16_t* p) { return *reinterpret_cast<const u32x4_t*>(p); }
 
 // Sum over the wavefront, in every lane, adding lane i to lane i ^ 32, then ^ 16, ^ 8, ^ 4, ^ 2, ^ 1, on the vector ALU: the
 // halves and the 16-lane rows change places (v_permlane32_swap, v_permlane16_swap), and inside a row a rotation by 8 is lane ^ 8, after

@@ -857,11 +857,22 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
         fp.users = d_users; fp.rt = rt; fp.d = d; fp.dh = dh; fp.n_prows = p.n_prows; fp.layer = l;
         fp.row_begin = r0; fp.row_end = r1; fp.n_mtiles = (r1 - r0 + 64 * kF1TM - 1) / (64 * kF1TM);
         fp.cm = cm; fp.q_mul = q_mul; fp.stream_out = (r1 - r0) >= kF1StreamMinRows ? 1 : 0;
-        // small tiles, deep pipeline, as long as they fit the chip at once (two a compute unit)
-        const int small = (r1 - r0 + 64 * kF1SmallTM - 1) / (64 * kF1SmallTM) * cm.nblk * (d / (64 * kF1TN));
-        if (small <= 2 * c->n_cus) {
-          fp.n_mtiles = (r1 - r0 + 64 * kF1SmallTM - 1) / (64 * kF1SmallTM);
-          hipLaunchKernelGGL((f1_gemm_bf16_kernel<HT, kF1SmallTM, kF1SmallStages>), dim3((small + 7) / 8 * 8), dim3(256), 0, st, fp);
+        // 64-token tiles as long as they fit the chip at once (see f1_stages)
+        const int mt64 = (r1 - r0 + 63) / 64, t64 = mt64 * cm.nblk * (d / 64), t128 = mt64 * cm.nblk * (d / 128);
+        if (t128 <= 2 * c->n_cus) {
+          fp.n_mtiles = mt64;
+          auto launch = [&](auto dim) {
+            constexpr int KT = decltype(dim)::value / kGemmKTile;
+            if (t64 <= c->n_cus) hipLaunchKernelGGL((f1_gemm_bf16_kernel<HT, 1, 1, f1_stages(1, KT), KT>), dim3((t64 + 7) / 8 * 8), dim3(256), 0, st, fp);
+            else if (t128 <= c->n_cus) hipLaunchKernelGGL((f1_gemm_bf16_kernel<HT, 1, 2, f1_stages(2, KT), KT>), dim3((t128 + 7) / 8 * 8), dim3(256), 0, st, fp);
+            else hipLaunchKernelGGL((f1_gemm_bf16_kernel<HT, 1, 2, (KT < 6 ? KT : 6), KT>), dim3((t128 + 7) / 8 * 8), dim3(256), 0, st, fp);
+          };
+          switch (d) {
+            case 128: launch(std::integral_constant<int, 128>()); break;
+            case 256: launch(std::integral_constant<int, 256>()); break;
+            case 512: launch(std::integral_constant<int, 512>()); break;
+            default: launch(std::integral_constant<int, 1024>()); break;
+          }
           return;
         }
         // then the weight-stationary kernel: one persistent workgroup per compute unit,
@@ -878,7 +889,7 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
           return;
         }
         int total = fp.n_mtiles * cm.nblk * (d / (64 * kF1TN));
-        hipLaunchKernelGGL((f1_gemm_bf16_kernel<HT, kF1TM, kF1Stages>), dim3((total + 7) / 8 * 8), dim3(256), 0, st, fp);
+        hipLaunchKernelGGL((f1_gemm_bf16_kernel<HT, kF1TM, kF1TN, kF1Stages, 0>), dim3((total + 7) / 8 * 8), dim3(256), 0, st, fp);
       }
     };
     if (last && p.n_prows) {

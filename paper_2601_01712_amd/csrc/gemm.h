@@ -17,7 +17,7 @@ typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
 // The two 16-bit storage types of the MFMA path (bf16: the benchmark's; fp16: the half precision the
 // paper mentions as lowering the rank stage, Section 4.2).  Kernels are written against this
 // interface: bit patterns in, fp32 out; pack2 rounds to nearest even; mfma is the 32x32x16 product
-// of two 8-element fragments, mfma16 the 16x16x32 one.
+// of two 8-element fragments (any 16-byte type), mfma16 the 16x16x32 one.
 struct Bf16 {
   using elem = __hip_bfloat16;
   static __device__ __forceinline__ float to_f32(uint16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
@@ -30,10 +30,12 @@ struct Bf16 {
   static __device__ __forceinline__ float dot2(uint32_t a, uint32_t b, float c) {
     return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, a), __builtin_bit_cast(bf16x2_t, b), c, false);
   }
-  static __device__ __forceinline__ f32x16_t mfma(uint4 a, uint4 b, f32x16_t c) {
+  template <typename A, typename B>
+  static __device__ __forceinline__ f32x16_t mfma(A a, B b, f32x16_t c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
   }
-  static __device__ __forceinline__ f32x4_t mfma16(uint4 a, uint4 b, f32x4_t c) {
+  template <typename A, typename B>
+  static __device__ __forceinline__ f32x4_t mfma16(A a, B b, f32x4_t c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
   }
 };
@@ -48,10 +50,12 @@ struct F16 {
   static __device__ __forceinline__ float dot2(uint32_t a, uint32_t b, float c) {
     return __builtin_amdgcn_fdot2(__builtin_bit_cast(f16x2_t, a), __builtin_bit_cast(f16x2_t, b), c, false);
   }
-  static __device__ __forceinline__ f32x16_t mfma(uint4 a, uint4 b, f32x16_t c) {
+  template <typename A, typename B>
+  static __device__ __forceinline__ f32x16_t mfma(A a, B b, f32x16_t c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, a), __builtin_bit_cast(f16x8_t, b), c, 0, 0, 0);
   }
-  static __device__ __forceinline__ f32x4_t mfma16(uint4 a, uint4 b, f32x4_t c) {
+  template <typename A, typename B>
+  static __device__ __forceinline__ f32x4_t mfma16(A a, B b, f32x4_t c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, a), __builtin_bit_cast(f16x8_t, b), c, 0, 0, 0);
   }
 };

@@ -70,82 +70,70 @@ struct GemmTile {
   static constexpr int LDS_ELEMS = NSTAGE * STAGE;
   static constexpr int LOADS_PER_WAVE = PIECES / 4;
   static_assert(PIECES % 4 == 0, "pieces are dealt evenly to the 4 wavefronts");
-  static_assert(TM == 1 || TM % 2 == 0, "a tile is half a 128-row panel or whole panels");
+  static_assert(TOK_PIECES % 4 == 0, "and a wavefront's n-th piece is the same operand's in all of them");
+  static_assert((TM == 1 || TM % 2 == 0) && (TN == 1 || TN % 2 == 0), "a tile is half a 128-row panel or whole panels");
+  // piece q of an operand of `blocks` 64-row blocks whose tile starts at row r0: byte offset from its first panel (K rows of 4 KiB per 16 k)
+  static __device__ __forceinline__ int piece_off(int blocks, int q, int r0, int KS) {
+    const int panel = blocks >= 2 ? q >> 3 : 0, ksl = blocks >= 2 ? (q >> 2) & 1 : q >> 1, rb = blocks >= 2 ? q & 3 : ((r0 >> 5) & 3) + (q & 1);
+    return (panel * KS + ksl) * 4096 + rb * 1024;
+  }
+  static __device__ __forceinline__ int frag(int blocks, int rb, int ksl) { return (blocks >= 2 ? ((rb >> 2) * 2 + ksl) * 4 + (rb & 3) : ksl * 2 + rb) * 512; }
 };
 
+// start() asks for the first stages; run() waits for them one by one.  What a kernel needs besides the operands it loads between
+// the two or before.  KT > 0: K is 32 * KT and the steps are unrolled, with the exact number of younger stages in each wait; KT <= NSTAGE:
+// the operands are asked for whole.  KT = 0: K is known at run time.
 // FEATURE_MAJOR: features are the MFMA row operand (lane = token column, 4-feature runs per lane).
-template <typename H, int TM, int TN, int NSTAGE, bool FEATURE_MAJOR>
-__device__ __forceinline__ void gemm_mainloop(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W, int K, int m0, int n0,
-                                              uint16_t* lds, f32x16_t (&acc)[TM][TN]) {
+template <typename H, int TM, int TN, int NSTAGE, int KT>
+struct GemmLoop {
   using G = GemmTile<TM, TN, NSTAGE>;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  const int KS = K >> 4;
-  // piece p of a stage: token pieces first, ordered [panel][ksl][rb]; then feature pieces [npanel][ksl][nb]
-  auto issue = [&](int kt, int slot) {
-    uint16_t* dst = lds + slot * G::STAGE;
-#pragma unroll
-    for (int p = wave; p < G::PIECES; p += 4) {
-      const uint16_t* src;
-      if (p < G::TOK_PIECES) {
-        if constexpr (TM >= 2) {     // whole 128-row panels: pieces ordered [panel][k-step][row block]
-          int panel = p >> 3, ksl = (p >> 2) & 1, rb = p & 3;
-          src = A + ((size_t)((m0 >> 7) + panel) * KS + (kt * 2 + ksl)) * 2048 + rb * 512;
-        } else {                     // a 64-row tile is half a panel (m0 is a multiple of 64): [k-step][row block]
-          int ksl = p >> 1, rb = ((m0 >> 5) & 3) + (p & 1);
-          src = A + ((size_t)(m0 >> 7) * KS + (kt * 2 + ksl)) * 2048 + rb * 512;
-        }
-      } else {
-        int q = p - G::TOK_PIECES;
-        int panel = q >> 3, ksl = (q >> 2) & 1, nb = q & 3;
-        src = W + ((size_t)((n0 >> 7) + panel) * KS + (kt * 2 + ksl)) * 2048 + nb * 512;
-      }
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + lane * 8),
-                                       (__attribute__((address_space(3))) void*)(dst + p * 512), 16, 0, 0);
-    }
-  };
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+  static constexpr bool WHOLE = KT > 0 && KT <= NSTAGE;
+  static constexpr int AHEAD = WHOLE ? KT : NSTAGE - 1;     // stages asked for before the first step
+  const char *a, *w;          // first panel of the tile's rows of each operand
+  uint16_t* lds;
+  int K, lane, wave, src[G::LOADS_PER_WAVE];
 
-  const int n_kt = K / kGemmKTile;
+  __device__ __forceinline__ GemmLoop(const uint16_t* A, const uint16_t* W, int K_, int m0, int n0, uint16_t* lds_)
+      : a(reinterpret_cast<const char*>(A + (size_t)(m0 >> 7) * (K_ >> 4) * 2048)),
+        w(reinterpret_cast<const char*>(W + (size_t)(n0 >> 7) * (K_ >> 4) * 2048)),
+        lds(lds_), K(K_), lane(threadIdx.x & 63), wave(__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) {
 #pragma unroll
-  for (int s = 0; s < NSTAGE - 1; ++s)
-    if (s < n_kt) issue(s, s);
-  int slot = 0;
-  for (int kt = 0; kt < n_kt; ++kt) {
-    // stage kt must have landed; the NSTAGE-2 younger stages may stay in flight (near the end fewer
-    // are outstanding, so wait for all of them there)
-    // (a bare s_barrier: __syncthreads() would also make the compiler wait for every outstanding load,
-    // i.e. for the stages that are meant to stay in flight)
-    if (kt + NSTAGE - 2 < n_kt) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NSTAGE - 2) * G::LOADS_PER_WAVE) : "memory");
-    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();   // also: every wavefront is past stage kt-1, whose slot is refilled next
-    asm volatile("" ::: "memory");
-    if (kt + NSTAGE - 1 < n_kt) issue(kt + NSTAGE - 1, slot == 0 ? NSTAGE - 1 : slot - 1);
+    for (int i = 0; i < G::LOADS_PER_WAVE; ++i) {
+      const int p = wave + 4 * i;
+      src[i] = 4 * i < G::TOK_PIECES ? G::piece_off(TM, p, m0, K >> 4) : G::piece_off(TN, p - G::TOK_PIECES, n0, K >> 4);
+    }
+  }
+  __device__ __forceinline__ void issue(int kt, int slot) {
+#pragma unroll
+    for (int i = 0; i < G::LOADS_PER_WAVE; ++i) {
+      // (scalar base and offset, one 32-bit offset per lane; not the buffer form, behind which the compiler waits for all stages
+      // wherever LDS is read)
+      const char* s = (4 * i < G::TOK_PIECES ? a : w) + (src[i] + kt * 8192);
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(s + (uint32_t)(lane * 16)),
+                                       (__attribute__((address_space(3))) void*)(lds + slot * G::STAGE + (wave + 4 * i) * 512), 16, 0, 0);
+    }
+  }
+  __device__ __forceinline__ void start() {
+#pragma unroll
+    for (int s = 0; s < AHEAD; ++s)
+      if (KT > 0 ? s < KT : s < K / kGemmKTile) issue(s, s);
+  }
+  template <bool FEATURE_MAJOR>
+  __device__ __forceinline__ void step(int slot, f32x16_t (&acc)[TM][TN]) {
+    const int wm = wave >> 1, wn = wave & 1;
     const uint16_t* tokp = lds + slot * G::STAGE + lane * 8;
     const uint16_t* featp = tokp + G::TOK_PIECES * 512;
     // fetch the fragments of both k-steps first, so that the second set's LDS latency hides under
     // the first set's MFMAs
-    uint4 tf[2][TM], ff[2][TN];
+    u32x4_t tf[2][TM], ff[2][TN];
 #pragma unroll
     for (int ksl = 0; ksl < 2; ++ksl) {
 #pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        int rbAll = wm * TM + i;   // 32-row block inside the workgroup tile
-        if constexpr (TM >= 2) tf[ksl][i] = *reinterpret_cast<const uint4*>(tokp + (((rbAll >> 2) * 2 + ksl) * 4 + (rbAll & 3)) * 512);
-        else tf[ksl][i] = *reinterpret_cast<const uint4*>(tokp + (ksl * 2 + rbAll) * 512);
-      }
+      for (int i = 0; i < TM; ++i) tf[ksl][i] = lds_read16(tokp + G::frag(TM, wm * TM + i, ksl));
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        int nbAll = wn * TN + j;
-        ff[ksl][j] = *reinterpret_cast<const uint4*>(featp + (((nbAll >> 2) * 2 + ksl) * 4 + (nbAll & 3)) * 512);
-      }
+      for (int j = 0; j < TN; ++j) ff[ksl][j] = lds_read16(featp + G::frag(TN, wn * TN + j, ksl));
     }
-    __builtin_amdgcn_sched_barrier(0);   // keep all twelve reads ahead of the MFMAs
+    __builtin_amdgcn_sched_barrier(0);   // keep all the reads ahead of the MFMAs
 #pragma unroll
     for (int ksl = 0; ksl < 2; ++ksl)
 #pragma unroll
@@ -153,10 +141,49 @@ __device__ __forceinline__ void gemm_mainloop(const uint16_t* __restrict__ A, co
 #pragma unroll
         for (int j = 0; j < TN; ++j)
           acc[i][j] = FEATURE_MAJOR ? H::mfma(ff[ksl][j], tf[ksl][i], acc[i][j]) : H::mfma(tf[ksl][i], ff[ksl][j], acc[i][j]);
-    slot = (slot == NSTAGE - 1) ? 0 : slot + 1;
   }
-  __syncthreads();   // every wavefront is done reading LDS: the epilogue may reuse it
-}
+  template <int YOUNGER>      // this stage must have landed, YOUNGER ones may stay in flight
+  __device__ __forceinline__ void wait() {
+    // (a bare s_barrier: __syncthreads() would also make the compiler wait for every outstanding load,
+    // i.e. for the stages that are meant to stay in flight)
+    // (and this wavefront's reads of the stage before are done: its slot is refilled next)
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(YOUNGER * G::LOADS_PER_WAVE) : "memory");
+    __builtin_amdgcn_s_barrier();   // so are every wavefront's
+    asm volatile("" ::: "memory");
+  }
+  template <bool FEATURE_MAJOR, int T>
+  __device__ __forceinline__ void steps(f32x16_t (&acc)[TM][TN]) {
+    if constexpr (T < KT) {
+      wait<(WHOLE || KT - 1 - T < NSTAGE - 2 ? KT - 1 - T : NSTAGE - 2)>();
+      if constexpr (!WHOLE && T + NSTAGE - 1 < KT) issue(T + NSTAGE - 1, (T + NSTAGE - 1) % NSTAGE);
+      step<FEATURE_MAJOR>(T % NSTAGE, acc);
+      steps<FEATURE_MAJOR, T + 1>(acc);
+    }
+  }
+  template <bool FEATURE_MAJOR>
+  __device__ __forceinline__ void run(f32x16_t (&acc)[TM][TN]) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    if constexpr (KT > 0) {
+      steps<FEATURE_MAJOR, 0>(acc);
+    } else {
+      const int n_kt = K / kGemmKTile;
+      int slot = 0;
+      for (int kt = 0; kt < n_kt; ++kt) {
+        if (kt + NSTAGE - 2 < n_kt) wait<NSTAGE - 2>();
+        else wait<0>();                 // near the end fewer are outstanding: wait for all of them
+        if (kt + NSTAGE - 1 < n_kt) issue(kt + NSTAGE - 1, slot == 0 ? NSTAGE - 1 : slot - 1);
+        step<FEATURE_MAJOR>(slot, acc);
+        slot = (slot == NSTAGE - 1) ? 0 : slot + 1;
+      }
+    }
+    lds_barrier();   // every wavefront is done reading LDS: the epilogue may reuse it
+  }
+};
 
 // ---- f1 -------------------------------------------------------------------------------------------
 struct F1Params {
@@ -187,60 +214,86 @@ __device__ __forceinline__ void st_out(uint16_t* dst, uint4 v, int stream) {
 }
 
 constexpr int kF1TM = 4, kF1TN = 2, kF1Stages = 3;   // 256 tokens x 128 features per workgroup
-constexpr int kStageLd = 64 * kF1TN + 8;          // epilogue staging row stride (elements)
-// Launches of a few hundred rows (one user's candidates): the big tile gives the chip a few dozen workgroups, each
-// waiting a memory round trip per k-step with two stages in flight.  The small tile (64 tokens) with six stages has
-// more than a third of K = 512 in flight per workgroup and four times the workgroups; six stages are 72 KiB of LDS, so
-// that a compute unit holds two such workgroups and a launch of up to 512 of them (2048 rows at d = 512) runs in one
-// round.  That is where its range ends: at d = 512 2048 rows take 12.9 us and 2112 rows 19.8 us, against 15.1 us for the
+// Launches of few rows take 64-token tiles and ask for as much of their operands at once as the LDS holds: what they take is the
+// round trips of the operand stream, 60 KiB in flight on a compute unit with six stages (0.29 us a step of 12 KiB) and up to 144 here.
+//   up to one 64 x 64 tile a compute unit     : 64 x 64, the whole of K up to d = 512 (128 KiB), else 18 stages
+//   up to one 64 x 128 tile a compute unit    : 64 x 128, the whole of K up to d = 256, else 12 stages
+//   up to two 64 x 128 tiles a compute unit   : 64 x 128, 6 stages (72 KiB), so that a unit holds two and the launch is one round
+// That is where their range ends: at d = 512 2048 rows take 12.9 us and 2112 rows 19.8 us, against 15.1 us for the
 // weight-stationary kernel below (d = 256: 4000 rows 9.4 against 11.0 us, 4100 rows 13.7 against 11.7 us; d = 1024, whose
 // alternative is the big tile: 1024 rows 22.1 against 29.0 us, 1500 rows 35.8 against 31.0 us).
-constexpr int kF1SmallTM = 1, kF1SmallStages = 6;
+constexpr int f1_stages(int tn, int kt) { return tn == 1 ? (kt <= 16 ? kt : 18) : (kt <= 8 ? kt : 12); }
 
-template <typename H, int TM, int NSTAGE>
+// KT: 32-wide steps of K, 0: known at run time (the big tile).
+template <typename H, int TM, int TN, int NSTAGE, int KT>
 __global__ __launch_bounds__(256, TM == 4 ? 2 : 1) void f1_gemm_bf16_kernel(F1Params p) {
-  constexpr int TN = kF1TN;
   constexpr int ROWS = 64 * TM;                  // tokens per workgroup tile
+  constexpr int kStageLd = 64 * TN + 8;          // epilogue staging row stride (elements)
   using G = GemmTile<TM, TN, NSTAGE>;
   constexpr int LDS_ELEMS = (G::LDS_ELEMS > ROWS * kStageLd) ? G::LDS_ELEMS : ROWS * kStageLd;
   __shared__ __attribute__((aligned(16))) uint16_t lds[LDS_ELEMS];
 
-  const int ntiles_per_blk = p.cm.d / G::BNf;
+  const int d = KT > 0 ? KT * kGemmKTile : p.d;
+  const int ntiles_per_blk = d / G::BNf;
   const int n_ntiles = p.cm.nblk * ntiles_per_blk;
   const int total = p.n_mtiles * n_ntiles;
   const int logical = xcd_remap(blockIdx.x, total);
   if (logical >= total) return;
-  const int mt = logical / n_ntiles, nt = logical - mt * n_ntiles;
+  // an XCD's workgroups take neighbouring tiles: of one row tile, or, where W1 is the larger operand, of one column tile, so that
+  // each XCD fetches its part of W1 and not all of it
+  const bool by_cols = TM == 1;
+  const int mt = by_cols ? logical % p.n_mtiles : logical / n_ntiles, nt = by_cols ? logical / p.n_mtiles : logical - mt * n_ntiles;
   const int m0 = p.row_begin + mt * G::BMt;
   const int blk = p.cm.blk[nt / ntiles_per_blk];           // 0 u, 1 v, 2 q, 3 k
   const int c0 = (nt % ntiles_per_blk) * G::BNf;            // first feature inside the block
-  const int n0 = blk * p.cm.d + c0;
+  const int n0 = blk * d + c0;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, g = lane >> 5;
-  const int d = p.d, dh = p.dh, dh_sh = 31 - __builtin_clz(dh);   // d_head is a power of two
-
+  const int dh = p.dh, dh_sh = 31 - __builtin_clz(dh);   // d_head is a power of two
   // A tile of prefix rows is one user's consecutive prefix positions starting at a multiple of 256
   // (row-space alignment), possibly followed by padding rows.
   const bool prefix_tile = m0 < p.n_prows;
   const int pos0 = prefix_tile ? p.rt.idx[m0] : 0;         // a multiple of 64
-  const UserDesc& tud = p.users[prefix_tile ? p.rt.user[m0] : 0];
-  const int L = tud.L, Lceil = (L + kTile - 1) / kTile * kTile;
-  if (prefix_tile && pos0 >= Lceil) return;                // filler behind the user's last K/V tile
-  uint16_t* kvb = reinterpret_cast<uint16_t*>(const_cast<void*>(tud.kv)) + tud.kv_tile0 + (int64_t)(pos0 >> 6) * tud.kv_tile_stride +
-                  (int64_t)p.layer * tud.kv_layer_stride;  // the K/V tile of the first 64 rows
-  const int64_t kv_stride = tud.kv_tile_stride;
+  const int tile_user = prefix_tile ? p.rt.user[m0] : 0;
+  if (prefix_tile && p.rt.kind[m0] == kRowPad) return;     // filler behind the user's last K/V tile
+
+  // In the store phase a thread owns 16-byte chunk tid % CH of rows tid / CH + RPP*it of the
+  // tile; the kinds of new rows (candidate or suffix) and the biases are asked for first, so that run()'s waits, which count younger loads, need not count them.
+  constexpr int CH = 8 * TN, RPP = 256 / CH, ITS = ROWS / RPP;   // chunks of a row, rows per pass of the store phase, passes
+  const bool by_kind = (blk == 1 || blk == 3) && !prefix_tile;
+  int kinds[ITS];
+#pragma unroll
+  for (int it = 0; it < ITS; ++it) kinds[it] = kRowCand;
+  if (by_kind) {
+#pragma unroll
+    for (int it = 0; it < ITS; ++it) kinds[it] = p.rt.kind[min(m0 + tid / CH + RPP * it, p.row_end - 1)];
+  }
+  uint2 bias[TN][4];
+#pragma unroll
+  for (int j = 0; j < TN; ++j)
+#pragma unroll
+    for (int e4 = 0; e4 < 4; ++e4) bias[j][e4] = *reinterpret_cast<const uint2*>(p.bias + n0 + wn * (32 * TN) + j * 32 + 8 * e4 + 4 * g);
+  asm volatile("" ::: "memory");
+  GemmLoop<H, TM, TN, NSTAGE, KT> loop(p.A, p.W, d, m0, n0, lds);
+  loop.start();                                             // before everything else that the tile needs
+
   f32x16_t acc[TM][TN];
 
   if (blk == 1 && prefix_tile) {
     // ---- V of prefix rows: token-major product; the accumulator of a 32-token x 32-feature block
     // is, lane for lane, two V-tile fragments (m = 0, 1), stored as 1 KiB contiguous runs.
-    gemm_mainloop<H, TM, TN, NSTAGE, false>(p.A, p.W, d, m0, n0, lds, acc);
+    loop.template run<false>(acc);
+    const UserDesc& tud = p.users[tile_user];               // (read here, not before the product: it is two more round trips)
+    const int L = tud.L, Lceil = (L + kTile - 1) / kTile * kTile;
+    const int64_t kv_stride = tud.kv_tile_stride;
+    uint16_t* kvb = reinterpret_cast<uint16_t*>(const_cast<void*>(tud.kv)) + tud.kv_tile0 + (int64_t)(pos0 >> 6) * kv_stride +
+                    (int64_t)p.layer * tud.kv_layer_stride;  // the K/V tile of the first 64 rows
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
-      const int c = c0 + wn * 64 + j * 32;                  // first feature of this 32-feature block
+      const int c = c0 + wn * (32 * TN) + j * 32;                  // first feature of this 32-feature block
       const int head = c >> dh_sh, db = (c - (head << dh_sh)) >> 5;
-      const float bias = H::to_f32(p.bias[n0 + wn * 64 + j * 32 + l32]);
+      const float bias = H::to_f32(p.bias[n0 + wn * (32 * TN) + j * 32 + l32]);
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
         const int tok0 = pos0 + wm * (32 * TM) + i * 32;    // first token of this 32-token block
@@ -272,29 +325,13 @@ __global__ __launch_bounds__(256, TM == 4 ? 2 : 1) void f1_gemm_bf16_kernel(F1Pa
 
   // ---- everything else: feature-major product, staged through LDS as [token][feature] so that
   // every global store is a 16-byte chunk of 8 consecutive features of one token.
-  // In the store phase a thread owns 16-byte chunk (tid & 15) of rows (tid >> 4) + 16*it of the
-  // tile; the kinds of new rows (candidate or suffix) are fetched now, and the biases, so that they arrive under the main loop.
-  constexpr int ITS = ROWS / 16;                 // 16 rows per pass of the store phase
-  const bool by_kind = (blk == 1 || blk == 3) && !prefix_tile;
-  int kinds[ITS];
-#pragma unroll
-  for (int it = 0; it < ITS; ++it) kinds[it] = kRowCand;
-  if (by_kind) {
-#pragma unroll
-    for (int it = 0; it < ITS; ++it) kinds[it] = p.rt.kind[min(m0 + (tid >> 4) + 16 * it, p.row_end - 1)];
-  }
-  uint2 bias[TN][4];
-#pragma unroll
-  for (int j = 0; j < TN; ++j)
-#pragma unroll
-    for (int e4 = 0; e4 < 4; ++e4) bias[j][e4] = *reinterpret_cast<const uint2*>(p.bias + n0 + wn * 64 + j * 32 + 8 * e4 + 4 * g);
-  gemm_mainloop<H, TM, TN, NSTAGE, true>(p.A, p.W, d, m0, n0, lds, acc);
+  loop.template run<true>(acc);
   const float mul = (blk == 2) ? p.q_mul : 1.0f;
 #pragma unroll
   for (int j = 0; j < TN; ++j)
 #pragma unroll
     for (int e4 = 0; e4 < 4; ++e4) {
-      const int f = wn * 64 + j * 32 + 8 * e4 + 4 * g;  // 4 consecutive features held by this lane
+      const int f = wn * (32 * TN) + j * 32 + 8 * e4 + 4 * g;  // 4 consecutive features held by this lane
       const uint2 bb = bias[j][e4];
       const float b0 = H::to_f32(bb.x & 0xFFFF), b1 = H::to_f32(bb.x >> 16);
       const float b2 = H::to_f32(bb.y & 0xFFFF), b3 = H::to_f32(bb.y >> 16);
@@ -307,24 +344,35 @@ __global__ __launch_bounds__(256, TM == 4 ? 2 : 1) void f1_gemm_bf16_kernel(F1Pa
         *reinterpret_cast<uint2*>(&lds[t * kStageLd + f]) = w;
       }
     }
-  __syncthreads();
-  // ROWS tokens x 16 chunks of 8 features
-  const int t0 = tid >> 4, fc = tid & 15, c = c0 + fc * 8;   // c: feature inside the block
+  lds_barrier();
+  // ROWS tokens x CH chunks of 8 features
+  const int t0 = tid / CH, fc = tid % CH, c = c0 + fc * 8;   // c: feature inside the block
   const int head = c >> dh_sh, f = c - (head << dh_sh);
   const int n_rows = p.row_end - m0;
   // (u and q of filler rows are written too: nothing reads them, and a filler row's inputs are zeros)
   uint16_t* rows_out = (blk == 0 ? p.u + (size_t)m0 * d : blk == 2 ? p.q + (size_t)m0 * d : (blk == 3 ? p.knew : p.vnew) + ((int64_t)m0 - p.n_prows) * d) + c;
+  if (blk == 3 && prefix_tile) {                             // K of prefix rows (V took the other path)
+    const UserDesc& tud = p.users[tile_user];               // (as above)
+    const int L = tud.L, Lceil = (L + kTile - 1) / kTile * kTile;
+    const int64_t kv_stride = tud.kv_tile_stride;
+    uint16_t* kvb = reinterpret_cast<uint16_t*>(const_cast<void*>(tud.kv)) + tud.kv_tile0 + (int64_t)(pos0 >> 6) * kv_stride +
+                    (int64_t)p.layer * tud.kv_layer_stride;  // the K/V tile of the first 64 rows
+#pragma unroll
+    for (int it = 0; it < ITS; ++it) {
+      const int t = t0 + RPP * it, pos = pos0 + t;
+      if (t >= n_rows || pos >= Lceil) continue;             // filler beyond the user's last tile
+      uint4 val = *reinterpret_cast<const uint4*>(&lds[t * kStageLd + fc * 8]);
+      if (pos >= L) val = make_uint4(0, 0, 0, 0);            // ragged tail of the last tile: zeros
+      st_out(kvb + (int64_t)(t >> 6) * kv_stride + head * 2 * kTile * dh + KvLayout16::k_off(t & 63, f, dh), val, 0);
+    }
+    return;
+  }
 #pragma unroll
   for (int it = 0; it < ITS; ++it) {
-    const int t = t0 + 16 * it;
+    const int t = t0 + RPP * it;
     if (t >= n_rows) continue;
-    uint4 val = *reinterpret_cast<const uint4*>(&lds[t * kStageLd + fc * 8]);
-    if (blk == 3 && prefix_tile) {                           // K of prefix rows (V took the other path)
-      const int pos = pos0 + t;
-      if (pos >= Lceil) continue;                            // filler beyond the user's last tile
-      if (pos >= L) val = make_uint4(0, 0, 0, 0);            // ragged tail of the last tile: zeros
-      st_out(kvb + (int64_t)(it >> 2) * kv_stride + head * 2 * kTile * dh + KvLayout16::k_off(t & 63, f, dh), val, 0);
-    } else if (kinds[it] == kRowCand) {
+    const uint4 val = *reinterpret_cast<const uint4*>(&lds[t * kStageLd + fc * 8]);
+    if (kinds[it] == kRowCand) {
       st_out(rows_out + (size_t)t * d, val, 0);
     } else {                                                 // k or v of a suffix row
       const int row = m0 + t, idx = p.rt.idx[row], rr = idx & 63;
@@ -1019,11 +1067,11 @@ __global__ __launch_bounds__(NW * 64, OCC == 2 ? 4 : 1) void f2_ln_bf16_kernel(F
   __builtin_amdgcn_sched_barrier(0);                         // (the residual rows are not waited for before this)
   add_bias();
   if constexpr (EARLY_LN && WL == 0) load_ln();
-  auto multiply = [&](int ks, const uint4 (&w)[FB]) {
+  auto multiply = [&](int ks, const auto& w) {
     const uint16_t* tk = &tok[tok_off<D>(l16, 4 * ks + q)];      // (the same chunk of every block of 16 rows)
 #pragma unroll
     for (int b = 0; b < TB; ++b) {
-      const uint4 tf = *reinterpret_cast<const uint4*>(tk + b * (16 * D));
+      const u32x4_t tf = lds_read16(tk + b * (16 * D));
 #pragma unroll
       for (int j = 0; j < FB; ++j) acc[b][j] = H::mfma16(w[j], tf, acc[b][j]);
     }
@@ -1046,9 +1094,9 @@ __global__ __launch_bounds__(NW * 64, OCC == 2 ? 4 : 1) void f2_ln_bf16_kernel(F
     k_steps(std::integral_constant<bool, (KS > PF + WL)>(), 0, PF + WL);
 #pragma unroll
     for (int i = 0; i < WL; ++i) {
-      uint4 wv[FB];
+      u32x4_t wv[FB];
 #pragma unroll
-      for (int j = 0; j < FB; ++j) wv[j] = *reinterpret_cast<const uint4*>(wlds + ((wave * WL + i) * FB + j) * 512 + lane * 8);
+      for (int j = 0; j < FB; ++j) wv[j] = lds_read16(wlds + ((wave * WL + i) * FB + j) * 512 + lane * 8);
       multiply((PF + i + rot) & (KS - 1), wv);
     }
     ks0 = PF + WL;
