@@ -857,21 +857,28 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
         fp.users = d_users; fp.rt = rt; fp.d = d; fp.dh = dh; fp.n_prows = p.n_prows; fp.layer = l;
         fp.row_begin = r0; fp.row_end = r1; fp.n_mtiles = (r1 - r0 + 64 * kF1TM - 1) / (64 * kF1TM);
         fp.cm = cm; fp.q_mul = q_mul; fp.stream_out = (r1 - r0) >= kF1StreamMinRows ? 1 : 0;
-        // 64-token tiles as long as they fit the chip at once (see f1_stages)
-        const int mt64 = (r1 - r0 + 63) / 64, t64 = mt64 * cm.nblk * (d / 64), t128 = mt64 * cm.nblk * (d / 128);
-        if (t128 <= 2 * c->n_cus) {
-          fp.n_mtiles = mt64;
-          auto launch = [&](auto dim) {
+        // tiles of 64 x 64, 64 x 128 and 128 x 128 as long as they fit the chip at once or in few equal rounds (see F1Tile)
+        const int cols128 = cm.nblk * (d / 128), mt64 = (r1 - r0 + 63) / 64, mt128 = (r1 - r0 + 127) / 128;
+        const F1Tile tile = f1_tile(d, 2 * mt64 * cols128, mt64 * cols128, mt128 * cols128, c->n_cus);
+        if (tile != F1Tile::kLarge) {
+          auto launch = [&](auto kernel, int mt, int cols) {
+            fp.n_mtiles = mt;
+            hipLaunchKernelGGL(kernel, dim3((mt * cols + 7) / 8 * 8), dim3(256), 0, st, fp);
+          };
+          auto launch_d = [&](auto dim) {
             constexpr int KT = decltype(dim)::value / kGemmKTile;
-            if (t64 <= c->n_cus) hipLaunchKernelGGL((f1_gemm_bf16_kernel<HT, 1, 1, f1_stages(1, KT), KT>), dim3((t64 + 7) / 8 * 8), dim3(256), 0, st, fp);
-            else if (t128 <= c->n_cus) hipLaunchKernelGGL((f1_gemm_bf16_kernel<HT, 1, 2, f1_stages(2, KT), KT>), dim3((t128 + 7) / 8 * 8), dim3(256), 0, st, fp);
-            else hipLaunchKernelGGL((f1_gemm_bf16_kernel<HT, 1, 2, (KT < 6 ? KT : 6), KT>), dim3((t128 + 7) / 8 * 8), dim3(256), 0, st, fp);
+            if (tile == F1Tile::k64x64) launch(f1_gemm_bf16_kernel<HT, 1, 1, (KT <= 16 ? KT : 18), KT>, mt64, 2 * cols128);
+            else if (tile == F1Tile::k64x128) launch(f1_gemm_bf16_kernel<HT, 1, 2, (KT < 6 ? KT : 6), KT>, mt64, cols128);
+            else if constexpr (KT >= 8) {
+              if (tile == F1Tile::k128x128) launch(f1_gemm_bf16_kernel<HT, 2, 2, 4, KT>, mt128, cols128);
+              else launch(f1_gemm_bf16_kernel<HT, 2, 2, 3, KT>, mt128, cols128);
+            }
           };
           switch (d) {
-            case 128: launch(std::integral_constant<int, 128>()); break;
-            case 256: launch(std::integral_constant<int, 256>()); break;
-            case 512: launch(std::integral_constant<int, 512>()); break;
-            default: launch(std::integral_constant<int, 1024>()); break;
+            case 128: launch_d(std::integral_constant<int, 128>()); break;
+            case 256: launch_d(std::integral_constant<int, 256>()); break;
+            case 512: launch_d(std::integral_constant<int, 512>()); break;
+            default: launch_d(std::integral_constant<int, 1024>()); break;
           }
           return;
         }

@@ -214,19 +214,30 @@ __device__ __forceinline__ void st_out(uint16_t* dst, uint4 v, int stream) {
 }
 
 constexpr int kF1TM = 4, kF1TN = 2, kF1Stages = 3;   // 256 tokens x 128 features per workgroup
-// Launches of few rows take 64-token tiles and ask for as much of their operands at once as the LDS holds: what they take is the
-// round trips of the operand stream, 60 KiB in flight on a compute unit with six stages (0.29 us a step of 12 KiB) and up to 144 here.
-//   up to one 64 x 64 tile a compute unit     : 64 x 64, the whole of K up to d = 512 (128 KiB), else 18 stages
-//   up to one 64 x 128 tile a compute unit    : 64 x 128, the whole of K up to d = 256, else 12 stages
-//   up to two 64 x 128 tiles a compute unit   : 64 x 128, 6 stages (72 KiB), so that a unit holds two and the launch is one round
-// That is where their range ends: at d = 512 2048 rows take 12.9 us and 2112 rows 19.8 us, against 15.1 us for the
-// weight-stationary kernel below (d = 256: 4000 rows 9.4 against 11.0 us, 4100 rows 13.7 against 11.7 us; d = 1024, whose
-// alternative is the big tile: 1024 rows 22.1 against 29.0 us, 1500 rows 35.8 against 31.0 us).
-constexpr int f1_stages(int tn, int kt) { return tn == 1 ? (kt <= 16 ? kt : 18) : (kt <= 8 ? kt : 12); }
+// Launches of few thousand rows: the largest tile that still gives the chip one round of workgroups (or two or three that share a
+// compute unit: their stages in flight then add up).  What such a launch takes is the round trips of its operand stream, so that the
+// smallest has the whole of K in flight (64 x 64: 128 KiB of LDS up to d = 512).
+enum class F1Tile { k64x64, k64x128, k128x128, k128x128x3, kLarge };
+// us a call of 4 layers over 64 keys by rows, 64 x 64 / 64 x 128 / 128 x 128 with 4 stages / with 3 / weight-stationary / 256 x 128:
+//   d = 512 :  512 93 / 95 / 103 / 105 / 125 / 129    1024 114 / 105 / 109 / 112 / 131 / 135    1536 132 / 123 / 113 / 114 / 137 / 142
+//             2048 148 / 124 / 119 / 119 / 138 / 140    3072 175 / 140 / 142 / 140 / 146 / 147    4096 220 / 165 / 158 / 163 / 163 / 158
+//             6144 307 / 219 / 219 / 203 / 214 / 211    8192 - / 266 / 260 / 240 / 243 / 241    16384 - / 467 / 435 / 419 / 414 / 434
+//   d = 256 : 1024 71 / 74 / 79    2048 84 / 83 / 85    4096 101 / 102 / 100 / 101 / 114    6144 123 / 120 / 127 / 127 / 133    8192 144 / 135 / 131 / 134 / 139
+//   d = 1024:  256 225 / 227 / 239    512 239 / 227 / 237    768 259 / 243 / 240    1536 320 / 269 / 280 / 278 / - / 289    2048 388 / 298 / 302 / 307 / - / 297
+// (64 x 128 with twelve stages instead of six was never the fastest.)  t64, t128, tbig: tiles of 64 x 64, 64 x 128 and 128 x 128 in the launch.
+inline F1Tile f1_tile(int d, int t64, int t128, int tbig, int n_cus) {
+  if (t64 <= n_cus) return F1Tile::k64x64;
+  if (t128 <= n_cus) return F1Tile::k64x128;
+  if (d > 128 && tbig <= n_cus) return F1Tile::k128x128;
+  if (t128 <= 3 * n_cus) return F1Tile::k64x128;
+  if (d > 128 && d <= 512 && tbig <= 2 * n_cus) return F1Tile::k128x128;
+  if (d > 128 && d <= 512 && tbig <= 3 * n_cus) return F1Tile::k128x128x3;
+  return F1Tile::kLarge;
+}
 
 // KT: 32-wide steps of K, 0: known at run time (the big tile).
 template <typename H, int TM, int TN, int NSTAGE, int KT>
-__global__ __launch_bounds__(256, TM == 4 ? 2 : 1) void f1_gemm_bf16_kernel(F1Params p) {
+__global__ __launch_bounds__(256, TM == 4 ? 2 : NSTAGE == 3 ? 3 : 1) void f1_gemm_bf16_kernel(F1Params p) {
   constexpr int ROWS = 64 * TM;                  // tokens per workgroup tile
   constexpr int kStageLd = 64 * TN + 8;          // epilogue staging row stride (elements)
   using G = GemmTile<TM, TN, NSTAGE>;
@@ -239,9 +250,9 @@ __global__ __launch_bounds__(256, TM == 4 ? 2 : 1) void f1_gemm_bf16_kernel(F1Pa
   const int total = p.n_mtiles * n_ntiles;
   const int logical = xcd_remap(blockIdx.x, total);
   if (logical >= total) return;
-  // an XCD's workgroups take neighbouring tiles: of one row tile, or, where W1 is the larger operand, of one column tile, so that
+  // an XCD's workgroups take neighbouring tiles: of one row tile, or, in launches of few rows, of one column tile, so that
   // each XCD fetches its part of W1 and not all of it
-  const bool by_cols = TM == 1;
+  constexpr bool by_cols = TM < 4;
   const int mt = by_cols ? logical % p.n_mtiles : logical / n_ntiles, nt = by_cols ? logical / p.n_mtiles : logical - mt * n_ntiles;
   const int m0 = p.row_begin + mt * G::BMt;
   const int blk = p.cm.blk[nt / ntiles_per_blk];           // 0 u, 1 v, 2 q, 3 k
@@ -389,7 +400,7 @@ __global__ __launch_bounds__(256, TM == 4 ? 2 : 1) void f1_gemm_bf16_kernel(F1Pa
 }
 
 // ---- f1, weight-stationary form ----------------------------------------------------------------
-// For launches of two thousand rows and more.  One persistent workgroup of 8 wavefronts per compute unit
+// For launches beyond the tiles above (F1Tile).  One persistent workgroup of 8 wavefronts per compute unit
 // keeps a 128-feature slice of W1 (128 x D, up to 128 KiB) in LDS for its whole life and walks 64-row units
 // of its share of the rows; the workgroups of one XCD take the same row groups, so that a token panel comes
 // from memory once per XCD.  Each wavefront owns whole units (64 rows x 128 features, 2 x 4 MFMA blocks):

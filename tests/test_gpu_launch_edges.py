@@ -1,6 +1,6 @@
 """GPU parity where a launch changes its kernel or its shape: row counts at both sides of the edges of the layer tail's workgroups
 (8, 16 and 32 rows, the partly filled last one) with few and with many partial sums a row, and of the projection's tiles (64 x 64,
-64 x 128 with deep and with six stages, the weight-stationary kernel, 256 x 128), with prefix, suffix and candidate rows.  Every case ranks on the cached prefix
+64 x 128, 128 x 128 with four and with three stages, 256 x 128), with prefix, suffix and candidate rows.  Every case ranks on the cached prefix
 and by full recompute, against the CPU oracle; at d = 128 with the boosted weights, which let attention reach the scores there."""
 import pytest
 
@@ -30,21 +30,23 @@ def test_layer_tail_edges(case, attention):
     run_three_routes(synth.ModelConfig(2, d, heads, dtype, attention=attention), 7100 + case, L, S, M, page_tokens=64, boost=BOOST if d == 128 else None)
 
 
-#   d, heads, dtype, prefix lengths, suffix lengths, candidates: new rows in tiles of 64
+#   d, heads, dtype, prefix lengths, suffix lengths, candidates
 PROJECTION = [
     (128, 2, "bf16", [70], [3], [64]),            # 64 x 64, two row tiles
     (128, 2, "fp16", [70, 0], [3, 1], [2100, 70]),    # 64 x 128
     (256, 4, "bf16", [70], [65], [959]),          # 1024 rows: the last launch of 64 x 64 tiles
-    (256, 4, "fp16", [70], [65], [960]),          # 1025: 64 x 128, K whole
-    (256, 4, "bf16", [70], [70], [2010]),         # 64 x 128, six stages
+    (256, 4, "fp16", [70], [65], [960]),          # 1025: 64 x 128
+    (256, 4, "bf16", [70], [70], [2010]),         # 2080: 128 x 128, four stages
     (512, 8, "bf16", [130], [5], [507]),          # 512 rows: the last of 64 x 64
-    (512, 8, "fp16", [130], [5], [508]),          # 513: 64 x 128, twelve stages
-    (512, 8, "bf16", [130], [5], [1020]),         # 1025: six stages
-    (512, 8, "bf16", [1990], [5], [60]),          # 2048 rows with the recomputed prefix: its filler tiles, V token-major
+    (512, 8, "fp16", [130], [5], [508]),          # 513: 64 x 128
+    (512, 8, "bf16", [130], [5], [1020]),         # 1025: 128 x 128, four stages
+    (512, 8, "bf16", [1990], [5], [60]),          # recomputed prefix of 2048 rows with filler, V token-major, in 64 x 128 tiles
+    (512, 8, "fp16", [1100], [70], [300]),        # 1650 rows with a prefix: 128 x 128 tiles, one of them half filler
+    (512, 8, "bf16", [200, 4100], [0, 5], [9, 700]),  # 128 x 128 with three stages, two users' prefixes
     (1024, 8, "bf16", [70], [33], [223]),         # 256 rows: 64 x 64 with a ring
-    (1024, 8, "fp16", [70], [33], [224]),         # 257: twelve stages
-    (1024, 8, "bf16", [70], [65], [500]),         # six stages
-    (1024, 8, "bf16", [70], [65], [970]),         # the 256 x 128 tile
+    (1024, 8, "fp16", [70], [33], [224]),         # 257: 64 x 128
+    (1024, 8, "bf16", [70], [65], [600]),         # 128 x 128
+    (1024, 8, "bf16", [70], [65], [1480]),        # 1545: the 256 x 128 tile
 ]
 
 
