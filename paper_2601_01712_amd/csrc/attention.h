@@ -73,7 +73,7 @@ __device__ __forceinline__ void attn_s_half(const uint16_t* __restrict__ khalf, 
     for (int e = 0; e < 16; ++e) s[qb][e] = 0.f;
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) {
-    const uint4 kf = *reinterpret_cast<const uint4*>(khalf + ks * 512);
+    const u32x4_t kf = lds_read16(khalf + ks * 512);
 #pragma unroll
     for (int qb = 0; qb < NQ; ++qb) s[qb] = H::mfma(kf, qf[qb][ks], s[qb]);
   }
@@ -87,7 +87,7 @@ __device__ __forceinline__ void attn_pv_half(const uint16_t* __restrict__ vhalf,
   for (int m = 0; m < 2; ++m) {
 #pragma unroll
     for (int db = 0; db < DB; ++db) {
-      const uint4 vf = *reinterpret_cast<const uint4*>(vhalf + (db * 4 + m) * 512);
+      const u32x4_t vf = lds_read16(vhalf + (db * 4 + m) * 512);
 #pragma unroll
       for (int qb = 0; qb < NQ; ++qb) {
         uint4 pp = make_uint4(pk[qb][4 * m], pk[qb][4 * m + 1], pk[qb][4 * m + 2], pk[qb][4 * m + 3]);
@@ -114,13 +114,13 @@ __device__ __forceinline__ void attn_step(const uint16_t* __restrict__ khalf, co
   constexpr int SLOTS = KS + 2 * DB;      // = DH / 8
   constexpr int EPS = 16 / SLOTS > 0 ? 16 / SLOTS : 1;   // score elements per row block and slot
   static_assert(SLOTS * EPS == 16 || (SLOTS == 16 && EPS == 1), "slot split");
-  uint4 kf[KS], vf[2][DB];
+  u32x4_t kf[KS], vf[2][DB];
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) kf[ks] = *reinterpret_cast<const uint4*>(khalf + ks * 512);
+  for (int ks = 0; ks < KS; ++ks) kf[ks] = lds_read16(khalf + ks * 512);
 #pragma unroll
   for (int m = 0; m < 2; ++m)
 #pragma unroll
-    for (int db = 0; db < DB; ++db) vf[m][db] = *reinterpret_cast<const uint4*>(vhalf + (db * 4 + m) * 512);
+    for (int db = 0; db < DB; ++db) vf[m][db] = lds_read16(vhalf + (db * 4 + m) * 512);
   float pv[NQ][16];
   const f32x16_t zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -342,23 +342,13 @@ __global__ __launch_bounds__(NW * GS * 64, (DH >= 128 || GS > 1) ? 1 : 512 / (NW
   const uint16_t* sfx_base = reinterpret_cast<const uint16_t*>(p.sfx) + at.sfx_tile0 + (int64_t)head * TILE;
   const int64_t sfx_stride = (int64_t)2 * kTile * p.d;
 
-  // HBM -> LDS, no registers in between: each wavefront moves CHUNKS consecutive 1 KiB pieces of the tile, one scalar base and
-  // LDS address per four of them, the rest in the instruction's immediate offset, which counts on both sides (address arithmetic
-  // per piece and lane cost 3 % of the kernel)
+  // HBM -> LDS, no registers in between: each wavefront moves CHUNKS consecutive 1 KiB pieces of the tile.  (The buffer form: scalar
+  // addresses, and the rows' own keys below can be waited for without the tiles behind them.)
   auto issue_tile = [&](int tt, int b) {
     const uint16_t* src = (tt < tr.nkp) ? kv_base + (int64_t)tt * at.kv_tile_stride : sfx_base + (int64_t)(tt - tr.nkp) * sfx_stride;
+    const BufferView tile(src, TILE * 2);
 #pragma unroll
-    for (int i = 0; i < CHUNKS; ++i) {
-      const int piece = wave_s * CHUNKS + (i & ~3);
-      auto* gp = (const __attribute__((address_space(1))) void*)(reinterpret_cast<const char*>(src + piece * 512) + lane * 16);
-      auto* lp = (__attribute__((address_space(3))) void*)(&bufs[b][piece * 512]);
-      switch (i & 3) {
-        case 0: __builtin_amdgcn_global_load_lds(gp, lp, 16, 0, 0); break;
-        case 1: __builtin_amdgcn_global_load_lds(gp, lp, 16, 1024, 0); break;
-        case 2: __builtin_amdgcn_global_load_lds(gp, lp, 16, 2048, 0); break;
-        default: __builtin_amdgcn_global_load_lds(gp, lp, 16, 3072, 0); break;
-      }
-    }
+    for (int i = 0; i < CHUNKS; ++i) tile.load_lds(&bufs[b][(wave_s * CHUNKS + i) * 512], lane * 16, (wave_s * CHUNKS + i) * 1024);
   };
 
   // a wavefront whose rows all lie beyond the work item's last row only helps move tiles
@@ -378,7 +368,7 @@ __global__ __launch_bounds__(NW * GS * 64, (DH >= 128 || GS > 1) ? 1 : 512 / (NW
     } else {
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
-    __syncthreads();
+    lds_barrier();
 
     // Pipeline state.  s_cur: first product of the half about to get its SiLU.  pk_prev: P of the
     // half before it, whose second product is still owed, with vprev pointing at its V half.

@@ -140,15 +140,19 @@ inline void attn_row_tiles(const std::vector<UserDesc>& users, int tile_rows, st
 // 8 users at d = 128 with 2048 keys and 272 new rows, 240 pieces of 7 tiles 115, 336 of 5 126; d = 1024, 2048 keys and 512
 // candidates, 128 pieces of 8 on 256 slots 611, 256 of 4 646.)  It is a number of pieces and no length, so that as long as
 // a launch is that small a row's sums do not depend on how long the histories of the call's other users are.
-constexpr int kMinPieceTiles = 8, kFinePieceTiles = 2, kMaxPieces = 8, kPieceRounds = 4, kMaxSlots = 512;
+// Lists with prefix rows are of unequal items that thin out towards their end, and small ones are launches of a few dozen workgroups: their least
+// piece is shorter, whatever the launch's size, so that small launches cut a prefix alike in any batch (pre-inference of one user, 4 layers,
+// us a call with at least 8 / 4 tiles: d = 512, 600 keys 92.0 / 85.2, 1000 97.3 / 92.3, 1500 116.7 / 116.9, 2000 128.3 / 124.1; d = 256, 1000
+// 72.5 / 66.8, 2000 87.5 / 84.5; d = 1024, 1000 216 / 212).
+constexpr int kMinPieceTiles = 8, kMinCausalPieceTiles = 4, kFinePieceTiles = 2, kMaxPieces = 8, kPieceRounds = 4, kMaxSlots = 512;
 // Pieces a cut list has at most: the launch has under kPieceRounds * kMaxSlots (row tile, head) pairs, each cut in at most kMaxPieces.
 inline int max_cut_items(int n_heads) { return kMaxPieces * kPieceRounds * kMaxSlots / n_heads; }
-inline int piece_tiles(int64_t items, int64_t total_key_tiles, int least_key_tiles, int most_key_tiles, int most_rows, int slots) {
+inline int piece_tiles(int64_t items, int64_t total_key_tiles, int least_key_tiles, int most_key_tiles, int most_rows, int slots, int min_piece) {
   if (items >= (int64_t)kPieceRounds * slots || items == 0) return std::max(1, most_key_tiles);
   auto into = [&](int64_t pieces) { pieces = std::max<int64_t>(1, std::min<int64_t>(pieces, kMaxPieces)); return (most_key_tiles + pieces - 1) / pieces; };
   const bool equal = 4 * (int64_t)least_key_tiles >= 3 * (int64_t)most_key_tiles;
   int64_t c = equal ? into(slots / items) : (total_key_tiles + slots - 1) / slots;
-  c = std::max<int64_t>({c, kMinPieceTiles, into(kMaxPieces)});
+  c = std::max<int64_t>({c, min_piece, into(kMaxPieces)});
   if (equal && most_rows <= 32 && slots / items >= 2) c = std::min(c, std::max<int64_t>(kMinPieceTiles / 2, into(2)));
   return (int)std::max<int64_t>(1, std::min<int64_t>(c, most_key_tiles));
 }
@@ -199,8 +203,9 @@ inline void cut_attention(const std::vector<AttnTile>& rows_new, const std::vect
   for (const AttnTile& a : rows_prefix) { const int k = key_tiles(a); kt_prefix += k; least_prefix = std::min(least_prefix, k); most_prefix = std::max(most_prefix, k); }
   const int slots = std::min(kMaxSlots, dh == 128 ? n_cus : 2 * n_cus);   // workgroups the chip takes at a time
   c.piece_all = piece_tiles((int64_t)(rows_new.size() + rows_prefix.size()) * heads, (kt_new + kt_prefix) * heads, std::min(least_new, least_prefix),
-                            std::max(most_new, most_prefix ? most_prefix + tile_rows / kTile : 0), most_prefix ? tile_rows : most_rows, slots);
-  c.piece_last = piece_tiles((int64_t)rows_new.size() * heads, kt_new * heads, least_new, most_new, most_rows, slots);
+                            std::max(most_new, most_prefix ? most_prefix + tile_rows / kTile : 0), most_prefix ? tile_rows : most_rows, slots,
+                            most_prefix ? kMinCausalPieceTiles : kMinPieceTiles);
+  c.piece_last = piece_tiles((int64_t)rows_new.size() * heads, kt_new * heads, least_new, most_new, most_rows, slots, kMinPieceTiles);
   const bool one_list = rows_prefix.empty();       // the last layer's list is then the same: not sent twice
   if (one_list) c.fine = fine_pieces((int64_t)rows_new.size() * heads, slots);
   auto cut = [&]() {
