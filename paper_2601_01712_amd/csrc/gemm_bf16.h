@@ -228,7 +228,7 @@ enum class F1Tile { k64x64, k64x128, k128x128, k128x128x3, kLarge };
 inline F1Tile f1_tile(int d, int t64, int t128, int tbig, int n_cus) {
   if (t64 <= n_cus) return F1Tile::k64x64;
   if (t128 <= n_cus) return F1Tile::k64x128;
-  if (d > 128 && tbig <= n_cus) return F1Tile::k128x128;
+  if (d > 256 && tbig <= n_cus) return F1Tile::k128x128;
   if (t128 <= 3 * n_cus) return F1Tile::k64x128;
   if (d > 128 && d <= 512 && tbig <= 2 * n_cus) return F1Tile::k128x128;
   if (d > 128 && d <= 512 && tbig <= 3 * n_cus) return F1Tile::k128x128x3;
@@ -492,11 +492,17 @@ __global__ __launch_bounds__(512, 1) void f1_ws_bf16_kernel(F1Params p) {
   const int n_units = (p.row_end - p.row_begin + 63) >> 6;
   const int upr = (n_units + n_rg - 1) / n_rg;
   const int u_begin = rg * upr, u_end = min(n_units, u_begin + upr);
+  // (the first unit's row kinds and the biases are touched while the slice is on its way, so that the unit's start finds them in the cache)
+  const int first_row = p.row_begin + (u_begin + wave) * 64 + lane;
+  int touched = 0;
+  if (first_row < p.row_end) touched = p.rt.kind[first_row];
+  touched ^= *reinterpret_cast<const int*>(p.bias + n0 + lane * 2);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   const uint16_t* wlane = wl + lane * 8;
   uint16_t* st = stage + wave * (32 * 64);
   const float mul = (blk == 2) ? p.q_mul : 1.0f;
+  if (touched == 0x5a17c0de && p.q_mul < 0.f) st[0] = 0;       // never taken: keeps the loads
 
   for (int unit = u_begin + wave; unit < u_end; unit += 8) {
     const int m0 = p.row_begin + unit * 64;                    // row_begin is a multiple of 64 (host)
@@ -505,14 +511,16 @@ __global__ __launch_bounds__(512, 1) void f1_ws_bf16_kernel(F1Params p) {
     const uint16_t* tp1 = p.A + ((size_t)((B + 1) >> 2) * KS) * 2048 + ((B + 1) & 3) * 512 + lane * 8;
     // a unit of prefix rows lies inside one user's (256-aligned) prefix region: consecutive positions from pos0
     const bool prefix_unit = m0 < p.n_prows;
-    const int tile_user = prefix_unit ? p.rt.user[m0] : 0;
-    const int pos0 = prefix_unit ? p.rt.idx[m0] : 0;           // a multiple of 64: the unit is one K/V tile
-    const UserDesc& tud = p.users[tile_user];
-    const int L = tud.L;
-    if (prefix_unit && pos0 >= (L + kTile - 1) / kTile * kTile) continue;   // filler behind the user's last tile
-    // the unit's K/V tile (all heads)
-    uint16_t* tile = reinterpret_cast<uint16_t*>(const_cast<void*>(tud.kv)) + tud.kv_tile0 + (int64_t)(pos0 >> 6) * tud.kv_tile_stride +
-                     (int64_t)p.layer * tud.kv_layer_stride;
+    int pos0 = 0, L = 0;
+    uint16_t* tile = nullptr;                                  // the unit's K/V tile (all heads)
+    if (prefix_unit) {
+      pos0 = p.rt.idx[m0];                                     // a multiple of 64: the unit is one K/V tile
+      const UserDesc& tud = p.users[p.rt.user[m0]];
+      L = tud.L;
+      if (pos0 >= (L + kTile - 1) / kTile * kTile) continue;   // filler behind the user's last tile
+      tile = reinterpret_cast<uint16_t*>(const_cast<void*>(tud.kv)) + tud.kv_tile0 + (int64_t)(pos0 >> 6) * tud.kv_tile_stride +
+             (int64_t)p.layer * tud.kv_layer_stride;
+    }
     // new rows: candidates throughout (their k and v go row-major, as u and q do), or suffix rows among them
     const int kind_row = m0 + lane < p.row_end ? p.rt.kind[m0 + lane] : kRowCand;
     f32x16_t acc[2][4];
