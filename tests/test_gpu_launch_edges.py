@@ -1,6 +1,7 @@
 """GPU parity where a launch changes its kernel or its shape: row counts at both sides of the edges of the layer tail's workgroups
 (8, 16 and 32 rows, the partly filled last one) with few and with many partial sums a row, and of the projection's tiles (64 x 64,
-64 x 128, 128 x 128 with four and with three stages, 256 x 128), with prefix, suffix and candidate rows.  Every case ranks on the cached prefix
+64 x 128, 128 x 128 with four and with three stages, 256 x 128), with prefix, suffix and candidate rows; and where a wavefront of the attention
+stops at its rows' last key tile before the others of its workgroup do.  Every case ranks on the cached prefix
 and by full recompute, against the CPU oracle; at d = 128 with the boosted weights, which let attention reach the scores there."""
 import pytest
 
@@ -54,3 +55,20 @@ PROJECTION = [
 def test_projection_tiles(case):
     d, heads, dtype, L, S, M = PROJECTION[case]
     run_three_routes(synth.ModelConfig(2, d, heads, dtype), 7200 + case, L, S, M, page_tokens=64, boost=BOOST if d == 128 else None)
+
+
+#   heads at d = 128, prefix lengths, suffix lengths, candidates
+CAUSAL = [
+    (2, [1, 63, 64, 65, 127, 128, 129], [1, 0, 65, 64, 3, 1, 0], [3, 1, 2, 1, 1, 2, 1]),   # 32 rows a wavefront
+    (2, [255, 256, 257, 700], [70, 200, 1, 129], [40, 1, 2, 3]),   # suffix rows behind a ragged last prefix tile
+    (4, [1, 65, 190, 257], [100, 0, 33, 1], [1, 3, 2, 2]),         # d_head 32
+    (1, [1, 65, 190, 257], [100, 0, 33, 1], [1, 3, 2, 2]),         # d_head 128
+    (2, [300] * 40 + [64, 129, 1000], [5] * 40 + [130, 0, 300], [2] * 43),   # 64 rows a wavefront
+]
+
+
+@pytest.mark.parametrize("attention", ["silu", "softmax"])
+@pytest.mark.parametrize("case", range(len(CAUSAL)))
+def test_causal_wavefronts(case, attention):
+    heads, L, S, M = CAUSAL[case]
+    run_three_routes(synth.ModelConfig(2, 128, heads, "bf16", attention=attention), 7300 + case, L, S, M, page_tokens=64, boost=BOOST)
