@@ -241,7 +241,7 @@ def kernel_rooflines(w: Loaded, kernel_ms, sampled_calls, half16, config_name):
         avg_ms = f1_ms / f1_n
         flops = mean_over("f1", 0)
         achieved = flops / (avg_ms * 1e-3) / 1e12
-        out["f1"] = {"kernel": "f1_ws_bf16_kernel (f1_gemm_bf16_kernel up to 2048 rows at d = 512)", "bound": "mfma", "achieved": round(achieved, 2),
+        out["f1"] = {"kernel": "f1_ws_bf16_kernel (f1_gemm_bf16_kernel up to 6144 rows at d = 512)", "bound": "mfma", "achieved": round(achieved, 2),
                      "peak": peak, "unit": "TFLOP/s", "frac": round(achieved / peak, 4), "avg_launch_ms": round(avg_ms, 4),
                      "launches": f1_n, "flop_per_launch": flops}
     f2_ms, f2_n = kernel_ms.get("f2", (0.0, 0))
