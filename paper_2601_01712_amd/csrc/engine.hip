@@ -961,42 +961,41 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
           fp.gate_gain = (const uint16_t*)lw.ln_at_g; fp.gate_offs = (const uint16_t*)lw.ln_at_b;
           fp.n_prows = p.n_prows; fp.dh = dh;
           fp.ml = softmax ? ml : nullptr; fp.ml_stride = (size_t)R * H * 2; fp.n_heads = H;
-          // four row blocks of 16 per workgroup halve the passes over W2 once that still leaves every
-          // compute unit two workgroups
-          const int rows = R - a0;
-          const bool rb2 = d <= 512 && rows >= 64 * 384;
-          // a few hundred rows (one user per call): 8 rows per workgroup, so that four times as many
-          // compute units share the split partial sums
-          const bool vr8 = (d == 256 || d == 512) && rows <= kTailVr8MaxRows;
-          const bool vr16 = (d == 256 || d == 512) && !vr8 && rows <= kTailVr16MaxRows;
-          dim3 grid(vr8 ? (rows + 7) / 8 : vr16 ? (rows + 15) / 16 : (rows + (rb2 ? 63 : 31)) / (rb2 ? 64 : 32));
-          const bool few = p.nsplit <= 2;   // (every row has at most two partial sums)
-          auto launch_tail = [&](auto sm) {
+          const int wg_rows = tail_rows(d, R - a0);
+          const bool rb2 = wg_rows == 64, vr8 = wg_rows == 8, vr16 = wg_rows == 16;
+          const dim3 grid((R - a0 + wg_rows - 1) / wg_rows);
+          auto launch_tail = [&](auto sm, auto sums) {
             constexpr bool SM = decltype(sm)::value;
+            constexpr int NB = decltype(sums)::value, NB2 = NB < 2 ? NB : 2;
             switch (d) {
               case 128:
-                if (rb2) hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 128, 4, 4, SM>), grid, dim3(256), 0, st, fp);
-                else hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 128, 4, 2, SM>), grid, dim3(256), 0, st, fp);
+                if (rb2) hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 128, 4, 4, SM, 1, 64, 0, NB2>), grid, dim3(256), 0, st, fp);
+                else hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 128, 4, 2, SM, 1, 32, 0, NB2>), grid, dim3(256), 0, st, fp);
                 break;
               case 256:
-                if (rb2) hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 256, 8, 4, SM>), grid, dim3(512), 0, st, fp);
-                else if (vr8) hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 256, 8, 1, SM, 1, 8, 4, 8>), grid, dim3(512), 0, st, fp);
-                else if (vr16 && few) hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 256, 8, 1, SM, 1, 16, 4, 2>), grid, dim3(512), 0, st, fp);
-                else if (vr16) hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 256, 8, 1, SM, 1, 16, 4, 8>), grid, dim3(512), 0, st, fp);
-                else hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 256, 8, 2, SM>), grid, dim3(512), 0, st, fp);
+                if (rb2) hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 256, 8, 4, SM, 1, 64, 0, NB2>), grid, dim3(512), 0, st, fp);
+                else if (vr8) hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 256, 8, 1, SM, 1, 8, 4, NB>), grid, dim3(512), 0, st, fp);
+                else if (vr16) hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 256, 8, 1, SM, 1, 16, 4, NB>), grid, dim3(512), 0, st, fp);
+                else hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 256, 8, 2, SM, 1, 32, 0, NB2>), grid, dim3(512), 0, st, fp);
                 break;
               case 512:
-                if (rb2) hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 512, 8, 4, SM, 2>), grid, dim3(512), 0, st, fp);
-                else if (vr8) hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 512, 8, 1, SM, 1, 8, 4, 8>), grid, dim3(512), 0, st, fp);
-                else if (vr16 && few) hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 512, 8, 1, SM, 1, 16, 4, 2>), grid, dim3(512), 0, st, fp);
-                else if (vr16) hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 512, 8, 1, SM, 1, 16, 4, 8>), grid, dim3(512), 0, st, fp);
-                else hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 512, 8, 2, SM>), grid, dim3(512), 0, st, fp);
+                if (rb2) hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 512, 8, 4, SM, 2, 64, 0, NB2>), grid, dim3(512), 0, st, fp);
+                else if (vr8) hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 512, 8, 1, SM, 1, 8, 4, NB>), grid, dim3(512), 0, st, fp);
+                else if (vr16) hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 512, 8, 1, SM, 1, 16, 4, NB>), grid, dim3(512), 0, st, fp);
+                else hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 512, 8, 2, SM, 1, 32, 0, NB2>), grid, dim3(512), 0, st, fp);
                 break;
-              default: hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 1024, 8, 2, SM>), grid, dim3(512), 0, st, fp); break;
+              default: hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 1024, 8, 2, SM, 1, 32, 0, 1>), grid, dim3(512), 0, st, fp); break;
             }
           };
-          if (softmax) launch_tail(std::true_type());
-          else launch_tail(std::false_type());
+          auto launch_sums = [&](auto sm) {
+            switch (sums_at_once(fp.parts_all, p.nsplit)) {
+              case 1: launch_tail(sm, std::integral_constant<int, 1>()); break;
+              case 2: launch_tail(sm, std::integral_constant<int, 2>()); break;
+              default: launch_tail(sm, std::integral_constant<int, kMaxPieces>()); break;
+            }
+          };
+          if (softmax) launch_sums(std::true_type());
+          else launch_sums(std::false_type());
         }
       }
     }

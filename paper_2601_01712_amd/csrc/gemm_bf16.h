@@ -22,6 +22,7 @@
 
 #include "common.h"
 #include "gemm.h"
+#include "launch_rules.h"
 
 namespace relaygr {
 
@@ -419,8 +420,6 @@ __global__ __launch_bounds__(256, TM == 4 ? 2 : NSTAGE == 3 ? 3 : 1) void f1_gem
 // read it straight back (8192 rows: the layer tail is 2 us slower behind streaming stores).
 constexpr int kF1WsPF = 4;          // k-steps of token fragments in flight per wavefront
 constexpr int kF1StreamMinRows = 16384;   // from here on a launch writes 64 MiB and more (at d = 512): streaming stores
-constexpr int kTailVr8MaxRows = 1024;   // layer tail: launches of at most this many rows use 8-row workgroups (d = 256, 512),
-constexpr int kTailVr16MaxRows = 4096;  // of at most this many 16-row workgroups: still at most one workgroup per compute unit
 
 template <typename H, int D, bool FEATURE_MAJOR>
 __device__ __forceinline__ void f1_ws_mainloop(const uint16_t* __restrict__ tp0, const uint16_t* __restrict__ tp1,
@@ -767,7 +766,8 @@ struct GateLoad {
   float2 mlb[NB][G];
 
   // (NB pieces of every row without a condition, so that the compiler can count the loads and wait for these alone: a row with
-  // fewer pieces repeats its last one, a cache hit, which add() leaves out)
+  // fewer pieces repeats its last one, which add() leaves out.  That is a load and NB - 1 times the registers for nothing where no row
+  // has that many, so that the launch picks NB: see sums_at_once)
   __device__ __forceinline__ void issue(const F2LnParams& p, int sp0) {
 #pragma unroll
     for (int k = 0; k < NB; ++k)
@@ -948,11 +948,10 @@ __device__ __forceinline__ void l2_touch(const void* base, int lines, int share,
 // few thousand rows (one user per call): with 32 rows each they would occupy a few dozen compute units, each
 // pulling 16 KiB of split partial sums per row through its own memory path; with VR = 8 or 16 four times or
 // twice as many units share that.
-// NB: pieces of each row's sums in flight: two where a wavefront has rows enough, all eight where it has one or two and the launch
-// has more than two pieces.
+// NB: pieces of each row's sums in flight (sums_at_once), with rows enough for every wavefront no more than two, at d = 1024 one.
 // WL > 0: launches of at most one workgroup per compute unit.  The first WL k-steps of each wavefront's weights go straight to
 // LDS and the next PF into registers, all requested before the gate, which waits for other memory; the product then finds them there.
-template <typename H, int D, int NW, int TB, bool SM, int OCC = 1, int VR = 16 * TB, int WL = 0, int NB = D >= 1024 ? 1 : 2>
+template <typename H, int D, int NW, int TB, bool SM, int OCC, int VR, int WL, int NB>
 __global__ __launch_bounds__(NW * 64, OCC == 2 ? 4 : 1) void f2_ln_bf16_kernel(F2LnParams p) {
   constexpr int KS = D / 32;            // k-steps
   constexpr int FB = D / 16 / NW;       // 16-feature blocks per wavefront

@@ -1,9 +1,10 @@
-// Host build of the attention plan (csrc/plan.h) for tests/test_attn_plan.py: plans one call and checks the plan row by row.
+// Host build of the attention plan (csrc/plan.h) and of the launch rules (csrc/launch_rules.h) for tests/plan_util.py: plans one call and
+// checks the plan row by row, and says which kernels the call's launches take.
 #include <cstdio>
 #include <cstring>
 #include <vector>
 
-#include "../paper_2601_01712_amd/csrc/plan.h"
+#include "../paper_2601_01712_amd/csrc/launch_rules.h"
 
 using namespace relaygr;
 
@@ -15,7 +16,8 @@ static int complain(char* msg, const char* what, int user, int row, int got, int
 }
 
 // computed[u]: the call computes user u's prefix rows; new_rows: it has suffix and candidate rows (no pre-inference call).
-// most_sums: partial sums a row may have for the call to fit its scratch.  info: row blocks, nsplit, gs, items, rows' filler max.
+// most_sums: partial sums a row may have for the call to fit its scratch.  info: row blocks, nsplit, gs, items, rows' filler max,
+// sums of a row in flight in the layer tail of the last layer and of the others.
 extern "C" int plan_check(int n, const int32_t* L, const int32_t* S, const int32_t* M, const uint8_t* computed, int new_rows,
                           int heads, int dh, int n_cus, int most_sums, int32_t* info, char* msg) {
   std::vector<UserDesc> users(n);
@@ -37,6 +39,7 @@ extern "C" int plan_check(int n, const int32_t* L, const int32_t* S, const int32
   cut_attention(rows_new, rows_prefix, heads, dh, rpt, n_cus, cut, [&](const AttnCut& k) { return k.nsplit <= most_sums; });
   set_user_parts(users, cut);
   info[0] = nq; info[1] = cut.nsplit; info[2] = cut.gs; info[3] = (int)cut.all.size(); info[4] = 0;
+  info[5] = sums_at_once(cut.parts_last, cut.nsplit); info[6] = sums_at_once(cut.parts_all, cut.nsplit);
 
   // every list holds each row tile's pieces once: numbered 0 .. parts - 1, the key tiles in order and without a gap
   const int n_rows = prow + nrow;
@@ -80,6 +83,7 @@ extern "C" int plan_check(int n, const int32_t* L, const int32_t* S, const int32
     for (int t = 0; ud.nrow0 >= 0 && t < ud.S + ud.M; ++t) {
       const RowEntry e = row_entry_at(ud, u, false, t, rpt, cut.piece_all);
       const int all = e.parts & 255, last = e.parts >> 8;
+      if (all > info[6] || last > info[5]) return complain(msg, "sums in flight", u, t, info[6], all);
       if (all != have_all[ud.nrow0 + t]) return complain(msg, "sums of a new row", u, t, all, have_all[ud.nrow0 + t]);
       if (own_last && last != have_last[ud.nrow0 + t]) return complain(msg, "sums of a new row, last layer", u, t, last, have_last[ud.nrow0 + t]);
       if (cut.parts_all && all != cut.parts_all) return complain(msg, "sums of every new row", u, t, all, cut.parts_all);
@@ -88,3 +92,5 @@ extern "C" int plan_check(int n, const int32_t* L, const int32_t* S, const int32
   }
   return 0;
 }
+
+extern "C" int tail_rows_of(int d, int rows) { return tail_rows(d, rows); }

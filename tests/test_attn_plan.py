@@ -1,37 +1,17 @@
 """The 16-bit path's attention plan (csrc/plan.h), built with the host compiler: pieces cover every row tile's keys once, and no
 row of the row space -- filler rows between users included -- is said to have more partial sums than the call lays out.  The
 layer tail reads what the row's entry says even where it drops the values, so this cannot be seen in any output."""
-import ctypes as C
-import os
 import random
-import shutil
-import subprocess
 
-import numpy as np
 import pytest
 
-HERE = os.path.dirname(os.path.abspath(__file__))
+import plan_util
+from plan_util import check
 
 
 @pytest.fixture(scope="module")
-def shim(tmp_path_factory):
-    if shutil.which("g++") is None:
-        pytest.skip("no g++")
-    lib = tmp_path_factory.mktemp("plan") / "attn_plan.so"
-    subprocess.run(["g++", "-std=c++17", "-O2", "-Wall", "-Wextra", "-Werror", "-shared", "-fPIC", os.path.join(HERE, "attn_plan_shim.cpp"), "-o", str(lib)], check=True)
-    return C.CDLL(str(lib))
-
-
-def check(shim, L, S=None, M=None, computed=None, heads=8, dh=64, n_cus=256, most_sums=8):
-    n = len(L)
-    new_rows = M is not None
-    arr = [np.asarray(a if a is not None else [0] * n, np.int32) for a in (L, S, M)]
-    comp = np.asarray([1] * n if computed is None else computed, np.uint8)
-    info, msg = np.zeros(5, np.int32), C.create_string_buffer(256)
-    rc = shim.plan_check(n, *(a.ctypes.data_as(C.c_void_p) for a in arr), comp.ctypes.data_as(C.c_void_p), int(new_rows), heads, dh, n_cus, most_sums,
-                         info.ctypes.data_as(C.c_void_p), msg)
-    assert rc == 0, f"L {list(L)} S {S} M {M} computed {computed} heads {heads} d_head {dh} units {n_cus} sums {most_sums}: {msg.value.decode()}"
-    return dict(zip(("blocks", "nsplit", "gs", "items", "filler"), info.tolist()))
+def shim():
+    return plan_util.shim()
 
 
 @pytest.mark.parametrize("L,heads,dh", [
@@ -62,6 +42,18 @@ def test_two_splits_share_a_workgroup_where_every_row_has_an_even_number(shim):
 def test_pieces_of_equal_items_fit_the_chip_and_small_launches_are_cut_finer(shim, L, S, M, heads, dh, sums, items):
     got = check(shim, L, S, M, [0] * len(L), heads, dh)
     assert (got["nsplit"] * got["gs"], got["items"]) == (sums, items)
+
+
+@pytest.mark.parametrize("L,M,computed,sums,last", [
+    ([4096] * 16, [512] * 16, 0, 1, 1), ([8192] * 32, [1000] * 32, 0, 1, 1),   # two pieces of a row meet inside a workgroup; uncut
+    ([64], [512], 0, 1, 1), ([256], [512], 0, 2, 2), ([384], [512], 0, 8, 8), ([4096], [512], 0, 8, 8),   # one user's candidates
+    ([100, 384], [30, 30], 0, 8, 8), ([64, 256], [30, 30], 0, 2, 2),           # rows with different numbers
+    ([4096], None, 1, 8, 1),                                                  # a pre-inference has no rows in its last layer
+    ([64], [64], 1, 1, 1), ([600], [200], 1, 8, 2),
+])
+def test_layer_tail_has_as_many_sums_in_flight_as_its_rows_have(shim, L, M, computed, sums, last):
+    """It loads that many of every row, needed or not: launches of one or two sums a row must not take the kernels for more."""
+    assert plan_util.sums_in_flight(L, M, computed=[computed] * len(L)) == (sums, last)
 
 
 @pytest.mark.parametrize("heads,dh", [(4, 32), (16, 32), (1, 128), (2, 64), (4, 64), (8, 64), (16, 64), (2, 128), (8, 128)])

@@ -5,6 +5,7 @@ stops at its rows' last key tile before the others of its workgroup do.  Every c
 and by full recompute, against the CPU oracle; at d = 128 with the boosted weights, which let attention reach the scores there."""
 import pytest
 
+import plan_util
 import synth
 from gpu_util import BOOST
 from test_gpu_parity import run_three_routes
@@ -29,6 +30,40 @@ TAIL = [
 def test_layer_tail_edges(case, attention):
     d, heads, dtype, L, S, M = TAIL[case]
     run_three_routes(synth.ModelConfig(2, d, heads, dtype, attention=attention), 7100 + case, L, S, M, page_tokens=64, boost=BOOST if d == 128 else None)
+
+
+#   d, heads, dtype, prefix lengths, suffix lengths, candidates; the cached ranking's rows a workgroup and sums in flight, and the most sums a row has
+SUMS = [
+    (512, 8, "bf16", [64], [0], [9], 8, 1, 1),
+    (256, 4, "fp16", [200], [0], [300], 8, 2, 2),
+    (512, 8, "fp16", [60, 250], [0, 1], [30, 75], 8, 8, 3),          # users with one and with three
+    (512, 8, "bf16", [1024], [0], [33], 8, 8, 8),
+    (256, 4, "bf16", [960], [9], [5], 8, 8, 8),
+    (512, 8, "bf16", [60], [0], [1025], 16, 1, 1),
+    (256, 4, "fp16", [250], [0], [1100], 16, 2, 2),
+    (256, 4, "bf16", [4033], [0], [1030], 16, 8, 8),
+    (128, 2, "bf16", [64], [0], [300], 32, 1, 1),
+    (128, 2, "fp16", [250], [0], [300], 32, 2, 2),
+    (128, 2, "bf16", [1100], [3], [290], 32, 8, 7),                  # (two at a time)
+    (256, 4, "bf16", [65] * 17, [0] * 17, [250] * 17, 32, 1, 1),
+    (512, 8, "bf16", [65] * 17, [0] * 17, [250] * 17, 32, 1, 1),
+    (128, 2, "bf16", [65] * 25, [0, 3] * 12 + [0], [1000] * 25, 64, 1, 1),
+    (256, 4, "fp16", [65] * 25, [0, 3] * 12 + [0], [1000] * 25, 64, 1, 1),
+    (512, 8, "bf16", [65] * 25, [0, 3] * 12 + [0], [1000] * 25, 64, 1, 1),
+    (256, 4, "bf16", [65] * 24 + [1500], [0] * 25, [1000] * 25, 64, 8, 3),   # (two at a time)
+]
+
+
+@pytest.mark.parametrize("attention", ["silu", "softmax"])
+@pytest.mark.parametrize("case", range(len(SUMS)))
+def test_layer_tail_sums_in_flight(case, attention):
+    d, heads, dtype, L, S, M, rows, sums, most = SUMS[case]
+    assert plan_util.tail_rows(d, sum(S) + sum(M)) == rows
+    cached = {"computed": [0] * len(L), "heads": heads, "dh": d // heads}
+    assert plan_util.sums_in_flight(L, M, S, **cached) == (sums, sums)
+    assert plan_util.check(plan_util.shim(), L, S, M, **cached)["nsplit"] == most
+    run_three_routes(synth.ModelConfig(1 if sum(L) + sum(M) > 5000 else 2, d, heads, dtype, attention=attention), 7400 + case, L, S, M, page_tokens=64,
+                     boost=BOOST if d == 128 else None)
 
 
 #   d, heads, dtype, prefix lengths, suffix lengths, candidates
