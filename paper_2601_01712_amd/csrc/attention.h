@@ -343,13 +343,24 @@ __global__ __launch_bounds__(NW * GS * 64, (DH >= 128 || GS > 1) ? 1 : 512 / (NW
   const uint16_t* sfx_base = reinterpret_cast<const uint16_t*>(p.sfx) + at.sfx_tile0 + (int64_t)head * TILE;
   const int64_t sfx_stride = (int64_t)2 * kTile * p.d;
 
-  // HBM -> LDS, no registers in between: each wavefront moves CHUNKS consecutive 1 KiB pieces of the tile.  (The buffer form: scalar
-  // addresses, and the rows' own keys below can be waited for without the tiles behind them.)
+  // HBM -> LDS, no registers in between: each wavefront moves CHUNKS consecutive 1 KiB pieces of the tile, one LDS address per four
+  // of them, the rest in the instruction's immediate offset, which counts on both sides: an address for every piece costs a scalar
+  // write of M0 and a wait state behind it (16 users of 4096 keys and 512 candidates, d = 512, us a call 1050 / 1042).  The buffer form:
+  // scalar addresses, and the rows' own keys below can be waited for without the tiles behind them.
   auto issue_tile = [&](int tt, int b) {
     const uint16_t* src = (tt < tr.nkp) ? kv_base + (int64_t)tt * at.kv_tile_stride : sfx_base + (int64_t)(tt - tr.nkp) * sfx_stride;
     const BufferView tile(src, TILE * 2);
 #pragma unroll
-    for (int i = 0; i < CHUNKS; ++i) tile.load_lds(&bufs[b][(wave_s * CHUNKS + i) * 512], lane * 16, (wave_s * CHUNKS + i) * 1024);
+    for (int i = 0; i < CHUNKS; ++i) {
+      const int piece = wave_s * CHUNKS + (i & ~3);
+      uint16_t* dst = &bufs[b][piece * 512];
+      switch (i & 3) {
+        case 0: tile.load_lds(dst, lane * 16, piece * 1024); break;
+        case 1: tile.load_lds<1024>(dst, lane * 16, piece * 1024); break;
+        case 2: tile.load_lds<2048>(dst, lane * 16, piece * 1024); break;
+        default: tile.load_lds<3072>(dst, lane * 16, piece * 1024); break;
+      }
+    }
   };
 
   // a wavefront whose rows all lie beyond the work item's last row only helps move tiles

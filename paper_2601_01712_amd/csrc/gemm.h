@@ -73,8 +73,9 @@ struct BufferView {
   __device__ __forceinline__ uint4 load(int lane_off, int off) const {
     return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane_off, off, 0));
   }
+  template <int IMM = 0>       // counts on both sides: dst + IMM takes off + IMM (below 4096)
   __device__ __forceinline__ void load_lds(void* dst, int lane_off, int off) const {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)dst, 16, lane_off, off, 0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)dst, 16, lane_off, off, IMM, 0);
   }
 };
 
