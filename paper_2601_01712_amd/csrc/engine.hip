@@ -871,7 +871,7 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
             else if (tile == F1Tile::k64x128) launch(f1_gemm_bf16_kernel<HT, 1, 2, (KT < 6 ? KT : 6), KT>, mt64, cols128);
             else if constexpr (KT >= 8) {
               if (tile == F1Tile::k128x128) launch(f1_gemm_bf16_kernel<HT, 2, 2, 4, KT>, mt128, cols128);
-              else launch(f1_gemm_bf16_kernel<HT, 2, 2, 3, KT>, mt128, cols128);
+              else if constexpr (KT <= 16) launch(f1_gemm_bf16_kernel<HT, 2, 2, 3, KT>, mt128, cols128);   // (d <= 512: f1_tile)
             }
           };
           switch (d) {
