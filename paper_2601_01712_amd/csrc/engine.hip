@@ -855,48 +855,32 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
         fp.A = (const uint16_t*)xh; fp.W = c->w1_packed[l]; fp.bias = (const uint16_t*)lw.b1;
         fp.u = (uint16_t*)ubuf; fp.q = (uint16_t*)qbuf; fp.knew = (uint16_t*)knew; fp.vnew = (uint16_t*)vnew; fp.sfx = (uint16_t*)sfx;
         fp.users = d_users; fp.rt = rt; fp.d = d; fp.dh = dh; fp.n_prows = p.n_prows; fp.layer = l;
-        fp.row_begin = r0; fp.row_end = r1; fp.n_mtiles = (r1 - r0 + 64 * kF1TM - 1) / (64 * kF1TM);
+        fp.row_begin = r0; fp.row_end = r1;           // (r0: a multiple of kPrefixRowAlign)
         fp.cm = cm; fp.q_mul = q_mul; fp.stream_out = (r1 - r0) >= kF1StreamMinRows ? 1 : 0;
-        // tiles of 64 x 64, 64 x 128 and 128 x 128 as long as they fit the chip at once or in few equal rounds (see F1Tile)
-        const int cols128 = cm.nblk * (d / 128), mt64 = (r1 - r0 + 63) / 64, mt128 = (r1 - r0 + 127) / 128;
-        const F1Tile tile = f1_tile(d, 2 * mt64 * cols128, mt64 * cols128, mt128 * cols128, c->n_cus);
-        if (tile != F1Tile::kLarge) {
-          auto launch = [&](auto kernel, int mt, int cols) {
-            fp.n_mtiles = mt;
-            hipLaunchKernelGGL(kernel, dim3((mt * cols + 7) / 8 * 8), dim3(256), 0, st, fp);
-          };
-          auto launch_d = [&](auto dim) {
-            constexpr int KT = decltype(dim)::value / kGemmKTile;
-            if (tile == F1Tile::k64x64) launch(f1_gemm_bf16_kernel<HT, 1, 1, (KT <= 16 ? KT : 18), KT>, mt64, 2 * cols128);
-            else if (tile == F1Tile::k64x128) launch(f1_gemm_bf16_kernel<HT, 1, 2, (KT < 6 ? KT : 6), KT>, mt64, cols128);
-            else if constexpr (KT >= 8) {
-              if (tile == F1Tile::k128x128) launch(f1_gemm_bf16_kernel<HT, 2, 2, 4, KT>, mt128, cols128);
-              else if constexpr (KT <= 16) launch(f1_gemm_bf16_kernel<HT, 2, 2, 3, KT>, mt128, cols128);   // (d <= 512: f1_tile)
-            }
-          };
-          switch (d) {
-            case 128: launch_d(std::integral_constant<int, 128>()); break;
-            case 256: launch_d(std::integral_constant<int, 256>()); break;
-            case 512: launch_d(std::integral_constant<int, 512>()); break;
-            default: launch_d(std::integral_constant<int, 1024>()); break;
+        const int cols = cm.nblk * (d / 128);
+        auto launch = [&](auto kernel, int tile_rows, int tile_cols) {
+          fp.n_mtiles = (r1 - r0 + tile_rows - 1) / tile_rows;
+          hipLaunchKernelGGL(kernel, dim3((fp.n_mtiles * tile_cols + 7) / 8 * 8), dim3(256), 0, st, fp);
+        };
+        auto launch_d = [&](auto dim) {               // (no tile that f1_tile does not take at a width is built for it)
+          constexpr int D = decltype(dim)::value, KT = D / kGemmKTile;
+          switch (f1_tile(D, cm.nblk, r1 - r0, c->n_cus)) {
+            case F1Tile::k64x64: launch(f1_gemm_bf16_kernel<HT, 1, 1, (KT <= 16 ? KT : 18), KT>, 64, 2 * cols); break;
+            case F1Tile::k64x128: launch(f1_gemm_bf16_kernel<HT, 1, 2, (KT < 6 ? KT : 6), KT>, 64, cols); break;
+            case F1Tile::k128x128: if constexpr (D >= 256) launch(f1_gemm_bf16_kernel<HT, 2, 2, 4, KT>, 128, cols); break;
+            case F1Tile::k128x128x3: if constexpr (D >= 256 && D <= 512) launch(f1_gemm_bf16_kernel<HT, 2, 2, 3, KT>, 128, cols); break;
+            case F1Tile::kStationary:
+              if constexpr (D <= 512) hipLaunchKernelGGL((f1_ws_bf16_kernel<HT, D>), dim3(cols * f1_row_groups(D, cm.nblk, c->n_cus)), dim3(512), 0, st, fp);
+              break;
+            default: launch(f1_gemm_bf16_kernel<HT, kF1TM, kF1TN, kF1Stages, 0>, 64 * kF1TM, cols); break;
           }
-          return;
+        };
+        switch (d) {
+          case 128: launch_d(std::integral_constant<int, 128>()); break;
+          case 256: launch_d(std::integral_constant<int, 256>()); break;
+          case 512: launch_d(std::integral_constant<int, 512>()); break;
+          default: launch_d(std::integral_constant<int, 1024>()); break;
         }
-        // then the weight-stationary kernel: one persistent workgroup per compute unit,
-        // (compute units / column slices) row groups, a multiple of 8 so that each XCD takes whole row groups
-        const int n_slices = cm.nblk * (d / 128);
-        const int n_rg = d <= 512 ? (c->n_cus / n_slices) & ~7 : 0;
-        if ((r0 & 63) == 0 && n_rg >= 8) {
-          const dim3 grid(n_slices * n_rg);
-          switch (d) {
-            case 128: hipLaunchKernelGGL((f1_ws_bf16_kernel<HT, 128>), grid, dim3(512), 0, st, fp); break;
-            case 256: hipLaunchKernelGGL((f1_ws_bf16_kernel<HT, 256>), grid, dim3(512), 0, st, fp); break;
-            default: hipLaunchKernelGGL((f1_ws_bf16_kernel<HT, 512>), grid, dim3(512), 0, st, fp); break;
-          }
-          return;
-        }
-        int total = fp.n_mtiles * cm.nblk * (d / (64 * kF1TN));
-        hipLaunchKernelGGL((f1_gemm_bf16_kernel<HT, kF1TM, kF1TN, kF1Stages, 0>), dim3((total + 7) / 8 * 8), dim3(256), 0, st, fp);
       }
     };
     if (last && p.n_prows) {

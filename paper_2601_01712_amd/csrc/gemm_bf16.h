@@ -215,27 +215,6 @@ __device__ __forceinline__ void st_out(uint16_t* dst, uint4 v, int stream) {
 }
 
 constexpr int kF1TM = 4, kF1TN = 2, kF1Stages = 3;   // 256 tokens x 128 features per workgroup
-// Launches of few thousand rows: the largest tile that still gives the chip one round of workgroups (or two or three that share a
-// compute unit: their stages in flight then add up).  What such a launch takes is the round trips of its operand stream, so that the
-// smallest has the whole of K in flight (64 x 64: 128 KiB of LDS up to d = 512).
-enum class F1Tile { k64x64, k64x128, k128x128, k128x128x3, kLarge };
-// us a call of 4 layers over 64 keys by rows, 64 x 64 / 64 x 128 / 128 x 128 with 4 stages / with 3 / weight-stationary / 256 x 128:
-//   d = 512 :  512 93 / 95 / 103 / 105 / 125 / 129    1024 114 / 105 / 109 / 112 / 131 / 135    1536 132 / 123 / 113 / 114 / 137 / 142
-//             2048 148 / 124 / 119 / 119 / 138 / 140    3072 175 / 140 / 142 / 140 / 146 / 147    4096 220 / 165 / 158 / 163 / 163 / 158
-//             6144 307 / 219 / 219 / 203 / 214 / 211    8192 - / 266 / 260 / 240 / 243 / 241    16384 - / 467 / 435 / 419 / 414 / 434
-//   d = 256 : 1024 71 / 74 / 79    2048 84 / 83 / 85    4096 101 / 102 / 100 / 101 / 114    6144 123 / 120 / 127 / 127 / 133    8192 144 / 135 / 131 / 134 / 139
-//   d = 1024:  256 225 / 227 / 239    512 239 / 227 / 237    768 259 / 243 / 240    1536 320 / 269 / 280 / 278 / - / 289    2048 388 / 298 / 302 / 307 / - / 297
-// (64 x 128 with twelve stages instead of six was never the fastest.)  t64, t128, tbig: tiles of 64 x 64, 64 x 128 and 128 x 128 in the launch.
-inline F1Tile f1_tile(int d, int t64, int t128, int tbig, int n_cus) {
-  if (t64 <= n_cus) return F1Tile::k64x64;
-  if (t128 <= n_cus) return F1Tile::k64x128;
-  if (d > 256 && tbig <= n_cus) return F1Tile::k128x128;
-  if (t128 <= 3 * n_cus) return F1Tile::k64x128;
-  if (d > 128 && d <= 512 && tbig <= 2 * n_cus) return F1Tile::k128x128;
-  if (d > 128 && d <= 512 && tbig <= 3 * n_cus) return F1Tile::k128x128x3;
-  return F1Tile::kLarge;
-}
-
 // KT: 32-wide steps of K, 0: known at run time (the big tile).
 template <typename H, int TM, int TN, int NSTAGE, int KT>
 __global__ __launch_bounds__(256, TM == 4 ? 2 : NSTAGE == 3 ? 3 : 1) void f1_gemm_bf16_kernel(F1Params p) {
@@ -401,7 +380,7 @@ __global__ __launch_bounds__(256, TM == 4 ? 2 : NSTAGE == 3 ? 3 : 1) void f1_gem
 }
 
 // ---- f1, weight-stationary form ----------------------------------------------------------------
-// For launches beyond the tiles above (F1Tile).  One persistent workgroup of 8 wavefronts per compute unit
+// For launches beyond the tiles above (f1_tile).  One persistent workgroup of 8 wavefronts per compute unit
 // keeps a 128-feature slice of W1 (128 x D, up to 128 KiB) in LDS for its whole life and walks 64-row units
 // of its share of the rows; the workgroups of one XCD take the same row groups, so that a token panel comes
 // from memory once per XCD.  Each wavefront owns whole units (64 rows x 128 features, 2 x 4 MFMA blocks):

@@ -6,6 +6,33 @@
 
 namespace relaygr {
 
+// Tiles of the projection, rows x columns of [u | v | q | k].  Launches of few thousand rows: the largest tile that still gives the chip one round of
+// workgroups; then those of which two (at d = 128 three) share a compute unit, up to three rounds' worth: their stages in flight add up.  What such a
+// launch takes is the round trips of its operand stream, so that the smallest has the whole of K in flight (64 x 64: 128 KiB of LDS up to d = 512).
+// Beyond them the weight-stationary form, at d = 1024 the 256 x 128 tile.
+enum class F1Tile { k64x64, k64x128, k128x128, k128x128x3, kStationary, k256x128 };
+// Row groups of the weight-stationary form: one persistent workgroup per compute unit, (units / slices of 128 columns) groups, a multiple of 8 so
+// that each XCD takes whole groups; 0: not that form.
+inline int f1_row_groups(int d, int nblk, int n_cus) { return d <= 512 ? n_cus / (nblk * (d / 128)) & ~7 : 0; }
+// us a call of 4 layers over 64 keys by rows, 64 x 64 / 64 x 128 / 128 x 128 with 4 stages / with 3 / weight-stationary / 256 x 128:
+//   d = 512 :  512 93 / 95 / 103 / 105 / 125 / 129    1024 114 / 105 / 109 / 112 / 131 / 135    1536 132 / 123 / 113 / 114 / 137 / 142
+//             2048 148 / 124 / 119 / 119 / 138 / 140    3072 175 / 140 / 142 / 140 / 146 / 147    4096 220 / 165 / 158 / 163 / 163 / 158
+//             6144 307 / 219 / 219 / 203 / 214 / 211    8192 - / 266 / 260 / 240 / 243 / 241    16384 - / 467 / 435 / 419 / 414 / 434
+//   d = 256 : 1024 71 / 74 / 79    2048 84 / 83 / 85    4096 101 / 102 / 100 / 101 / 114    6144 123 / 120 / 127 / 127 / 133    8192 144 / 135 / 131 / 134 / 139
+//   d = 1024:  256 225 / 227 / 239    512 239 / 227 / 237    768 259 / 243 / 240    1536 320 / 269 / 280 / 278 / - / 289    2048 388 / 298 / 302 / 307 / - / 297
+//   d = 128 , 64 x 128 / weight-stationary: 8250 107.8 / 116.6    9000 116.9 / 120.1    10 200 118.3 / 123.6    12 200 114.8 / 128.4
+// (64 x 128 with twelve stages instead of six was never the fastest.)  nblk: column blocks of width d in the launch.
+inline F1Tile f1_tile(int d, int nblk, int rows, int n_cus) {
+  const int cols = nblk * (d / 128), t128 = (rows + 63) / 64 * cols, t64 = 2 * t128, tbig = (rows + 127) / 128 * cols;   // workgroups of each tile
+  if (t64 <= n_cus) return F1Tile::k64x64;
+  if (t128 <= n_cus) return F1Tile::k64x128;
+  if (d > 256 && tbig <= n_cus) return F1Tile::k128x128;
+  if (t128 <= 3 * n_cus) return F1Tile::k64x128;
+  if (d > 128 && d <= 512 && tbig <= 2 * n_cus) return F1Tile::k128x128;
+  if (d > 128 && d <= 512 && tbig <= 3 * n_cus) return F1Tile::k128x128x3;
+  return f1_row_groups(d, nblk, n_cus) >= 8 ? F1Tile::kStationary : F1Tile::k256x128;
+}
+
 // Rows of a layer-tail workgroup.  A few hundred rows (one user per call): 8 each, so that four times as many compute units share the split partial
 // sums; then 16; both as long as that is at most one workgroup per compute unit.  Four row blocks of 16 halve the passes over W2 once that still
 // leaves every compute unit about two workgroups.

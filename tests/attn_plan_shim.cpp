@@ -94,3 +94,4 @@ extern "C" int plan_check(int n, const int32_t* L, const int32_t* S, const int32
 }
 
 extern "C" int tail_rows_of(int d, int rows) { return tail_rows(d, rows); }
+extern "C" int f1_tile_of(int d, int nblk, int rows, int n_cus) { return (int)f1_tile(d, nblk, rows, n_cus); }

@@ -48,3 +48,16 @@ def sums_in_flight(L, M=None, S=None, computed=None, heads=8, dh=64):
 def tail_rows(d, rows):
     """Rows of a layer-tail workgroup."""
     return shim().tail_rows_of(d, rows)
+
+
+def projection_tile(d, rows, nblk=4, n_cus=256):
+    """Tile of a projection launch: `nblk` of the four column blocks [u | v | q | k] of `rows` rows."""
+    return ("64x64", "64x128", "128x128", "128x128/3", "stationary", "256x128")[shim().f1_tile_of(d, nblk, rows, n_cus)]
+
+
+def projection_tiles(d, L, S, M):
+    """Tiles of a two-layer model: ranking on the cache; pre-inference's first and last layer (K and V alone); full recompute's first and
+    last layer (K and V of the prefix again; the new rows there are the cached ranking's launch)."""
+    prefix, new = sum((n + 255) // 256 * 256 for n in L), sum(S) + sum(M)
+    kv = projection_tile(d, prefix, 2)
+    return {"cached": projection_tile(d, new), "prefill": projection_tile(d, prefix), "full": projection_tile(d, prefix + new), "kv": kv}

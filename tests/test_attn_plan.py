@@ -1,4 +1,4 @@
-"""The 16-bit path's attention plan (csrc/plan.h), built with the host compiler: pieces cover every row tile's keys once, and no
+"""The 16-bit path's attention plan (csrc/plan.h) and launch rules (csrc/launch_rules.h), built with the host compiler: pieces cover every row tile's keys once, and no
 row of the row space -- filler rows between users included -- is said to have more partial sums than the call lays out.  The
 layer tail reads what the row's entry says even where it drops the values, so this cannot be seen in any output."""
 import random
@@ -83,3 +83,27 @@ def test_every_row_has_the_sums_its_pieces_write(shim, heads, dh):
         if sum(L) + sum(M or []) == 0:
             continue
         check(shim, L, S, M, computed, heads, dh, rng.choice([256, 256, 304, 64]), rng.choice([8, 8, 1, 2, 3, 5]))
+
+
+@pytest.mark.parametrize("d,nblk,borders", [
+    (128, 4, [(1, "64x64"), (2049, "64x128"), (12289, "stationary")]),
+    (128, 2, [(1, "64x64"), (4097, "64x128"), (24577, "stationary")]),
+    (256, 4, [(1, "64x64"), (1025, "64x128"), (6145, "128x128"), (8193, "128x128/3"), (12289, "stationary")]),
+    (256, 2, [(1, "64x64"), (2049, "64x128"), (12289, "128x128"), (16385, "128x128/3"), (24577, "stationary")]),
+    (512, 4, [(1, "64x64"), (513, "64x128"), (1025, "128x128"), (2049, "64x128"), (3073, "128x128"), (4097, "128x128/3"), (6145, "stationary")]),
+    (512, 2, [(1, "64x64"), (1025, "64x128"), (2049, "128x128"), (4097, "64x128"), (6145, "128x128"), (8193, "128x128/3"), (12289, "stationary")]),
+    (1024, 4, [(1, "64x64"), (257, "64x128"), (513, "128x128"), (1025, "64x128"), (1537, "256x128")]),
+    (1024, 2, [(1, "64x64"), (513, "64x128"), (1025, "128x128"), (2049, "64x128"), (3073, "256x128")]),
+])
+def test_projection_tiles_by_rows(d, nblk, borders):
+    """Where a projection launch changes its tile: a border that moves takes the GPU tests of that border with it."""
+    tiles = [(rows, plan_util.projection_tile(d, rows, nblk)) for rows in range(1, 30001)]
+    assert [t for t, before in zip(tiles, [(0, "")] + tiles) if t[1] != before[1]] == borders
+
+
+@pytest.mark.parametrize("n_cus", [64, 104, 256, 304])
+def test_projection_tiles_are_built_for_their_width(n_cus):
+    built = {128: {"64x64", "64x128", "stationary", "256x128"}, 1024: {"64x64", "64x128", "128x128", "256x128"}}
+    for d, tiles in built.items():
+        for nblk in (2, 4):
+            assert {plan_util.projection_tile(d, rows, nblk, n_cus) for rows in range(1, 40001, 63)} <= tiles

@@ -1,6 +1,6 @@
 """GPU parity where a launch changes its kernel or its shape: row counts at both sides of the edges of the layer tail's workgroups
 (8, 16 and 32 rows, the partly filled last one) with few and with many partial sums a row, and of the projection's tiles (64 x 64,
-64 x 128, 128 x 128 with four and with three stages, 256 x 128), with prefix, suffix and candidate rows; and where a wavefront of the attention
+64 x 128, 128 x 128 with four and with three stages, 256 x 128, the weight-stationary form), with prefix, suffix and candidate rows; and where a wavefront of the attention
 stops at its rows' last key tile before the others of its workgroup do.  Every case ranks on the cached prefix
 and by full recompute, against the CPU oracle; at d = 128 with the boosted weights, which let attention reach the scores there."""
 import pytest
@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 
 #   d, heads, dtype, prefix lengths, suffix lengths, candidates
 TAIL = [
-    (256, 4, "bf16", [600], [0], [1]),            # one row of eight pieces
+    (256, 4, "bf16", [600], [0], [1]),            # one row of five pieces
     (512, 8, "bf16", [600], [3], [4]),            # 7 rows: a workgroup of 8 not full
     (512, 8, "fp16", [520], [0], [17]),           # 8 + 8 + 1
     (256, 4, "bf16", [600, 70], [0, 5], [1019, 0]),   # 1024 rows: the last launch of 8-row workgroups
@@ -66,30 +66,51 @@ def test_layer_tail_sums_in_flight(case, attention):
                      boost=BOOST if d == 128 else None)
 
 
-#   d, heads, dtype, prefix lengths, suffix lengths, candidates
+#   d, heads, dtype, prefix lengths, suffix lengths, candidates; tiles of the launches of all four columns: cached ranking, full recompute
 PROJECTION = [
-    (128, 2, "bf16", [70], [3], [64]),            # 64 x 64, two row tiles
-    (128, 2, "fp16", [70, 0], [3, 1], [2100, 70]),    # 64 x 128
-    (256, 4, "bf16", [70], [65], [959]),          # 1024 rows: the last launch of 64 x 64 tiles
-    (256, 4, "fp16", [70], [65], [960]),          # 1025: 64 x 128
-    (256, 4, "bf16", [70], [70], [2010]),         # 2080: 128 x 128, four stages
-    (512, 8, "bf16", [130], [5], [507]),          # 512 rows: the last of 64 x 64
-    (512, 8, "fp16", [130], [5], [508]),          # 513: 64 x 128
-    (512, 8, "bf16", [130], [5], [1020]),         # 1025: 128 x 128, four stages
-    (512, 8, "bf16", [1990], [5], [60]),          # recomputed prefix of 2048 rows with filler, V token-major, in 64 x 128 tiles
-    (512, 8, "fp16", [1100], [70], [300]),        # 1650 rows with a prefix: 128 x 128 tiles, one of them half filler
-    (512, 8, "bf16", [200, 4100], [0, 5], [9, 700]),  # 128 x 128 with three stages, two users' prefixes
-    (1024, 8, "bf16", [70], [33], [223]),         # 256 rows: 64 x 64 with a ring
-    (1024, 8, "fp16", [70], [33], [224]),         # 257: 64 x 128
-    (1024, 8, "bf16", [70], [65], [600]),         # 128 x 128
-    (1024, 8, "bf16", [70], [65], [1480]),        # 1545: the 256 x 128 tile
+    (128, 2, "bf16", [70], [3], [64], "64x64", "64x64"),              # two row tiles
+    (128, 2, "fp16", [70, 0], [3, 1], [2100, 70], "64x128", "64x128"),
+    (256, 4, "bf16", [70], [65], [959], "64x64", "64x128"),           # 1024 rows: the last launch of 64 x 64 tiles
+    (256, 4, "fp16", [70], [65], [960], "64x128", "64x128"),          # 1025
+    (256, 4, "bf16", [70], [70], [2010], "64x128", "64x128"),
+    (256, 4, "bf16", [130], [65], [6079], "64x128", "128x128"),       # 6144
+    (256, 4, "fp16", [700, 130], [65, 0], [6000, 80], "128x128", "128x128"),   # 6145; two users' prefixes with filler between them
+    (256, 4, "bf16", [700, 130], [65, 0], [6000, 80], "128x128", "128x128"),
+    (256, 4, "fp16", [300], [0], [8192], "128x128", "128x128/3"),     # 8192
+    (256, 4, "bf16", [1100], [70], [8123], "128x128/3", "128x128/3"), # 8193
+    (512, 8, "bf16", [130], [5], [507], "64x64", "64x128"),           # 512 rows: the last of 64 x 64
+    (512, 8, "fp16", [130], [5], [508], "64x128", "64x128"),          # 513
+    (512, 8, "bf16", [130], [5], [1020], "128x128", "128x128"),       # 1025
+    (512, 8, "bf16", [1990], [5], [60], "64x64", "64x128"),           # recomputed prefix of 2048 rows with filler, V token-major
+    (512, 8, "fp16", [1100], [70], [300], "64x64", "128x128"),        # 1650 rows with a prefix, one of the tiles half filler
+    (512, 8, "bf16", [130], [5], [3068], "128x128", "128x128"),       # 3073: the second range of four stages
+    (512, 8, "fp16", [70], [1], [4096], "128x128/3", "128x128/3"),    # 4097
+    (512, 8, "bf16", [200, 4100], [0, 5], [9, 700], "64x128", "128x128/3"),   # two users' prefixes
+    (1024, 8, "bf16", [70], [33], [223], "64x64", "64x128"),          # 256 rows: 64 x 64 with a ring
+    (1024, 8, "fp16", [70], [33], [224], "64x128", "128x128"),        # 257
+    (1024, 8, "bf16", [70], [65], [600], "128x128", "128x128"),
+    (1024, 8, "bf16", [70], [65], [1480], "256x128", "256x128"),      # 1545
 ]
 
 
 @pytest.mark.parametrize("case", range(len(PROJECTION)))
 def test_projection_tiles(case):
-    d, heads, dtype, L, S, M = PROJECTION[case]
+    d, heads, dtype, L, S, M, cached, full = PROJECTION[case]
+    tiles = plan_util.projection_tiles(d, L, S, M)
+    assert (tiles["cached"], tiles["full"]) == (cached, full)
     run_three_routes(synth.ModelConfig(2, d, heads, dtype), 7200 + case, L, S, M, page_tokens=64, boost=BOOST if d == 128 else None)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp16"])
+@pytest.mark.parametrize("d,heads,users", [(128, 2, 97), (256, 4, 97), (512, 8, 49)])
+def test_every_launch_takes_the_weight_stationary_projection(dtype, d, heads, users):
+    """Pre-inference into the pool, its last layer's K and V alone, ranking on the cache and full recompute: prefixes with ragged last tiles
+    and filler behind them, suffix rows scattered into suffix tiles, candidates, a last unit that ends inside a 64-row block."""
+    L = [(1, 63, 64, 65, 128, 129, 255, 256)[u % 8] if u < 16 else 70 + u * 41 % 187 for u in range(users)]
+    S = [(0, 0, 70, 3)[u % 4] for u in range(users)]
+    M = [120 + u * 13 % 17 for u in range(users)]
+    assert set(plan_util.projection_tiles(d, L, S, M).values()) == {"stationary"} and (sum(S) + sum(M)) % 64
+    run_three_routes(synth.ModelConfig(2, d, heads, dtype), 7250 + d, L, S, M, page_tokens=64, boost=BOOST if d < 512 else None)
 
 
 #   heads at d = 128, prefix lengths, suffix lengths, candidates

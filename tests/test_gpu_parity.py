@@ -13,6 +13,7 @@ import torch
 
 import oracle
 import paper_2601_01712_amd as rg
+import plan_util
 import synth
 from gpu_util import BOOST, Harness, assert_close, build_case, oracle_scores, TOL
 from synth.generator import user_slices
@@ -127,15 +128,17 @@ def test_bf16_head_sizes(d, H):
 
 @pytest.mark.parametrize("dtype", ["bf16", "fp16"])
 @pytest.mark.parametrize("d,H,boost", [(128, 2, BOOST), (256, 4, BOOST), (512, 8, None)])
-def test_launches_of_thousands_of_rows_take_the_weight_stationary_projection(dtype, d, H, boost):
-    """Row counts above 4096 per projection launch (the persistent, weight-stationary form of the u|v|q|k
-    GEMM) with everything its epilogue has to place: prefix rows of three users with ragged last tiles and
+def test_launches_of_thousands_of_rows(dtype, d, H, boost):
+    """3328 to 9240 rows per projection launch: 64 x 128 tiles at d = 128, 64 x 128 and 128 x 128 ones at d = 256 and 512, there in full
+    recompute the weight-stationary form; with everything the epilogues have to place: prefix rows of three users with ragged last tiles and
     filler rows between them, K and V tiles of the pool (cached users) and of scratch (the uncached user),
-    suffix rows scattered into suffix tiles, candidate rows, a last unit that ends inside a 64-row block;
-    ranking on the cache runs the same launch over new rows only, full recompute over prefix and new rows
+    suffix rows scattered into suffix tiles, candidate rows, a last tile that ends inside a 64-row block;
+    ranking on the cache runs the same launch over new rows and one user's prefix, full recompute over prefix and new rows
     in one row space.  Boosted weights at the small widths, so that a misplaced K/V element shows."""
-    run_three_routes(synth.ModelConfig(2, d, H, dtype), 530 + d, [2500, 1300, 700], [70, 5, 0], [2100, 1900, 301],
-                     page_tokens=128, miss=(1,), boost=boost)
+    L, S, M = [2500, 1300, 700], [70, 5, 0], [2100, 1900, 301]
+    tiles = plan_util.projection_tiles(d, L, S, M)
+    assert (tiles["prefill"], tiles["full"]) == {128: ("64x128", "64x128"), 256: ("64x128", "128x128/3"), 512: ("128x128/3", "stationary")}[d]
+    run_three_routes(synth.ModelConfig(2, d, H, dtype), 530 + d, L, S, M, page_tokens=128, miss=(1,), boost=boost)
 
 
 @pytest.mark.parametrize("attention", ["silu", "softmax"])
@@ -185,9 +188,14 @@ def test_rows_with_different_numbers_of_key_pieces(attention, d, H, L, S, M):
     run_three_routes(synth.ModelConfig(2, d, H, "bf16", attention=attention), 700 + d + H, L, S, M, boost=BOOST, miss=(1,) if len(L) > 1 else ())
 
 
-@pytest.mark.parametrize("d,H,M", [(512, 8, 2048), (512, 8, 2049), (256, 4, 4096), (256, 4, 4097)])
-def test_row_counts_on_both_sides_of_the_projection_kernels_border(d, H, M):
-    """The last launch size whose 64-row tiles fit the chip at once, and the first that takes the weight-stationary kernel."""
+@pytest.mark.parametrize("d,H,M,tile", [
+    (512, 8, 2048, "128x128"), (512, 8, 2049, "64x128"), (512, 8, 6144, "128x128/3"), (512, 8, 6145, "stationary"),
+    (256, 4, 4096, "64x128"), (256, 4, 4097, "64x128"), (256, 4, 12288, "128x128/3"), (256, 4, 12289, "stationary"),
+    (128, 2, 12288, "64x128"), (128, 2, 12289, "stationary"),
+])
+def test_row_counts_on_both_sides_of_the_projection_kernels_border(d, H, M, tile):
+    """The last launch size that takes the tiled kernel and the first that takes the weight-stationary one, and the tiles' borders below them."""
+    assert plan_util.projection_tile(d, M) == tile
     run_three_routes(synth.ModelConfig(1, d, H, "bf16"), 750, [64], [0], [M])
 
 
