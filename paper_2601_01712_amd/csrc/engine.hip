@@ -975,6 +975,7 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
             switch (sums_at_once(fp.parts_all, p.nsplit)) {
               case 1: launch_tail(sm, std::integral_constant<int, 1>()); break;
               case 2: launch_tail(sm, std::integral_constant<int, 2>()); break;
+              case 4: launch_tail(sm, std::integral_constant<int, 4>()); break;
               default: launch_tail(sm, std::integral_constant<int, kMaxPieces>()); break;
             }
           };

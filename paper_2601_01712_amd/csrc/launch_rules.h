@@ -45,15 +45,17 @@ inline int tail_rows(int d, int rows) {
   return d <= 512 && rows >= kTailVr64MinRows ? 64 : 32;
 }
 
-// Partial sums of a row that the layer tail has in flight at once: one, two, or all a row can have.  It loads that many of every row, whether
-// the row has them or not, so that launches whose rows have one or two (every batch that is not cut along the keys, or whose pieces meet inside a
-// workgroup) take kernels that ask for no more.  (us a call with as many as before, two in large launches and eight in those of up to 1024 rows /
-// with as many as there are: one sum, d = 512, 8 layers, 6144 rows 544.0 / 538.9, 20 000 in fp16 1358 / 1348, 32 000 1938 / 1926, and in the softmax
-// form 2012 / 1984, in fp16 2099 / 2032; 4 layers, 512 rows 91.5 / 87.8; d = 256, 512 rows 67.0 / 65.0.  Two sums, 512 rows, d = 512 95.8 / 92.6;
-// d = 256, softmax 68.3 / 65.5.)  parts_all: the number all rows of the launch have, 0 where they differ; nsplit: the most a row of the call has.
+// Partial sums of a row that the layer tail has in flight at once: one, two, four, or all a row can have.  It loads that many of every row, whether
+// the row has them or not, so that launches whose rows have fewer take kernels that ask for fewer: every batch that is not cut along the keys, or whose
+// pieces meet inside a workgroup, has one; short histories have three or four.  (us a call with as many as before, two in large launches and
+// eight in those of up to 1024 rows / with as many as there are: one sum, d = 512, 8 layers, 6144 rows 544.0 / 538.9, 20 000 in fp16 1358 / 1348, 32 000
+// 1938 / 1926, and in the softmax form 2012 / 1984, in fp16 2099 / 2032; 4 layers, 512 rows 91.5 / 87.8; d = 256, 512 rows 67.0 / 65.0.  Two sums, 512
+// rows, d = 512 95.8 / 92.6; d = 256, softmax 68.3 / 65.5.  Three sums, 1000 rows, d = 512 113.8 / 111.0; four, 512 rows 101.3 / 98.7, softmax in fp16
+// 99.7 / 97.1, 1600 rows 154.7 / 150.8; d = 256, 2000 rows 98.6 / 96.7.)
+// parts_all: the number all rows of the launch have, 0 where they differ; nsplit: the most a row of the call has.
 inline int sums_at_once(int parts_all, int nsplit) {
   const int most = parts_all ? parts_all : nsplit;
-  return most <= 2 ? most : kMaxPieces;
+  return most <= 2 ? most : most <= 4 ? 4 : kMaxPieces;
 }
 
 }  // namespace relaygr

@@ -46,10 +46,10 @@ def test_pieces_of_equal_items_fit_the_chip_and_small_launches_are_cut_finer(shi
 
 @pytest.mark.parametrize("L,M,computed,sums,last", [
     ([4096] * 16, [512] * 16, 0, 1, 1), ([8192] * 32, [1000] * 32, 0, 1, 1),   # two pieces of a row meet inside a workgroup; uncut
-    ([64], [512], 0, 1, 1), ([256], [512], 0, 2, 2), ([384], [512], 0, 8, 8), ([4096], [512], 0, 8, 8),   # one user's candidates
-    ([100, 384], [30, 30], 0, 8, 8), ([64, 256], [30, 30], 0, 2, 2),           # rows with different numbers
-    ([4096], None, 1, 8, 1),                                                  # a pre-inference has no rows in its last layer
-    ([64], [64], 1, 1, 1), ([600], [200], 1, 8, 2),
+    ([64], [512], 0, 1, 1), ([256], [512], 0, 2, 2), ([384], [512], 0, 4, 4), ([512], [512], 0, 4, 4), ([520], [512], 0, 8, 8), ([4096], [512], 0, 8, 8),   # one user's candidates
+    ([100, 384], [30, 30], 0, 4, 4), ([64, 256], [30, 30], 0, 2, 2),           # rows with different numbers
+    ([4096], None, 1, 4, 1),                                                  # a pre-inference has no rows in its last layer
+    ([64], [64], 1, 1, 1), ([600], [200], 1, 4, 2),
 ])
 def test_layer_tail_has_as_many_sums_in_flight_as_its_rows_have(shim, L, M, computed, sums, last):
     """It loads that many of every row, needed or not: launches of one or two sums a row must not take the kernels for more."""

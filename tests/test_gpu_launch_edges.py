@@ -36,11 +36,15 @@ def test_layer_tail_edges(case, attention):
 SUMS = [
     (512, 8, "bf16", [64], [0], [9], 8, 1, 1),
     (256, 4, "fp16", [200], [0], [300], 8, 2, 2),
-    (512, 8, "fp16", [60, 250], [0, 1], [30, 75], 8, 8, 3),          # users with one and with three
+    (512, 8, "fp16", [60, 250], [0, 1], [30, 75], 8, 4, 3),          # users with one and with three
+    (256, 4, "bf16", [440], [3], [20], 8, 4, 4),
+    (512, 8, "bf16", [512], [0], [9], 8, 4, 4),
     (512, 8, "bf16", [1024], [0], [33], 8, 8, 8),
     (256, 4, "bf16", [960], [9], [5], 8, 8, 8),
     (512, 8, "bf16", [60], [0], [1025], 16, 1, 1),
     (256, 4, "fp16", [250], [0], [1100], 16, 2, 2),
+    (256, 4, "bf16", [440], [3], [1030], 16, 4, 4),
+    (512, 8, "fp16", [330], [0], [1100], 16, 4, 3),
     (256, 4, "bf16", [4033], [0], [1030], 16, 8, 8),
     (128, 2, "bf16", [64], [0], [300], 32, 1, 1),
     (128, 2, "fp16", [250], [0], [300], 32, 2, 2),
@@ -50,7 +54,7 @@ SUMS = [
     (128, 2, "bf16", [65] * 25, [0, 3] * 12 + [0], [1000] * 25, 64, 1, 1),
     (256, 4, "fp16", [65] * 25, [0, 3] * 12 + [0], [1000] * 25, 64, 1, 1),
     (512, 8, "bf16", [65] * 25, [0, 3] * 12 + [0], [1000] * 25, 64, 1, 1),
-    (256, 4, "bf16", [65] * 24 + [1500], [0] * 25, [1000] * 25, 64, 8, 3),   # (two at a time)
+    (256, 4, "bf16", [65] * 24 + [1500], [0] * 25, [1000] * 25, 64, 4, 3),   # (two at a time)
 ]
 
 
