@@ -141,10 +141,16 @@ inline void attn_row_tiles(const std::vector<UserDesc>& users, int tile_rows, st
 // candidates, 128 pieces of 8 on 256 slots 611, 256 of 4 646.)  It is a number of pieces and no length, so that as long as
 // a launch is that small a row's sums do not depend on how long the histories of the call's other users are.
 // Lists with prefix rows are of unequal items that thin out towards their end, and small ones are launches of a few dozen workgroups: their least
-// piece is shorter, whatever the launch's size, so that small launches cut a prefix alike in any batch (pre-inference of one user, 4 layers,
-// us a call with at least 8 / 4 tiles: d = 512, 600 keys 92.0 / 85.2, 1000 97.3 / 92.3, 1500 116.7 / 116.9, 2000 128.3 / 124.1; d = 256, 1000
-// 72.5 / 66.8, 2000 87.5 / 84.5; d = 1024, 1000 216 / 212).
+// piece is kMinCausalPieceTiles.  How far that pays is a matter of the slots that the list fills uncut: three eighths of them without new rows, and
+// three sixteenths with new rows, whose sums the last layer reads as well (us a call with at least 8 / 4 tiles, d = 256 and 512 of 4 and 8 layers.
+// Pre-inference of 600 keys 66.2 / 60.1 and 189 / 178, four users of 600 85.6 / 81.2 and 273 / 267, of 1000 92.1 / 90.4 and, at half of the slots,
+// 313 / 322; 16 users of 1000 194.8 / 204.7.  Full recompute of 600 keys and 64 candidates 82.5 / 77.1 and 216 / 208, of 1000 and 64 255 / 248; beyond
+// the line four users of 1000 and 256, one of them uncached, 278 / 286, 32 users of 1000 and 64, nine uncached, 213 / 239.)
 constexpr int kMinPieceTiles = 8, kMinCausalPieceTiles = 4, kFinePieceTiles = 2, kMaxPieces = 8, kPieceRounds = 4, kMaxSlots = 512;
+inline int least_piece(size_t rows_new, size_t rows_prefix, int heads, int slots) {      // (row tiles)
+  const bool few = 16 * (rows_new + rows_prefix) * heads <= (size_t)(rows_new ? 3 : 6) * slots;
+  return rows_prefix && few ? kMinCausalPieceTiles : kMinPieceTiles;
+}
 // Pieces a cut list has at most: the launch has under kPieceRounds * kMaxSlots (row tile, head) pairs, each cut in at most kMaxPieces.
 inline int max_cut_items(int n_heads) { return kMaxPieces * kPieceRounds * kMaxSlots / n_heads; }
 inline int piece_tiles(int64_t items, int64_t total_key_tiles, int least_key_tiles, int most_key_tiles, int most_rows, int slots, int min_piece) {
@@ -204,7 +210,7 @@ inline void cut_attention(const std::vector<AttnTile>& rows_new, const std::vect
   const int slots = std::min(kMaxSlots, dh == 128 ? n_cus : 2 * n_cus);   // workgroups the chip takes at a time
   c.piece_all = piece_tiles((int64_t)(rows_new.size() + rows_prefix.size()) * heads, (kt_new + kt_prefix) * heads, std::min(least_new, least_prefix),
                             std::max(most_new, most_prefix ? most_prefix + tile_rows / kTile : 0), most_prefix ? tile_rows : most_rows, slots,
-                            most_prefix ? kMinCausalPieceTiles : kMinPieceTiles);
+                            least_piece(rows_new.size(), rows_prefix.size(), heads, slots));
   c.piece_last = piece_tiles((int64_t)rows_new.size() * heads, kt_new * heads, least_new, most_new, most_rows, slots, kMinPieceTiles);
   const bool one_list = rows_prefix.empty();       // the last layer's list is then the same: not sent twice
   if (one_list) c.fine = fine_pieces((int64_t)rows_new.size() * heads, slots);

@@ -56,6 +56,17 @@ def test_layer_tail_has_as_many_sums_in_flight_as_its_rows_have(shim, L, M, comp
     assert plan_util.sums_in_flight(L, M, computed=[computed] * len(L)) == (sums, last)
 
 
+@pytest.mark.parametrize("L,M,computed,heads,dh,sums", [
+    ([600], None, 1, 4, 64, 3), ([1000] * 4, None, 4, 4, 64, 4), ([600] * 8, None, 8, 4, 64, 3), ([1000], None, 1, 8, 128, 4),    # up to 3/8 of the slots
+    ([1000] * 4, None, 4, 8, 64, 2), ([1000] * 16, None, 16, 4, 64, 2), ([600] * 16, None, 16, 4, 64, 2), ([1000] * 2, None, 2, 8, 128, 2),
+    ([600], [64], 1, 8, 64, 3), ([1000] * 4, [64] * 4, 1, 8, 64, 4), ([600], [64], 1, 8, 128, 3),                                 # with new rows 3/16
+    ([1000] * 4, [256] * 4, 1, 8, 64, 2), ([1000] * 16, [128] * 16, 4, 4, 64, 2), ([1000] * 32, [64] * 32, 9, 4, 64, 2),
+])
+def test_lists_with_prefix_rows_are_cut_finer_only_while_they_are_small(shim, L, M, computed, heads, dh, sums):
+    got = check(shim, L, None, M, [int(u < computed) for u in range(len(L))], heads=heads, dh=dh)
+    assert got["nsplit"] == sums
+
+
 @pytest.mark.parametrize("heads,dh", [(4, 32), (16, 32), (1, 128), (2, 64), (4, 64), (8, 64), (16, 64), (2, 128), (8, 128)])
 def test_every_row_has_the_sums_its_pieces_write(shim, heads, dh):
     rng = random.Random(heads * 1000 + dh)
