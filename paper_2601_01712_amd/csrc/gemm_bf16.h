@@ -647,8 +647,10 @@ __global__ __launch_bounds__(512, 1) void f1_ws_bf16_kernel(F1Params p) {
 // a lane-local sum, two lane exchanges and one exchange between wavefronts through LDS.
 // What bounds it: a chain of memory round trips.  A compute unit takes about 64 bytes a clock, and W2 is 512 KB of that for every
 // workgroup (d = 512), so global loads that depend on no result go out as early as the registers allow: the rows' split sums, W2's first
-// k-steps and the residual rows before the first wait; and every wait is for its own loads only, which takes loads the compiler can
-// count (none behind a branch, none in the global_load_lds form: see BufferView) and barriers that wait for LDS alone.
+// k-steps and the residual rows before the first wait; and the gate waits for its own loads only, which takes loads the compiler can
+// count (none behind a branch, none in the global_load_lds form: see BufferView) and barriers that wait for LDS alone.  Not so: the launches with
+// weights in LDS wait once, between gate and product, for all that has been asked for; and where EARLY_LN is false (64-row workgroups at d = 512,
+// d = 1024) gain and offset are loaded in the output pass, one round trip for each feature block behind the stores of the one before.
 // Of the launch's time from its first workgroup's start to its last one's end, at 512 rows of 8 pieces, d = 512: split sums summed after
 // 2.2 us, tokens written 2.7, first weights there 4.6, product 6.5, statistics 7.6, end 9.4; before (32x32x16, weights requested
 // behind the sums, two-pass statistics behind barriers that waited for the residual stores) 2.3, 3.2, 4.6, 7.4, 9.1, 10.5.
@@ -1061,7 +1063,7 @@ __global__ __launch_bounds__(NW * 64, OCC == 2 ? 4 : 1) void f2_ln_bf16_kernel(F
   lds_barrier();
   if ((touched[0] ^ touched[1] ^ touched[2] ^ touched[3]) == 0x5a17c0de && p.eps < 0.f) red[0] = 0.f;   // never taken: keeps the warm-up loads
   if constexpr (!EARLY_W) { prefetch_w(); load_residual(); }
-  __builtin_amdgcn_sched_barrier(0);                         // (the residual rows are not waited for before this)
+  __builtin_amdgcn_sched_barrier(0);                         // (where no weights are in LDS, the residual rows are not waited for before this)
   add_bias();
   if constexpr (EARLY_LN && WL == 0) load_ln();
   auto multiply = [&](int ks, const auto& w) {
