@@ -145,34 +145,43 @@ def test_launches_of_thousands_of_rows(dtype, d, H, boost):
 @pytest.mark.parametrize("dtype", ["bf16", "fp16"])
 @pytest.mark.parametrize("d,H,boost", [(256, 4, BOOST), (512, 8, None)])
 def test_one_user_calls_take_the_eight_row_layer_tail(dtype, attention, d, H, boost):
-    """One user per call: the key range is cut into 8 splits, and the layer tail of a launch of at most 1024
-    rows runs with 8 rows per workgroup, every split of a row in flight at once; 342 new rows end inside an
-    8-row group.  The full-recompute route of the same user (1442 rows) takes the 32-row tail."""
+    """One user per call: the key range is cut into 7 pieces, and the layer tail of a launch of at most 1024
+    rows runs with 8 rows per workgroup, every sum of a row in flight at once; 342 new rows end inside an
+    8-row group.  The full-recompute route of the same user (1622 rows with the filler behind its prefix) takes the 16-row tail."""
     cfg = synth.ModelConfig(2, d, H, dtype, attention=attention)
+    assert plan_util.check(plan_util.shim(), [1100], [9], [333], [0], heads=H, dh=d // H)["nsplit"] == 7
+    assert (plan_util.tail_rows(d, 342), plan_util.tail_rows(d, 1280 + 342)) == (8, 16)
     run_three_routes(cfg, 810 + d, [1100], [9], [333], boost=boost)
 
 
 @pytest.mark.parametrize("attention", ["silu", "softmax"])
 @pytest.mark.parametrize("dtype", ["bf16", "fp16"])
-def test_two_key_splits_added_inside_one_workgroup(dtype, attention):
+@pytest.mark.parametrize("L,gs,sums", [
+    ([770, 800, 830, 833, 890, 900, 960, 961, 1000, 1023, 1024, 780, 850, 930, 990, 1010], 2, 1),
+    ([130, 200, 257, 320, 385, 450, 513, 577, 640, 705, 150, 330, 460, 590, 720, 260], 1, 2),     # too unequal to be paired
+])
+def test_two_key_splits_added_inside_one_workgroup(dtype, attention, L, gs, sums):
     """32 work items of up to 256 rows x 8 heads of 64: ranking on the cache cuts the key range in two, and the two
     halves go to the two wavefront groups of ONE workgroup, which add their sums in LDS (in the softmax form after
     bringing them to a common reference score).  Prefix lengths give odd
     and even tile counts (the groups then walk different numbers of tiles), two users bring suffix tiles, the second
     work item of every user ends inside a row block."""
-    L = [130, 200, 257, 320, 385, 450, 513, 577, 640, 705, 150, 330, 460, 590, 720, 260]
     S = [0, 0, 70, 0, 0, 0, 0, 3, 0, 0, 0, 0, 0, 0, 0, 0]
     M = [300, 300, 230, 300, 300, 300, 300, 297, 300, 300, 300, 300, 300, 300, 300, 300]
-    assert sum((s + m + 255) // 256 for s, m in zip(S, M)) * 8 == 256      # the shape that selects that kernel
+    plan = plan_util.check(plan_util.shim(), L, S, M, [0] * 16, heads=8, dh=64)      # the shape that selects that kernel
+    assert (plan["blocks"], plan["gs"], plan["nsplit"]) == (2, gs, sums)
     run_three_routes(synth.ModelConfig(2, 512, 8, dtype, attention=attention), 611, L, S, M)
 
 
 @pytest.mark.parametrize("attention", ["silu", "softmax"])
-def test_four_key_splits_on_128_row_items_pair_up_inside_workgroups(attention):
+@pytest.mark.parametrize("L,gs,sums", [(1900, 2, 2), (1100, 1, 3)])
+def test_four_key_splits_on_128_row_items_pair_up_inside_workgroups(attention, L, gs, sums):
     """One user with 2048 candidates: 16 work items of 128 rows x 8 heads and four key splits, which the two
-    wavefront groups of a workgroup take in pairs (two partial sums reach the layer tail instead of four); 18
-    key tiles over four splits leave the last group with fewer tiles than its partner."""
-    run_three_routes(synth.ModelConfig(2, 512, 8, "bf16", attention=attention), 613, [1100], [0], [2048])
+    wavefront groups of a workgroup take in pairs (two partial sums reach the layer tail instead of four); 30
+    key tiles over four splits leave the last group with fewer tiles than its partner.  18 tiles are cut in three, not paired."""
+    plan = plan_util.check(plan_util.shim(), [L], [0], [2048], [0], heads=8, dh=64)
+    assert (plan["blocks"], plan["gs"], plan["nsplit"]) == (1, gs, sums)
+    run_three_routes(synth.ModelConfig(2, 512, 8, "bf16", attention=attention), 613, [L], [0], [2048])
 
 
 @pytest.mark.parametrize("attention", ["silu", "softmax"])
