@@ -25,7 +25,7 @@ namespace relaygr {
 
 struct AttnParams {
   const AttnTile* tiles;
-  const void* q;      // [rows][d]
+  const void* q;      // [rows][d], 16-bit SiLU form: row octets (octet_off)
   const void* sfx;    // suffix K/V space (single layer)
   float* part;        // [nsplit][rows][d]
   size_t split_stride;
@@ -37,10 +37,11 @@ struct AttnParams {
   float score_mul;    // multiplies <q,k> before SiLU (alpha, or 1 if q is stored pre-scaled)
   // MFMA kernel, SiLU form: a candidate's own key (the diagonal of the candidate block: a per-row dot product, never an
   // M x M tile) is where the sums of one of the row's pieces start (row block qb: piece qb mod pieces), from the
-  // row-major k and v of the new rows; null: left to the layer-tail kernel
+  // k and v of the new rows, in row octets like q; null: left to the layer-tail kernel
   const void* knew;   // [new rows][d]
   const void* vnew;
   int n_prows;        // rows before the first new row
+  int n_rows;
   int gs;             // key splits taken inside one workgroup and added in LDS: 16-bit 1 or 2 (wavefront groups), fp32 1 or 8 (wavefronts)
 };
 
@@ -266,9 +267,10 @@ __global__ __launch_bounds__(NW * GS * 64, (DH >= 128 || GS > 1) ? 1 : 512 / (NW
     int row = at.row0 + (ok ? lr : 0);
     lim[qb] = at.lim(lr);
     if (ok) last_lim = max(last_lim, lim[qb]);
-    const uint16_t* qr = qbase + (size_t)row * p.d + head * DH + g * 8;
+    const int step = SOFTMAX ? 8 : octet_step(row, p.n_rows);         // elements between chunks of eight features
+    const uint16_t* qr = qbase + (SOFTMAX ? (size_t)row * p.d : octet_off(row, p.d)) + (head * (DH / 8) + g) * step;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qf[qb][ks] = *reinterpret_cast<const uint4*>(qr + ks * 16);
+    for (int ks = 0; ks < KS; ++ks) qf[qb][ks] = *reinterpret_cast<const uint4*>(qr + ks * 2 * step);
   }
 
   f32x16_t oacc[DB][NQ];
@@ -297,15 +299,16 @@ __global__ __launch_bounds__(NW * GS * 64, (DH >= 128 || GS > 1) ? 1 : 512 / (NW
     const int lr = wave * 32 * NQ + qb * 32 + l32;
     cand[qb] = own_key && (qb % nsplit) == split && lr < at.nrows && at.pos0 + lr >= at.S;   // new rows: suffix rows, then candidates
     if (cand[qb]) {
-      const size_t nb = (size_t)(at.row0 + lr - p.n_prows) * p.d + head * DH;
+      const int nr = at.row0 + lr - p.n_prows, step = octet_step(nr, p.n_rows - p.n_prows);
+      const size_t nb = octet_off(nr, p.d) + head * (DH / 8) * step;
       const uint16_t* kn = reinterpret_cast<const uint16_t*>(p.knew) + nb;
       const uint16_t* vn = reinterpret_cast<const uint16_t*>(p.vnew) + nb;
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) kself[qb][ks] = *reinterpret_cast<const uint4*>(kn + ks * 16 + g * 8);
+      for (int ks = 0; ks < KS; ++ks) kself[qb][ks] = *reinterpret_cast<const uint4*>(kn + (2 * ks + g) * step);
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll
-        for (int e4 = 0; e4 < 4; ++e4) vself[qb][db][e4] = *reinterpret_cast<const uint2*>(vn + db * 32 + 8 * e4 + 4 * g);
+        for (int e4 = 0; e4 < 4; ++e4) vself[qb][db][e4] = *reinterpret_cast<const uint2*>(vn + (4 * db + e4) * step + 4 * g);
     }
   }
   auto start_from_own_key = [&]() {

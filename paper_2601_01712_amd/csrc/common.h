@@ -113,6 +113,13 @@ __host__ __device__ __forceinline__ size_t panel_off(int row, int k, int K) {
   return ((size_t)panel * (K >> 4) + ks) * 2048 + (size_t)rb * 512 + (g * 32 + l32) * 8 + j;
 }
 
+// Row octets: q, and the new rows' k and v, of the 16-bit SiLU form.  Eight rows at a time, in them the 16-byte chunks of eight features, each of
+// the eight rows: [row/8][feature/8][row%8][feature%8].  The last octet of an array holds as many rows as are left, so that the array is as large as
+// in row-major order.  `chunk`: feature / 8.  Whoever takes a chunk of 32 consecutive rows (an operand of the attention's product) reads 128 bytes
+// in a run, where row-major order gives a memory line for every row.
+__device__ __forceinline__ int octet_step(int row, int n_rows) { return min(8, n_rows - (row & ~7)) * 8; }     // elements between a row's chunks
+__device__ __forceinline__ size_t octet_off(int row, int d) { return (size_t)(row & ~7) * d + (row & 7) * 8; }  // its chunk 0
+
 // Barrier for data that went through LDS only: unlike __syncthreads() it does not wait for global stores and loads in flight.
 __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");

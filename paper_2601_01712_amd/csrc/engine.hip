@@ -856,7 +856,7 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
         fp.u = (uint16_t*)ubuf; fp.q = (uint16_t*)qbuf; fp.knew = (uint16_t*)knew; fp.vnew = (uint16_t*)vnew; fp.sfx = (uint16_t*)sfx;
         fp.users = d_users; fp.rt = rt; fp.d = d; fp.dh = dh; fp.n_prows = p.n_prows; fp.layer = l;
         fp.row_begin = r0; fp.row_end = r1;           // (r0: a multiple of kPrefixRowAlign)
-        fp.cm = cm; fp.q_mul = q_mul; fp.stream_out = (r1 - r0) >= kF1StreamMinRows ? 1 : 0;
+        fp.cm = cm; fp.q_mul = q_mul; fp.octets = softmax ? 0 : 1; fp.stream_out = (r1 - r0) >= kF1StreamMinRows ? 1 : 0;
         const int cols = cm.nblk * (d / 128);
         auto launch = [&](auto kernel, int tile_rows, int tile_cols) {
           fp.n_mtiles = (r1 - r0 + tile_rows - 1) / tile_rows;
@@ -901,7 +901,7 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
     ap.ml = ml; ap.ml_stride = (size_t)R * H * 2; ap.gs = cut.gs;
     // 16-bit SiLU form: the attention kernel adds the candidates' own keys, so the layer tail does not read q, k, v again
     const bool self_in_attn = bf16 && !softmax;
-    ap.knew = self_in_attn ? (const void*)knew : nullptr; ap.vnew = vnew; ap.n_prows = p.n_prows;
+    ap.knew = self_in_attn ? (const void*)knew : nullptr; ap.vnew = vnew; ap.n_prows = p.n_prows; ap.n_rows = R;
     const bool own_list = bf16 && last && p.n_prows > 0;
     const int nt = (int)(own_list ? cut.last.size() : !bf16 && last ? rows_new.size() : cut.all.size());   // (fp32: new rows first)
     ap.n_tiles = nt;

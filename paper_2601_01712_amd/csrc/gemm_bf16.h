@@ -197,6 +197,7 @@ struct F1Params {
   int d, dh, n_prows, layer, row_begin, row_end, n_mtiles;
   ColMap cm;
   float q_mul;
+  int octets;               // q, and k and v of new rows, leave in row octets (octet_off) and not row-major
   int stream_out;           // weight-stationary kernel: outputs leave with streaming stores (launches that write far more than L2 holds)
 };
 
@@ -249,16 +250,18 @@ __global__ __launch_bounds__(256, TM == 4 ? 2 : NSTAGE == 3 ? 3 : 1) void f1_gem
   const int tile_user = prefix_tile ? p.rt.user[m0] : 0;
   if (prefix_tile && p.rt.kind[m0] == kRowPad) return;     // filler behind the user's last K/V tile
 
-  // In the store phase a thread owns 16-byte chunk tid % CH of rows tid / CH + RPP*it of the
-  // tile; the kinds of new rows (candidate or suffix) and the biases are asked for first, so that run()'s waits, which count younger loads, need not count them.
+  // In the store phase a thread owns 16-byte chunk fc of rows t0 + RPP*it of the tile.  Neighbouring threads take neighbouring chunks of a row where
+  // rows are stored whole, and one chunk of the eight rows of an octet where these lie side by side (row octets, K tiles).  The kinds of new rows (candidate or suffix) and the biases are asked for first, so that run()'s waits, which count younger loads, need not count them.
   constexpr int CH = 8 * TN, RPP = 256 / CH, ITS = ROWS / RPP;   // chunks of a row, rows per pass of the store phase, passes
   const bool by_kind = (blk == 1 || blk == 3) && !prefix_tile;
+  const bool octets = p.octets && (blk == 2 || by_kind), rows_first = octets || (blk == 3 && prefix_tile);
+  const int t0 = rows_first ? (tid & 7) + tid / (8 * CH) * 8 : tid / CH, fc = rows_first ? (tid >> 3) % CH : tid % CH;
   int kinds[ITS];
 #pragma unroll
   for (int it = 0; it < ITS; ++it) kinds[it] = kRowCand;
   if (by_kind) {
 #pragma unroll
-    for (int it = 0; it < ITS; ++it) kinds[it] = p.rt.kind[min(m0 + tid / CH + RPP * it, p.row_end - 1)];
+    for (int it = 0; it < ITS; ++it) kinds[it] = p.rt.kind[min(m0 + t0 + RPP * it, p.row_end - 1)];
   }
   uint2 bias[TN][4];
 #pragma unroll
@@ -337,11 +340,11 @@ __global__ __launch_bounds__(256, TM == 4 ? 2 : NSTAGE == 3 ? 3 : 1) void f1_gem
     }
   lds_barrier();
   // ROWS tokens x CH chunks of 8 features
-  const int t0 = tid / CH, fc = tid % CH, c = c0 + fc * 8;   // c: feature inside the block
+  const int c = c0 + fc * 8;                                 // feature inside the block
   const int head = c >> dh_sh, f = c - (head << dh_sh);
   const int n_rows = p.row_end - m0;
   // (u and q of filler rows are written too: nothing reads them, and a filler row's inputs are zeros)
-  uint16_t* rows_out = (blk == 0 ? p.u + (size_t)m0 * d : blk == 2 ? p.q + (size_t)m0 * d : (blk == 3 ? p.knew : p.vnew) + ((int64_t)m0 - p.n_prows) * d) + c;
+  uint16_t* rows_out = blk == 0 ? p.u + (size_t)m0 * d : blk == 2 ? p.q + (size_t)m0 * d : (blk == 3 ? p.knew : p.vnew) + ((int64_t)m0 - p.n_prows) * d;
   if (blk == 3 && prefix_tile) {                             // K of prefix rows (V took the other path)
     const UserDesc& tud = p.users[tile_user];               // (as above)
     const int L = tud.L, Lceil = (L + kTile - 1) / kTile * kTile;
@@ -364,7 +367,7 @@ __global__ __launch_bounds__(256, TM == 4 ? 2 : NSTAGE == 3 ? 3 : 1) void f1_gem
     if (t >= n_rows) continue;
     const uint4 val = *reinterpret_cast<const uint4*>(&lds[t * kStageLd + fc * 8]);
     if (kinds[it] == kRowCand) {
-      st_out(rows_out + (size_t)t * d, val, 0);
+      st_out(rows_out + (octets ? octet_off(t, d) + (c >> 3) * octet_step(t, n_rows) : (size_t)t * d + c), val, 0);
     } else {                                                 // k or v of a suffix row
       const int row = m0 + t, idx = p.rt.idx[row], rr = idx & 63;
       uint16_t* base = p.sfx + p.users[p.rt.user[row]].sfx_tile0 + (int64_t)(idx >> 6) * (2 * kTile * d) + head * 2 * kTile * dh;
@@ -563,7 +566,9 @@ __global__ __launch_bounds__(512, 1) void f1_ws_bf16_kernel(F1Params p) {
     const bool any_suffix = !prefix_unit && __builtin_amdgcn_ballot_w64(kind_row != kRowCand) != 0;
     // where 16-byte chunk (row tk of block i, features c0 + jh*64 + fc*8 ..) goes: row-major, or the K tile of a prefix unit
     const bool row_major = blk == 0 || blk == 2 || !prefix_unit;
-    const int tk0 = lane >> 3;                                   // this lane stores chunk lane & 7 of rows tk0 + 8 n of a 32-row block
+    // this lane stores chunk fc of rows tk0 + 8 n of a 32-row block (neighbouring lanes: see the tiled kernel)
+    const bool octets = p.octets && row_major && blk != 0, rows_first = octets || !row_major;
+    const int tk0 = rows_first ? lane & 7 : lane >> 3;
     uint16_t* rows_out = blk == 0 ? p.u + (size_t)m0 * d : blk == 2 ? p.q + (size_t)m0 * d : (blk == 3 ? p.knew : p.vnew) + ((int64_t)m0 - p.n_prows) * d;
     const int n_rows = p.row_end - m0;
 #pragma unroll
@@ -583,7 +588,7 @@ __global__ __launch_bounds__(512, 1) void f1_ws_bf16_kernel(F1Params p) {
           }
         }
         __builtin_amdgcn_wave_barrier();   // LDS serves a wavefront's accesses in order: the reads below see the writes above
-        int fc = lane & 7;
+        int fc = rows_first ? lane >> 3 : lane & 7;
         // (opaque to the compiler: otherwise it hoists the index arithmetic of the rare suffix-V scatter below out of
         // the unit loop, 32 values per lane that it then has to spill -- 16 MiB of scratch writes per launch)
         asm volatile("" : "+v"(fc));
@@ -594,10 +599,12 @@ __global__ __launch_bounds__(512, 1) void f1_ws_bf16_kernel(F1Params p) {
         };
         if (row_major && !(any_suffix && (blk == 1 || blk == 3))) {
           // (u and q of filler rows are written too: nothing reads them, and a filler row's inputs are zeros)
-          uint16_t* dst = rows_out + (i * 32 + tk0) * d + c;
+          uint16_t* dst = rows_out + (octets ? i * 32 * d + tk0 * 8 : (i * 32 + tk0) * d + c);
 #pragma unroll
-          for (int n = 0; n < 4; ++n)
-            if (i * 32 + tk0 + 8 * n < n_rows) st_out(dst + n * 8 * d, staged(n), p.stream_out);
+          for (int n = 0; n < 4; ++n) {
+            const int rl = i * 32 + tk0 + 8 * n;
+            if (rl < n_rows) st_out(dst + n * 8 * d + (octets ? (c >> 3) * octet_step(rl, n_rows) : 0), staged(n), p.stream_out);
+          }
         } else if (prefix_unit) {                                // K of prefix rows (V took the other path)
           uint16_t* kt = tile + head * 2 * kTile * dh;
 #pragma unroll
@@ -613,7 +620,10 @@ __global__ __launch_bounds__(512, 1) void f1_ws_bf16_kernel(F1Params p) {
             const int rl = i * 32 + tk0 + 8 * n, row = m0 + rl;
             if (rl >= n_rows) break;
             const uint4 v = staged(n);
-            if (p.rt.kind[row] == kRowCand) { st_out(rows_out + rl * d + c, v, p.stream_out); continue; }
+            if (p.rt.kind[row] == kRowCand) {
+              st_out(rows_out + (octets ? octet_off(rl, d) + (c >> 3) * octet_step(rl, n_rows) : (size_t)(rl * d + c)), v, p.stream_out);
+              continue;
+            }
             const int pos = p.rt.idx[row], rr = pos & 63;
             uint16_t* base = p.sfx + p.users[p.rt.user[row]].sfx_tile0 + (int64_t)(pos >> 6) * (2 * kTile * d) + head * 2 * kTile * dh;
             if (blk == 3) {

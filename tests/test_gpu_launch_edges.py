@@ -132,3 +132,12 @@ CAUSAL = [
 def test_causal_wavefronts(case, attention):
     heads, L, S, M = CAUSAL[case]
     run_three_routes(synth.ModelConfig(2, 128, heads, "bf16", attention=attention), 7300 + case, L, S, M, page_tokens=64, boost=BOOST)
+
+
+@pytest.mark.parametrize("heads", [1, 2, 4])
+@pytest.mark.parametrize("first", [1, 3, 7, 8, 9, 33])
+def test_rows_that_end_inside_an_octet(first, heads):
+    """q and the new rows' k and v lie in groups of eight rows, the last one as large as what is left: a user whose rows start inside a group, suffix
+    rows in the first and the last one, all new rows less than one group, the last group of one to eight rows (heads: d_head 128, 64, 32)."""
+    run_three_routes(synth.ModelConfig(2, 128, heads, "bf16"), 7500 + first, [70, 9], [0, 3], [first, 2], page_tokens=64, boost=BOOST)
+    run_three_routes(synth.ModelConfig(2, 128, heads, "fp16"), 7550 + first, [70], [first % 3], [first], page_tokens=64, boost=BOOST)
