@@ -96,8 +96,8 @@ inline int key_tiles(const AttnTile& a) {
   return a.kind == 0 ? (a.pos0 + a.nrows + kTile - 1) / kTile : (a.L + kTile - 1) / kTile + (a.S + kTile - 1) / kTile;
 }
 
-// 32-row blocks per wavefront of the 16-bit kernel (a work item is 128 rows of each).  It reads half as much LDS and L2 per
-// score element with 256-row items; they are used when that still yields at least one workgroup per compute unit.
+// 128-row blocks of a work item of the 16-bit kernel: two 32-row blocks for each of four wavefronts (d_head 128: one for each of eight).  It reads half as
+// much L2 (d_head 64: and LDS) per score element with 256-row items; they are used when that still yields at least one workgroup per compute unit.
 inline int attn_row_blocks(const std::vector<UserDesc>& users, int heads, int dh) {
   if (dh != 64 && dh != 128) return 1;
   int64_t items256 = 0;

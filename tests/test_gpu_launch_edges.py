@@ -141,3 +141,15 @@ def test_rows_that_end_inside_an_octet(first, heads):
     rows in the first and the last one, all new rows less than one group, the last group of one to eight rows (heads: d_head 128, 64, 32)."""
     run_three_routes(synth.ModelConfig(2, 128, heads, "bf16"), 7500 + first, [70, 9], [0, 3], [first, 2], page_tokens=64, boost=BOOST)
     run_three_routes(synth.ModelConfig(2, 128, heads, "fp16"), 7550 + first, [70], [first % 3], [first], page_tokens=64, boost=BOOST)
+
+
+@pytest.mark.parametrize("attention", ["silu", "softmax"])
+@pytest.mark.parametrize("dtype", ["bf16", "fp16"])
+def test_d_head_128_items_of_eight_wavefronts(dtype, attention):
+    """64 users x 4 heads of 128 make 256-row work items: rows that end in the first, in the last and just behind a wavefront's 32, behind a whole
+    item, suffix rows, key tiles that only some of an item's wavefronts see (causal rows of 1 to 300 keys), pieces of one key tile."""
+    L = [(1, 63, 64, 65, 130, 191, 257, 300)[u % 8] for u in range(64)]
+    S = [(0, 0, 3, 0, 65)[u % 5] for u in range(64)]
+    M = [(1, 31, 33, 10, 97, 5, 64)[u % 7] for u in range(63)] + [257]
+    assert plan_util.check(plan_util.shim(), L, S, M, [0] * 64, heads=4, dh=128)["blocks"] == plan_util.check(plan_util.shim(), L, heads=4, dh=128)["blocks"] == 2
+    run_three_routes(synth.ModelConfig(2, 512, 4, dtype, attention=attention), 7700, L, S, M, page_tokens=64)
