@@ -95,3 +95,4 @@ extern "C" int plan_check(int n, const int32_t* L, const int32_t* S, const int32
 
 extern "C" int tail_rows_of(int d, int rows) { return tail_rows(d, rows); }
 extern "C" int f1_tile_of(int d, int nblk, int rows, int n_cus) { return (int)f1_tile(d, nblk, rows, n_cus); }
+extern "C" int attn_groups_of(int softmax, int64_t pieces, int longest, int n_cus) { return attn_groups(softmax != 0, pieces, longest, n_cus); }

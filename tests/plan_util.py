@@ -50,6 +50,11 @@ def tail_rows(d, rows):
     return shim().tail_rows_of(d, rows)
 
 
+def attention_groups(softmax, pieces, longest, n_cus=256):
+    """Wavefront groups of an attention workgroup at d_head 64, for a ranking of cached users whose pieces are not paired already."""
+    return shim().attn_groups_of(int(softmax), C.c_int64(pieces), longest, n_cus)
+
+
 def projection_tile(d, rows, nblk=4, n_cus=256):
     """Tile of a projection launch: `nblk` of the four column blocks [u | v | q | k] of `rows` rows."""
     return ("64x64", "64x128", "128x128", "128x128/3", "stationary", "256x128")[shim().f1_tile_of(d, nblk, rows, n_cus)]

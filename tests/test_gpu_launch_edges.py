@@ -153,3 +153,25 @@ def test_d_head_128_items_of_eight_wavefronts(dtype, attention):
     M = [(1, 31, 33, 10, 97, 5, 64)[u % 7] for u in range(63)] + [257]
     assert plan_util.check(plan_util.shim(), L, S, M, [0] * 64, heads=4, dh=128)["blocks"] == plan_util.check(plan_util.shim(), L, heads=4, dh=128)["blocks"] == 2
     run_three_routes(synth.ModelConfig(2, 512, 4, dtype, attention=attention), 7700, L, S, M, page_tokens=64)
+
+
+#   attention, dtype, prefix lengths, suffix lengths, candidates; pieces, the longest one's key tiles and the groups that take it (4 heads of 64)
+GROUPS = [
+    ("silu", "bf16", [3300], [0], [130], 64, 7, 1),            # too short
+    ("silu", "fp16", [3900], [70], [130], 64, 8, 2),           # four tiles a group, the last piece one tile short
+    ("silu", "bf16", [4100, 0, 60], [3, 0, 65], [129, 5, 0], 76, 9, 2),     # users of one piece: no key, one tile and suffix tiles
+    ("softmax", "bf16", [7300], [0], [33], 32, 15, 1),
+    ("softmax", "fp16", [7700, 64], [9, 0], [33, 4], 36, 16, 2),
+]
+
+
+@pytest.mark.parametrize("case", range(len(GROUPS)))
+def test_pieces_by_two_groups_of_wavefronts(case):
+    """Launches of no more pieces than compute units: the two groups of a workgroup take the halves of a piece and add them in LDS, pieces of odd
+    lengths, of one key tile and of none among them."""
+    attention, dtype, L, S, M, pieces, longest, groups = GROUPS[case]
+    plan = plan_util.check(plan_util.shim(), L, S, M, [0] * len(L), heads=4, dh=64)
+    tiles = (max(L) + 63) // 64 + (S[0] + 63) // 64
+    assert (plan["blocks"], plan["gs"], plan["items"] * 4, -(-tiles // plan["nsplit"])) == (1, 1, pieces, longest)
+    assert plan_util.attention_groups(attention == "softmax", pieces, longest) == groups
+    run_three_routes(synth.ModelConfig(2, 256, 4, dtype, attention=attention), 7800 + case, L, S, M)
