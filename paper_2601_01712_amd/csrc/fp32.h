@@ -323,9 +323,10 @@ __global__ __launch_bounds__(256, TB == 1 ? 4 : 2) void f1_f32_kernel(F1F32Param
 // As in the 16-bit path everything between the attention and the next projections is local to a row: a workgroup takes 16
 // rows over the full width.  Each of its 16 wavefronts gates a row (lane = d/64 features) into LDS; the product is feature-major
 // (16x16x4: a lane ends up with 4 consecutive features of one token), W2 streamed from L2 straight into registers, PF
-// groups of 16 k ahead; LayerNorm statistics by two lane exchanges and one exchange between wavefronts.  512 rows at d = 256:
-// 14 us, bound by the chain of trips to memory and by W2 (256 KiB) through one compute unit's path.  More of W2 in flight, up to a
-// wavefront's whole share of it in registers with the residual row, made it 15.4 us.
+// groups of 16 k ahead, the two that share the rows' lines together; LayerNorm statistics by two lane exchanges and one exchange between
+// wavefronts.  512 rows at d = 256: 12.2 us (13.4 with the groups apart), bound by the chain of trips to memory and by W2 (256 KiB) through one
+// compute unit's path.  With the groups apart, more of W2 in flight, up to a wavefront's whole share of it in registers with the residual row, made
+// it 15.4 us.
 struct TailF32Params {
   const float* part; int nsplit; size_t split_stride;
   const float* ml; size_t ml_stride; int n_heads;   // softmax form
@@ -474,16 +475,20 @@ __global__ __launch_bounds__(1024) void tail_f32_kernel(TailF32Params p) {
 #pragma unroll
     for (int s = 0; s < PF; ++s) {
       const float4 y = *reinterpret_cast<const float4*>(yl + 16 * (m0 + s));
-      float4 cw[FB];
-#pragma unroll
-      for (int j = 0; j < FB; ++j) cw[j] = wf[s][j];
-      // (unconditional, so that the compiler can count what is outstanding)
-#pragma unroll
-      for (int j = 0; j < FB; ++j) wf[s][j] = *reinterpret_cast<const float4*>(w[j] + 16 * min(m0 + s + PF, MS - 1));
 #pragma unroll
       for (int t = 0; t < 4; ++t)
 #pragma unroll
-        for (int j = 0; j < FB; ++j) acc[j] = mfma16_f32(f4_at(cw[j], t), f4_at(y, t), acc[j]);
+        for (int j = 0; j < FB; ++j) acc[j] = mfma16_f32(f4_at(wf[s][j], t), f4_at(y, t), acc[j]);
+      // (the next fragments by twos: two groups of 16 k are one 128-byte line of each row, and sixteen wavefronts ask for more between one
+      // group and the next than the L1 holds, so that it fetched every line twice.  By fours, fewer are in flight: d = 512 344 -> 349 us a call.
+      // Unconditional, so that the compiler can count what is outstanding.)
+      if (s & 1) {
+#pragma unroll
+        for (int j = 0; j < FB; ++j)
+#pragma unroll
+          for (int h = 1; h >= 0; --h) wf[s - h][j] = *reinterpret_cast<const float4*>(w[j] + 16 * min(m0 + s - h + PF, MS - 1 - h));
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
   }
   const bool want_score = p.scores != nullptr;
