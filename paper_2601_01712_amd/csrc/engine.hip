@@ -977,7 +977,11 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
                 else if (vr16) hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 512, 8, 1, SM, 1, 16, 4, NB>), grid, dim3(512), 0, st, fp);
                 else hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 512, 8, 2, SM, 1, 32, 0, NB2>), grid, dim3(512), 0, st, fp);
                 break;
-              default: hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 1024, 8, 2, SM, 1, 32, 0, 1>), grid, dim3(512), 0, st, fp); break;
+              default:
+                if (vr8) hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 1024, 8, 1, SM, 1, 8, 0, NB>), grid, dim3(512), 0, st, fp);
+                else if (vr16) hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 1024, 8, 1, SM, 1, 16, 0, 1>), grid, dim3(512), 0, st, fp);
+                else hipLaunchKernelGGL((f2_ln_bf16_kernel<HT, 1024, 8, 2, SM, 1, 32, 0, 1>), grid, dim3(512), 0, st, fp);
+                break;
             }
           };
           auto launch_sums = [&](auto sm) {

@@ -659,8 +659,8 @@ __global__ __launch_bounds__(512, 1) void f1_ws_bf16_kernel(F1Params p) {
 // workgroup (d = 512), so global loads that depend on no result go out as early as the registers allow: the rows' split sums, W2's first
 // k-steps and the residual rows before the first wait; and the gate waits for its own loads only, which takes loads the compiler can
 // count (none behind a branch, none in the global_load_lds form: see BufferView) and barriers that wait for LDS alone.  Not so: the launches with
-// weights in LDS wait once, between gate and product, for all that has been asked for; and where EARLY_LN is false (64-row workgroups at d = 512,
-// d = 1024) gain and offset are loaded in the output pass, one round trip for each feature block behind the stores of the one before.
+// weights in LDS wait once, between gate and product, for all that has been asked for; and where EARLY_LN is false (64-row workgroups at
+// d = 512) gain and offset are loaded in the output pass, one round trip for each feature block behind the stores of the one before.
 // Of the launch's time from its first workgroup's start to its last one's end, at 512 rows of 8 pieces, d = 512: split sums summed after
 // 2.2 us, tokens written 2.7, first weights there 4.6, product 6.5, statistics 7.6, end 9.4; before (32x32x16, weights requested
 // behind the sums, two-pass statistics behind barriers that waited for the residual stores) 2.3, 3.2, 4.6, 7.4, 9.1, 10.5.
@@ -939,14 +939,16 @@ __device__ __forceinline__ void l2_touch(const void* base, int lines, int share,
 // few thousand rows (one user per call): with 32 rows each they would occupy a few dozen compute units, each
 // pulling 16 KiB of split partial sums per row through its own memory path; with VR = 8 or 16 four times or
 // twice as many units share that.
-// NB: pieces of each row's sums in flight (sums_at_once), with rows enough for every wavefront no more than two, at d = 1024 one.
+// NB: pieces of each row's sums in flight (sums_at_once), with rows enough for every wavefront no more than two, at d = 1024 with more than 8 rows one.
+// d = 1024 keeps four k-steps of weights (softmax form, with q, k and v of the rows: two) and two rows' sums in flight, 254 registers of 256: with one of
+// each, 130 registers, 40 users of 1000 keys 3524 -> 3501 us a call, one of 4096 and 512 candidates 610 -> 598 (32 rows a workgroup).
 // WL > 0: launches of at most one workgroup per compute unit.  The first WL k-steps of each wavefront's weights go straight to
 // LDS and the next PF into registers, all requested before the gate, which waits for other memory; the product then finds them there.
 template <typename H, int D, int NW, int TB, bool SM, int OCC, int VR, int WL, int NB>
 __global__ __launch_bounds__(NW * 64, OCC == 2 ? 4 : 1) void f2_ln_bf16_kernel(F2LnParams p) {
   constexpr int KS = D / 32;            // k-steps
   constexpr int FB = D / 16 / NW;       // 16-feature blocks per wavefront
-  constexpr int PF = FB >= 8 ? 1 : (OCC == 2 ? 2 : 4);   // k-steps of weight fragments in flight per wavefront
+  constexpr int PF = FB >= 8 ? (SM ? 2 : 4) : (OCC == 2 ? 2 : 4);   // k-steps of weight fragments in flight per wavefront
   constexpr int ROWS = 16 * TB;         // rows of the product: TB blocks of 16 share one pass over W2
   static_assert(NW == tail_waves(D) && FB == tail_blocks(D) && FB * NW * 16 == D && (KS - WL) % PF == 0 && KS - WL >= PF, "shape");
   __shared__ __attribute__((aligned(16))) uint16_t tok[ROWS * D];         // tok_off
@@ -965,7 +967,7 @@ __global__ __launch_bounds__(NW * 64, OCC == 2 ? 4 : 1) void f2_ln_bf16_kernel(F
   // The gate makes the tokens: each wavefront takes VROWS/NW rows, a few at a time
   // so that their loads are in flight together.  The first group's loads go out before anything
   // else, since they are what the workgroup needs first.
-  constexpr int RPW = VROWS / NW, GMAX = OCC == 2 ? 2 : (D >= 1024 ? 1 : TB * FB >= 16 ? 2 : (SM ? 2 : 4)), GROUP = RPW < GMAX ? RPW : GMAX;
+  constexpr int RPW = VROWS / NW, GMAX = OCC == 2 ? 2 : (D >= 1024 ? (SM ? 1 : 2) : TB * FB >= 16 ? 2 : (SM ? 2 : 4)), GROUP = RPW < GMAX ? RPW : GMAX;
   static_assert(RPW >= 1 && RPW % GROUP == 0, "rows per wavefront");
   GateRow<D / 64, SM> gr[GROUP];
   uint32_t gw[D / 128], ow[D / 128];
@@ -1040,7 +1042,7 @@ __global__ __launch_bounds__(NW * 64, OCC == 2 ? 4 : 1) void f2_ln_bf16_kernel(F
   };
   // gain and offset of the LayerNorm that follows the product: requested early where the registers allow it,
   // so that the output pass does not wait for them
-  constexpr bool EARLY_LN = OCC == 1 && FB <= 4;
+  constexpr bool EARLY_LN = OCC == 1;
   uint2 lng[FB], lno[FB];
   auto load_ln = [&]() {
 #pragma unroll

@@ -35,10 +35,12 @@ inline F1Tile f1_tile(int d, int nblk, int rows, int n_cus) {
 
 // Rows of a layer-tail workgroup.  A few hundred rows (one user per call): 8 each, so that four times as many compute units share the split partial
 // sums; then 16; both as long as that is at most one workgroup per compute unit.  Four row blocks of 16 halve the passes over W2 once that still
-// leaves every compute unit about two workgroups.
+// leaves every compute unit about two workgroups.  (d = 1024, 8 layers, us a call with 32 rows / with 8 or 16: one user of 4096 keys and 512 candidates 599 /
+// 442, 100 and 1000 keys 516 / 376, 1000 and 1000 540 / 447, 1500 and 1000 590 / 519; 5 users of 500 and 1000 772 / 713, 8 864 / 831; pre-inference of
+// 3500 keys 889 / 845.  At d = 128 not tried.)
 constexpr int kTailVr8MaxRows = 1024, kTailVr16MaxRows = 4096, kTailVr64MinRows = 64 * 384;
 inline int tail_rows(int d, int rows) {
-  if (d == 256 || d == 512) {
+  if (d >= 256) {
     if (rows <= kTailVr8MaxRows) return 8;
     if (rows <= kTailVr16MaxRows) return 16;
   }

@@ -175,3 +175,21 @@ def test_pieces_by_two_groups_of_wavefronts(case):
     assert (plan["blocks"], plan["gs"], plan["items"] * 4, -(-tiles // plan["nsplit"])) == (1, 1, pieces, longest)
     assert plan_util.attention_groups(attention == "softmax", pieces, longest) == groups
     run_three_routes(synth.ModelConfig(2, 256, 4, dtype, attention=attention), 7800 + case, L, S, M)
+
+
+#   prefix lengths, suffix lengths, candidates; rows a workgroup
+WIDE_TAIL = [
+    ([600], [3], [4], 8),                              # 7 rows of five sums: a workgroup not full
+    ([2100, 70], [0, 5], [520, 0], 8),                 # unequal numbers of sums
+    ([70], [0], [1024], 8),
+    ([600], [1], [1024], 16),                          # 1025: a workgroup of one row
+    ([65] * 17, [0] * 17, [250] * 17, 32),             # 4250
+]
+
+
+@pytest.mark.parametrize("attention", ["silu", "softmax"])
+@pytest.mark.parametrize("case", range(len(WIDE_TAIL)))
+def test_layer_tail_edges_at_width_1024(case, attention):
+    L, S, M, rows = WIDE_TAIL[case]
+    assert plan_util.tail_rows(1024, sum(S) + sum(M)) == rows
+    run_three_routes(synth.ModelConfig(2, 1024, 8, "fp16" if case % 2 else "bf16", attention=attention), 7900 + case, L, S, M, page_tokens=64)
