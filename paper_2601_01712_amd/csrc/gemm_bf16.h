@@ -940,15 +940,18 @@ __device__ __forceinline__ void l2_touch(const void* base, int lines, int share,
 // pulling 16 KiB of split partial sums per row through its own memory path; with VR = 8 or 16 four times or
 // twice as many units share that.
 // NB: pieces of each row's sums in flight (sums_at_once), with rows enough for every wavefront no more than two, at d = 1024 with more than 8 rows one.
-// d = 1024 keeps four k-steps of weights (softmax form, with q, k and v of the rows: two) and two rows' sums in flight, 254 registers of 256: with one of
-// each, 130 registers, 40 users of 1000 keys 3524 -> 3501 us a call, one of 4096 and 512 candidates 610 -> 598 (32 rows a workgroup).
+// d = 1024, 32 rows a workgroup: one k-step of weights in flight; two rows' sums, and gain and offset of the output pass behind the gate (us a call with one
+// row's and in the output pass / so: 16 users of 4096 keys 2146 / 2132, 40 of 1000 3527 / 3510, 12 of 2000 1419 / 1412; with four k-steps as well 2130,
+// 3512, 1415, the same within what the runs differ by, 2 to 8).  8 and 16 rows: four k-steps (softmax form, with q, k and v of the rows: two), which
+// 16 rows gain from (one of each / so: five users of 500 keys and 800 candidates 816 / 804, pre-inference of 3500 keys 838 / 827, full recompute of
+// 2000 752 / 742; 8 rows, one user of 4096 keys and 512 candidates 428 / 430).
 // WL > 0: launches of at most one workgroup per compute unit.  The first WL k-steps of each wavefront's weights go straight to
 // LDS and the next PF into registers, all requested before the gate, which waits for other memory; the product then finds them there.
 template <typename H, int D, int NW, int TB, bool SM, int OCC, int VR, int WL, int NB>
 __global__ __launch_bounds__(NW * 64, OCC == 2 ? 4 : 1) void f2_ln_bf16_kernel(F2LnParams p) {
   constexpr int KS = D / 32;            // k-steps
   constexpr int FB = D / 16 / NW;       // 16-feature blocks per wavefront
-  constexpr int PF = FB >= 8 ? (SM ? 2 : 4) : (OCC == 2 ? 2 : 4);   // k-steps of weight fragments in flight per wavefront
+  constexpr int PF = FB >= 8 ? (TB > 1 ? 1 : SM ? 2 : 4) : (OCC == 2 ? 2 : 4);   // k-steps of weight fragments in flight per wavefront
   constexpr int ROWS = 16 * TB;         // rows of the product: TB blocks of 16 share one pass over W2
   static_assert(NW == tail_waves(D) && FB == tail_blocks(D) && FB * NW * 16 == D && (KS - WL) % PF == 0 && KS - WL >= PF, "shape");
   __shared__ __attribute__((aligned(16))) uint16_t tok[ROWS * D];         // tok_off
