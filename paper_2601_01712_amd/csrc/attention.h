@@ -43,6 +43,7 @@ struct AttnParams {
   int n_prows;        // rows before the first new row
   int n_rows;
   int gs;             // key splits taken inside one workgroup and added in LDS: 16-bit 1 or 2 (wavefront groups), fp32 1 or 8 (wavefronts)
+  int shared_tiles;   // 16-bit, gs = 2: key tiles from which on a piece is shared between the groups (attn_shared_tiles)
 };
 
 // ---- bf16 MFMA kernel ---------------------------------------------------------------------------
@@ -213,8 +214,9 @@ __device__ __forceinline__ void softmax_track(const f32x16_t (&s)[NQ], const int
 // consecutive key splits with a tile ring of its own, and at the end the second group's sums go through LDS to the
 // first, which adds them (first + second, a fixed order; in the softmax form after bringing both to the larger of their
 // reference scores) and writes one partial sum: two key splits cost the layer tail the HBM traffic of one, or, in launches of no
-// more workgroups than compute units, a piece takes half as long (attn_groups).  Both
-// groups pass the same barriers; a group with fewer tiles pads with empty ones.
+// more workgroups than compute units, a piece takes half as long (attn_shared_tiles: the short pieces of such a launch are the first
+// group's alone, which sums them as a workgroup of one group does).  Both groups pass the same barriers; a group with fewer tiles pads
+// with empty ones.
 template <typename H, int DH, int NQ, int NW, bool SOFTMAX, int GS = 1>
 __global__ __launch_bounds__(NW * GS * 64, (DH >= 128 || GS > 1) ? 1 : 512 / (NW * 64)) void attn_bf16_kernel(AttnParams p) {   // DH = 128: the 96 KiB tile ring admits one workgroup per compute unit
   constexpr int KS = DH / 16;              // k-steps of the first product
@@ -247,11 +249,12 @@ __global__ __launch_bounds__(NW * GS * 64, (DH >= 128 || GS > 1) ? 1 : 512 / (NW
   const int grp = GS == 1 ? 0 : __builtin_amdgcn_readfirstlane((tid >> 6) / NW);    // wavefront group (a scalar: loop counts below depend on it)
   const int wave = (tid >> 6) - grp * NW;           // wavefront inside its group: its rows, its share of a tile
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);
-  const int split = split_ext * GS + grp, nsplit = at.parts * GS;   // this group's key split of all
+  const bool shared = GS == 2 && at.t1 - at.t0 >= p.shared_tiles;   // both groups take part of the piece (uniform over the workgroup)
+  const int split = shared ? split_ext * 2 + grp : split_ext, nsplit = shared ? at.parts * 2 : at.parts;   // this group's key split of all
   struct { int nkp, nfull, t0, t1; } tr;   // prefix tiles in the item's list, those every row sees whole, this group's range
   tr.nkp = ((at.kind == 0 ? at.pos0 + at.nrows : at.L) + kTile - 1) / kTile;
   tr.nfull = (at.kind == 0 ? at.pos0 + 1 : at.L) / kTile;
-  const int per_group = (at.t1 - at.t0 + GS - 1) / GS;
+  const int per_group = shared ? (at.t1 - at.t0 + 1) / 2 : at.t1 - at.t0;
   tr.t0 = min(at.t0 + grp * per_group, at.t1);
   tr.t1 = min(tr.t0 + per_group, at.t1);
   uint16_t (*bufs)[TILE] = bufs_all[grp];
@@ -291,7 +294,7 @@ __global__ __launch_bounds__(NW * GS * 64, (DH >= 128 || GS > 1) ? 1 : 512 / (NW
   // row's q fragments are split over its two lanes (g = 0, 1).
   // With several key splits the row blocks' own keys are dealt over the splits' work items (block qb to split qb mod nsplit),
   // so that no work item carries all of them.
-  const bool own_key = !SOFTMAX && p.knew != nullptr && at.kind == 1 && split < NQ;
+  const bool own_key = !SOFTMAX && p.knew != nullptr && at.kind == 1 && split < NQ && (shared || grp == 0);
   uint4 kself[NQ][KS];
   uint2 vself[NQ][DB][4];
   bool cand[NQ];
@@ -313,7 +316,7 @@ __global__ __launch_bounds__(NW * GS * 64, (DH >= 128 || GS > 1) ? 1 : 512 / (NW
     }
   }
   auto start_from_own_key = [&]() {
-    if (!own_key) return;                       // uniform over the workgroup
+    if (!own_key) return;                       // uniform over the group
 #pragma unroll
     for (int qb = 0; qb < NQ; ++qb) {
       float dot = 0.f;
@@ -454,53 +457,57 @@ __global__ __launch_bounds__(NW * GS * 64, (DH >= 128 || GS > 1) ? 1 : 512 / (NW
   }
 
   if constexpr (GS == 2) {
-    // A group passed nt barriers above (none if it had no tiles); both groups pass nt_all, then two more around the
-    // hand-over of the second group's sums.  Nothing below returns before the last of them.
+    // A group passed nt barriers above (none if it had no tiles); both groups pass nt_all, then, if they share the piece, two more
+    // around the hand-over of the second group's sums.  Nothing below returns before the last of them.
     for (int e = nt; e < nt_all; ++e) __syncthreads();
-    __syncthreads();                                  // both groups are done with their tile rings
-    float* xch = reinterpret_cast<float*>(&bufs_all[0][0][0]);
-    const int slot = wave * 64 + lane;                // lane of the first group that holds the same rows and features
-    if (grp == 1) {
+    if (shared) {
+      __syncthreads();                                  // both groups are done with their tile rings
+      float* xch = reinterpret_cast<float*>(&bufs_all[0][0][0]);
+      const int slot = wave * 64 + lane;                // lane of the first group that holds the same rows and features
+      if (grp == 1) {
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int qb = 0; qb < NQ; ++qb)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) xch[((db * NQ + qb) * 16 + e) * (NW * 64) + slot] = oacc[db][qb][e];
+        if constexpr (SOFTMAX) {
+#pragma unroll
+          for (int qb = 0; qb < NQ; ++qb) {
+            xch[(DB * NQ * 16 + 2 * qb) * (NW * 64) + slot] = mref[qb];
+            xch[(DB * NQ * 16 + 2 * qb + 1) * (NW * 64) + slot] = lsum[qb];
+          }
+        }
+      }
+      __syncthreads();
+      if (grp == 1) return;
+      // softmax form: both groups' sums are brought to the larger of their two reference scores first
+      float c0[NQ], c1[NQ];
+#pragma unroll
+      for (int qb = 0; qb < NQ; ++qb) {
+        c0[qb] = 1.0f; c1[qb] = 1.0f;
+        if constexpr (SOFTMAX) {
+          const float m1 = xch[(DB * NQ * 16 + 2 * qb) * (NW * 64) + slot], l1 = xch[(DB * NQ * 16 + 2 * qb + 1) * (NW * 64) + slot];
+          const float M = fmaxf(mref[qb], m1);
+          c0[qb] = (mref[qb] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mref[qb] - M);
+          c1[qb] = (m1 == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m1 - M);
+          lsum[qb] = lsum[qb] * c0[qb] + l1 * c1[qb];
+          mref[qb] = M;
+        }
+      }
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll
         for (int qb = 0; qb < NQ; ++qb)
 #pragma unroll
-          for (int e = 0; e < 16; ++e) xch[((db * NQ + qb) * 16 + e) * (NW * 64) + slot] = oacc[db][qb][e];
-      if constexpr (SOFTMAX) {
-#pragma unroll
-        for (int qb = 0; qb < NQ; ++qb) {
-          xch[(DB * NQ * 16 + 2 * qb) * (NW * 64) + slot] = mref[qb];
-          xch[(DB * NQ * 16 + 2 * qb + 1) * (NW * 64) + slot] = lsum[qb];
-        }
-      }
+          for (int e = 0; e < 16; ++e) {
+            const float x = xch[((db * NQ + qb) * 16 + e) * (NW * 64) + slot];
+            if constexpr (SOFTMAX) oacc[db][qb][e] = oacc[db][qb][e] * c0[qb] + x * c1[qb];
+            else oacc[db][qb][e] += x;
+          }
+    } else if (grp == 1) {
+      return;
     }
-    __syncthreads();
-    if (grp == 1) return;
-    // softmax form: both groups' sums are brought to the larger of their two reference scores first
-    float c0[NQ], c1[NQ];
-#pragma unroll
-    for (int qb = 0; qb < NQ; ++qb) {
-      c0[qb] = 1.0f; c1[qb] = 1.0f;
-      if constexpr (SOFTMAX) {
-        const float m1 = xch[(DB * NQ * 16 + 2 * qb) * (NW * 64) + slot], l1 = xch[(DB * NQ * 16 + 2 * qb + 1) * (NW * 64) + slot];
-        const float M = fmaxf(mref[qb], m1);
-        c0[qb] = (mref[qb] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mref[qb] - M);
-        c1[qb] = (m1 == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m1 - M);
-        lsum[qb] = lsum[qb] * c0[qb] + l1 * c1[qb];
-        mref[qb] = M;
-      }
-    }
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int qb = 0; qb < NQ; ++qb)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const float x = xch[((db * NQ + qb) * 16 + e) * (NW * 64) + slot];
-          if constexpr (SOFTMAX) oacc[db][qb][e] = oacc[db][qb][e] * c0[qb] + x * c1[qb];
-          else oacc[db][qb][e] += x;
-        }
   }
 
   // element e of oacc[db][qb]: feature db*32 + 8*(e/4) + 4*g + e%4, row l32 of block qb

@@ -810,9 +810,7 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
   const int R = p.n_rows;
   constexpr bool kPanel = !std::is_same<T, float>::value;   // bf16: xh / y are written as MFMA panels
 
-  int attn_gs = cut.gs;
-  if (bf16 && dh == 64 && cut.gs == 1 && p.n_prows == 0 && !cut.all.empty())       // (the list is sorted, longest first)
-    attn_gs = attn_groups(softmax, (int64_t)cut.all.size() * H, cut.all[0].t1 - cut.all[0].t0, c->n_cus);
+  const int shared_tiles = bf16 ? attn_shared_tiles(softmax, H, dh, !rows_prefix.empty(), cut, c->n_cus) : kNoneShared;
 
   for (int l = 0; l < NL; ++l) {
     const relaygr_layer_weights& lw = c->layers[l];
@@ -907,7 +905,8 @@ static int run_typed(relaygr_ctx* c, KvPool* pool, const relaygr_batch* b, Mode 
     AttnParams ap;
     ap.tiles = d_tiles; ap.q = qbuf; ap.sfx = sfx; ap.part = part;
     ap.split_stride = (size_t)R * d; ap.nsplit = p.nsplit; ap.d = d; ap.n_heads = H; ap.layer = l; ap.score_mul = score_mul;
-    ap.ml = ml; ap.ml_stride = (size_t)R * H * 2; ap.gs = attn_gs;
+    ap.ml = ml; ap.ml_stride = (size_t)R * H * 2; ap.gs = shared_tiles < kNoneShared ? 2 : cut.gs;
+    ap.shared_tiles = shared_tiles;
     // 16-bit SiLU form: the attention kernel adds the candidates' own keys, so the layer tail does not read q, k, v again
     const bool self_in_attn = bf16 && !softmax;
     ap.knew = self_in_attn ? (const void*)knew : nullptr; ap.vnew = vnew; ap.n_prows = p.n_prows; ap.n_rows = R;

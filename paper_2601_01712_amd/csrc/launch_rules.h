@@ -60,15 +60,23 @@ inline int sums_at_once(int parts_all, int nsplit) {
   return most <= 2 ? most : most <= 4 ? 4 : kMaxPieces;
 }
 
-// Wavefront groups of an attention workgroup at d_head 64 in rankings of cached users whose pieces, of at most `longest` key tiles, are no more than the
-// chip has compute units: a workgroup then has its unit to itself, and a second group of wavefronts that takes half of the piece's keys and whose sums are
-// added in LDS gives every SIMD a second wavefront, one's SiLU beside the other's products, without a partial sum more.  The hand-over costs about as
+// Key tiles from which on the two wavefront groups of an attention workgroup share a piece (kNoneShared: workgroups of one group).  Pairs that the plan has
+// made are always shared.  Else, at d_head 64, in rankings of cached users with no more pieces than the chip has compute units: a workgroup then has its
+// unit to itself, and a second group that takes half of a long piece's keys and whose sums are added in LDS gives every SIMD a second wavefront, one's
+// SiLU beside the other's products, without a partial sum more.  The hand-over costs about as
 // much as four key tiles of the SiLU form, and eight of the softmax form, which does half as much on the vector ALU and has the sums to rescale (one user, us
 // a call with one group / two, longest piece in brackets: d = 512, 512 candidates and 4096 keys [8] 231.2 / 231.4, 6144 [12] 250.9 / 247.5, 8192 [16] 268.5 /
 // 264.3; 100 and 4096 [8] 212.0 / 209.0, 6144 [12] 233.1 / 225.9, 8192 [16] 254.7 / 242.7; 250 and 16 000 [32] 365.7 / 328.2; d = 256, 256 and 10 000 [20]
-// 119.5 / 112.0.  Below: three users of 256 and 2048 at d = 256 [5] 87.8 / 89.0, seven of 32 and 800 [4] 181.6 / 184.9, 16 of 512 and 300 [5] 497.0 / 504.5.
-// Softmax: 512 and 2000 [4] 225 / 233, 4096 [8] 238.4 / 241.0, 8000 [16] 276.2 / 272.2; 100 and 8192 [16] 257.5 / 248.0; 250 and 16 000 [32] 367.6 / 328.6.
-// Lists with prefix rows, whose causal pieces end in tiles that only some wavefronts see: pre-inference of 1000 keys 193 / 200).
-inline int attn_groups(bool softmax, int64_t pieces, int longest, int n_cus) { return pieces <= n_cus && longest >= (softmax ? 16 : 8) ? 2 : 1; }
+// 119.5 / 112.0.  Softmax: 512 and 2000 [4] 225 / 233, 4096 [8] 238.4 / 241.0, 8000 [16] 276.2 / 272.2; 100 and 8192 [16] 257.5 / 248.0; 250 and 16 000 [32]
+// 367.6 / 328.6.  Lists with prefix rows, whose causal pieces end in tiles that only some wavefronts see: pre-inference of 1000 keys 193 / 200).
+// The pieces of a launch decide one by one, so that a row's sums do not depend on the other users' pieces, and short ones do not pay for a hand-over
+// (three users of 256 and 2048 at d = 256 [5] 87.8 / 89.0, seven of 32 and 800 [4] 181.6 / 184.9, 16 of 512 and 300 [5] 497.0 / 504.5).
+constexpr int kNoneShared = 1 << 20;
+inline int attn_shared_tiles(bool softmax, int heads, int dh, bool prefix_rows, const AttnCut& cut, int n_cus) {
+  if (cut.gs == 2) return 0;
+  const int least = softmax ? 16 : 8;
+  const bool pays = dh == 64 && !prefix_rows && (int64_t)cut.all.size() * heads <= n_cus;
+  return pays && !cut.all.empty() && cut.all[0].t1 - cut.all[0].t0 >= least ? least : kNoneShared;    // (the list is sorted, longest first)
+}
 
 }  // namespace relaygr

@@ -138,8 +138,9 @@ inline void attn_row_tiles(const std::vector<UserDesc>& users, int tile_rows, st
 // slots free, of no less than kFinePieceTiles.  (d = 512, one user, us a call in pieces of 8 / 4 / 2 / 1 tiles: 512 keys and 64
 // candidates 257 / 238 / 231 / 231, 1024 and 512 263 / 250 / 254; 2048 and 64 in pieces of 8 / 4 263 / 247.  More than half full:
 // 8 users at d = 128 with 2048 keys and 272 new rows, 240 pieces of 7 tiles 115, 336 of 5 126; d = 1024, 2048 keys and 512
-// candidates, 128 pieces of 8 on 256 slots 611, 256 of 4 646.)  It is a number of pieces and no length, so that as long as
-// a launch is that small a row's sums do not depend on how long the histories of the call's other users are.
+// candidates, 128 pieces of 8 on 256 slots 611, 256 of 4 646.)  It is a number of pieces and no length, so that where it is
+// kMaxPieces, up to slots / (2 kMaxPieces) (row tile, head) pairs, a row's sums do not depend on how long the histories of the call's other
+// users are.
 // Lists with prefix rows are of unequal items that thin out towards their end, and small ones are launches of a few dozen workgroups: their least
 // piece is kMinCausalPieceTiles.  How far that pays is a matter of the slots that the list fills uncut: three eighths of them without new rows, and
 // three sixteenths with new rows, whose sums the last layer reads as well (us a call with at least 8 / 4 tiles, d = 256 and 512 of 4 and 8 layers.

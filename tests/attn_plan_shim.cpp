@@ -17,7 +17,8 @@ static int complain(char* msg, const char* what, int user, int row, int got, int
 
 // computed[u]: the call computes user u's prefix rows; new_rows: it has suffix and candidate rows (no pre-inference call).
 // most_sums: partial sums a row may have for the call to fit its scratch.  info: row blocks, nsplit, gs, items, rows' filler max,
-// sums of a row in flight in the layer tail of the last layer and of the others.
+// sums of a row in flight in the layer tail of the last layer and of the others, key tiles from which on two wavefront groups share a piece
+// in the SiLU and in the softmax form, key tiles of the longest piece.
 extern "C" int plan_check(int n, const int32_t* L, const int32_t* S, const int32_t* M, const uint8_t* computed, int new_rows,
                           int heads, int dh, int n_cus, int most_sums, int32_t* info, char* msg) {
   std::vector<UserDesc> users(n);
@@ -40,6 +41,8 @@ extern "C" int plan_check(int n, const int32_t* L, const int32_t* S, const int32
   set_user_parts(users, cut);
   info[0] = nq; info[1] = cut.nsplit; info[2] = cut.gs; info[3] = (int)cut.all.size(); info[4] = 0;
   info[5] = sums_at_once(cut.parts_last, cut.nsplit); info[6] = sums_at_once(cut.parts_all, cut.nsplit);
+  for (int sm = 0; sm < 2; ++sm) info[7 + sm] = attn_shared_tiles(sm, heads, dh, !rows_prefix.empty(), cut, n_cus);
+  info[9] = cut.all.empty() ? 0 : cut.all[0].t1 - cut.all[0].t0;
 
   // every list holds each row tile's pieces once: numbered 0 .. parts - 1, the key tiles in order and without a gap
   const int n_rows = prow + nrow;
@@ -93,6 +96,31 @@ extern "C" int plan_check(int n, const int32_t* L, const int32_t* S, const int32
   return 0;
 }
 
+// Pieces of a cached user's first row tile in a ranking of cached users: first and last key tile of each, and whether two wavefront groups share it.
+extern "C" int user_pieces(int n, const int32_t* L, const int32_t* S, const int32_t* M, int user, int softmax, int heads, int dh, int n_cus, int32_t* out) {
+  std::vector<UserDesc> users(n);
+  int nrow = 0;
+  for (int u = 0; u < n; ++u) {
+    UserDesc& ud = users[u];
+    memset(&ud, 0, sizeof(ud));
+    ud.L = L[u]; ud.S = S[u]; ud.M = M[u]; ud.prow0 = -1; ud.nrow0 = nrow;
+    nrow += ud.S + ud.M;
+  }
+  const int nq = attn_row_blocks(users, heads, dh);
+  std::vector<AttnTile> rows_new, rows_prefix;
+  attn_row_tiles(users, 128 * nq, rows_new, rows_prefix);
+  AttnCut cut;
+  cut_attention(rows_new, rows_prefix, heads, dh, 128 * nq, n_cus, cut, [&](const AttnCut& k) { return k.nsplit <= kMaxPieces; });
+  const int least = attn_shared_tiles(softmax != 0, heads, dh, !rows_prefix.empty(), cut, n_cus);
+  int count = 0;
+  for (const AttnTile& a : cut.all)
+    if (a.user == user && a.pos0 == 0) {
+      const int32_t piece[3] = {a.t0, a.t1, a.t1 - a.t0 >= least};
+      memcpy(out + 3 * a.part, piece, sizeof(piece));
+      ++count;
+    }
+  return count;
+}
+
 extern "C" int tail_rows_of(int d, int rows) { return tail_rows(d, rows); }
 extern "C" int f1_tile_of(int d, int nblk, int rows, int n_cus) { return (int)f1_tile(d, nblk, rows, n_cus); }
-extern "C" int attn_groups_of(int softmax, int64_t pieces, int longest, int n_cus) { return attn_groups(softmax != 0, pieces, longest, n_cus); }

@@ -27,7 +27,7 @@ def _plan(shim, L, S, M, computed, heads, dh, n_cus, most_sums):
     new_rows = M is not None
     arr = [np.asarray(a if a is not None else [0] * n, np.int32) for a in (L, S, M)]
     comp = np.asarray([1] * n if computed is None else computed, np.uint8)
-    info, msg = np.zeros(7, np.int32), C.create_string_buffer(256)
+    info, msg = np.zeros(10, np.int32), C.create_string_buffer(256)
     rc = shim.plan_check(n, *(a.ctypes.data_as(C.c_void_p) for a in arr), comp.ctypes.data_as(C.c_void_p), int(new_rows), heads, dh, n_cus, most_sums,
                          info.ctypes.data_as(C.c_void_p), msg)
     assert rc == 0, f"L {list(L)} S {S} M {M} computed {computed} heads {heads} d_head {dh} units {n_cus} sums {most_sums}: {msg.value.decode()}"
@@ -50,9 +50,19 @@ def tail_rows(d, rows):
     return shim().tail_rows_of(d, rows)
 
 
-def attention_groups(softmax, pieces, longest, n_cus=256):
-    """Wavefront groups of an attention workgroup at d_head 64, for a ranking of cached users whose pieces are not paired already."""
-    return shim().attn_groups_of(int(softmax), C.c_int64(pieces), longest, n_cus)
+def shared_pieces(attention, L, S, M, computed=None, heads=8, dh=64):
+    """Key tiles of the longest piece of the call's attention, and from how many on two wavefront groups share a piece (None: one group)."""
+    silu, softmax, longest = _plan(shim(), L, S, M, [0] * len(L) if computed is None else computed, heads, dh, 256, 8)[7:10]
+    least = silu if attention == "silu" else softmax
+    return longest, least if least < 1 << 20 else None
+
+
+def user_pieces(L, S, M, user, attention="silu", heads=8, dh=64, n_cus=256):
+    """(first, last key tile, shared by two wavefront groups) of the pieces of a user's first row tile in a ranking of cached users."""
+    arr = [np.asarray(a, np.int32) for a in (L, S, M)]
+    out = np.zeros(24, np.int32)
+    count = shim().user_pieces(len(L), *(a.ctypes.data_as(C.c_void_p) for a in arr), user, int(attention == "softmax"), heads, dh, n_cus, out.ctypes.data_as(C.c_void_p))
+    return [tuple(p) for p in out.reshape(8, 3)[:count].tolist()]
 
 
 def projection_tile(d, rows, nblk=4, n_cus=256):

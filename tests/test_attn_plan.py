@@ -96,6 +96,24 @@ def test_every_row_has_the_sums_its_pieces_write(shim, heads, dh):
         check(shim, L, S, M, computed, heads, dh, rng.choice([256, 256, 304, 64]), rng.choice([8, 8, 1, 2, 3, 5]))
 
 
+@pytest.mark.parametrize("attention", ["silu", "softmax"])
+@pytest.mark.parametrize("heads,dh,n_cus", [(2, 64, 256), (8, 64, 256), (8, 64, 104), (4, 128, 256), (4, 32, 256)])
+def test_a_users_pieces_in_a_small_call_do_not_depend_on_the_other_histories(attention, heads, dh, n_cus):
+    """Up to slots / 16 (row tile, head) pairs.  The pieces and the groups that take them are the order in which a row's sums are added."""
+    rng = random.Random(heads * dh)
+    pairs = min(512, n_cus if dh == 128 else 2 * n_cus) // 16
+    for _ in range(300):
+        n = rng.randint(2, 4)
+        M = [rng.randint(1, 300) for _ in range(n)]
+        if sum((m + 127) // 128 for m in M) * heads > pairs:
+            continue
+        S = [0] * n
+        own = rng.choice([rng.randint(0, 1500), rng.randint(0, 20000)])
+        seen = {str(plan_util.user_pieces([own] + [rng.choice([rng.randint(0, 1500), rng.randint(0, 20000)]) for _ in range(n - 1)], S, M, 0, attention, heads, dh, n_cus))
+                for _ in range(8)}
+        assert len(seen) == 1, (own, M, seen)
+
+
 @pytest.mark.parametrize("d,nblk,borders", [
     (128, 4, [(1, "64x64"), (2049, "64x128"), (12289, "stationary")]),
     (128, 2, [(1, "64x64"), (4097, "64x128"), (24577, "stationary")]),

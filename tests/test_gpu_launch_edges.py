@@ -3,11 +3,13 @@
 64 x 128, 128 x 128 with four and with three stages, 256 x 128, the weight-stationary form), with prefix, suffix and candidate rows; and where a wavefront of the attention
 stops at its rows' last key tile before the others of its workgroup do.  Every case ranks on the cached prefix
 and by full recompute, against the CPU oracle; at d = 128 with the boosted weights, which let attention reach the scores there."""
+import numpy as np
 import pytest
 
+import paper_2601_01712_amd as rg
 import plan_util
 import synth
-from gpu_util import BOOST
+from gpu_util import BOOST, Harness, build_case
 from test_gpu_parity import run_three_routes
 
 pytestmark = pytest.mark.gpu
@@ -167,14 +169,38 @@ GROUPS = [
 
 @pytest.mark.parametrize("case", range(len(GROUPS)))
 def test_pieces_by_two_groups_of_wavefronts(case):
-    """Launches of no more pieces than compute units: the two groups of a workgroup take the halves of a piece and add them in LDS, pieces of odd
-    lengths, of one key tile and of none among them."""
+    """Launches of no more pieces than compute units: the two groups of a workgroup take the halves of a long piece and add them in LDS; pieces of odd
+    lengths, and beside them short ones, which the first group takes alone, of one key tile and of none."""
     attention, dtype, L, S, M, pieces, longest, groups = GROUPS[case]
     plan = plan_util.check(plan_util.shim(), L, S, M, [0] * len(L), heads=4, dh=64)
     tiles = (max(L) + 63) // 64 + (S[0] + 63) // 64
     assert (plan["blocks"], plan["gs"], plan["items"] * 4, -(-tiles // plan["nsplit"])) == (1, 1, pieces, longest)
-    assert plan_util.attention_groups(attention == "softmax", pieces, longest) == groups
+    least = plan_util.shared_pieces(attention, L, S, M, heads=4)[1]
+    assert (2 if least else 1) == groups and least in (None, 8, 16)
     run_three_routes(synth.ModelConfig(2, 256, 4, dtype, attention=attention), 7800 + case, L, S, M)
+
+
+@pytest.mark.parametrize("attention", ["silu", "softmax"])
+def test_a_users_scores_do_not_depend_on_the_history_beside_it(attention):
+    """Users whose pieces are short beside one whose pieces two groups of wavefronts share, and beside another short one: the same bits."""
+    L, M = [2000, 1900, 8192, 700], [100, 90, 90, 40]
+    cfg = synth.ModelConfig(2, 512, 8, "bf16", attention=attention)
+    shared = [[p[2] for p in plan_util.user_pieces([L[u] for u in us], [0] * 3, [M[u] for u in us], 1, attention)] for us in ((0, 1, 3), (0, 2, 3))]
+    assert not any(shared[0]) and all(shared[1]) and len(shared[1]) == 8
+    weights, batch = build_case(cfg, 7850, L, [0] * 4, M)
+    h = Harness(cfg, weights, batch, page_tokens=64)
+    try:
+        h.prefill()
+
+        def scores(users):
+            b = h.sub_batch(users)
+            b.set_handles([h.handles[u] for u in users])
+            return rg.relaygr_rank_with_cache(h.ctx, h.pool, b).cpu().numpy()
+
+        short, long = scores([0, 1, 3]), scores([0, 2, 3])
+        assert np.array_equal(short[:100], long[:100]) and np.array_equal(short[190:], long[190:])
+    finally:
+        h.close()
 
 
 #   prefix lengths, suffix lengths, candidates; rows a workgroup
