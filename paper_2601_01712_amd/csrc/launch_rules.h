@@ -63,18 +63,21 @@ inline int sums_at_once(int parts_all, int nsplit) {
 // Key tiles from which on the two wavefront groups of an attention workgroup share a piece (kNoneShared: workgroups of one group).  Pairs that the plan has
 // made are always shared.  Else, at d_head 64, in rankings of cached users with no more pieces than the chip has compute units: a workgroup then has its
 // unit to itself, and a second group that takes half of a long piece's keys and whose sums are added in LDS gives every SIMD a second wavefront, one's
-// SiLU beside the other's products, without a partial sum more.  The hand-over costs about as
-// much as four key tiles of the SiLU form, and eight of the softmax form, which does half as much on the vector ALU and has the sums to rescale (one user, us
-// a call with one group / two, longest piece in brackets: d = 512, 512 candidates and 4096 keys [8] 231.2 / 231.4, 6144 [12] 250.9 / 247.5, 8192 [16] 268.5 /
-// 264.3; 100 and 4096 [8] 212.0 / 209.0, 6144 [12] 233.1 / 225.9, 8192 [16] 254.7 / 242.7; 250 and 16 000 [32] 365.7 / 328.2; d = 256, 256 and 10 000 [20]
-// 119.5 / 112.0.  Softmax: 512 and 2000 [4] 225 / 233, 4096 [8] 238.4 / 241.0, 8000 [16] 276.2 / 272.2; 100 and 8192 [16] 257.5 / 248.0; 250 and 16 000 [32]
-// 367.6 / 328.6.  Lists with prefix rows, whose causal pieces end in tiles that only some wavefronts see: pre-inference of 1000 keys 193 / 200).
-// The pieces of a launch decide one by one, so that a row's sums do not depend on the other users' pieces, and short ones do not pay for a hand-over
-// (three users of 256 and 2048 at d = 256 [5] 87.8 / 89.0, seven of 32 and 800 [4] 181.6 / 184.9, 16 of 512 and 300 [5] 497.0 / 504.5).
+// SiLU beside the other's products, without a partial sum more.  The hand-over costs about as much as five key tiles of the SiLU form, and more of the
+// softmax form, which does half as much on the vector ALU and has the sums to rescale.  us a call with one group / two, key tiles of a piece in brackets, d =
+// 512, two runs of one side differ by 0.1 to 2 us: one user of 512 candidates [7] 230.1 / 231.9, [8] 231.8 / 230.7, [9] 241.2 / 240.1, [10] 241.6 / 238.5, [12]
+// 254.9 / 249.7; of 100 [8] 211.8 / 209.6, [9] 217.1 / 215.5, [10] 221.9 / 217.9, [14] 243.7 / 235.9; of 32 [17] 245.2 / 236.2; of 250 [32] 365.7 / 328.2; two
+// of 256 [11] 240.3 / 240.7, [17] 286.0 / 282.7; three of 100 [4] 198.2 / 211.6, [9] 222.9 / 225.5, [10] 241.1 / 238.8, [13] 266.7 / 260.8; seven of 32 [8]
+// 205.7 / 210.1, [11] 227.9 / 228.9, [17] 270.0 / 271.2 (bound by the K/V they fetch); d = 256, 256 candidates [8] 82.6 / 81.8, [10] 88.3 / 86.8, [12] 94.1 /
+// 91.3.  Softmax: 512 [8] 238.4 / 241.0, [10] 247.6 / 248.1, [16] 275.3 / 268.9; 100 [16] 257.0 / 247.1; two of 32 [9] 210.4 / 214.4, [17] 280.9 / 265.2; three
+// of 100 [9] 224.3 / 228.2, [17] 301.3 / 295.2; seven of 32 [8] 206.9 / 213.5, [17] 271.5 / 271.1.
+// The pieces of a launch decide one by one, so that a row's sums do not depend on the other users' pieces, and short ones do not pay for a hand-over.
+// (256-row items are that few only where each unit has one uncut, of at most 8 key tiles.)  Not for lists with prefix rows, whose causal pieces end in
+// tiles that only some wavefronts see (pre-inference of 1000 keys 193 / 200).
 constexpr int kNoneShared = 1 << 20;
 inline int attn_shared_tiles(bool softmax, int heads, int dh, bool prefix_rows, const AttnCut& cut, int n_cus) {
   if (cut.gs == 2) return 0;
-  const int least = softmax ? 16 : 8;
+  const int least = softmax ? 16 : 10;
   const bool pays = dh == 64 && !prefix_rows && (int64_t)cut.all.size() * heads <= n_cus;
   return pays && !cut.all.empty() && cut.all[0].t1 - cut.all[0].t0 >= least ? least : kNoneShared;    // (the list is sorted, longest first)
 }

@@ -96,6 +96,18 @@ def test_every_row_has_the_sums_its_pieces_write(shim, heads, dh):
         check(shim, L, S, M, computed, heads, dh, rng.choice([256, 256, 304, 64]), rng.choice([8, 8, 1, 2, 3, 5]))
 
 
+@pytest.mark.parametrize("attention,L,M,computed,longest,shared", [
+    ("silu", [4096], [512], 0, 8, False), ("silu", [4608], [512], 0, 9, False), ("silu", [5120], [512], 0, 10, True), ("silu", [16384], [100], 0, 32, True),
+    ("softmax", [7680], [512], 0, 15, False), ("softmax", [8192], [512], 0, 16, True),
+    ("silu", [16384] * 5, [512] * 5, 0, 86, False),              # more pieces than compute units
+    ("silu", [512] * 16, [512] * 16, 0, 8, False),                  # 256-row items, one a unit; longer ones are paired by the plan
+    ("silu", [8192], [64], 1, 35, False), ("silu", [8192], None, 1, 32, False),                      # lists with prefix rows
+])
+def test_long_pieces_of_few_128_row_items_are_shared(attention, L, M, computed, longest, shared):
+    got = plan_util.shared_pieces(attention, L, None, M, [computed] * len(L))
+    assert got == (longest, (16 if attention == "softmax" else 10) if shared else None)
+
+
 @pytest.mark.parametrize("attention", ["silu", "softmax"])
 @pytest.mark.parametrize("heads,dh,n_cus", [(2, 64, 256), (8, 64, 256), (8, 64, 104), (4, 128, 256), (4, 32, 256)])
 def test_a_users_pieces_in_a_small_call_do_not_depend_on_the_other_histories(attention, heads, dh, n_cus):

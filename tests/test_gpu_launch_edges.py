@@ -159,9 +159,9 @@ def test_d_head_128_items_of_eight_wavefronts(dtype, attention):
 
 #   attention, dtype, prefix lengths, suffix lengths, candidates; pieces, the longest one's key tiles and the groups that take it (4 heads of 64)
 GROUPS = [
-    ("silu", "bf16", [3300], [0], [130], 64, 7, 1),            # too short
-    ("silu", "fp16", [3900], [70], [130], 64, 8, 2),           # four tiles a group, the last piece one tile short
-    ("silu", "bf16", [4100, 0, 60], [3, 0, 65], [129, 5, 0], 76, 9, 2),     # users of one piece: no key, one tile and suffix tiles
+    ("silu", "bf16", [4500], [0], [130], 64, 9, 1),            # too short
+    ("silu", "fp16", [4900], [70], [130], 64, 10, 2),          # five tiles a group, the last piece one tile short
+    ("silu", "bf16", [5300, 0, 60], [3, 0, 65], [129, 5, 0], 76, 11, 2),    # six and five tiles; users of one piece: no key, one tile and suffix tiles
     ("softmax", "bf16", [7300], [0], [33], 32, 15, 1),
     ("softmax", "fp16", [7700, 64], [9, 0], [33, 4], 36, 16, 2),
 ]
@@ -175,8 +175,7 @@ def test_pieces_by_two_groups_of_wavefronts(case):
     plan = plan_util.check(plan_util.shim(), L, S, M, [0] * len(L), heads=4, dh=64)
     tiles = (max(L) + 63) // 64 + (S[0] + 63) // 64
     assert (plan["blocks"], plan["gs"], plan["items"] * 4, -(-tiles // plan["nsplit"])) == (1, 1, pieces, longest)
-    least = plan_util.shared_pieces(attention, L, S, M, heads=4)[1]
-    assert (2 if least else 1) == groups and least in (None, 8, 16)
+    assert plan_util.shared_pieces(attention, L, S, M, heads=4) == (longest, None if groups == 1 else 10 if attention == "silu" else 16)
     run_three_routes(synth.ModelConfig(2, 256, 4, dtype, attention=attention), 7800 + case, L, S, M)
 
 
