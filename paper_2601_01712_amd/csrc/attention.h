@@ -231,16 +231,16 @@ __global__ __launch_bounds__(NW * GS * 64, (DH >= 128 || GS > 1) ? 1 : 512 / (NW
   // Each of the 8 XCDs (own L2 each; workgroups are dealt to them round-robin) takes whole heads, or with fewer than 8 heads
   // every (8 / heads)-th item of one head, and walks the list of items in its order, longest first: row tiles of one user are
   // neighbours in the list, so a K/V tile is fetched from HBM once per XCD that needs it, and every XCD gets the same mix
-  // of long and short items.  (The number of heads is a power of two.)
-  const int xcd = blockIdx.x & 7, turn = blockIdx.x >> 3;
+  // of long and short items.  (The number of heads is a power of two: shifts, for a division is forty instructions ahead of the first load.)
+  const int xcd = blockIdx.x & 7, turn = blockIdx.x >> 3, heads_sh = __builtin_ctz(p.n_heads);
   int head, tile_i;
   if (p.n_heads >= 8) {
-    const int per_xcd = p.n_heads >> 3;
-    head = xcd * per_xcd + turn % per_xcd;
-    tile_i = turn / per_xcd;
+    const int sh = heads_sh - 3;          // log2 of the heads of an XCD
+    head = (xcd << sh) + (turn & ((1 << sh) - 1));
+    tile_i = turn >> sh;
   } else {
-    head = xcd % p.n_heads;
-    tile_i = turn * (8 / p.n_heads) + xcd / p.n_heads;
+    head = xcd & (p.n_heads - 1);
+    tile_i = (turn << (3 - heads_sh)) + (xcd >> heads_sh);
   }
   if (tile_i >= p.n_tiles) return;
   const AttnTile at = p.tiles[tile_i];
@@ -260,21 +260,24 @@ __global__ __launch_bounds__(NW * GS * 64, (DH >= 128 || GS > 1) ? 1 : 512 / (NW
   uint16_t (*bufs)[TILE] = bufs_all[grp];
   const int l32 = lane & 31, g = lane >> 5;
 
-  // this lane's rows: block qb covers rows wave*32*NQ + qb*32 + l32 of the work item
+  // this lane's rows: block qb covers rows wave*32*NQ + qb*32 + l32 of the work item.  Where a row's chunks lie: 32-bit byte offsets from the octet of
+  // the item's first row, the same in q and in k and v of the new rows (the rows before these are whole octets), so that the bases are scalars
   int lim[NQ], last_lim = 0;
   uint4 qf[NQ][KS];
-  const uint16_t* qbase = reinterpret_cast<const uint16_t*>(p.q);
+  uint32_t row_at[NQ], step[NQ];           // chunk 0 of the head's features; bytes from one chunk to the next
+  const int row_o = at.row0 & ~7;
+  const char* qbase = reinterpret_cast<const char*>(p.q) + (size_t)row_o * p.d * 2;
 #pragma unroll
   for (int qb = 0; qb < NQ; ++qb) {
     int lr = wave * 32 * NQ + qb * 32 + l32;
     bool ok = lr < at.nrows;
-    int row = at.row0 + (ok ? lr : 0);
+    const int row = (at.row0 & 7) + (ok ? lr : 0);
     lim[qb] = at.lim(lr);
     if (ok) last_lim = max(last_lim, lim[qb]);
-    const int step = SOFTMAX ? 8 : octet_step(row, p.n_rows);         // elements between chunks of eight features
-    const uint16_t* qr = qbase + (SOFTMAX ? (size_t)row * p.d : octet_off(row, p.d)) + (head * (DH / 8) + g) * step;
+    step[qb] = SOFTMAX ? 16 : 2 * octet_step(row, p.n_rows - row_o);
+    row_at[qb] = 2 * (SOFTMAX ? row * p.d : octet_off(row, p.d)) + head * (DH / 8) * step[qb];
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qf[qb][ks] = *reinterpret_cast<const uint4*>(qr + ks * 2 * step);
+    for (int ks = 0; ks < KS; ++ks) qf[qb][ks] = *reinterpret_cast<const uint4*>(qbase + (row_at[qb] + (2 * ks + g) * step[qb]));
   }
 
   f32x16_t oacc[DB][NQ];
@@ -303,16 +306,15 @@ __global__ __launch_bounds__(NW * GS * 64, (DH >= 128 || GS > 1) ? 1 : 512 / (NW
     const int lr = wave * 32 * NQ + qb * 32 + l32;
     cand[qb] = own_key && (qb % nsplit) == split && lr < at.nrows && at.pos0 + lr >= at.S;   // new rows: suffix rows, then candidates
     if (cand[qb]) {
-      const int nr = at.row0 + lr - p.n_prows, step = octet_step(nr, p.n_rows - p.n_prows);
-      const size_t nb = octet_off(nr, p.d) + head * (DH / 8) * step;
-      const uint16_t* kn = reinterpret_cast<const uint16_t*>(p.knew) + nb;
-      const uint16_t* vn = reinterpret_cast<const uint16_t*>(p.vnew) + nb;
+      const int64_t new_o = (int64_t)(row_o - p.n_prows) * p.d * 2;
+      const char* kn = reinterpret_cast<const char*>(p.knew) + new_o;
+      const char* vn = reinterpret_cast<const char*>(p.vnew) + new_o;
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) kself[qb][ks] = *reinterpret_cast<const uint4*>(kn + (2 * ks + g) * step);
+      for (int ks = 0; ks < KS; ++ks) kself[qb][ks] = *reinterpret_cast<const uint4*>(kn + (row_at[qb] + (2 * ks + g) * step[qb]));
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll
-        for (int e4 = 0; e4 < 4; ++e4) vself[qb][db][e4] = *reinterpret_cast<const uint2*>(vn + (4 * db + e4) * step + 4 * g);
+        for (int e4 = 0; e4 < 4; ++e4) vself[qb][db][e4] = *reinterpret_cast<const uint2*>(vn + (row_at[qb] + (4 * db + e4) * step[qb] + 8 * g));
     }
   }
   auto start_from_own_key = [&]() {

@@ -116,9 +116,12 @@ __host__ __device__ __forceinline__ size_t panel_off(int row, int k, int K) {
 // Row octets: q, and the new rows' k and v, of the 16-bit SiLU form.  Eight rows at a time, in them the 16-byte chunks of eight features, each of
 // the eight rows: [row/8][feature/8][row%8][feature%8].  The last octet of an array holds as many rows as are left, so that the array is as large as
 // in row-major order.  `chunk`: feature / 8.  Whoever takes a chunk of 32 consecutive rows (an operand of the attention's product) reads 128 bytes
-// in a run, where row-major order gives a memory line for every row.
+// in a run, where row-major order gives a memory line for every row.  us a call, d = 512, row-major / octets: one user of 4096 keys and 512 candidates 238 /
+// 232, of 800 and 100 183.4 / 177.8; eight of 2048 and 272 new rows at d = 256 126.9 / 122.8.  With at most 32 rows a user one of a workgroup's four
+// wavefronts has rows, and there is little to gain: seven of 800 and 32 177.9 / 179.0, 14 of 300 and 32 175.6 / 177.3 (180.7 and 181.3 with the addresses worked
+// out in 64 bits for each lane).
 __device__ __forceinline__ int octet_step(int row, int n_rows) { return min(8, n_rows - (row & ~7)) * 8; }     // elements between a row's chunks
-__device__ __forceinline__ size_t octet_off(int row, int d) { return (size_t)(row & ~7) * d + (row & 7) * 8; }  // its chunk 0
+__device__ __forceinline__ int octet_off(int row, int d) { return (row & ~7) * d + (row & 7) * 8; }  // its chunk 0 (row: in a tile, from an octet's first row on)
 
 // Barrier for data that went through LDS only: unlike __syncthreads() it does not wait for global stores and loads in flight.
 __device__ __forceinline__ void lds_barrier() {

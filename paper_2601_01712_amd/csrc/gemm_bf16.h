@@ -255,7 +255,8 @@ __global__ __launch_bounds__(256, TM == 4 ? 2 : NSTAGE == 3 ? 3 : 1) void f1_gem
   constexpr int CH = 8 * TN, RPP = 256 / CH, ITS = ROWS / RPP;   // chunks of a row, rows per pass of the store phase, passes
   const bool by_kind = (blk == 1 || blk == 3) && !prefix_tile;
   const bool octets = p.octets && (blk == 2 || by_kind), rows_first = octets || (blk == 3 && prefix_tile);
-  const int t0 = rows_first ? (tid & 7) + tid / (8 * CH) * 8 : tid / CH, fc = rows_first ? (tid >> 3) % CH : tid % CH;
+  const int rsh = rows_first ? 3 : 0;                        // (a scalar: selected by lane, it would be two branches ahead of the first loads)
+  const int t0 = (tid >> rsh) / CH << rsh | (tid & ((1 << rsh) - 1)), fc = (tid >> rsh) % CH;
   int kinds[ITS];
 #pragma unroll
   for (int it = 0; it < ITS; ++it) kinds[it] = kRowCand;
@@ -271,6 +272,15 @@ __global__ __launch_bounds__(256, TM == 4 ? 2 : NSTAGE == 3 ? 3 : 1) void f1_gem
   asm volatile("" ::: "memory");
   GemmLoop<H, TM, TN, NSTAGE, KT> loop(p.A, p.W, d, m0, n0, lds);
   loop.start();                                             // before everything else that the tile needs
+  // Where this thread's chunks go, worked out while the tiles are on their way (the compiler would load the pointers behind the product, a round trip
+  // before the first store: 608 workgroups of 64 x 128 tiles 14.35 / 14.19 us).  Row-major: octets of one row.  A pass is whole octets, so that a
+  // thread's places are one row stride apart.
+  // (u and q of filler rows are written too: nothing reads them, and a filler row's inputs are zeros)
+  const int in_octet = octets ? 7 : 0;
+  uint32_t at0 = (t0 & ~in_octet) * d * 2 + (t0 & in_octet) * 16 + (c0 / 8 + fc) * (in_octet + 1) * 16;
+  int n_rows = p.row_end - m0;
+  uint16_t* rows_out = blk == 0 ? p.u + (size_t)m0 * d : blk == 2 ? p.q + (size_t)m0 * d : (blk == 3 ? p.knew : p.vnew) + ((int64_t)m0 - p.n_prows) * d;
+  asm volatile("" : "+v"(at0), "+s"(n_rows), "+s"(rows_out));
 
   f32x16_t acc[TM][TN];
 
@@ -342,9 +352,6 @@ __global__ __launch_bounds__(256, TM == 4 ? 2 : NSTAGE == 3 ? 3 : 1) void f1_gem
   // ROWS tokens x CH chunks of 8 features
   const int c = c0 + fc * 8;                                 // feature inside the block
   const int head = c >> dh_sh, f = c - (head << dh_sh);
-  const int n_rows = p.row_end - m0;
-  // (u and q of filler rows are written too: nothing reads them, and a filler row's inputs are zeros)
-  uint16_t* rows_out = blk == 0 ? p.u + (size_t)m0 * d : blk == 2 ? p.q + (size_t)m0 * d : (blk == 3 ? p.knew : p.vnew) + ((int64_t)m0 - p.n_prows) * d;
   if (blk == 3 && prefix_tile) {                             // K of prefix rows (V took the other path)
     const UserDesc& tud = p.users[tile_user];               // (as above)
     const int L = tud.L, Lceil = (L + kTile - 1) / kTile * kTile;
@@ -361,13 +368,16 @@ __global__ __launch_bounds__(256, TM == 4 ? 2 : NSTAGE == 3 ? 3 : 1) void f1_gem
     }
     return;
   }
+  const bool ragged = octets && n_rows < ROWS && (n_rows & 7);
 #pragma unroll
   for (int it = 0; it < ITS; ++it) {
     const int t = t0 + RPP * it;
     if (t >= n_rows) continue;
     const uint4 val = *reinterpret_cast<const uint4*>(&lds[t * kStageLd + fc * 8]);
     if (kinds[it] == kRowCand) {
-      st_out(rows_out + (octets ? octet_off(t, d) + (c >> 3) * octet_step(t, n_rows) : (size_t)t * d + c), val, 0);
+      uint32_t at = at0 + RPP * it * d * 2;
+      if (ragged && t >= (n_rows & ~7)) at -= (c >> 3) * (8 - (n_rows & 7)) * 16;      // the last octet, of the rows that are left
+      st_out(reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(rows_out) + at), val, 0);
     } else {                                                 // k or v of a suffix row
       const int row = m0 + t, idx = p.rt.idx[row], rr = idx & 63;
       uint16_t* base = p.sfx + p.users[p.rt.user[row]].sfx_tile0 + (int64_t)(idx >> 6) * (2 * kTile * d) + head * 2 * kTile * dh;
@@ -621,7 +631,7 @@ __global__ __launch_bounds__(512, 1) void f1_ws_bf16_kernel(F1Params p) {
             if (rl >= n_rows) break;
             const uint4 v = staged(n);
             if (p.rt.kind[row] == kRowCand) {
-              st_out(rows_out + (octets ? octet_off(rl, d) + (c >> 3) * octet_step(rl, n_rows) : (size_t)(rl * d + c)), v, p.stream_out);
+              st_out(rows_out + (octets ? octet_off(rl, d) + (c >> 3) * octet_step(rl, n_rows) : rl * d + c), v, p.stream_out);
               continue;
             }
             const int pos = p.rt.idx[row], rr = pos & 63;

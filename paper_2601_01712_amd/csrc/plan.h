@@ -48,7 +48,7 @@ struct AttnTile {
   // 16-bit kernel: an item is one of `parts` pieces of its rows' key sequence, key tiles [t0, t1) of the concatenated list
   // [prefix tiles | suffix tiles], and writes partial sum number `part`
   int32_t t0, t1;
-  int16_t part, parts;
+  int32_t part : 16, parts : 16;   // (one word, which a kernel reads with the scalars around it; a 16-bit field takes a vector load)
   const void* kv;          // the user's prefix tile 0, layer 0, head 0 (pool slab or scratch)
   int64_t kv_tile_stride;  // elements between its tiles
   int64_t sfx_tile0;       // UserDesc::sfx_tile0

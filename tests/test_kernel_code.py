@@ -30,3 +30,13 @@ def test_attention_tiles_take_one_lds_address_per_four_pieces(tmp_path, dh, piec
     own = [ld for ld in loads if "offset:" not in ld]
     assert loads and len(loads) % pieces == 0
     assert len(own) == len(loads) // pieces * ((pieces + 3) // 4)
+
+
+@pytest.mark.parametrize("instance", ["64, 1, 4, false, 1", "64, 2, 4, false, 2", "128, 1, 8, true, 1"])
+def test_attention_reads_its_work_item_by_scalar_loads(tmp_path, instance):
+    """A field narrower than a word takes a vector load, a round trip to memory that the loads of the candidates' own keys wait for; and the rows' own
+    chunks are 32-bit offsets from scalar bases."""
+    text = assembly(tmp_path, "attention.h", f"relaygr::attn_bf16_kernel<Bf16, {instance}>(AttnParams)")
+    start = text[:text.index("s_barrier")]
+    assert not re.search(r"global_load_(u|s)(byte|short)", start)
+    assert re.search(r"global_load_dwordx4 v\[\d+:\d+\], v\d+, s\[", start)
