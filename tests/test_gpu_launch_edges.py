@@ -23,7 +23,7 @@ TAIL = [
     (256, 4, "fp16", [600, 70], [0, 5], [1020, 0]),   # 1025: the first one of 16-row workgroups, unequal pieces
     (512, 8, "bf16", [130], [1], [1033]),         # 16-row workgroups, few pieces
     (128, 2, "bf16", [100], [0], [33]),           # the d = 128 kernel: 32 + 1
-    (1024, 8, "bf16", [70], [0], [33]),           # the d = 1024 kernel: 32 + 1
+    (1024, 8, "bf16", [70], [0], [33]),           # d = 1024: workgroups of 8, the last of one row (32: WIDE_TAIL)
 ]
 
 
@@ -176,7 +176,7 @@ def test_pieces_by_two_groups_of_wavefronts(case):
     tiles = (max(L) + 63) // 64 + (S[0] + 63) // 64
     assert (plan["blocks"], plan["gs"], plan["items"] * 4, -(-tiles // plan["nsplit"])) == (1, 1, pieces, longest)
     assert plan_util.shared_pieces(attention, L, S, M, heads=4) == (longest, None if groups == 1 else 10 if attention == "silu" else 16)
-    run_three_routes(synth.ModelConfig(2, 256, 4, dtype, attention=attention), 7800 + case, L, S, M)
+    run_three_routes(synth.ModelConfig(2, 256, 4, dtype, attention=attention), 7800 + case, L, S, M, boost=BOOST)
 
 
 @pytest.mark.parametrize("attention", ["silu", "softmax"])
@@ -209,6 +209,7 @@ WIDE_TAIL = [
     ([70], [0], [1024], 8),
     ([600], [1], [1024], 16),                          # 1025: a workgroup of one row
     ([65] * 17, [0] * 17, [250] * 17, 32),             # 4250
+    ([65] * 16 + [1500], [0] * 17, [241] * 17, 32),    # 4097, and 9729 in full recompute: a last workgroup of one row; one and three sums
 ]
 
 
