@@ -602,7 +602,7 @@ static int launch_attention16(const relaygr_model_config& cfg, const AttnParams&
       break;
     case 128:
       // 256-row items: eight wavefronts of 32 rows.  With four of 64 rows a lane needs 458 registers, so that the scores come out of accumulation
-      // registers one move each and a SIMD has one wavefront; with eight it needs 212, without moves, and two share a SIMD: 9 % fewer cycles.  The
+      // registers one move each and a SIMD has one wavefront; with eight it needs 212, without moves, and two share a SIMD: 262 -> 240 k cycles.  The
       // fragments are read from LDS twice as often, and the clock sinks with the load, so that less of it shows (us a call at d = 1024, 512 candidates
       // each, four / eight wavefronts: 16 users of 1000 keys 1381 / 1367, of 4096 2069 / 2058 and 2144 / 2159 on another card, of 8000 3070 / 3033; 24 of
       // 4000 3437 / 3351, of 12 000 6646 / 6679; 40 of 1000 3655 / 3569, of 2000 in the softmax form 4414 / 4285; full recompute of 12 000 keys 3962 / 3854).
